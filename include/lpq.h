@@ -112,7 +112,7 @@ int lpq_encode(const lpq_quantizer *q, const float *x_dev, int64_t n, int64_t ld
 /* Flat index for up to `capacity` items (1 <= capacity < 2^31).  The index takes a copy
  * of the quantizer's constants (later changes to q do not affect it) and allocates, with
  * hipMalloc, the int8 codes (rows zero padded to 64, 96, 128, 192, 256, 384, 512, 768, 1024 or
- * 1536 bytes, beyond 1536 features to a multiple of 32 bytes) and the integer norms.
+ * 1536 bytes, beyond 1536 features to a multiple of 128 bytes) and the integer norms.
  * d <= 32 768 keeps every integer distance inside int32. */
 int lpq_index_create(lpq_index **out, const lpq_quantizer *q, int64_t capacity);
 
@@ -159,9 +159,9 @@ size_t lpq_search_workspace_bytes(const lpq_index *idx, int64_t nq, int k, int m
  *                          IP the integer inner product, descending.
  * Equal distances are ordered by ascending id, so the result is unique.
  * 1 <= k <= min(size, 1024).  nq = 0 is a no-op.  Asynchronous on `stream`.
- * Every shape returns the same exact result; speed differs: indexes of up to 1536 features are
- * searched on the matrix cores for every k and batch size once they hold enough items for a
- * threshold sample (a few ten thousand), longer vectors and smaller indexes by a plain
+ * Every shape returns the same exact result; speed differs: an index of any number of features is
+ * searched on the matrix cores for every k and batch size once it holds enough items for a
+ * threshold sample (64 k of them, at most half of the items); smaller indexes go through a plain
  * dot-product kernel (about two orders of magnitude slower per contraction). */
 int lpq_search(const lpq_index *idx, const float *q_dev, int64_t nq, int64_t ld, int k,
                int metric, int32_t *ids_dev, int32_t *dist_dev, void *workspace_dev,

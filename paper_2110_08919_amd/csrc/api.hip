@@ -319,9 +319,10 @@ extern "C" void lpq_index_destroy(lpq_index *idx)
 // Row length an index stores d features in: a length the matrix-core scans have where one exists.
 static int padded_row_length(int d)
 {
-    // up to 1536 features: the row lengths the matrix-core kernels take; beyond: the generic kernel's
+    // up to 1536 features: the row lengths of the scans that keep queries in registers; beyond: whole
+    // stages of the scan that streams them
     return d <= 64 ? 64 : d <= 96 ? 96 : d <= 128 ? 128 : d <= 192 ? 192 : d <= 256 ? 256
-           : d <= 384 ? 384 : d <= 512 ? 512 : d <= 768 ? 768 : d <= 1024 ? 1024 : d <= 1536 ? 1536 : (int)round_up(d, 32);
+           : d <= 384 ? 384 : d <= 512 ? 512 : d <= 768 ? 768 : d <= 1024 ? 1024 : d <= 1536 ? 1536 : (int)round_up(d, 128);
 }
 
 static int index_create_impl(lpq_index **out, const lpq_quantizer *q, int64_t capacity, bool packed)
@@ -498,6 +499,9 @@ struct Plan {
     int Sr = 0;             // PLAN_MFMA_COLLECT: splits of the register-list kernel for many overflowed queries (0 = none)
     int rounds = 0;         // PLAN_MFMA_COLLECT: further rounds of the collecting scan, with tighter bounds, for overflowed queries
     int wave_queries = 64;  // PLAN_MFMA_COLLECT: queries per wave of the scan
+    bool stream = false;    // PLAN_MFMA_COLLECT: the scan that streams both operands (search_mfma_stream.hip)
+    int seed_tiles = 0;     // ... its seeding pass: tiles of 256 rows, in runs of 16 rows
+    int64_t run_stride = 0; // ... every run_stride rows
     int expect = 0;         // PLAN_MFMA_COLLECT: expected candidates per query
     size_t off_qcodes = 0, off_qnorms = 0, off_lists1 = 0, off_seedlist = 0, off_seeds = 0, off_lists2 = 0,
            off_gmax = 0, off_merge_tmp = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_qlist = 0, off_redo = 0, off_bounds2 = 0, off_over2 = 0,
@@ -516,7 +520,8 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
     Plan p;
     const int64_t n = idx->size;
     const int64_t want = tune(LPQ_TUNE_PATH);
-    const bool regs = mfma_reg_supported(idx->d_pad, k), coll = mfma_collect_supported(idx->d_pad, k);
+    const bool regs = mfma_reg_supported(idx->d_pad, k), stream = !idx->packed && mfma_stream_rows(idx->d_pad);
+    const bool coll = stream ? k <= MAX_K : mfma_collect_supported(idx->d_pad, k);
     // Large batches of short rows: the collecting variant with 128 queries per wave beats the
     // register lists at any k it takes (fewer LDS reads and less per-stage overhead per contraction).
     // (Not for codes of fewer than WIDE_MIN_BITS bits: there many items tie at the seed
@@ -583,7 +588,9 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             // proportion to k n / rows: the sum is least at rows ~ sqrt(k n) (coefficient measured:
             // 125 000 rows at n = 1M, k = 10).  At least k n / 1500, so that the ~1.15 k n / rows
             // candidates of a query stay well inside the 4096 the selection kernel sorts; at most n / 4.
-            const double by_cost = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
+            // (Streamed rows: a sampled row costs d / 128 times as much, a candidate no more.)
+            double by_cost = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
+            if (stream) by_cost *= std::sqrt(128.0 / (double)idx->d);
             const double by_room = (double)k * (double)n / 1500.0;
             const double want_rows = by_cost > by_room ? by_cost : by_room;
             // (k beyond 512: half the corpus, or the ~4.6 k candidates a quarter lets through would not fit)
@@ -638,13 +645,29 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             if (qt > 512) p.nq_pad = round_up(nq > 0 ? nq : 1, qt);   // query rows (codes, group maxima) cover whole tiles
             if (mfma_long_waves(idx->d_pad, nq) == 8) slots_now = 256;   // one workgroup per CU
         }
+        p.stream = p.mode == PLAN_MFMA_COLLECT && stream;
+        if (p.stream) {
+            qt = 64 * mfma_stream_wq(nq);
+            slots_now = 256;   // one workgroup per CU
+        }
     }
     const int64_t tiles_q = ceil_div(nq > 0 ? nq : 1, qt);
     const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : 512;
     if (seed) {
         // group maxima per query: 2 per split and segment (8 when rows are split), at most 2048 (4096 for k > 512)
         p.S1 = splits_for(seed, tiles_q, min_rows, slots_now, gmode ? (p.rsplit ? 256 : 1024) : merge_max_lists(k));
-        if (gmode) {
+        if (p.stream) {
+            // tiles of 256 rows made of runs of 16 rows spread evenly over the corpus
+            const int row_waves = mfma_stream_row_waves(nq);
+            const int most = 2048 / (2 * row_waves);
+            if (p.S1 > most) p.S1 = most;
+            p.SEG = mfma_seed_segments(p.S1, k, row_waves);
+            p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
+            p.seed_tiles = (int)ceil_div(ceil_div(seed, 256), p.S1) * p.S1;
+            if ((int64_t)p.seed_tiles * 256 > n) p.seed_tiles = (int)(seed / 256);
+            p.run_stride = n / (16 * (int64_t)p.seed_tiles);
+            seed = (int64_t)p.seed_tiles * 256;
+        } else if (gmode) {
             p.SEG = mfma_seed_segments(p.S1, k, p.rs_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, p.rs_waves);
             // systematic sample: one stage every seed_stride rows, shared out over the S1 splits
@@ -760,7 +783,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
 {
     SearchArgs a;
     a.codes = idx->codes; a.norms = idx->norms; a.cinit = idx->cinit; a.parity = idx->parity;
-    a.n = idx->size; a.d_pad = idx->d_pad;
+    a.n = idx->size; a.d = idx->d; a.d_pad = idx->d_pad;
     a.packed = idx->packed;
     a.qcodes = qcodes;
     a.nq = nq; a.k = k; a.metric = metric;
@@ -797,7 +820,8 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         {
             KernelSpan span(st, LPQ_PROFILE_SEED);
             a.wave_queries = p.wave_queries;   // same query tiling as the scan it seeds
-            hipError_t e = p.piece_stride ? launch_seed_mfma(a, 0, a.n, p.S1, p.SEG, gmax, st, 0, 0, p.piece_stride, p.piece_stages)
+            hipError_t e = p.stream ? launch_stream_seed(a, p.seed_tiles, p.run_stride, p.S1, p.SEG, gmax, st)
+                           : p.piece_stride ? launch_seed_mfma(a, 0, a.n, p.S1, p.SEG, gmax, st, 0, 0, p.piece_stride, p.piece_stages)
                            : p.seed_stride ? launch_seed_mfma(a, 0, a.n, p.S1, p.SEG, gmax, st, p.seed_stride, p.seed_stages)
                                            : launch_seed_mfma(a, 0, p.seed_rows, p.S1, p.SEG, gmax, st);
             a.wave_queries = 64;
@@ -810,13 +834,17 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         cand_t *cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf);
         int32_t *ccnt = reinterpret_cast<int32_t *>(ws + p.off_ccnt);
         int32_t *over = reinterpret_cast<int32_t *>(ws + p.off_over);
+        auto collect = [&](SearchArgs &args, const cand_t *bounds) -> hipError_t {
+            if (p.stream) return launch_stream_collect(args, p.S2, bounds, cbuf, ccnt, p.Cs, st);
+            args.wave_queries = p.wave_queries;
+            const hipError_t e = launch_collect_mfma(args, 0, args.n, p.S2, bounds, cbuf, ccnt, p.Cs, st);
+            args.wave_queries = 64;
+            return e;
+        };
         HIP_TRY(seed_pass());
         {
             KernelSpan span(st);
-            a.wave_queries = p.wave_queries;
-            hipError_t e = launch_collect_mfma(a, 0, a.n, p.S2, seeds, cbuf, ccnt, p.Cs, st);
-            a.wave_queries = 64;
-            HIP_TRY(e);
+            HIP_TRY(collect(a, seeds));
         }
         int32_t *qlist = reinterpret_cast<int32_t *>(ws + p.off_qlist), *qcount = qlist + nq;
         HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over, qlist, qcount, ids, dist, qnorms, emit_mode, st,
@@ -850,9 +878,8 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
                 HIP_TRY(launch_collect_refine(cbuf, ccnt, nq, p.SS, p.Cs, k, over_prev, count_prev, min_prev, bounds_prev,
                                               bounds2, count_r, st));
                 SearchArgs ar = a;
-                ar.wave_queries = p.wave_queries;
                 ar.redo_flags = over_prev; ar.redo_count = count_prev; ar.redo_min = min_prev;
-                HIP_TRY(launch_collect_mfma(ar, 0, a.n, p.S2, bounds2, cbuf, ccnt, p.Cs, st));
+                HIP_TRY(collect(ar, bounds2));
                 HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over_r, qlist_r, count_r, ids, dist, qnorms,
                                               emit_mode, st, 0, over_prev, count_prev, min_prev));
                 over_prev = over_r; count_prev = count_r; min_prev = 0; bounds_prev = bounds2;

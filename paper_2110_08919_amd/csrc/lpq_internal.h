@@ -104,6 +104,7 @@ struct SearchArgs {
     const int32_t *cinit;   // [round_up(n,32)]
     const uint32_t *parity; // [ceil(n/32)]
     int64_t n;
+    int d = 0;              // features (bytes of a row that are not padding)
     int d_pad;
     const int8_t *qcodes;   // [nq_pad][d_pad], zero padded
     int64_t nq;
@@ -174,6 +175,18 @@ bool mfma_collect_supported(int d_pad, int k);
 int mfma_collect_regions(int S, int rs_waves);
 hipError_t launch_collect_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int S, const cand_t *seeds,
                                cand_t *cbuf, int32_t *ccnt, int Cs, hipStream_t st);
+// Scan for rows beyond what fits the kernels above (search_mfma_stream.hip): both operands stream through
+// LDS.  Collecting mode with one region per split (SS = S), and its seeding pass: tiles of 256 rows,
+// each made of 16 runs of 16 rows; run i of tile g starts at row (i * tiles + g) * run_stride, split s
+// takes tiles s, s + S, ..., and gmax holds G = mfma_seed_groups(S, SEG, mfma_stream_row_waves(nq))
+// entries per query.
+bool mfma_stream_rows(int d_pad);
+int mfma_stream_wq(int64_t nq);          // a workgroup takes 64 times this many queries (1, 2 or 4)
+int mfma_stream_row_waves(int64_t nq);   // ... and splits the rows of a tile between this many of its waves
+hipError_t launch_stream_seed(const SearchArgs &a, int tiles, int64_t run_stride, int S, int SEG, int32_t *gmax,
+                              hipStream_t st);
+hipError_t launch_stream_collect(const SearchArgs &a, int S, const cand_t *seeds, cand_t *cbuf, int32_t *ccnt, int Cs,
+                                 hipStream_t st);
 // Per query: if no region overflowed and at most 4096 candidates were collected, sort them, write
 // the k best as the final result and set over[q] = 0; otherwise set over[q] = 1 and write nothing.
 // expected_candidates (per query, 0 = unknown) picks the one-wave-per-query kernel when small (k <= 32,
