@@ -772,23 +772,21 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     }
 }
 
-// ---- rows of 384 to 1536 bytes, and large batches on rows of 192 and 256 bytes -----------------
+// ---- rows of 384 and 512 bytes, and large batches on rows of 192 and 256 bytes -----------------
 // The collecting scan and its seeding pass for rows whose operands no longer fit the scheme above
 // (query fragments AND two row blocks' worth of corpus fragments in registers).  What changes:
-//   - a wave holds the fragments of 32 queries (rows of 768, 1024 or 1536 bytes), 64 (384 or 512
-//     bytes) or 128 (192 or 256 bytes): 128 registers at most, 192 on rows of 1536 bytes;
-//   - a stage is one block of 32 rows (two where an eight-wave workgroup has the LDS for it) by one
-//     segment of the row (the whole row up to 512 bytes, else a half or a third), 6 to 32 KB, in a ring of three
-//     to six; the accumulators of a row block live across its segments, are seeded when its first
-//     segment starts and filtered when its last one ends;
+//   - a wave holds the fragments of 64 queries (rows of 384 or 512 bytes) or 128 (192 or 256 bytes):
+//     128 registers at most;
+//   - a stage is one block of 32 rows (two where an eight-wave workgroup has the LDS for it), 6 to
+//     32 KB, in a ring of three to six;
 //   - corpus fragments come from LDS two to four k-steps at a time, one group ahead of the matrix
 //     instructions that use them; the group that crosses into the next stage is read right after the
 //     workgroup barrier that says the stage has landed.
-// Chunks (16 bytes) of a row segment are swizzled inside aligned groups of 2^SWB chunks: with the
+// Chunks (16 bytes) of a row are swizzled inside aligned groups of 2^SWB chunks: with the
 // row stride of 512 bytes (a multiple of the 256 bytes the 64 banks cover) the low four bits of the
 // row number do it; with 384 bytes odd rows start half way round the banks, so three bits taken
 // from bit 1 up give 16 consecutive rows 16 different bank groups as well.
-// (Segments of 256 bytes behave like 512, and with 192 bytes a row starts at one of four places
+// (Rows of 256 bytes behave like 512, and with 192 bytes a row starts at one of four places
 // round the banks, so two bits taken from bit 2 up do it, in groups of four chunks.)
 template <int CPS>
 __device__ __forceinline__ int long_slot(int c, int r)
@@ -799,45 +797,43 @@ __device__ __forceinline__ int long_slot(int c, int r)
 }
 
 // blocks of 32 queries per wave: as many as 128 registers of query fragments allow
-constexpr int long_nb(int kseg, int nseg) { return nseg >= 2 ? 1 : (kseg >= 12 ? 2 : 4); }
+constexpr int long_nb(int ks) { return ks >= 12 ? 2 : 4; }
 // rows per stage: two row blocks where one workgroup has the CU's LDS to itself (eight waves; the
 // seeding pass samples the same stages): twice the matrix instructions per barrier, copy wait and
 // loop turn
 // (not the seeding pass of rows up to 256 bytes: with 128 queries per wave and no branch between
 // its row blocks the compiler schedules both as one region and spills 24 to 45 registers)
-constexpr int long_rs(int kseg, bool seed, int nw) { return (nw == 8 && !(seed && kseg <= 8)) ? 64 : 32; }
-constexpr int long_nst(int kseg, int nw, int rs)
+constexpr int long_rs(int ks, bool seed, int nw) { return (nw == 8 && !(seed && ks <= 8)) ? 64 : 32; }
+constexpr int long_nst(int ks, int nw, int rs)
 {
-    return nw == 4 ? (kseg <= 8 ? 4 : 3) : (rs == 64 ? (kseg == 6 ? 5 : (kseg == 16 ? 3 : 4)) : (kseg <= 12 ? 6 : 5));
+    return nw == 4 ? (ks <= 8 ? 4 : 3) : (rs == 64 ? (ks == 6 ? 5 : (ks == 16 ? 3 : 4)) : (ks <= 12 ? 6 : 5));
 }
-constexpr size_t long_lds_bytes(int kseg, int nb, bool seed, int nw, int rs)
+constexpr size_t long_lds_bytes(int ks, int nb, bool seed, int nw, int rs)
 {
-    return (size_t)long_nst(kseg, nw, rs) * rs * kseg * 32 + (size_t)long_nst(kseg, nw, rs) * (rs + 4) * 4 + 64 +
+    return (size_t)long_nst(ks, nw, rs) * rs * ks * 32 + (size_t)long_nst(ks, nw, rs) * (rs + 4) * 4 + 64 +
            (seed ? 0 : nw * waveq_bytes(nb * 32));
 }
 
-template <int KSEG, int NSEG, bool L2, bool SEED, int NW>
+template <int KSEG, bool L2, bool SEED, int NW>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
     SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, int qtiles, MfmaIo o)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    static_assert(((KSEG == 12 || KSEG == 16) && (NSEG == 1 || NSEG == 2)) || ((KSEG == 6 || KSEG == 8) && NSEG == 1) ||
-                  (KSEG == 16 && NSEG == 3), "rows of 192, 256, 384, 512, 768, 1024 or 1536 bytes");
+    static_assert(KSEG == 6 || KSEG == 8 || KSEG == 12 || KSEG == 16, "rows of 192, 256, 384 or 512 bytes");
     static_assert(NW == 4 || NW == 8, "four waves (two workgroups per CU) or eight (one)");
-    constexpr int NB = long_nb(KSEG, NSEG);    // blocks of 32 queries per wave
+    constexpr int NB = long_nb(KSEG);          // blocks of 32 queries per wave
     constexpr int QW = NB * 32, QT = NW * QW;
-    constexpr int KTOT = KSEG * NSEG;          // k-steps (32 bytes) per row
-    constexpr int ROWB = KTOT * 32, SEGB = KSEG * 32;
-    constexpr int CPS = SEGB / 16;             // chunks per row segment
+    constexpr int ROWB = KSEG * 32;            // bytes per row, KSEG k-steps of 32
+    constexpr int CPS = ROWB / 16;             // chunks per row
     constexpr int RS = long_rs(KSEG, SEED, NW);   // rows per stage
     constexpr int BPS = RS / 32;               // row blocks per stage
     constexpr int NST = long_nst(KSEG, NW, RS);
-    constexpr int STAGE_BYTES = RS * SEGB;
+    constexpr int STAGE_BYTES = RS * ROWB;
     constexpr int NI = RS * CPS / 64;          // copy instructions per stage: wave w issues w, w + NW, ...
     constexpr int IPW = (NI + NW - 1) / NW;    // ... at most this many
     constexpr int AUX_INTS = RS + 4;           // accumulator seeds of the 32 rows, then their parity word
-    constexpr int GS = KSEG == 6 ? 3 : ((KSEG == 8 || NSEG == 3) ? 2 : 4);   // k-steps per group of fragments (each feeds NB matrix instructions)
-    constexpr int NG = KSEG / GS;              // groups per segment
+    constexpr int GS = KSEG == 6 ? 3 : (KSEG == 8 ? 2 : 4);   // k-steps per group of fragments (each feeds NB matrix instructions)
+    constexpr int NG = KSEG / GS;              // groups per row
     constexpr int PER = CPS % 16 == 0 ? 8 : (CPS % 8 == 0 ? 4 : 2);   // k-steps after which a lane's swizzle pattern repeats
     static_assert((NST - 1) * (IPW + 1) <= 63, "wait_vmcnt covers 0..63");
 
@@ -870,7 +866,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
         const int64_t left = (row1 > rs) ? (row1 - rs + bstride - 1) / bstride : 0;
         RB = (int)(left < split_rows / RS ? left : split_rows / RS);
     }
-    const int T = RB * NSEG;
+    const int T = RB;
     const int64_t re = row1;
 
     unsigned char *ring = smem;
@@ -911,11 +907,11 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
     }
     wave_lds_sync();
 
-    v4i B[NB][KTOT];
+    v4i B[NB][KSEG];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int ks = 0; ks < KTOT; ++ks)
+        for (int ks = 0; ks < KSEG; ++ks)
             B[nb][ks] = *reinterpret_cast<const v4i *>(a.qcodes + (q_first + nb * 32 + col) * a.d_pad + ks * 32 + half * 16);
     int thr[NB], gm[NB];
 #pragma unroll
@@ -924,13 +920,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
         gm[nb] = INT32_MIN;
     }
     int qcnt = 0;
-    // Byte offset, inside a stage, of this lane's fragment of k-step ks (of the segment): the chunk
+    // Byte offset, inside a stage, of this lane's fragment of k-step ks: the chunk
     // 2 ks + half sits in slot long_slot(2 ks + half, col), which differs from the slot of k-step 0
     // only in the bits ks % PER sets (the row's start has those address bits clear), so one register
     // and an exclusive-or with a constant per read replace a table of PER offsets:
     // offset(ks) = (a_base ^ ((ks % PER) << 5)) + (ks / PER) * PER * 32.
-    const int a_base = col * SEGB + long_slot<CPS>(half, col) * 16;
-    static_assert(SEGB % (PER * 32) == 0, "a row starts on a multiple of the swizzle group");
+    const int a_base = col * ROWB + long_slot<CPS>(half, col) * 16;
+    static_assert(ROWB % (PER * 32) == 0, "a row starts on a multiple of the swizzle group");
 
     // Stage loader: LDS position p (16 bytes) of a stage = (row p / CPS, slot p % CPS); copy instruction
     // i of a stage fills positions [64 i, 64 i + 64), each lane fetching the chunk that belongs in its
@@ -948,8 +944,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
 #define LPQL_ISSUE(ST, SLOT)                                                                            \
     do {                                                                                                \
         const int st_ = (ST), slot_ = (SLOT);                                                           \
-        const int64_t r0_ = rs + (int64_t)(st_ / NSEG) * bstride;                                       \
-        const int8_t *src_ = a.codes + r0_ * ROWB + (st_ % NSEG) * SEGB;                                \
+        const int64_t r0_ = rs + (int64_t)st_ * bstride;                                                \
+        const int8_t *src_ = a.codes + r0_ * ROWB;                                                      \
         _Pragma("unroll") for (int j = 0; j < IPW; ++j)                                                 \
             if (NI % NW == 0 || j < mine) {                                                             \
                 int near_ = src_off[j];   /* one register each: the 64-bit address is formed here, not */ \
@@ -964,10 +960,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
         }                                                                                               \
     } while (0)
 
-    // fragments of group G (k-steps GS G .. GS G + GS - 1 of the segment) of row block BLK of the stage in ring slot SLOT
+    // fragments of group G (k-steps GS G .. GS G + GS - 1 of the row) of row block BLK of the stage in ring slot SLOT
 #define LPQL_LOAD_GROUP(SLOT, BLK, G, AREG)                                                             \
     do {                                                                                                \
-        const unsigned char *sb_ = ring + (size_t)(SLOT) * STAGE_BYTES + (BLK) * 32 * SEGB;             \
+        const unsigned char *sb_ = ring + (size_t)(SLOT) * STAGE_BYTES + (BLK) * 32 * ROWB;             \
         _Pragma("unroll") for (int i = 0; i < GS; ++i) {                                                \
             const int ks_ = (G) * GS + i;                                                               \
             AREG[i] = *reinterpret_cast<const v4i *>(sb_ + (a_base ^ ((ks_ % PER) << 5)) + (ks_ / PER) * (PER * 32)); \
@@ -1051,7 +1047,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
     // Seeds and parity word of a row block are read along with its first fragment group, one group
     // ahead - except where the query fragments fill all 128 registers they may have and the 16 more
     // are not there: the block then reads its seeds as it starts.
-    constexpr bool SEEDS_AHEAD = KTOT * NB * 4 < 128;
+    constexpr bool SEEDS_AHEAD = KSEG * NB * 4 < 128;
     v4i An[GS];          // the group read ahead
     v16i Cn;             // seeds and parity word of the row block that starts next
     unsigned Pn = 0;
@@ -1065,94 +1061,91 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
         if (SEEDS_AHEAD) LPQL_LOAD_SEEDS(0, 0, Cn, Pn);
     }
     int t = 0;
-    for (int rb = 0; rb < RB; ++rb) {   // rb: a group of RS rows = BPS row blocks; its NSEG stages follow each other
+    for (int rb = 0; rb < RB; ++rb, ++t) {   // rb: a stage of RS rows = BPS row blocks
         v16i acc[BPS][NB];
         v16i Cc;
         unsigned Pc[BPS];
 #pragma unroll
-        for (int seg = 0; seg < NSEG; ++seg, ++t) {
+        for (int blk = 0; blk < BPS; ++blk) {
 #pragma unroll
-            for (int blk = 0; blk < BPS; ++blk) {
+            for (int g = 0; g < NG; ++g) {
+                v4i Ac[GS];
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    v4i Ac[GS];
-#pragma unroll
-                    for (int i = 0; i < GS; ++i) Ac[i] = An[i];
-                    if (seg == 0 && g == 0) {
-                        if (SEEDS_AHEAD) { Cc = Cn; Pc[blk] = Pn; }
-                        else LPQL_LOAD_SEEDS(slot, blk, Cc, Pc[blk]);   // the stage's slot is refilled only after its last group
+                for (int i = 0; i < GS; ++i) Ac[i] = An[i];
+                if (g == 0) {
+                    if (SEEDS_AHEAD) { Cc = Cn; Pc[blk] = Pn; }
+                    else LPQL_LOAD_SEEDS(slot, blk, Cc, Pc[blk]);   // the stage's slot is refilled only after its last group
+                }
+                if (g + 1 < NG) {
+                    LPQL_LOAD_GROUP(slot, blk, g + 1, An);
+                } else if (blk + 1 < BPS) {   // on to the next row block of the same stage
+                    LPQL_LOAD_GROUP(slot, blk + 1, 0, An);
+                    if (SEEDS_AHEAD) LPQL_LOAD_SEEDS(slot, blk + 1, Cn, Pn);
+                } else {
+                    // the last group of stage t is in registers once the LDS counter is down: this wave
+                    // is done reading the stage
+                    // (the matrix instructions of the group before are issued first: they run meanwhile)
+                    __builtin_amdgcn_sched_barrier(0);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    // every fourth stage the waves tell each other whether a queue is half full, and
+                    // if one is, all drain together (a wave whose queue overflows in between drains alone)
+                    const bool xchg = !SEED && (t & 3) == 3;
+                    if (xchg && lane == 0) flags[wave] = qcnt >= TRIG;
+                    if (t + NST - 1 < T) {
+                        // stages 0 .. t+NST-1 have been issued and stage t+1 must have landed: all but
+                        // the copies of the NST-2 newest stages (a constant count per wave, without the
+                        // run-time dispatch of wait_vmcnt)
+                        if (lpt == IPW) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * IPW));
+                        else if (lpt == IPW + 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * (IPW + 1)));
+                        else wait_vmcnt((NST - 2) * lpt);
+                    } else if (t + 1 < T) {   // the tail: stages up to T-1 have been issued
+                        wait_vmcnt((T - 1 - (t + 1)) * lpt);
                     }
-                    if (g + 1 < NG) {
-                        LPQL_LOAD_GROUP(slot, blk, g + 1, An);
-                    } else if (blk + 1 < BPS) {   // on to the next row block of the same stage
-                        LPQL_LOAD_GROUP(slot, blk + 1, 0, An);
-                        if (SEEDS_AHEAD && seg == 0) LPQL_LOAD_SEEDS(slot, blk + 1, Cn, Pn);
-                    } else {
-                        // the last group of stage t is in registers once the LDS counter is down: this wave
-                        // is done reading the stage
-                        // (the matrix instructions of the group before are issued first: they run meanwhile)
-                        __builtin_amdgcn_sched_barrier(0);
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        // every fourth stage the waves tell each other whether a queue is half full, and
-                        // if one is, all drain together (a wave whose queue overflows in between drains alone)
-                        const bool xchg = !SEED && (t & 3) == 3;
-                        if (xchg && lane == 0) flags[wave] = qcnt >= TRIG;
-                        if (t + NST - 1 < T) {
-                            // stages 0 .. t+NST-1 have been issued and stage t+1 must have landed: all but
-                            // the copies of the NST-2 newest stages (a constant count per wave, without the
-                            // run-time dispatch of wait_vmcnt)
-                            if (lpt == IPW) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * IPW));
-                            else if (lpt == IPW + 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * (IPW + 1)));
-                            else wait_vmcnt((NST - 2) * lpt);
-                        } else if (t + 1 < T) {   // the tail: stages up to T-1 have been issued
-                            wait_vmcnt((T - 1 - (t + 1)) * lpt);
+                    __syncthreads();
+                    if (t + NST < T) LPQL_ISSUE(t + NST, slot);   // refills the slot of stage t
+                    if (xchg) {   // (the next exchange is four barriers away: no wave can overwrite a flag early)
+                        const v4i fl0 = *reinterpret_cast<const v4i *>(flags);
+                        int any = fl0[0] | fl0[1] | fl0[2] | fl0[3];
+                        if (NW > 4) {
+                            const v4i fl1 = *reinterpret_cast<const v4i *>(flags + 4);
+                            any |= fl1[0] | fl1[1] | fl1[2] | fl1[3];
                         }
-                        __syncthreads();
-                        if (t + NST < T) LPQL_ISSUE(t + NST, slot);   // refills the slot of stage t
-                        if (xchg) {   // (the next exchange is four barriers away: no wave can overwrite a flag early)
-                            const v4i fl0 = *reinterpret_cast<const v4i *>(flags);
-                            int any = fl0[0] | fl0[1] | fl0[2] | fl0[3];
-                            if (NW > 4) {
-                                const v4i fl1 = *reinterpret_cast<const v4i *>(flags + 4);
-                                any |= fl1[0] | fl1[1] | fl1[2] | fl1[3];
-                            }
-                            if (any) {
-                                drain_queue<L2, 0, 1>(w, qcnt, re, lane, lst, seedC, cbase, qstride, o.Cs);
-                                qcnt = 0;
-                            }
+                        if (any) {
+                            drain_queue<L2, 0, 1>(w, qcnt, re, lane, lst, seedC, cbase, qstride, o.Cs);
+                            qcnt = 0;
                         }
-                        const int nslot = slot + 1 == NST ? 0 : slot + 1;
-                        if (t + 1 < T) {
-                            LPQL_LOAD_GROUP(nslot, 0, 0, An);
-                            if (SEEDS_AHEAD && seg + 1 == NSEG) LPQL_LOAD_SEEDS(nslot, 0, Cn, Pn);
-                        }
-                        slot = nslot;
                     }
-#pragma unroll
-                    for (int i = 0; i < GS; ++i)
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[blk][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                                Ac[i], B[nb][seg * KSEG + g * GS + i], (seg == 0 && g == 0 && i == 0) ? Cc : acc[blk][nb], 0, 0, 0);
-                    // Keep the reads of the next group in front of this group's matrix instructions: left
-                    // alone, the compiler moves each read down to the instruction that needs it and every
-                    // matrix instruction then waits out a full LDS round trip.  The same two groups keep
-                    // ALL matrix instructions of the block in front of its first filter epilogue.  That
-                    // matters: with the completing group issued query block by query block and each
-                    // epilogue one chain later (as in the kernel above) the scheduler put the last
-                    // matrix instruction of a chain four instructions before the branch that ends the
-                    // epilogue before it, the next epilogue read that chain's first accumulators five
-                    // issue slots after it with no wait inserted, and candidates in those rows went
-                    // missing now and then (two runs of one binary disagreed).
-                    __builtin_amdgcn_sched_group_barrier(0x100, GS, 0);        // the group's LDS reads
-                    __builtin_amdgcn_sched_group_barrier(0x008, GS * NB, 0);   // GS * NB matrix instructions
-                    if (seg == NSEG - 1 && g == NG - 1) {   // the row block is complete
-                        // nothing of the contraction may drift down among the epilogues (see above)
-                        __builtin_amdgcn_sched_barrier(0);
-                        const int rowbase = (int)(rs + (int64_t)rb * bstride) + blk * 32;
-#pragma unroll
-                        for (int nbi = 0; nbi < NB; ++nbi) LPQL_EPI(acc[blk][nbi], nbi, rowbase, Pc[blk]);
+                    const int nslot = slot + 1 == NST ? 0 : slot + 1;
+                    if (t + 1 < T) {
+                        LPQL_LOAD_GROUP(nslot, 0, 0, An);
+                        if (SEEDS_AHEAD) LPQL_LOAD_SEEDS(nslot, 0, Cn, Pn);
                     }
+                    slot = nslot;
+                }
+#pragma unroll
+                for (int i = 0; i < GS; ++i)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[blk][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                            Ac[i], B[nb][g * GS + i], (g == 0 && i == 0) ? Cc : acc[blk][nb], 0, 0, 0);
+                // Keep the reads of the next group in front of this group's matrix instructions: left
+                // alone, the compiler moves each read down to the instruction that needs it and every
+                // matrix instruction then waits out a full LDS round trip.  The same two groups keep
+                // ALL matrix instructions of the block in front of its first filter epilogue.  That
+                // matters: with the completing group issued query block by query block and each
+                // epilogue one chain later (as in the kernel above) the scheduler put the last
+                // matrix instruction of a chain four instructions before the branch that ends the
+                // epilogue before it, the next epilogue read that chain's first accumulators five
+                // issue slots after it with no wait inserted, and candidates in those rows went
+                // missing now and then (two runs of one binary disagreed).
+                __builtin_amdgcn_sched_group_barrier(0x100, GS, 0);        // the group's LDS reads
+                __builtin_amdgcn_sched_group_barrier(0x008, GS * NB, 0);   // GS * NB matrix instructions
+                if (g == NG - 1) {   // the row block is complete
+                    // nothing of the contraction may drift down among the epilogues (see above)
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int rowbase = (int)(rs + (int64_t)rb * bstride) + blk * 32;
+#pragma unroll
+                    for (int nbi = 0; nbi < NB; ++nbi) LPQL_EPI(acc[blk][nbi], nbi, rowbase, Pc[blk]);
                 }
             }
         }
@@ -1338,16 +1331,16 @@ bool takes_long_scan(const SearchArgs &a)
     return mfma_long_rows(a.d_pad, a.nq) && !a.rsplit && !a.packed && a.wave_queries == mfma_long_wave_queries(a.d_pad);
 }
 
-// Rows of 384 to 1536 bytes (and large batches on 192 and 256): the collecting scan (o.cbuf) or its seeding pass (o.gmax).
-template <int KSEG, int NSEG, bool L2, bool SEED, int NW>
+// Rows of 384 and 512 bytes (and large batches on 192 and 256): the collecting scan (o.cbuf) or its seeding pass (o.gmax).
+template <int KSEG, bool L2, bool SEED, int NW>
 hipError_t launch_long_nw(const SearchArgs &a, int64_t row0, int64_t row1, int S, MfmaIo o, hipStream_t st)
 {
-    constexpr int NB = long_nb(KSEG, NSEG);
+    constexpr int NB = long_nb(KSEG);
     if (a.rsplit || a.packed || a.wave_queries != NB * 32) return hipErrorInvalidValue;
     const int64_t split_rows = o.split_stride ? o.split_stride_rows : round_up(ceil_div(row1 - row0, S), 128);
     if (!o.split_stride) o.split_stride = split_rows;
     const int qtiles = (int)ceil_div(a.nq, NW * NB * 32);
-    auto kern = search_long_kernel<KSEG, NSEG, L2, SEED, NW>;
+    auto kern = search_long_kernel<KSEG, L2, SEED, NW>;
     static bool attr_set = false;  // per instantiation
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1360,25 +1353,23 @@ hipError_t launch_long_nw(const SearchArgs &a, int64_t row0, int64_t row1, int S
     return hipGetLastError();
 }
 
-template <int KSEG, int NSEG, bool L2, bool SEED>
+template <int KSEG, bool L2, bool SEED>
 hipError_t launch_long_one(const SearchArgs &a, int64_t row0, int64_t row1, int S, const MfmaIo &o, hipStream_t st)
 {
-    if constexpr (NSEG < 3) {
-        if (mfma_long_waves(a.d_pad, a.nq) == 8) return launch_long_nw<KSEG, NSEG, L2, SEED, 8>(a, row0, row1, S, o, st);
-    }
-    return launch_long_nw<KSEG, NSEG, L2, SEED, 4>(a, row0, row1, S, o, st);
+    return mfma_long_waves(a.d_pad, a.nq) == 8 ? launch_long_nw<KSEG, L2, SEED, 8>(a, row0, row1, S, o, st)
+                                               : launch_long_nw<KSEG, L2, SEED, 4>(a, row0, row1, S, o, st);
 }
 
-template <int KSEG, int NSEG>
+template <int KSEG>
 hipError_t launch_long(const SearchArgs &a, int64_t row0, int64_t row1, int S, const MfmaIo &o, hipStream_t st)
 {
     const bool l2 = a.metric == LPQ_METRIC_L2SQ;
     if (o.gmax)
-        return l2 ? launch_long_one<KSEG, NSEG, true, true>(a, row0, row1, S, o, st)
-                  : launch_long_one<KSEG, NSEG, false, true>(a, row0, row1, S, o, st);
+        return l2 ? launch_long_one<KSEG, true, true>(a, row0, row1, S, o, st)
+                  : launch_long_one<KSEG, false, true>(a, row0, row1, S, o, st);
     if (o.cbuf)
-        return l2 ? launch_long_one<KSEG, NSEG, true, false>(a, row0, row1, S, o, st)
-                  : launch_long_one<KSEG, NSEG, false, false>(a, row0, row1, S, o, st);
+        return l2 ? launch_long_one<KSEG, true, false>(a, row0, row1, S, o, st)
+                  : launch_long_one<KSEG, false, false>(a, row0, row1, S, o, st);
     return hipErrorInvalidValue;   // no register lists beside rows this long
 }
 
@@ -1388,13 +1379,10 @@ hipError_t launch_any(const SearchArgs &a, int64_t row0, int64_t row1, int S, co
     if (row0 % 128 || o.split_stride % 128) return hipErrorInvalidValue;  // stages and parity words cover aligned blocks
     if (takes_long_scan(a) && (o.gmax || o.cbuf)) {
         switch (a.d_pad / 32) {
-        case 6: return launch_long<6, 1>(a, row0, row1, S, o, st);
-        case 8: return launch_long<8, 1>(a, row0, row1, S, o, st);
-        case 12: return launch_long<12, 1>(a, row0, row1, S, o, st);
-        case 16: return launch_long<16, 1>(a, row0, row1, S, o, st);
-        case 24: return launch_long<12, 2>(a, row0, row1, S, o, st);
-        case 32: return launch_long<16, 2>(a, row0, row1, S, o, st);
-        case 48: return launch_long<16, 3>(a, row0, row1, S, o, st);
+        case 6: return launch_long<6>(a, row0, row1, S, o, st);
+        case 8: return launch_long<8>(a, row0, row1, S, o, st);
+        case 12: return launch_long<12>(a, row0, row1, S, o, st);
+        case 16: return launch_long<16>(a, row0, row1, S, o, st);
         default: break;
         }
     }
@@ -1414,7 +1402,7 @@ bool shape_ok(int d_pad)
     return d_pad % 32 == 0 && (ks == 2 || ks == 3 || ks == 4 || ks == 6 || ks == 8);
 }
 
-bool long_shape_ok(int d_pad) { return d_pad == 384 || d_pad == 512 || d_pad == 768 || d_pad == 1024 || d_pad == 1536; }
+bool long_shape_ok(int d_pad) { return d_pad == 384 || d_pad == 512; }
 
 }  // namespace
 
@@ -1424,7 +1412,7 @@ int mfma_queries_per_workgroup(int64_t nq, int d_pad, bool wide)
     return mfma_row_split(nq, d_pad) ? 64 : (wide ? 512 : 256);
 }
 
-// Rows of more than 256 bytes (384, 512, 768 or 1024: the collecting scan and its seeding pass only).
+// Rows of 384 and 512 bytes (the collecting scan and its seeding pass only).
 bool mfma_long_rows(int d_pad, int64_t nq)
 {
     // Rows of 192 and 256 bytes: the same scan with 128 queries per wave (eight-wave workgroups,
@@ -1437,17 +1425,14 @@ bool mfma_long_rows(int d_pad, int64_t nq)
     return long_shape_ok(d_pad);
 }
 
-int mfma_long_wave_queries(int d_pad) { return d_pad <= 256 ? 128 : (d_pad <= 512 ? 64 : 32); }
+int mfma_long_wave_queries(int d_pad) { return d_pad <= 256 ? 128 : 64; }
 
 int mfma_long_stage_rows(int d_pad, int64_t nq) { return (mfma_long_waves(d_pad, nq) == 8 && d_pad > 256) ? 64 : 32; }
 
 // Eight waves per workgroup (one workgroup per CU, a ring of five or six stages) for large batches:
 // half the corpus bytes per contraction go through the L2, measured 4 to 14 % faster at 10 000
-// queries; four waves (two workgroups per CU) finish small batches sooner (16 queries on
-// 500K x 1024: 0.18 against 0.22 ms).
-// (rows of 1536 bytes: four waves always - 192 registers of query fragments leave no room for the
-// second row block's accumulators)
-int mfma_long_waves(int d_pad, int64_t nq) { return (d_pad <= 256 || (nq > 512 && d_pad <= 1024)) ? 8 : 4; }
+// queries; four waves (two workgroups per CU) finish small batches sooner.
+int mfma_long_waves(int d_pad, int64_t nq) { return (d_pad <= 256 || nq > 512) ? 8 : 4; }
 
 // Collecting mode: 128 queries per wave when the rows are short enough for the registers to hold them.
 // (Not for 513 to 768 queries: three tiles of 256 - register lists up to k = 10, the collecting scan

@@ -388,8 +388,11 @@ hipError_t launch_stream(const SearchArgs &a, int64_t row_end, int S, const Stre
 
 }  // namespace
 
-// (Rows of up to 1536 bytes keep their queries in registers.)
-bool mfma_stream_rows(int d_pad) { return d_pad > 1536 && d_pad % KB == 0; }
+// Rows of 384 and 512 bytes stay with the long-row scan, whose waves hold 64 queries there (500K rows,
+// 1000 queries: 0.236 and 0.291 ms against 0.247 and 0.298 here).  From 768 bytes on it held 32 and lost
+// at every batch size (same corpus, L2: 768 bytes 0.458 -> 0.413 ms, 10 000 queries 4.08 -> 3.60, 16
+// queries 0.141 -> 0.131; 300K x 1024, 10 000 queries: 3.22 -> 3.04; 300K x 1536, 1000 queries: 0.641 -> 0.498).
+bool mfma_stream_rows(int d_pad) { return d_pad >= 768 && d_pad % KB == 0; }
 
 // The narrowest tile that holds the batch: small batches are bound by the corpus bytes, and a wider
 // tile would spend matrix time on queries that are not there.
