@@ -205,8 +205,9 @@ hipError_t launch_collect_refine(const cand_t *cbuf, const int32_t *ccnt, int64_
                                  const int32_t *over, const int32_t *qcount, int min_flagged, const cand_t *bounds_in,
                                  cand_t *bounds_out, int32_t *zero_word, hipStream_t st);
 // zero_word (optional): one int the kernel also sets to 0 (the counter of the redo list).
+// kth_out (optional): the k-th largest maximum itself per query, INT32_MIN where there is none (seeds may then be null).
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
-                                int32_t *zero_word = nullptr);
+                                int32_t *zero_word = nullptr, int32_t *kth_out = nullptr);
 
 // Merge P lists of k candidates per query into one (merge.hip).  If ids/dists are given the
 // result is final: ids, and dist = key + qnorm (L2SQ) or -key/2 (IP).  Otherwise the merged
@@ -237,7 +238,20 @@ hipError_t launch_gather_dist(const int8_t *codes, const int32_t *norms, int64_t
 hipError_t launch_rerank_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq, int d,
                              const int32_t *cand, int kc, int k, int metric, int32_t *ids, float *dists, hipStream_t st);
 
-// ---- fp32 exact search (search_f32.hip) ---------------------------------------------
+// ---- fp32 exact search (search_f32.hip, search_mfma_f32.hip) -------------------------
+// Matrix-core filter in front of the direct sums: plan of its passes and where its buffers lie.
+struct F32Filter {
+    bool use = false;         // the direct kernel alone otherwise
+    int wq = 0, qtiles = 0, dp = 0, S1 = 0, S2 = 0, SEG = 0, G = 0, seed_tiles = 0, Cs = 0;
+    int64_t nq_pad = 0, run_stride = 0;
+    size_t off_qh = 0, off_ql = 0, off_qn = 0, off_gmax = 0, off_kth = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_list = 0,
+           total = 0;
+};
+F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k);
+// Rows that may be among the k nearest of each query -> regions cbuf[nq][S2][Cs] (the low half of a
+// candidate holds the row), ccnt[nq][S2]; the counter behind the redo list is cleared.
+hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
+                             int d, int k, bool l2, char *ws, hipStream_t st);
 size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k);
 int f32_max_d(int k);   // largest d the fp32 search takes for k results (its LDS holds a query and its candidates)
 hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq,

@@ -47,7 +47,7 @@ __device__ __forceinline__ void halve_sums(float (&red)[N], bool upper)
 template <bool VEC, int QT, bool L2>
 __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
     const float *__restrict__ x, int64_t n, int64_t ldx, const float *__restrict__ qv, int64_t ldq, int64_t nq,
-    int d, int k, int mode, int S, int64_t split_rows, cand_t *__restrict__ lists, int cap)
+    int d, int k, int mode, int S, int64_t split_rows, cand_t *__restrict__ lists, int cap, const int32_t *__restrict__ only)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);                 // [QT][cap]
@@ -62,6 +62,11 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
     const int64_t q0 = (int64_t)(wk % tiles) * QT;
     const int s = wk / tiles;
     const int chunks = (d + 3) >> 2, dp = 4 * chunks;
+    if (only) {   // only queries flagged by the filter; the same answer in every thread
+        int any = 0;
+        for (int j = 0; j < QT; ++j) any |= q0 + j < nq ? only[q0 + j] : 0;
+        if (!any) return;
+    }
     const int64_t rs = (int64_t)s * split_rows;
     const int64_t re = (rs + split_rows < n) ? rs + split_rows : n;
     constexpr bool l2 = L2;
@@ -179,6 +184,72 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
     }
 }
 
+// Directly summed distances of the rows the filter collected: eight lanes per row, each with the same
+// chunks of four features in the same order, the eight partial sums added in the same pairs, as in the
+// kernel above, so a distance comes out with the same bits.  `share` workgroups per query; the key half
+// of every collected candidate is written in place.  Bound by the gathered rows (4 KB each at 1024 features).
+constexpr int DIST_REGIONS = 256;   // regions whose counts the kernel lists in LDS
+template <bool VEC>
+__global__ __launch_bounds__(F32_THREADS) void f32_distances_kernel(const float *__restrict__ x, int64_t ldx,
+                                                                    const float *__restrict__ qv, int64_t ldq, int d, bool l2,
+                                                                    int SS, int Cs, int share, const int32_t *__restrict__ ccnt,
+                                                                    cand_t *__restrict__ cbuf)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *qs = reinterpret_cast<float *>(smem);              // the query, zero beyond d
+    __shared__ int s_end[DIST_REGIONS];                       // candidates of regions 0 .. r together
+    const int64_t q = blockIdx.x / share;
+    const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3, chunks = (d + 3) >> 2;
+    for (int i = tid; i < 4 * chunks; i += F32_THREADS) qs[i] = i < d ? qv[q * ldq + i] : 0.0f;
+    int mine = 0;
+    if (tid < SS) {
+        const int have = ccnt[q * SS + tid];
+        mine = have > Cs ? 0 : have;                          // overflowed: searched again anyway
+    }
+    s_end[tid] = mine;
+    __syncthreads();
+    for (int o = 1; o < F32_THREADS; o <<= 1) {
+        const int v = tid >= o ? s_end[tid - o] : 0;
+        __syncthreads();
+        s_end[tid] += v;
+        __syncthreads();
+    }
+    const int total = s_end[F32_THREADS - 1];
+    for (int i = (int)(blockIdx.x % share) * F32_ROWS + grp; i < total; i += share * F32_ROWS) {
+        int lo = 0, hi = SS - 1;                              // first region that ends beyond i
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_end[mid] > i) hi = mid; else lo = mid + 1;
+        }
+        cand_t *at = cbuf + ((size_t)q * SS + lo) * Cs + (i - (lo ? s_end[lo - 1] : 0));
+        const uint32_t row = cand_id(*at);
+        const float *xr = x + (int64_t)row * ldx;
+        float acc = 0.0f;
+#pragma unroll 4
+        for (int c = sub; c < chunks; c += 8) {
+            float xa[4];
+            if (VEC && 4 * c + 3 < d) {
+                const float4 t = *reinterpret_cast<const float4 *>(xr + 4 * c);
+                xa[0] = t.x; xa[1] = t.y; xa[2] = t.z; xa[3] = t.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xa[e] = 4 * c + e < d ? xr[4 * c + e] : 0.0f;
+            }
+            const float4 qq = *reinterpret_cast<const float4 *>(qs + 4 * c);
+            const float qa[4] = {qq.x, qq.y, qq.z, qq.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (l2) { const float t = qa[e] - xa[e]; acc = fmaf(t, t, acc); }
+                else acc = fmaf(qa[e], xa[e], acc);
+            }
+        }
+        acc += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(acc)));
+        acc += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(acc)));
+        acc += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(acc)));
+        if (sub == 0) *at = make_cand(float_to_sortable(l2 ? acc : -acc), row);
+    }
+}
+
 int f32_cap(int k) { return next_pow2((2 * k > k + 2 * F32_STEP) ? 2 * k : k + 2 * F32_STEP); }
 
 // queries per workgroup: as many as fit in 48 KB of LDS with their candidate buffers, at most 8
@@ -203,12 +274,12 @@ int f32_splits(int64_t n, int64_t nq, int d, int k)
 template <int QT>
 hipError_t launch_f32_tile(bool vec, unsigned blocks, size_t shmem, hipStream_t st, const float *x, int64_t n,
                            int64_t ldx, const float *q, int64_t ldq, int64_t nq, int d, int k, int mode, int S,
-                           int64_t split_rows, cand_t *lists, int cap)
+                           int64_t split_rows, cand_t *lists, int cap, const int32_t *only)
 {
     const bool l2 = mode == MODE_F32_L2;
     auto kern = vec ? (l2 ? search_f32_kernel<true, QT, true> : search_f32_kernel<true, QT, false>)
                     : (l2 ? search_f32_kernel<false, QT, true> : search_f32_kernel<false, QT, false>);
-    kern<<<blocks, F32_THREADS, shmem, st>>>(x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap);
+    kern<<<blocks, F32_THREADS, shmem, st>>>(x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap, only);
     return hipGetLastError();
 }
 
@@ -222,9 +293,14 @@ int f32_max_d(int k)
     return room < 16 ? 0 : (int)(room / 16 * 4);
 }
 
+static size_t f32_lists_bytes(int64_t n, int64_t nq, int d, int k)
+{
+    return ((size_t)nq * f32_splits(n, nq, d, k) * k * sizeof(cand_t) + 255) & ~size_t(255);
+}
+
 size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k)
 {
-    return (size_t)nq * f32_splits(n, nq, d, k) * k * sizeof(cand_t);
+    return f32_lists_bytes(n, nq, d, k) + f32_filter_plan(n, nq, d, k).total;
 }
 
 hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
@@ -241,15 +317,39 @@ hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float
     const bool vec = ((uintptr_t)x % 16 == 0) && (ldx % 4 == 0);
     const unsigned blocks = (unsigned)(ceil_div(nq, qt) * S);
     hipError_t e;
+    // Larger batches: the matrix-core filter, direct sums of what it leaves, selection; the direct kernel
+    // then only works on query tiles that hold a query whose candidates did not fit.
+    const F32Filter fp = f32_filter_plan(n, nq, d, k);
+    const int32_t *only = nullptr;
+    if (fp.use) {
+        char *fws = (char *)ws + f32_lists_bytes(n, nq, d, k);
+        cand_t *cbuf = reinterpret_cast<cand_t *>(fws + fp.off_cbuf);
+        int32_t *ccnt = reinterpret_cast<int32_t *>(fws + fp.off_ccnt), *over = reinterpret_cast<int32_t *>(fws + fp.off_over);
+        int32_t *list = reinterpret_cast<int32_t *>(fws + fp.off_list);
+        e = launch_f32_filter(fp, x, n, ldx, q, nq, ldq, d, k, mode == MODE_F32_L2, fws, st);
+        if (e != hipSuccess) return e;
+        static_assert(DIST_REGIONS == F32_THREADS, "a thread per region");
+        if (fp.S2 > DIST_REGIONS) return hipErrorInvalidValue;
+        const int share = nq >= 2048 ? 1 : (int)(2048 / nq < 16 ? 2048 / nq : 16);   // workgroups per query: fill the chip
+        (vec ? f32_distances_kernel<true> : f32_distances_kernel<false>)<<<(unsigned)(nq * share), F32_THREADS,
+                                                                         (size_t)((d + 3) / 4) * 16, st>>>(
+            x, ldx, q, ldq, d, mode == MODE_F32_L2, fp.S2, fp.Cs, share, ccnt, cbuf);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = launch_collect_select(cbuf, ccnt, nq, fp.S2, fp.Cs, k, over, list, list + nq, ids, reinterpret_cast<int32_t *>(dists),
+                                  nullptr, mode, st);
+        if (e != hipSuccess) return e;
+        only = over;
+    }
     switch (qt) {
-    case 8: e = launch_f32_tile<8>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap); break;
-    case 4: e = launch_f32_tile<4>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap); break;
-    case 2: e = launch_f32_tile<2>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap); break;
-    default: e = launch_f32_tile<1>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap); break;
+    case 8: e = launch_f32_tile<8>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap, only); break;
+    case 4: e = launch_f32_tile<4>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap, only); break;
+    case 2: e = launch_f32_tile<2>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap, only); break;
+    default: e = launch_f32_tile<1>(vec, blocks, shmem, st, x, n, ldx, q, ldq, nq, d, k, mode, S, split_rows, lists, cap, only); break;
     }
     if (e != hipSuccess) return e;
     return launch_merge(lists, nq, S, k, nullptr, nullptr, nullptr, ids, reinterpret_cast<int32_t *>(dists),
-                        nullptr, mode, st, true);
+                        nullptr, mode, st, true, only);
 }
 
 }  // namespace lpq

@@ -1179,7 +1179,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
 // the value with wave-wide counts.
 template <int E>
 __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k,
-                                                            cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word)
+                                                            cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word,
+                                                            int32_t *__restrict__ kth_out)
 {
     const int lane = threadIdx.x & 63;
     if (zero_word && blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0;
@@ -1233,7 +1234,8 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
         kth = (int)lo;
     }
     // at least k items have E >= kth, hence key <= -2 kth
-    if (lane == 0) seeds[q] = (G < k || kth == INT32_MIN) ? CAND_NONE : make_cand(-2 * kth, 0xFFFFFFFFu);
+    if (lane == 0 && seeds) seeds[q] = (G < k || kth == INT32_MIN) ? CAND_NONE : make_cand(-2 * kth, 0xFFFFFFFFu);
+    if (lane == 0 && kth_out) kth_out[q] = G < k ? INT32_MIN : kth;
 }
 
 size_t lds_bytes(int ks, bool seed, int nw, bool rsplit, int nb, bool pack, bool big = false)
@@ -1518,16 +1520,16 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
 }
 
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
-                                int32_t *zero_word)
+                                int32_t *zero_word, int32_t *kth_out)
 {
     if (nq <= 0) return hipSuccess;
     if (G > 4096) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)ceil_div(nq, (int64_t)4);
-    if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word);
-    else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word);
-    else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word);
-    else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word);
-    else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word);
+    if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
+    else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
+    else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
+    else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
+    else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,521 @@
+// Matrix-core filter of the exact fp32 search.
+//
+// The exact search sums (q - x)^2 (or q x) directly in fp32, one multiply-add per value on the vector
+// units.  Almost all of that work rejects items that are nowhere near: this file does the rejecting on
+// the matrix cores and leaves the direct sums to the few items that may be among the k nearest.  The
+// results are the ones of the direct kernel bit for bit, because the final distances are formed by the
+// same operations in the same order (search_f32.hip) and the filter never loses an item that belongs:
+//
+//   score       s = q.x - |x|^2 / 2 (L2; larger = nearer) or q.x (inner product)
+//   split       q = qh + ql, x = xh + xl in bf16 (round to nearest), and
+//               acc = qh.xh + qh.xl + ql.xh accumulated in fp32
+//   error       |acc - q.x| <= 3 2^-18 sum |q x|  (what the split drops: ql.xl and the remainders)
+//                            + 3 d 2^-23 (sum |q x| + |x|^2 / 2)  (3 d accumulations, each off by an ulp)
+//               |x|^2 is off by d 2^-24 of itself, the directly summed distance by (d / 8 + 8) 2^-24 of
+//               itself, at most (d / 4 + 16) 2^-24 (|q|^2 + |x|^2) on the score's scale;
+//               sum |q x| <= (|q|^2 + |x|^2) / 2, so all of it together stays below
+//               C (|q|^2 + |x|^2) / 2   with   C = 2^-15 + d 2^-20
+//
+// so  acc - |x|^2 / 2 -+ C (|q|^2 + |x|^2) / 2  bounds an item's score from both sides, split into a part
+// per item and a part per query.  A seeding pass over a sample takes, per query, the k-th largest
+// group maximum of the lower bounds (at least k items reach it); the scan collects every item whose
+// upper bound does.  (An absolute 2^-110 covers products that underflow.)  Queries that collect too many (data whose distances are
+// tiny next to its norms), vectors beyond 1e30 in square and anything not finite go through the
+// direct kernel instead.
+//
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.5 -> 0.94 ms (the scan 0.81 = 0.97 PFLOP/s
+// of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  The scan is bound by LDS
+// traffic: a k-step of a wave reads eight fragments for twelve matrix instructions.
+//
+// Layout: workgroups of eight waves on tiles of 256 items x 64 WQ queries, as in search_mfma_stream.hip;
+// a stage is 32 features.  Items come from HBM in fp32 through registers (one stage ahead), are split
+// and written to LDS as two bf16 planes, their squared norms summed on the way; the queries, split
+// once per search, are copied asynchronously.
+#include <cmath>
+#include <type_traits>
+
+#include "mfma_common.h"
+#include "wave_ops.h"
+
+namespace lpq {
+
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v4b __attribute__((ext_vector_type(4)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+
+constexpr int FW = 8;                 // waves per workgroup
+constexpr int TILE_ROWS = 256;
+constexpr int KF = 32;                // features per stage
+constexpr int PB = KF * 2;            // bytes of a row in one plane of a stage
+constexpr int RUN = 16;               // a tile is 16 runs of 16 rows
+constexpr float HUGE_NORM = 1e30f;
+
+
+struct FilterIo {
+    const float *x;
+    int64_t n, ldx;
+    int d, dp;                // dp: d rounded up to whole stages
+    const __bf16 *qh, *ql;    // [nq_pad][dp] the queries' two planes
+    const float *qn;          // [nq_pad] squared norms
+    int64_t nq;
+    int qtiles, S;
+    int tiles;                // as in search_mfma_stream.hip: split s takes tiles s, s + S, ...
+    int64_t tile_stride, run_gap;
+    float h;                  // an item's bound is acc - h |x|^2
+    float c;                  // C above
+    int32_t *gmax;            // seeding pass: [nq_pad][G] group maxima (order-preserving images), G = S * SEG * 2 * (8 / WQ)
+    int SEG;
+    const int32_t *kth;       // scan: [nq] k-th largest group maximum
+    cand_t *cbuf;             // [nq][S][Cs] rows that may belong (the key half is filled in later)
+    int32_t *ccnt;            // [nq][S]
+    int Cs;
+};
+
+constexpr int FDUMPS = 32;
+constexpr size_t filter_lds_bytes(int wq, bool seed)
+{
+    return (size_t)2 * (TILE_ROWS + 64 * wq) * 2 * PB + 4 * TILE_ROWS * 4 + (size_t)64 * wq * 8 + 256 +
+           (seed ? 0 : (size_t)FW * FDUMPS * 80);
+}
+
+__device__ __forceinline__ void split4(v4f v, v4b &hi, v4b &lo)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        hi[e] = (__bf16)v[e];
+        lo[e] = (__bf16)(v[e] - (float)hi[e]);
+    }
+}
+
+// One wave per query row: its two planes (zero beyond d and for rows beyond nq) and its squared norm.
+__global__ __launch_bounds__(256) void split_queries_kernel(const float *__restrict__ q, int64_t ldq, int64_t nq, int64_t rows,
+                                                            int d, int dp, __bf16 *__restrict__ qh, __bf16 *__restrict__ ql,
+                                                            float *__restrict__ qn)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= rows) return;
+    float ss = 0.0f;
+    for (int c = lane; c < dp; c += 64) {
+        const float v = (r < nq && c < d) ? q[r * ldq + c] : 0.0f;
+        const __bf16 hi = (__bf16)v;
+        qh[r * dp + c] = hi;
+        ql[r * dp + c] = (__bf16)(v - (float)hi);
+        ss = fmaf(v, v, ss);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    if (lane == 0) qn[r] = ss;
+}
+
+template <bool SEED, int WQ, bool VEC>
+__global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int WR = FW / WQ, RB = WQ, QT = 64 * WQ;
+    constexpr int AP = TILE_ROWS * PB, BP = QT * PB;      // bytes of a plane: items, queries
+    constexpr int STAGE = 2 * AP + 2 * BP;                // xh, xl, qh, ql
+    constexpr int BC = 2 * BP / 1024;                     // query copies per stage: 16 rows of one plane each
+    constexpr int DUMPS = FDUMPS;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int wr = wave / WQ, wq = wave % WQ;
+
+    // each XCD gets a contiguous range of (split, query tile) pairs: the query tiles of a split share its L2
+    const int S = o.S, total = o.qtiles * S, per = total / 8, b = blockIdx.x;
+    const int wk = (b < per * 8) ? (b % 8) * per + b / 8 : b;
+    const int s = wk / o.qtiles, qt = wk % o.qtiles;
+
+    float *nx = reinterpret_cast<float *>(smem + 2 * STAGE);       // [4][256] squared norms, by tile & 3
+    float *thr_l = nx + 4 * TILE_ROWS;                             // [QT]
+    int *fill = reinterpret_cast<int *>(thr_l + QT);               // [QT]
+    int *bad = fill + QT;                                          // a row that is not finite, or huge, was seen
+    float *dval = reinterpret_cast<float *>(bad + 64) + wave * (DUMPS * 20);
+    v4i *dmeta = reinterpret_cast<v4i *>(dval + DUMPS * 16);
+    const int64_t q_tile = (int64_t)qt * QT, q_first = q_tile + wq * 64;
+
+    if (!SEED) {
+        for (int i = tid; i < QT; i += FW * 64) {
+            float t = NAN;                                         // nothing compares: a slot that never collects
+            if (q_tile + i < o.nq && o.qn[q_tile + i] <= HUGE_NORM) {
+                const int32_t kth = o.kth[q_tile + i];
+                t = kth == INT32_MIN ? -INFINITY
+                                     : sortable_to_float(kth) - o.c * o.qn[q_tile + i] * 1.00001f - 0x1p-110f;
+            }
+            thr_l[i] = t;
+            fill[i] = 0;
+        }
+    }
+    if (tid == 0) *bad = 0;
+    __syncthreads();
+    float thr[2] = {NAN, NAN}, gm[2] = {-INFINITY, -INFINITY};
+    if (!SEED) { thr[0] = thr_l[wq * 64 + col]; thr[1] = thr_l[wq * 64 + 32 + col]; }
+
+    const int nt = (o.tiles > s) ? (o.tiles - s + S - 1) / S : 0;
+    const int kst = o.dp / KF, T = nt * kst;
+
+    // ---- items: registers -> two planes in LDS --------------------------------------------------
+    // Eight lanes share a row of a stage (16 bytes each); a wave loads rows wave * 32 + 8 i + lane / 8.
+    // Chunk c (16 bytes of a plane) of row r sits in slot c ^ ((r >> 2) & 3).
+    const int lrow = lane >> 3, lcol = (lane & 7) * 4;
+    v4f pre[2][4];                    // stages on their way, stage t in set t & 1
+    const float *src[4];
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    int ft = 0, fk = 0;               // tile (of this split) and stage of the tile that is fetched next
+    int pt = 0, pk = 0;               // ... and that goes to LDS next
+    auto fetch_tile = [&]() {
+        const int64_t t0 = ((int64_t)s + (int64_t)ft * S) * o.tile_stride;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int64_t row = t0 + (int64_t)(wave * 2 + (i >> 1)) * o.run_gap + (i & 1) * 8 + lrow;
+            row = row < o.n ? row : o.n - 1;     // rows past the end: any row, rejected later
+            src[i] = o.x + row * o.ldx + lcol;
+        }
+    };
+    auto fetch = [&](v4f (&to)[4]) {  // loads of stage (ft, fk); at least four of them
+        const int k0 = fk * KF;
+        if (VEC && k0 + KF <= o.d) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) to[i] = *reinterpret_cast<const v4f *>(src[i] + k0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) to[i][e] = (k0 + lcol + e < o.d) ? src[i][k0 + e] : 0.0f;
+        }
+        if (++fk == kst) {
+            fk = 0;
+            if (++ft < nt) fetch_tile();
+        }
+    };
+    auto put = [&](const v4f (&from)[4], int slot) {   // a fetched stage goes to LDS
+        unsigned char *base = smem + slot * STAGE;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = wave * 32 + i * 8 + lrow;
+            const int at = r * PB + (((lane & 7) >> 1) ^ ((r >> 2) & 3)) * 16 + (lane & 1) * 8;
+            v4b hi, lo;
+            split4(from[i], hi, lo);
+            *reinterpret_cast<v4b *>(base + at) = hi;
+            *reinterpret_cast<v4b *>(base + AP + at) = lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[i] = fmaf(from[i][e], from[i][e], part[i]);
+        }
+    };
+    auto put_done = [&]() {           // ... and, at the end of a tile, its rows' norms
+        if (++pk == kst) {
+            float *dst = nx + (pt & 3) * TILE_ROWS;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float p = part[i];
+                p += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(p)));
+                p += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(p)));
+                p += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(p)));
+                if ((lane & 7) == 0) dst[wave * 32 + i * 8 + lrow] = p;
+                if (!SEED && !(p <= HUGE_NORM)) *bad = 1;
+                part[i] = 0.0f;
+            }
+            pk = 0;
+            ++pt;
+        }
+    };
+
+    // ---- queries: asynchronous copies -----------------------------------------------------------
+    // Copy instruction i of a stage brings 64 bytes of 16 rows of one plane.
+    const unsigned lds0 = lds_offset(smem);
+    const unsigned q_off = (unsigned)(((lane >> 2) * o.dp) * 2 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16));
+    int qk = 0;
+    auto copy_queries = [&](int slot) {
+#pragma unroll
+        for (int e = 0; e < (BC + FW - 1) / FW; ++e) {
+            const int i = wave + e * FW, plane = i / (QT / 16), r16 = i % (QT / 16);
+            const __bf16 *base = (plane ? o.ql : o.qh) + (q_tile + r16 * 16) * o.dp + qk * KF;
+            const unsigned dst = lds0 + slot * STAGE + 2 * AP + plane * BP + r16 * 1024;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(q_off), "s"(base) : "memory");
+        }
+        qk = qk + 1 == kst ? 0 : qk + 1;
+    };
+    static_assert(BC % FW == 0, "every wave copies the same number of times");
+
+    // ---- fragments ------------------------------------------------------------------------------
+    const int sw = (half ^ ((col >> 2) & 3)) * 16;
+    const int a_off = (wr * RB * 32 + col) * PB + sw, b_off = 2 * AP + (wq * 64 + col) * PB + sw;
+    v8b A[2][2][RB], B[2][2][2];      // [k-step][plane][block]
+#define LPQF_LOAD(SLOT, KSTEP, F)                                                                       \
+    do {                                                                                                \
+        const unsigned char *sb_ = smem + (SLOT) * STAGE;                                               \
+        const unsigned char *pa_ = sb_ + (a_off ^ ((KSTEP) * 32)), *pb_ = sb_ + (b_off ^ ((KSTEP) * 32)); \
+        _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                 \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j) B[F][p][j] = *reinterpret_cast<const v8b *>(pb_ + p * BP + j * 32 * PB); \
+            _Pragma("unroll") for (int i = 0; i < RB; ++i) A[F][p][i] = *reinterpret_cast<const v8b *>(pa_ + p * AP + i * 32 * PB); \
+        }                                                                                               \
+    } while (0)
+    v16f acc[RB][2];
+#define LPQF_MFMA(F)                                                                                    \
+    _Pragma("unroll") for (int pp = 0; pp < 3; ++pp)   /* xh qh, xh ql, xl qh */                        \
+        _Pragma("unroll") for (int i = 0; i < RB; ++i)                                                  \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j)                                               \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[F][pp == 2][i], B[F][pp == 1][j], acc[i][j], 0, 0, 0)
+
+#define LPQF_ORDER() __builtin_amdgcn_sched_barrier(0)
+    const int G = S * o.SEG * 2 * WR;
+    auto flush_segment = [&](int seg) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            o.gmax[(size_t)(q_first + j * 32 + col) * G + (((size_t)s * o.SEG + seg) * WR + wr) * 2 + half] = float_to_sortable(gm[j]);
+            gm[j] = -INFINITY;
+        }
+    };
+    if (SEED) {   // segments this split never reaches keep the neutral value
+        for (int g = 0; g < o.SEG; ++g) flush_segment(g);
+    }
+    cand_t *cbase = SEED ? nullptr : o.cbuf + ((size_t)q_tile * S + s) * o.Cs;
+    const size_t qstride = (size_t)S * o.Cs;
+    auto drain = [&](int dumps) {     // queued scores that reach their query's threshold go to its region
+        wave_lds_sync();
+        for (int base = 0; base < dumps * 16; base += 64) {
+            const int at = base + lane;
+            if (at < dumps * 16) {
+                const float u = dval[at];
+                const v4i m4 = dmeta[at >> 4];
+                const int ql = m4[1] & 255, r = at & 15;
+                const int64_t row = (int64_t)(unsigned)m4[0] + 8 * (r >> 2) + 4 * (m4[1] >> 8) + (r & 3);
+                if (u >= thr_l[ql] && row < o.n) {
+                    const int pos = atomicAdd(&fill[ql], 1);
+                    if (pos < o.Cs) cbase[(size_t)ql * qstride + pos] = (cand_t)row;
+                }
+            }
+        }
+        wave_lds_sync();
+    };
+
+    if (T > 0) {
+        fetch_tile();
+        fetch(pre[0]);
+        copy_queries(0);
+        put(pre[0], 0);
+        put_done();
+        if (T > 1) copy_queries(1);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        if (T > 1) fetch(pre[1]);
+        if (T > 2) fetch(pre[0]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        LPQF_LOAD(0, 0, 0);
+    }
+    int t = 0, seg = 0, partial = 0;
+    // Stage t, whose parity P is a constant: the sets of registers cannot be indexed at run time.
+    auto stage = [&](auto parity) {
+        constexpr int P = decltype(parity)::value;
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // the first k-step's fragments are there; do not wait for the second's below
+        LPQF_LOAD(P, 1, 1);
+        LPQF_MFMA(0);
+        // stage t + 1 goes into the other slot, which was read out before the last barrier (after the
+        // last stage: stale values that nobody reads)
+        put(pre[P ^ 1], P ^ 1);
+        LPQF_ORDER();
+        if (t + 1 < T) put_done();
+        // My reads of stage t, my writes and my query copies of stage t + 1 are complete; of the vector
+        // memory operations only the four or more loads of stage t + 2 may be newer than those copies.
+        if (t + 2 < T) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        LPQF_LOAD(P ^ 1, 0, 0);               // (after the last stage: whatever the slot holds, unused)
+        if (t + 2 < T) copy_queries(P);
+        if (t + 3 < T) fetch(pre[P ^ 1]);
+        LPQF_MFMA(1);
+        ++t;
+    };
+#pragma clang loop unroll(disable)
+    for (int tile = 0; tile < nt; ++tile) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+        int k = kst;
+        if (t & 1) { stage(std::integral_constant<int, 1>{}); --k; }
+#pragma clang loop unroll(disable)
+        for (; k >= 2; k -= 2) {
+            stage(std::integral_constant<int, 0>{});
+            stage(std::integral_constant<int, 1>{});
+        }
+        if (k) stage(std::integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);        // nothing of the contraction drifts down into the epilogue
+        const int64_t row0 = ((int64_t)s + (int64_t)tile * S) * o.tile_stride;
+        int dumps = 0;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const float *np = nx + (tile & 3) * TILE_ROWS + (wr * RB + i) * 32 + 4 * half;
+            v4f nv[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) nv[g] = *reinterpret_cast<const v4f *>(np + 8 * g);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                v16f v = acc[i][j];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[e] = fmaf(-o.h, nv[e >> 2][e & 3], v[e]);
+                float m = v[0];
+#pragma unroll
+                for (int e = 1; e < 16; ++e) m = fmaxf(m, v[e]);
+                if (SEED) {
+                    gm[j] = fmaxf(gm[j], m);
+                } else {
+                    unsigned long long mask = __ballot(m >= thr[j]);
+                    while (__builtin_expect(mask != 0, 0)) {   // queue the 16 scores of the lanes that pass
+                        int lane_ = lane;
+                        asm volatile("" : "+v"(lane_));
+                        const int at = dumps + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                                         __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                        const bool put_ = ((mask >> lane_) & 1) && at < DUMPS;
+                        if (put_) {
+                            v4f *dst = reinterpret_cast<v4f *>(dval + at * 16);
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) dst[g] = v4f{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                            dmeta[at] = v4i{(int)(row0 + (wr * RB + i) * 32), (wq * 64 + j * 32 + (lane_ & 31)) | ((lane_ >> 5) << 8), 0, 0};
+                        }
+                        const unsigned long long done = __ballot(put_);
+                        dumps += __popcll(done);
+                        mask &= ~done;
+                        if (mask) { drain(dumps); dumps = 0; }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (!SEED && dumps) drain(dumps);
+        if (SEED) {   // tile i belongs to segment i SEG / nt
+            partial += o.SEG;
+            if (partial >= nt || tile + 1 == nt) flush_segment(seg);
+            for (; partial >= nt; partial -= nt) ++seg;
+        }
+    }
+#undef LPQF_LOAD
+#undef LPQF_MFMA
+#undef LPQF_ORDER
+
+    if (!SEED) {
+        __syncthreads();
+        // a row the bounds do not hold for: all queries of the tile overflow
+        for (int i = tid; i < QT; i += FW * 64)
+            if (q_tile + i < o.nq) o.ccnt[(size_t)(q_tile + i) * S + s] = *bad ? o.Cs + 1 : fill[i];
+    }
+}
+
+template <bool SEED, int WQ>
+hipError_t launch_filter(const FilterIo &o, hipStream_t st)
+{
+    const bool vec = ((uintptr_t)o.x % 16 == 0) && (o.ldx % 4 == 0);
+    auto kern = vec ? filter_f32_kernel<SEED, WQ, true> : filter_f32_kernel<SEED, WQ, false>;
+    static bool attr_set[2] = {false, false};
+    if (!attr_set[vec]) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set[vec] = true;
+    }
+    kern<<<(unsigned)(o.qtiles * o.S), FW * 64, filter_lds_bytes(WQ, SEED), st>>>(o);
+    return hipGetLastError();
+}
+
+size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+}  // namespace
+
+F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
+{
+    F32Filter p;
+    // (Few queries too: the direct kernel sorts its candidate buffers several times per workgroup, 0.2 ms
+    // whatever the size.  One query, k = 10: 10 000 x 128 0.23 -> 0.04 ms, 1M x 128 0.28 -> 0.16.)
+    if (nq < 1 || n < 4096) return p;
+    p.wq = nq <= 64 ? 1 : 2;
+    const int qt = 64 * p.wq, row_waves = FW / p.wq;
+    p.qtiles = (int)ceil_div(nq, qt);
+    p.nq_pad = round_up(nq, 128);
+    p.dp = (int)round_up(d, KF);
+    // The sample costs a contraction per row and query (or, for few queries, the bytes of its rows), each
+    // item it lets through - about k n / rows per query - the bytes of a row: least at rows ~ sqrt(k n)
+    // (~ sqrt(nq k n); the factors are measured, 1M x 128: one query 0.16 ms with 19 000 rows, 0.18 with 8300).
+    const double per = 1.5 * std::sqrt((double)nq);
+    const double by_cost = (per < 6.0 ? 6.0 : (per < 13.0 ? per : 13.0)) * std::sqrt((double)k * (double)n);
+    const double by_room = (double)k * (double)n / 1200.0;
+    int64_t seed = (int64_t)(by_cost > by_room ? by_cost : by_room);
+    if (seed > n / 4) seed = n / 4;
+    if (seed < 64 * (int64_t)k) seed = 64 * (int64_t)k;
+    p.seed_tiles = (int)ceil_div(seed, TILE_ROWS);
+    if ((int64_t)p.seed_tiles * TILE_ROWS * 2 > n) return p;   // too few items to sample: the direct kernel
+    const int slots = 256;                                      // one workgroup per CU
+    int s1 = slots / p.qtiles;
+    if (s1 > p.seed_tiles) s1 = p.seed_tiles;
+    if (s1 > 2048 / (2 * row_waves)) s1 = 2048 / (2 * row_waves);
+    p.S1 = s1 < 1 ? 1 : s1;
+    p.seed_tiles = (int)ceil_div(p.seed_tiles, p.S1) * p.S1;
+    while ((int64_t)p.seed_tiles * TILE_ROWS > n) p.seed_tiles -= p.S1;
+    if (p.seed_tiles < 1) return p;
+    p.run_stride = n / (16 * (int64_t)p.seed_tiles);
+    p.SEG = mfma_seed_segments(p.S1, k, row_waves);
+    p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
+    if (p.G < k || p.G > 4096) return p;
+    const int64_t tiles = ceil_div(n, TILE_ROWS);
+    int64_t s2 = slots / p.qtiles;
+    if (s2 > tiles) s2 = tiles;
+    p.S2 = (int)(s2 < 1 ? 1 : s2);
+    const double expect = 1.5 * (double)k * (double)n / ((double)p.seed_tiles * TILE_ROWS);
+    if (expect > 3000.0) return p;                              // the selection sorts up to 4096
+    int64_t cs = 64;
+    while ((double)cs < 3.0 * expect / p.S2 && cs < 4096) cs <<= 1;
+    p.Cs = (int)cs;
+    size_t o = 0;
+    p.off_qh = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
+    p.off_ql = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
+    p.off_qn = o;   o = align256(o + (size_t)p.nq_pad * 4);
+    p.off_gmax = o; o = align256(o + (size_t)p.nq_pad * p.G * 4);
+    p.off_kth = o;  o = align256(o + (size_t)nq * 4);
+    p.off_cbuf = o; o = align256(o + (size_t)nq * p.S2 * p.Cs * sizeof(cand_t));
+    p.off_ccnt = o; o = align256(o + (size_t)nq * p.S2 * 4);
+    p.off_over = o; o = align256(o + (size_t)nq * 4);
+    p.off_list = o; o = align256(o + ((size_t)nq + 1) * 4);
+    p.total = o;
+    p.use = true;
+    return p;
+}
+
+hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
+                             int d, int k, bool l2, char *ws, hipStream_t st)
+{
+    __bf16 *qh = reinterpret_cast<__bf16 *>(ws + p.off_qh), *ql = reinterpret_cast<__bf16 *>(ws + p.off_ql);
+    float *qn = reinterpret_cast<float *>(ws + p.off_qn);
+    int32_t *gmax = reinterpret_cast<int32_t *>(ws + p.off_gmax), *kth = reinterpret_cast<int32_t *>(ws + p.off_kth);
+    int32_t *count = reinterpret_cast<int32_t *>(ws + p.off_list) + nq;
+    split_queries_kernel<<<(unsigned)ceil_div(p.nq_pad, (int64_t)4), 256, 0, st>>>(q, ldq, nq, p.nq_pad, d, p.dp, qh, ql, qn);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    FilterIo o = {};
+    o.x = x; o.n = n; o.ldx = ldx; o.d = d; o.dp = p.dp;
+    o.qh = qh; o.ql = ql; o.qn = qn; o.nq = nq; o.qtiles = p.qtiles;
+    o.c = 0x1p-15f + (float)d * 0x1p-20f;
+    // seeding pass: lower bounds of the scores of a sample (runs of 16 rows spread over the corpus)
+    o.S = p.S1; o.SEG = p.SEG; o.gmax = gmax;
+    o.tiles = p.seed_tiles; o.tile_stride = p.run_stride; o.run_gap = (int64_t)p.seed_tiles * p.run_stride;
+    if (p.run_stride < RUN || ((int64_t)16 * p.seed_tiles - 1) * p.run_stride + RUN > n) return hipErrorInvalidValue;
+    o.h = l2 ? 0.5f * (1.0f + o.c) : 0.5f * o.c;
+    e = p.wq == 1 ? launch_filter<true, 1>(o, st) : launch_filter<true, 2>(o, st);
+    if (e != hipSuccess) return e;
+    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, count, kth);
+    if (e != hipSuccess) return e;
+    // scan: every item whose upper bound reaches the k-th lower bound
+    o.S = p.S2; o.kth = kth;
+    o.cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf); o.ccnt = reinterpret_cast<int32_t *>(ws + p.off_ccnt); o.Cs = p.Cs;
+    o.tiles = (int)ceil_div(n, (int64_t)TILE_ROWS); o.tile_stride = TILE_ROWS; o.run_gap = RUN;
+    o.h = l2 ? 0.5f * (1.0f - o.c) : -0.5f * o.c;
+    return p.wq == 1 ? launch_filter<false, 1>(o, st) : launch_filter<false, 2>(o, st);
+}
+
+}  // namespace lpq
