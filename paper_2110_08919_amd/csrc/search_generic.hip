@@ -499,76 +499,96 @@ __global__ __launch_bounds__(256) void collect_refine_kernel(
     if (tid == 0) bounds_out[q] = (kth == CAND_NONE) ? bounds_in[q] : kth + 1;
 }
 
-// Merge of lists that are each sorted ascending, for small k and many lists: one workgroup per
-// query; every wave takes k times the smallest head among its share of the lists (each lane owns
-// the lists first + lane, first + lane + 64, ...), then wave 0 does the same over the four wave
-// results.  Duplicated values come out once per copy, as a sort would give them.
-// A lane keeps the head and the position of each of its LPL lists in registers, so a round costs the
-// winner one LDS read (the next entry of the list it took from) instead of a walk over positions and
-// heads in LDS (512 lists of 10: 16.9 -> see the profile of the small-batch workload).
-template <int LPL>
+// Merge of lists that are each sorted ascending, for k <= 32 and up to 1024 lists: one workgroup per
+// query, LPL lists per thread.  The k-th smallest of the threads' smallest heads bounds the k-th best
+// from above (k threads own one candidate at least as good), and only the candidates up to it - found
+// by walking the few lists whose head is - are gathered and sorted: at most k threads' LPL lists of k.
+// Two register sorts of 64 or 128 candidates give the bound.  The lists are not staged anywhere: a list
+// costs one 8-byte load unless its head passes.  Measured on 512 lists of 10: 14.3 -> 6 us for one
+// query against k rounds of "smallest head" per wave over all lists held in LDS.
+constexpr int MERGE_SORTED_BUF = 4096;      // k * LPL * k candidates at most
+template <int LPL, int E>
 __global__ __launch_bounds__(256) void merge_sorted_kernel(
     const cand_t *__restrict__ lists, int P, int k, const cand_t *__restrict__ extra,
     cand_t *__restrict__ out_lists, cand_t *__restrict__ seeds_out, int32_t *__restrict__ ids,
     int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    cand_t *buf = reinterpret_cast<cand_t *>(smem);     // [MERGE_SORTED_BUF]
+    __shared__ cand_t best[64 * E], bound;              // k <= 16 E smallest of each wave
+    __shared__ int count;
     const int Pt = P + (extra ? 1 : 0);
-    cand_t *buf = reinterpret_cast<cand_t *>(smem);     // [Pt][k]
-    cand_t *wres = buf + (size_t)Pt * k;                // [4][k]
     const int64_t q = blockIdx.x;
-    const int m = P * k, mt = Pt * k;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < mt; i += 256) buf[i] = (i < m) ? lists[q * m + i] : extra[q * k + (i - m)];
-    __syncthreads();
-
-    const int lpw = (Pt + 3) >> 2;                      // lists per wave, <= 64 LPL
-    const int first = wave * lpw, last = (first + lpw < Pt) ? first + lpw : Pt;
-    cand_t head[LPL];
-    int pos[LPL];
+    cand_t head[LPL], mn = CAND_NONE;
 #pragma unroll
     for (int j = 0; j < LPL; ++j) {
-        const int l = first + lane + 64 * j;
-        pos[j] = 0;
-        head[j] = (l < last) ? buf[(size_t)l * k] : CAND_NONE;
+        const int l = threadIdx.x + 256 * j;
+        head[j] = l < P ? lists[(q * P + l) * k] : (l < Pt ? extra[q * k] : CAND_NONE);
+        mn = head[j] < mn ? head[j] : mn;
     }
-    for (int r = 0; r < k; ++r) {
-        cand_t best = head[0];
+    {
+        cand_t v[1] = {mn};
+        wave_sort<1>(v, lane);                          // lane i: the wave's i-th smallest
+        if (lane < 16 * E) best[wave * 16 * E + lane] = v[0];
+    }
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    if (wave == 0) {
+        cand_t v[E];
 #pragma unroll
-        for (int j = 1; j < LPL; ++j) best = head[j] < best ? head[j] : best;
-        const cand_t mn = wave_min_cand(best);
-        const int win = __ffsll((unsigned long long)__ballot(best == mn)) - 1;
-        if (lane == win) {
-            wres[wave * k + r] = mn;
-            if (mn != CAND_NONE) {
-                bool taken = false;                     // the first of my lists whose head is the minimum moves on
+        for (int j = 0; j < E; ++j) v[j] = best[E * lane + j];
+        wave_sort<E>(v, lane);
 #pragma unroll
-                for (int j = 0; j < LPL; ++j) {
-                    if (!taken && head[j] == mn) {
-                        taken = true;
-                        pos[j] += 1;
-                        head[j] = (pos[j] < k) ? buf[(size_t)(first + lane + 64 * j) * k + pos[j]] : CAND_NONE;
-                    }
-                }
+        for (int j = 0; j < E; ++j)
+            if (E * lane + j == k - 1) bound = v[j];
+    }
+    __syncthreads();
+    const cand_t top = bound;
+#pragma unroll
+    for (int j = 0; j < LPL; ++j) {
+        if (head[j] <= top && head[j] != CAND_NONE) {
+            const int l = threadIdx.x + 256 * j;
+            const cand_t *list = l < P ? lists + (q * P + l) * k : extra + q * k;
+            cand_t c = head[j];
+            for (int i = 1;; ++i) {
+                const int at = atomicAdd(&count, 1);
+                if (at < MERGE_SORTED_BUF) buf[at] = c;
+                if (i == k) break;
+                c = list[i];
+                if (c > top || c == CAND_NONE) break;
             }
         }
     }
     __syncthreads();
-    if (wave != 0) return;
-    int p2 = 0;
-    cand_t best = (lane < 4) ? wres[lane * k] : CAND_NONE;
-    for (int r = 0; r < k; ++r) {
-        const cand_t mn = wave_min_cand(best);
-        const int win = __ffsll((unsigned long long)__ballot(best == mn)) - 1;
-        if (lane == win) {
-            if (out_lists) out_lists[q * k + r] = mn;
-            if (seeds_out && r == k - 1) seeds_out[q] = mn;
-            if (ids) emit_result(mn, q * k + r, q, ids, dists, qnorms, metric);
-            if (lane < 4 && mn != CAND_NONE) {
-                ++p2;
-                best = (p2 < k) ? wres[lane * k + p2] : CAND_NONE;
-            }
-        }
+    const int m = count < MERGE_SORTED_BUF ? count : MERGE_SORTED_BUF;   // >= k wherever the lists hold k candidates
+    auto emit = [&](cand_t c, int r) {
+        if (r >= k) return;
+        if (out_lists) out_lists[q * k + r] = c;
+        if (seeds_out && r == k - 1) seeds_out[q] = c;
+        if (ids) emit_result(c, q * k + r, q, ids, dists, qnorms, metric);
+    };
+    auto sorted = [&](auto tag) {                       // up to 64 S candidates, by one wave in registers
+        constexpr int S = decltype(tag)::value;
+        cand_t v[S];
+#pragma unroll
+        for (int j = 0; j < S; ++j) { const int i = j * 64 + lane; v[j] = i < m ? buf[i] : CAND_NONE; }
+        wave_sort<S>(v, lane);
+#pragma unroll
+        for (int j = 0; j < S; ++j) emit(v[j], lane * S + j);
+    };
+    if (m <= 64) {
+        if (wave == 0) sorted(std::integral_constant<int, 1>{});
+    } else if (m <= 128) {
+        if (wave == 0) sorted(std::integral_constant<int, 2>{});
+    } else if (m <= 256) {
+        if (wave == 0) sorted(std::integral_constant<int, 4>{});
+    } else {
+        const int cap = next_pow2(m);
+        for (int i = m + threadIdx.x; i < cap; i += 256) buf[i] = CAND_NONE;
+        __syncthreads();
+        block_bitonic_sort(buf, cap);
+        for (int r = threadIdx.x; r < k; r += 256) emit(buf[r], r);
     }
 }
 
@@ -606,15 +626,8 @@ namespace {
 
 int merge_max_lists(int k) { return 4096 / k - 1; }
 
-// Lists of k that are each sorted and short (k <= 32) merge by repeated extraction, which needs
-// no power-of-two buffer: as many lists as 128 KB of LDS hold, at most 1024.
-static size_t merge_sorted_lds(int lists, int k) { return (size_t)(lists + 4) * k * sizeof(cand_t); }
-int merge_max_sorted_lists(int k)
-{
-    if (k > 32) return merge_max_lists(k);
-    int p = (int)((131072 - 32 * (size_t)k) / (8 * (size_t)k + 4)) - 1;   // one spare for an extra list
-    return p > 1024 ? 1024 : p;
-}
+// Lists of k that are each sorted and short (k <= 32): at most 1024 of them, less one for an extra list.
+int merge_max_sorted_lists(int k) { return k > 32 ? merge_max_lists(k) : 1023; }
 
 hipError_t launch_collect_refine(const cand_t *cbuf, const int32_t *ccnt, int64_t nq, int SS, int Cs, int k,
                                  const int32_t *over, const int32_t *qcount, int min_flagged, const cand_t *bounds_in,
@@ -685,26 +698,20 @@ hipError_t launch_merge(const cand_t *lists, int64_t nq, int P, int k, const can
 {
     if (nq <= 0) return hipSuccess;
     const int total = P * k + (extra_lists ? k : 0);
-    if (!only && !gate_count && sorted_lists && k <= 32 && total >= 1024 && P <= merge_max_sorted_lists(k)) {   // many short sorted lists
-        const int Pt = P + (extra_lists ? 1 : 0);
-        const size_t lds = merge_sorted_lds(Pt, k);
-        const int lpl = (int)ceil_div(ceil_div(Pt, 4), 64);   // lists a lane owns
-        static bool attr_set[4] = {false, false, false, false};   // per instantiation
-        auto launch = [&](auto kern, int slot) -> hipError_t {
-            if (!attr_set[slot]) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-                if (e != hipSuccess) return e;
-                attr_set[slot] = true;
-            }
+    // sorted lists of up to 32 (a sort of everything is as fast while it stays small: 39 lists of 10)
+    if (!only && !gate_count && sorted_lists && k <= 32 && total > 256 && P <= merge_max_sorted_lists(k)) {
+        const size_t lds = MERGE_SORTED_BUF * sizeof(cand_t);
+        const int lpl = (int)ceil_div(P + (extra_lists ? 1 : 0), 256);   // lists a thread owns
+        auto launch = [&](auto kern) -> hipError_t {
             kern<<<(unsigned)nq, 256, lds, st>>>(lists, P, k, extra_lists, out_lists, seeds_out, ids, dists, qnorms, metric);
             return hipGetLastError();
         };
-        if (lpl <= 1) return launch(merge_sorted_kernel<1>, 0);
-        if (lpl <= 2) return launch(merge_sorted_kernel<2>, 1);
-        if (lpl <= 4) return launch(merge_sorted_kernel<4>, 2);
-        if (lpl <= 8) return launch(merge_sorted_kernel<8>, 3);
-        return hipErrorInvalidValue;   // more than 2048 lists: merge_max_sorted_lists allows 1024
+        if (k <= 16) {
+            if (lpl <= 1) return launch(merge_sorted_kernel<1, 1>);
+            return lpl <= 2 ? launch(merge_sorted_kernel<2, 1>) : launch(merge_sorted_kernel<4, 1>);
+        }
+        if (lpl <= 1) return launch(merge_sorted_kernel<1, 2>);
+        return lpl <= 2 ? launch(merge_sorted_kernel<2, 2>) : launch(merge_sorted_kernel<4, 2>);
     }
     const int cap = next_pow2(total < 2 ? 2 : total);
     if (cap > 4096) return hipErrorInvalidValue;
