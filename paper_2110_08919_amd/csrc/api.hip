@@ -535,6 +535,10 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
     // Lists of 11 to 16 entries: the 16-entry register lists cost more per accepted candidate than
     // collecting does; collecting measured 11 to 40 % faster at every batch size (d = 64 to 128).
     const bool long_lists = coll && k > 10;
+    // Batches of 65 to 256 queries on corpora of up to a million rows: the register lists fill from nothing
+    // in every split (10 000 x 128, 100 queries: 0.068 ms against 0.041 collecting; 50 000: 0.043 / 0.039; 300 000,
+    // 200 queries: 0.055 / 0.052; even at 1M; 4M x 64, 256 queries: 0.100 / 0.110, left to the lists).
+    const bool few_rows = coll && nq > 64 && n <= 1000000;
     // Packed rows: the row-split register-list kernel (callers tile the queries by 64), or for large
     // batches the collecting scan over all queries at once; the generic kernel on request.
     // (lists of more than 16 entries: the collecting scan at every batch size; rows of 32 packed
@@ -544,7 +548,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
     if (idx->packed) p.mode = want == 1 ? PLAN_GENERIC : (packed_collect ? PLAN_MFMA_COLLECT
                                                           : (regs ? PLAN_MFMA_REG : PLAN_GENERIC));
     else if (want == 3 && coll) p.mode = PLAN_MFMA_COLLECT;
-    else if (want != 1 && want != 4 && (wide || long_rows || long_lists)) p.mode = PLAN_MFMA_COLLECT;
+    else if (want != 1 && want != 4 && (wide || long_rows || long_lists || few_rows)) p.mode = PLAN_MFMA_COLLECT;
     else if (want != 1 && regs) p.mode = PLAN_MFMA_REG;
     else if (want != 1 && want != 4 && coll) p.mode = PLAN_MFMA_COLLECT;
     else if (want != 1 && mfma_lds_supported(idx->d_pad, k)) p.mode = PLAN_MFMA_LDS;
@@ -593,8 +597,9 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             if (stream) by_cost *= std::sqrt(128.0 / (double)idx->d);
             const double by_room = (double)k * (double)n / 1500.0;
             const double want_rows = by_cost > by_room ? by_cost : by_room;
-            // (k beyond 512: half the corpus, or the ~4.6 k candidates a quarter lets through would not fit)
-            const int64_t most = k > 512 ? n / 2 : n / 4;
+            // (k beyond 512: half the corpus, or the ~4.6 k candidates a quarter lets through would not fit;
+            // streamed rows up to two fifths: 33 527 x 904, 7013 queries, k = 76: 0.482 -> 0.450 ms)
+            const int64_t most = k > 512 ? n / 2 : (stream ? n / 5 * 2 : n / 4);
             seed = want_rows > (double)most ? most : (int64_t)want_rows;
         }
     }
@@ -652,22 +657,33 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
         }
     }
     const int64_t tiles_q = ceil_div(nq > 0 ? nq : 1, qt);
-    const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : 512;
+    // Fewest rows of a split.  Small corpora need every workgroup they can get: 10 000 x 128, k = 10, 1000
+    // queries: 0.104 ms with splits of 512 rows, 0.065 with 256, 0.054 with 128; 100 queries 0.065 -> 0.041;
+    // 30 000 x 128, 100 queries, k = 100: 0.127 -> 0.082; 64 rows gain nothing more.
+    // (Packed rows: from 64K items on 128 splits are enough, more only spread the candidates thinner.)
+    const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : (idx->packed && n >= 65536 ? 512 : 128);
     if (seed) {
         // group maxima per query: 2 per split and segment (8 when rows are split), at most 2048 (4096 for k > 512)
-        p.S1 = splits_for(seed, tiles_q, min_rows, slots_now, gmode ? (p.rsplit ? 256 : 1024) : merge_max_lists(k));
+        // (row-split launches: up to 128 splits; with 256 the 2048 maxima cost the threshold kernel 3 us more
+        // than the pass gains)
+        p.S1 = splits_for(seed, tiles_q, min_rows, slots_now, gmode ? (p.rsplit ? 128 : 1024) : merge_max_lists(k));
         if (p.stream) {
             // tiles of 256 rows made of runs of 16 rows spread evenly over the corpus
             const int row_waves = mfma_stream_row_waves(nq);
             const int most = 2048 / (2 * row_waves);
             if (p.S1 > most) p.S1 = most;
+            const SampleShape shape = sample_that_covers(n, ceil_div(seed, 256), 16, p.S1);
+            p.S1 = shape.splits;
             p.SEG = mfma_seed_segments(p.S1, k, row_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
-            p.seed_tiles = (int)ceil_div(ceil_div(seed, 256), p.S1) * p.S1;
+            p.seed_tiles = (int)shape.per_split * p.S1;
             if ((int64_t)p.seed_tiles * 256 > n) p.seed_tiles = (int)(seed / 256);
             p.run_stride = n / (16 * (int64_t)p.seed_tiles);
             seed = (int64_t)p.seed_tiles * 256;
         } else if (gmode) {
+            SampleShape shape = {p.S1, ceil_div(seed / 64, p.S1)};
+            if (!p.rsplit && !long_scan) shape = sample_that_covers(n, seed / 64, 8, p.S1);   // runs of 8 rows, see below
+            p.S1 = shape.splits;
             p.SEG = mfma_seed_segments(p.S1, k, p.rs_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, p.rs_waves);
             // systematic sample: one stage every seed_stride rows, shared out over the S1 splits
@@ -683,7 +699,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             // (For k > 16 on a corpus sorted by norm a split's groups then span wide slices of the order
             // and up to a tenth of the queries overflow; the further rounds of the scan take those.)
             if (!p.rsplit && !long_scan) {
-                const int64_t pstages = ceil_div(stages, p.S1);                 // as many rows as the stage-wise sample
+                const int64_t pstages = shape.per_split;                        // about as many rows as the stage-wise sample
                 const int64_t pstride = pstages > 0 ? n / (8 * pstages * p.S1) : 0;   // all pieces inside the corpus
                 if (pstride >= 16 && pstages >= 1) {
                     p.piece_stride = pstride;

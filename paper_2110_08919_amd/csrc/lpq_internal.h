@@ -57,6 +57,28 @@ __host__ __device__ static inline int next_pow2(int v)
 }
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// A systematic sample takes splits * per_split * runs_per_unit runs of rows a whole number of rows apart, so
+// up to one row per run is left over at the end of the corpus, and a cluster stored there would not be
+// sampled at all.  Looks near `units` units in `most` splits (an eighth more or less, then fewer splits,
+// down to three quarters) for the first sample that leaves less than one row in two hundred over, or the
+// one that leaves the fewest.
+struct SampleShape { int splits; int64_t per_split; };
+static inline SampleShape sample_that_covers(int64_t n, int64_t units, int runs_per_unit, int most)
+{
+    SampleShape best = {most, ceil_div(units, most)};
+    int64_t best_left = n;
+    for (int s = most; s >= 1 && 4 * s >= 3 * most; --s) {
+        const int64_t base = ceil_div(units, s);
+        for (int64_t step = 0; step <= base / 8 * 2; ++step) {   // base, base - 1, base + 1, base - 2, ...
+            const int64_t per = base + ((step & 1) ? -(step + 1) / 2 : step / 2), runs = per * s * runs_per_unit;
+            if (per < 1 || runs > n) continue;
+            const int64_t left = n % runs;
+            if (left < best_left) { best = {s, per}; best_left = left; }
+            if (left * 200 < n) return best;
+        }
+    }
+    return best;
+}
 
 enum { MAX_K = 1024, MAX_D = 32768, MAX_K_PACKED = 128, MAX_D_PACKED = 256 };
 

@@ -455,8 +455,9 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     int s1 = slots / p.qtiles;
     if (s1 > p.seed_tiles) s1 = p.seed_tiles;
     if (s1 > 2048 / (2 * row_waves)) s1 = 2048 / (2 * row_waves);
-    p.S1 = s1 < 1 ? 1 : s1;
-    p.seed_tiles = (int)ceil_div(p.seed_tiles, p.S1) * p.S1;
+    const SampleShape shape = sample_that_covers(n, p.seed_tiles, 16, s1 < 1 ? 1 : s1);
+    p.S1 = shape.splits;
+    p.seed_tiles = (int)shape.per_split * p.S1;
     while ((int64_t)p.seed_tiles * TILE_ROWS > n) p.seed_tiles -= p.S1;
     if (p.seed_tiles < 1) return p;
     p.run_stride = n / (16 * (int64_t)p.seed_tiles);
