@@ -240,12 +240,15 @@ extern "C" int lpq_quantizer_calibrate(lpq_quantizer *q, const float *x_dev, int
     if (scope != LPQ_SCOPE_PER_FEATURE && scope != LPQ_SCOPE_GLOBAL && scope != LPQ_SCOPE_SHARED_WIDTH) return fail(LPQ_EINVAL, "unknown scope %d", scope);
     if (mode == LPQ_CALIB_GAUSS && !(sigma_mult > 0.0f)) return fail(LPQ_EINVAL, "sigma_mult must be > 0");
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(launch_calibrate(x_dev, n, ld, q->d, q->bits, mode, scope, (double)sigma_mult, q->scratch,
-                             q->staging, q->flag, st));
     int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, q->flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (bad) return fail(LPQ_ENONFINITE, "calibration data holds a NaN or an infinity");
+    for (int windows = 1; windows >= 0; --windows) {   // a second time only if a quantile's window missed it
+        HIP_TRY(launch_calibrate(x_dev, n, ld, q->d, q->bits, mode, scope, (double)sigma_mult, q->scratch,
+                                 q->staging, q->flag, st, windows != 0));
+        HIP_TRY(hipMemcpyAsync(&bad, q->flag, sizeof(int), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (bad != 2) break;
+    }
+    if (bad & 1) return fail(LPQ_ENONFINITE, "calibration data holds a NaN or an infinity");
     HIP_TRY(hipMemcpyAsync(q->params, q->staging, sizeof(float) * 4 * q->d, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     q->ready = true;

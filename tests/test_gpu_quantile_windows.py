@@ -1,0 +1,64 @@
+"""Quantile-clip calibration from sampled windows: the constants are the exact order statistics, against
+numpy's sort.  Needs a real MI355X."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lpq():
+    from paper_2110_08919_amd import lpq as m
+    assert torch.cuda.is_available(), "no GPU visible"
+    m.lib()
+    return m
+
+
+def _check(lpq, x, p, scope="per_feature"):
+    _, sb, se, _ = lpq.Quantizer(x.shape[1], 8).calibrate(x, "quantile", scope, p).get_params()
+    s, p64, last = np.sort(x.cpu().numpy(), axis=0), float(np.float32(p)), x.shape[0] - 1
+    assert np.array_equal(sb, s[int(np.floor(p64 * last))])
+    assert np.array_equal(se, s[int(np.ceil((1.0 - p64) * last))])
+
+
+# rows that fit the sample and rows that do not, tiles of 4 to 128 columns with and without 16-byte loads
+@pytest.mark.parametrize("n,d", [(1, 4), (2, 3), (500, 1), (4096, 5), (4097, 33), (20_000, 128), (30_001, 130), (12_000, 300)])
+@pytest.mark.parametrize("p", [0.0, 0.001, 0.05, 0.49])
+def test_window_quantiles_are_the_order_statistics(lpq, n, d, p):
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    _check(lpq, torch.randn((n, d), generator=g, device="cuda"), p)
+
+
+@pytest.mark.parametrize("p", [0.001, 0.2])
+def test_window_quantiles_of_ties_zeros_and_constants(lpq, p):
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randint(-2, 3, (40_000, 12), generator=g, device="cuda").float()
+    x[:, 3] = 7.0                       # one value only
+    x[:, 5] = 0.0                       # both zeros, in equal parts
+    x[::2, 5] = -0.0
+    x[:, 6] *= 1e38
+    _check(lpq, x, p)
+
+
+def test_window_quantiles_when_the_sample_misses(lpq):
+    """The sampled rows hold other values than the rest: the windows miss and the call is repeated with
+    the radix selection."""
+    n, m = 100_000, 4096
+    x = torch.randn((n, 8), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+    rows = (torch.arange(m, dtype=torch.float64) * n / m).long()
+    x[rows.cuda()] = 1000.0
+    _check(lpq, x, 0.01)
+
+
+def test_window_quantiles_reject_values_that_are_not_finite(lpq):
+    x = torch.randn((20_000, 20), device="cuda")
+    q = lpq.Quantizer(20, 8).calibrate(x, "quantile", "per_feature", 0.01)
+    before = q.get_params()
+    for v in (float("nan"), float("inf"), -float("inf")):
+        y = x.clone()
+        y[12_345, 7] = v
+        with pytest.raises(lpq.LpqError) as e:
+            q.calibrate(y, "quantile", "per_feature", 0.01)
+        assert e.value.code == lpq.ENONFINITE
+    assert all(np.array_equal(a, b) for a, b in zip(before, q.get_params()))
