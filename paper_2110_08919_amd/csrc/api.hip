@@ -3,6 +3,7 @@
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -188,6 +189,7 @@ struct lpq_quantizer {
     float *staging = nullptr;  // device [4][d]: calibration result before it is committed
     void *scratch = nullptr;   // calibration partials
     int *flag = nullptr;       // device: non-finite value seen
+    void *block = nullptr;     // the allocation all of these lie in
 };
 
 static QuantParams view(const float *params, int d, int bits)
@@ -201,10 +203,7 @@ static QuantParams view(const float *params, int d, int bits)
 extern "C" void lpq_quantizer_destroy(lpq_quantizer *q)
 {
     if (!q) return;
-    (void)hipFree(q->params);
-    (void)hipFree(q->staging);
-    (void)hipFree(q->scratch);
-    (void)hipFree(q->flag);
+    (void)hipFree(q->block);
     delete q;
 }
 
@@ -217,14 +216,19 @@ extern "C" int lpq_quantizer_create(lpq_quantizer **out, int d, int bits)
     lpq_quantizer *q = new (std::nothrow) lpq_quantizer;
     if (!q) return fail(LPQ_ENOMEM, "host allocation failed");
     q->d = d; q->bits = bits;
-    hipError_t e = hipMalloc(&q->params, sizeof(float) * 4 * d);
-    if (e == hipSuccess) e = hipMalloc(&q->staging, sizeof(float) * 4 * d);
-    if (e == hipSuccess) e = hipMalloc(&q->scratch, calib_scratch_bytes(d));
-    if (e == hipSuccess) e = hipMalloc(&q->flag, 256);
+    // One allocation for everything: an allocation and its release cost tens of microseconds each,
+    // which a program that calibrates often pays every time.
+    const size_t set = ((size_t)4 * d * sizeof(float) + 255) & ~size_t(255);
+    const hipError_t e = hipMalloc(&q->block, 256 + 2 * set + calib_scratch_bytes(d));
     if (e != hipSuccess) {
         lpq_quantizer_destroy(q);
         return fail(e == hipErrorOutOfMemory ? LPQ_ENOMEM : LPQ_EDEVICE, "hipMalloc: %s", hipGetErrorString(e));
     }
+    char *p = static_cast<char *>(q->block);
+    q->flag = reinterpret_cast<int *>(p);
+    q->params = reinterpret_cast<float *>(p + 256);
+    q->staging = reinterpret_cast<float *>(p + 256 + set);
+    q->scratch = p + 256 + 2 * set;
     *out = q;
     return LPQ_OK;
 }
@@ -243,14 +247,12 @@ extern "C" int lpq_quantizer_calibrate(lpq_quantizer *q, const float *x_dev, int
     int bad = 0;
     for (int windows = 1; windows >= 0; --windows) {   // a second time only if a quantile's window missed it
         HIP_TRY(launch_calibrate(x_dev, n, ld, q->d, q->bits, mode, scope, (double)sigma_mult, q->scratch,
-                                 q->staging, q->flag, st, windows != 0));
+                                 q->staging, q->params, q->flag, st, windows != 0));
         HIP_TRY(hipMemcpyAsync(&bad, q->flag, sizeof(int), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if (bad != 2) break;
     }
     if (bad & 1) return fail(LPQ_ENONFINITE, "calibration data holds a NaN or an infinity");
-    HIP_TRY(hipMemcpyAsync(q->params, q->staging, sizeof(float) * 4 * q->d, hipMemcpyDeviceToDevice, st));
-    HIP_TRY(hipStreamSynchronize(st));
     q->ready = true;
     return LPQ_OK;
 }
@@ -274,10 +276,17 @@ extern "C" int lpq_quantizer_get_params(const lpq_quantizer *q, float *k, float 
     if (!q->ready) return fail(LPQ_ESTATE, "quantizer has no constants yet");
     const size_t bytes = sizeof(float) * q->d;
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(k, q->params, bytes, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(s_b, q->params + q->d, bytes, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(s_e, q->params + 2 * q->d, bytes, hipMemcpyDeviceToHost));
-    if (m) HIP_TRY(hipMemcpy(m, q->params + 3 * q->d, bytes, hipMemcpyDeviceToHost));
+    float *all = static_cast<float *>(std::malloc(4 * bytes));   // the four arrays in one copy
+    if (!all) return fail(LPQ_ENOMEM, "host allocation failed");
+    const hipError_t e = hipMemcpy(all, q->params, 4 * bytes, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) {
+        std::memcpy(k, all, bytes);
+        std::memcpy(s_b, all + q->d, bytes);
+        std::memcpy(s_e, all + 2 * (size_t)q->d, bytes);
+        if (m) std::memcpy(m, all + 3 * (size_t)q->d, bytes);
+    }
+    std::free(all);
+    HIP_TRY(e);
     return LPQ_OK;
 }
 

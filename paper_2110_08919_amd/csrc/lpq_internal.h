@@ -95,8 +95,8 @@ size_t calib_scratch_bytes(int d);
 // *flag: bit 0 a value is not finite; bit 1 (only with `windows`) a quantile lies outside the window its
 // sample gave, and the call has to be repeated without windows.
 hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bits, int mode,
-                            int scope, double sigma_mult, void *scratch, float *params_out,
-                            int *flag, hipStream_t st, bool windows);
+                            int scope, double sigma_mult, void *scratch, float *params_out, float *params_committed,
+                            int *flag, hipStream_t st, bool windows);   // committed: written only if *flag stays 0
 hipError_t launch_derive_m(float *params, int d, int bits, hipStream_t st);
 // Equation 1 on n rows.  zero_pad_to > d additionally writes zero bytes for columns
 // d .. zero_pad_to-1 of each row; n_out > n additionally writes rows n .. n_out-1 as zero codes

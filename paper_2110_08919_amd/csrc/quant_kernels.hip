@@ -773,9 +773,15 @@ __device__ inline float derive_m(float sb, float se, int bits)
 __global__ __launch_bounds__(CAL_THREADS) void calib_params_kernel(
     int d, int64_t n, int bits, int mode, int scope, double sigma_mult,
     const float *__restrict__ mn, const float *__restrict__ mx, const double *__restrict__ mu,
-    const double *__restrict__ css, float *__restrict__ params)
+    const double *__restrict__ css, float *params, const int *flag, float *committed)
 {
     __shared__ double shd[CAL_THREADS];
+    // the constants become the quantizer's if nothing was wrong with the data
+    auto commit = [&]() {
+        __syncthreads();
+        if (*flag == 0)
+            for (int i = threadIdx.x; i < 4 * d; i += CAL_THREADS) committed[i] = params[i];
+    };
     double gss = 0.0;
     if (mode == LPQ_CALIB_GAUSS && scope == LPQ_SCOPE_GLOBAL) {
         for (int c = threadIdx.x; c < d; c += CAL_THREADS) gss += css[c];
@@ -808,7 +814,10 @@ __global__ __launch_bounds__(CAL_THREADS) void calib_params_kernel(
         params[2 * d + c] = se;
         params[3 * d + c] = derive_m(sb, se, bits);
     }
-    if (scope != LPQ_SCOPE_SHARED_WIDTH) return;
+    if (scope != LPQ_SCOPE_SHARED_WIDTH) {
+        commit();
+        return;
+    }
     // One width for all dimensions: every range keeps its centre and takes the half-width of
     // the widest one (binary64 arithmetic on the binary32 constants just written).
     __syncthreads();
@@ -823,6 +832,7 @@ __global__ __launch_bounds__(CAL_THREADS) void calib_params_kernel(
         params[2 * d + c] = se;
         params[3 * d + c] = derive_m(sb, se, bits);
     }
+    commit();
 }
 
 __global__ void derive_m_kernel(float *params, int d, int bits)
@@ -1059,8 +1069,8 @@ size_t calib_scratch_bytes(int d)
 }
 
 hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bits, int mode, int scope,
-                            double sigma_mult, void *scratch, float *params_out, int *nonfinite_flag,
-                            hipStream_t st, bool windows)
+                            double sigma_mult, void *scratch, float *params_out, float *params_committed,
+                            int *nonfinite_flag, hipStream_t st, bool windows)
 {
     const int G = calib_blocks(d);
     CalibScratch s = carve(scratch, d);
@@ -1087,7 +1097,8 @@ hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bi
             else
                 quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, s.qlist, cap, nonfinite_flag);
             quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, s.qwin, s.qcount, s.qlist, cap, s.mn, s.mx, nonfinite_flag);
-            calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out);
+            calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out,
+                                                           nonfinite_flag, params_committed);
             return hipGetLastError();
         }
     }
@@ -1170,7 +1181,7 @@ hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bi
                                                                            nullptr, s.css);
     }
     calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css,
-                                                   params_out);
+                                                   params_out, nonfinite_flag, params_committed);
     return hipGetLastError();
 }
 

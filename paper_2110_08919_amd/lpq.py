@@ -196,7 +196,8 @@ class Quantizer:
     def encode(self, x: torch.Tensor, with_norms=False, ld_codes=None):
         p, n, ld = _dev_matrix(x, torch.float32)
         ldc = ld_codes or self.d
-        codes = torch.zeros((n, ldc), dtype=torch.int8, device=x.device)
+        # (a wider stride leaves bytes behind each row that the call does not write)
+        codes = (torch.empty if ldc == self.d else torch.zeros)((n, ldc), dtype=torch.int8, device=x.device)
         norms = torch.empty(n, dtype=torch.int32, device=x.device) if with_norms else None
         _check(lib().lpq_encode(self._h, p, n, ld, codes.data_ptr(), ldc, _ptr(norms), _stream()))
         codes = codes[:, :self.d]
