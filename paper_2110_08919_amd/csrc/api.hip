@@ -525,7 +525,6 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 constexpr int WIDE_MIN_BITS = 2;
 constexpr int64_t PACKED_BATCH_MIN = 128;  // packed index: larger batches take one collecting scan instead of tiles of 64 queries
 constexpr int REFINE_ROUNDS = 2;        // further rounds of the collecting scan for queries that overflowed (k > 16)
-constexpr int REFINE_GENERIC_MAX = 16;  // ... unless the first round flags no more than this many (generic kernel then)   // narrowest codes that take the 128-queries-per-wave collecting scan
 
 Plan make_plan(const lpq_index *idx, int64_t nq, int k)
 {
@@ -855,8 +854,11 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
             a.wave_queries = 64;
             if (e != hipSuccess) return e;
         }
-        return launch_seed_finalize(gmax, nq, p.G, k, seeds, st,
-                                    p.mode == PLAN_MFMA_COLLECT ? reinterpret_cast<int32_t *>(ws + p.off_qlist) + nq : nullptr);
+        // (it also clears the counters of the redo lists)
+        const bool coll = p.mode == PLAN_MFMA_COLLECT;
+        return launch_seed_finalize(gmax, nq, p.G, k, seeds, st, coll ? reinterpret_cast<int32_t *>(ws + p.off_qlist) + nq : nullptr,
+                                    nullptr, coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
+                                    coll ? p.rounds : 0, nq + 1);
     };
     if (p.mode == PLAN_MFMA_COLLECT) {
         cand_t *cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf);
@@ -875,48 +877,37 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
             HIP_TRY(collect(a, seeds));
         }
         int32_t *qlist = reinterpret_cast<int32_t *>(ws + p.off_qlist), *qcount = qlist + nq;
+        cand_t *bounds2 = p.rounds ? reinterpret_cast<cand_t *>(ws + p.off_bounds2) : nullptr;
         HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over, qlist, qcount, ids, dist, qnorms, emit_mode, st,
-                                      p.expect));
-        // Queries whose candidates did not fit are searched again, exactly: a few by the generic kernel;
-        // many (a corpus full of duplicates or ties) by a pass of the register-list kernel over the
-        // query tiles that hold one.  Both are launched; the count on the device decides which works.
-        // (row-split plans - up to 64 queries - never start with the generic kernel: one query there
-        // takes longer than a round of the scan for all of them)
-        const int few = p.Sr ? REDO_GENERIC_MAX : (p.rounds ? (p.rsplit ? -1 : REFINE_GENERIC_MAX) : INT32_MAX);
-        if (few >= 0) {
-            HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist, qcount, lists2, st, few));
-            HIP_TRY(launch_merge(lists2, nq, p.Sg, k, nullptr, nullptr, nullptr, ids, dist, qnorms, emit_mode, st, false, over,
-                                 (p.Sr || p.rounds) ? qcount : nullptr, 0, few));
-        }
-        if (p.rounds) {
-            // Lists too long for the register-list kernel: the flagged queries get bounds from what the
-            // scan collected for them and the scan runs again over the query tiles that hold one, up to
-            // p.rounds times (what a round collects is the FIRST candidates of each region in scan
-            // order, not the best, so one round may still leave too many: each round cuts the number
-            // that pass by about k / (candidates the regions hold)).  What overflows even then goes
-            // through the generic kernel.  Every launch is gated on the device by the count of queries
-            // the round before flagged: more than `few` for the first round, any for the later ones.
-            cand_t *bounds2 = reinterpret_cast<cand_t *>(ws + p.off_bounds2);
-            const int32_t *over_prev = over, *count_prev = qcount;
-            int min_prev = few < 0 ? 0 : few;
-            const cand_t *bounds_prev = seeds;
-            for (int r = 0; r < p.rounds; ++r) {
-                int32_t *over_r = reinterpret_cast<int32_t *>(ws + p.off_over2) + (size_t)r * nq;
-                int32_t *qlist_r = reinterpret_cast<int32_t *>(ws + p.off_qlist2) + (size_t)r * (nq + 1), *count_r = qlist_r + nq;
-                HIP_TRY(launch_collect_refine(cbuf, ccnt, nq, p.SS, p.Cs, k, over_prev, count_prev, min_prev, bounds_prev,
-                                              bounds2, count_r, st));
-                SearchArgs ar = a;
-                ar.redo_flags = over_prev; ar.redo_count = count_prev; ar.redo_min = min_prev;
-                HIP_TRY(collect(ar, bounds2));
-                HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over_r, qlist_r, count_r, ids, dist, qnorms,
-                                              emit_mode, st, 0, over_prev, count_prev, min_prev));
-                over_prev = over_r; count_prev = count_r; min_prev = 0; bounds_prev = bounds2;
-                if (r + 1 == p.rounds) {
-                    HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist_r, count_r, lists2, st, INT32_MAX));
-                    HIP_TRY(launch_merge(lists2, nq, p.Sg, k, nullptr, nullptr, nullptr, ids, dist, qnorms, emit_mode, st,
-                                         false, over_r));
-                }
-            }
+                                      p.expect, nullptr, nullptr, 0, seeds, bounds2));
+        // Queries whose candidates did not fit are searched again, exactly.  Short lists on short rows: a few
+        // by the generic kernel, many (a corpus full of duplicates or ties) by a pass of the register-list
+        // kernel over the query tiles that hold one; both are launched and the count on the device decides.
+        if (p.Sr)
+            HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist, qcount, lists2, over, ids, dist, qnorms, emit_mode, st,
+                                               REDO_GENERIC_MAX));
+        // Otherwise the selection has also left a bound per flagged query, taken from what the scan did
+        // collect for it, and the scan runs again over the query tiles that hold one, up to p.rounds times
+        // (what a round collects is the FIRST candidates of each region in scan order, not the best, so one
+        // round may still leave too many: each cuts the number that pass by about k / (candidates the regions
+        // hold)).  What overflows even then goes through the generic kernel.  All of it returns at once when
+        // nothing is flagged, so the number of these launches is what a search pays: scan and selection per
+        // round and one more (with the bounds and the merge in launches of their own and the generic kernel in
+        // front, ten instead of five, 1000 queries on 500K x 768 took 15 us longer).
+        const int32_t *over_prev = over, *count_prev = qcount;
+        for (int r = 0; r < p.rounds; ++r) {
+            int32_t *over_r = reinterpret_cast<int32_t *>(ws + p.off_over2) + (size_t)r * nq;
+            int32_t *qlist_r = reinterpret_cast<int32_t *>(ws + p.off_qlist2) + (size_t)r * (nq + 1), *count_r = qlist_r + nq;
+            SearchArgs ar = a;
+            ar.redo_flags = over_prev; ar.redo_count = count_prev; ar.redo_min = 0;
+            HIP_TRY(collect(ar, bounds2));
+            const bool last = r + 1 == p.rounds;
+            HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over_r, qlist_r, count_r, ids, dist, qnorms,
+                                          emit_mode, st, 0, over_prev, count_prev, 0, bounds2, last ? nullptr : bounds2));
+            over_prev = over_r; count_prev = count_r;
+            if (last)
+                HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist_r, count_r, lists2, over_r, ids, dist, qnorms,
+                                                   emit_mode, st));
         }
         if (p.Sr) {
             cand_t *lists_r = reinterpret_cast<cand_t *>(ws + p.off_redo);

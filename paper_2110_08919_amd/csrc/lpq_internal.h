@@ -156,11 +156,13 @@ constexpr int REDO_GENERIC_MAX = 64;
 // Writes lists[(q * S + s) * k + r], sorted ascending, CAND_NONE-filled.
 hipError_t launch_search_generic(const SearchArgs &a, int64_t row0, int64_t row1, int S,
                                  const cand_t *seeds, cand_t *lists, hipStream_t st);
-// The same for the *qcount queries listed in qlist (device memory, written by an earlier kernel):
-// a fixed grid shares out the (query, split) pairs; lists of other queries are left untouched.
-// Does nothing if more than max_listed queries are listed.
+// The same for the *qcount queries listed in qlist (device memory, written by an earlier kernel): a fixed
+// grid shares out the (query, split) pairs, and a query's lists are merged into its final result (S k <=
+// 4096).  flags[q] is 1 for a listed query and stays non-zero.  Does nothing if more than max_listed
+// queries are listed.
 hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const int32_t *qlist,
-                                      const int32_t *qcount, cand_t *lists, hipStream_t st, int max_listed = INT32_MAX);
+                                      const int32_t *qcount, cand_t *lists, int32_t *flags, int32_t *ids, int32_t *dists,
+                                      const int32_t *qnorms, int metric, hipStream_t st, int max_listed = INT32_MAX);
 
 // Matrix-core kernels.  search_mfma.hip keeps the k best of a query in registers (k <= 16) and
 // has a seeding pass; search_mfma_lds.hip keeps them in LDS (larger k).  launch_search_mfma
@@ -220,18 +222,17 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
                                  int32_t *over, int32_t *qlist, int32_t *qcount, int32_t *ids, int32_t *dists,
                                  const int32_t *qnorms, int metric, hipStream_t st, int expected_candidates = 0,
                                  const int32_t *only = nullptr,   // only (optional): int[nq]; other queries just get over[q] = 0,
-                                 const int32_t *gate_count = nullptr, int gate_min = 0);   // and so do all unless *gate_count > gate_min
-// Second round of the collecting scan for queries flagged by launch_collect_select: bounds_out[q] =
-// the k-th best of what the first round collected for q (a bound on its final k-th best), or
-// bounds_in[q] if that was fewer than k; queries not flagged, and all of them unless
-// *qcount > min_flagged, get the bound that nothing passes.  zero_word (optional) is set to 0.
-hipError_t launch_collect_refine(const cand_t *cbuf, const int32_t *ccnt, int64_t nq, int SS, int Cs, int k,
-                                 const int32_t *over, const int32_t *qcount, int min_flagged, const cand_t *bounds_in,
-                                 cand_t *bounds_out, int32_t *zero_word, hipStream_t st);
-// zero_word (optional): one int the kernel also sets to 0 (the counter of the redo list).
+                                 const int32_t *gate_count = nullptr, int gate_min = 0,    // and so do all unless *gate_count > gate_min
+                                 // bounds_out (optional): per query the bound of a further round of the scan, one after
+                                 // the k-th best of what was collected for a flagged query (bounds_in[q] if that was fewer
+                                 // than k), for any other query the bound that nothing passes
+                                 const cand_t *bounds_in = nullptr, cand_t *bounds_out = nullptr);
+// zero_word (optional): one int the kernel also sets to 0 (the counter of the redo list), and zero_more further
+// ones, the i-th at zero_word2 + i * zero_stride.
 // kth_out (optional): the k-th largest maximum itself per query, INT32_MIN where there is none (seeds may then be null).
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
-                                int32_t *zero_word = nullptr, int32_t *kth_out = nullptr);
+                                int32_t *zero_word = nullptr, int32_t *kth_out = nullptr, int32_t *zero_word2 = nullptr,
+                                int zero_more = 0, int64_t zero_stride = 0);
 
 // Merge P lists of k candidates per query into one (merge.hip).  If ids/dists are given the
 // result is final: ids, and dist = key + qnorm (L2SQ) or -key/2 (IP).  Otherwise the merged

@@ -100,29 +100,6 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_kernel(
     generic_scan(a, rs, re, q, seeds, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
 }
 
-// The same scan for a LIST of queries (the ones a collecting scan could not finish): the
-// workgroups of a fixed-size grid share out the (listed query, split) pairs, so a handful of
-// queries is spread over the whole chip and an empty list costs one tiny launch.
-__global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
-    SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, const int32_t *__restrict__ qlist,
-    const int32_t *__restrict__ qcount, cand_t *__restrict__ lists, int cap, int max_listed)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    cand_t *buf = reinterpret_cast<cand_t *>(smem);
-    uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
-    __shared__ int s_count;
-    __shared__ cand_t s_thr;
-    if (*qcount > max_listed) return;                       // too many for this path: another kernel takes them
-    const int64_t items = (int64_t)(*qcount) * S;           // same for every thread of the grid
-    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const int64_t q = qlist[item / S];
-        const int s = (int)(item % S);
-        const int64_t rs = row0 + (int64_t)s * split_rows;
-        const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
-        generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
-    }
-}
-
 // 64-bit minimum over the wave; every lane gets the result.
 __device__ __forceinline__ cand_t wave_min_cand(cand_t c) { return wave_min_u64(c); }
 
@@ -141,6 +118,50 @@ __device__ __forceinline__ void emit_result(cand_t c, int64_t at, int64_t q, int
         v = __float_as_int(metric == MODE_F32_L2 ? f : -f);
     }
     dists[at] = v;
+}
+
+// First candidate in (key, id) order that a bound taken from candidate c does not let through.
+__device__ __forceinline__ cand_t next_bound(cand_t c) { return c + 1; }
+
+// The same scan for a LIST of queries (the ones a collecting scan could not finish): the
+// workgroups of a fixed-size grid share out the (listed query, split) pairs, so a handful of
+// queries is spread over the whole chip and an empty list costs one tiny launch.  The workgroup that
+// finishes a query's last split merges its lists: flags[q], 1 when listed, counts the finished ones (and
+// stays non-zero), so no second launch is needed, and none waits for another.
+__global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
+    SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, const int32_t *__restrict__ qlist,
+    const int32_t *__restrict__ qcount, cand_t *lists, int cap, int max_listed, int32_t *flags, int32_t *__restrict__ ids,
+    int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    cand_t *buf = reinterpret_cast<cand_t *>(smem);
+    uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
+    __shared__ int s_count, s_last;
+    __shared__ cand_t s_thr;
+    if (*qcount > max_listed) return;                       // too many for this path: another kernel takes them
+    const int64_t items = (int64_t)(*qcount) * S;           // same for every thread of the grid
+    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const int64_t q = qlist[item / S];
+        const int s = (int)(item % S);
+        const int64_t rs = row0 + (int64_t)s * split_rows;
+        const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
+        generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
+        __threadfence();                                    // this thread's part of the list is visible to the chip
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(&flags[q], 1) == S;
+        __syncthreads();
+        if (s_last) {                                       // the same answer in every thread of the workgroup
+            __threadfence();
+            const int m = S * a.k;
+            int mcap = 2;
+            while (mcap < m) mcap <<= 1;
+            for (int i = threadIdx.x; i < mcap; i += GEN_THREADS) buf[i] = i < m ? lists[q * m + i] : CAND_NONE;
+            __syncthreads();
+            block_bitonic_sort(buf, mcap);
+            for (int i = threadIdx.x; i < a.k; i += GEN_THREADS) emit_result(buf[i], q * a.k + i, q, ids, dists, qnorms, metric);
+            __syncthreads();
+        }
+    }
 }
 
 // One workgroup per query: sort all candidates of its P lists (plus an optional extra list).
@@ -279,27 +300,35 @@ __device__ __forceinline__ void wave_sort(cand_t (&v)[E], int lane)
 // as needed, each found by a search over the prefix counts), sorts them in registers and keeps the
 // best 128 in its first 16 lanes; further candidates come in 384 at a time through the other 48 lanes.  Any number
 // of candidates the regions hold is handled; a query with an overflowed region or fewer than k
-// candidates is flagged in over[] instead.
+// candidates is flagged in over[] instead, and gets a tighter bound for the next round where bounds_out
+// is given (see next_bound; zero for the others).
 __global__ __launch_bounds__(256) void collect_select_sort_kernel(
     const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t nq, int SS, int Cs, int k,
     int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
-    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
+    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric,
+    const cand_t *__restrict__ bounds_in, cand_t *__restrict__ bounds_out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t q = (int64_t)blockIdx.x * 4 + wave;
     if (q >= nq) return;                                   // wave-uniform
-    const int c = (lane < SS) ? ccnt[q * SS + lane] : 0;
-    const bool bad = c > Cs || c < 0;
-    int incl = bad ? 0 : c;                                // inclusive prefix sum of the counts over the lanes
+    const int offered = (lane < SS) ? ccnt[q * SS + lane] : 0;
+    const bool bad = offered > Cs || offered < 0;
+    const int c = offered < 0 ? 0 : (offered < Cs ? offered : Cs);   // what the region holds
+    int incl = c;                                          // inclusive prefix sum of the counts over the lanes
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int t = __shfl_up(incl, o, 64);
         if (lane >= o) incl += t;
     }
     const int total = __shfl(incl, 63, 64);
-    if (__ballot(bad) || total < k) {
+    const bool flagged = __ballot(bad) || total < k;       // wave-uniform
+    if (flagged) {
         if (lane == 0) { over[q] = 1; qlist[atomicAdd(qcount, 1)] = (int32_t)q; }
-        return;
+        if (!bounds_out) return;
+        if (total < k) {                                   // nothing better than the old bound
+            if (lane == 0) bounds_out[q] = bounds_in[q];
+            return;
+        }
     }
     const int excl = incl - c;                             // index of the first candidate of this lane's region
     const cand_t *base = cbuf + (size_t)q * SS * Cs;
@@ -313,6 +342,13 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
         const int first = __shfl(excl, r, 64);
         return i < total ? base[(size_t)r * Cs + (i - first)] : CAND_NONE;
     };
+    auto put = [&](cand_t v, int e) {                      // the e-th best
+        if (flagged) {
+            if (e == k - 1) bounds_out[q] = next_bound(v);
+        } else if (e < k) {
+            emit_result(v, q * k + e, q, ids, dists, qnorms, metric);
+        }
+    };
     // few candidates: a smaller network (2 or 4 per lane) does
     auto small = [&](auto tag) {
         constexpr int E = decltype(tag)::value;
@@ -321,10 +357,7 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
         for (int j = 0; j < E; ++j) v[j] = fetch(j * 64 + lane);
         wave_sort<E>(v, lane);
 #pragma unroll
-        for (int j = 0; j < E; ++j) {
-            const int e = lane * E + j;
-            if (e < k) emit_result(v[j], q * k + e, q, ids, dists, qnorms, metric);
-        }
+        for (int j = 0; j < E; ++j) put(v[j], lane * E + j);
     };
     if (total <= 128) {                                    // wave-uniform
         small(std::integral_constant<int, 2>{});
@@ -344,12 +377,74 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
             wave_sort<8>(v, lane);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int e = lane * 8 + j;
-            if (e < k) emit_result(v[j], q * k + e, q, ids, dists, qnorms, metric);
+        for (int j = 0; j < 8; ++j) put(v[j], lane * 8 + j);
+    }
+    if (lane == 0 && !flagged) {
+        over[q] = 0;
+        if (bounds_out) bounds_out[q] = 0;
+    }
+}
+
+// A query whose regions overflowed: whatever the scan did collect for it are real items, so the k-th
+// best of them bounds its final k-th best from above - and far more closely than the seeding pass did,
+// since they all passed its bound.  The scan passes candidates strictly below a bound, and the k-th best
+// itself must pass: the bound of the next round is the candidate right after it in (key, id) order, so ties
+// of its key with larger ids do not pass (a region keeps its FIRST arrivals, the lowest ids among equal
+// keys, which is what makes this converge on codes of few bits).
+//
+// By one workgroup, when there may be more candidates than the sort takes: every region gives its first
+// min(count, Cs, maxc / SS) candidates; when the regions hold more, every candidate no worse than the k-th
+// best of those - about k Cs / per of them - is sorted again, and the k-th best of ALL collected ones comes
+// out.  (If even those do not fit, the first estimate stands: it is a valid bound either way.)
+__device__ cand_t refined_bound(const cand_t *cbuf, const int32_t *ccnt, int64_t q, int SS, int Cs, int k, int maxc,
+                                cand_t *buf, cand_t old_bound)
+{
+    __shared__ int s_n;
+    const int tid = threadIdx.x;
+    const int per = maxc / SS < Cs ? maxc / SS : Cs;           // slots per region, >= 1
+    const int used = SS * per;
+    int cap = 2;
+    while (cap < used) cap <<= 1;
+    __syncthreads();                                           // buf is free
+    for (int i = tid; i < cap; i += 256) {
+        cand_t c = CAND_NONE;
+        if (i < used) {
+            const int r = i / per, j = i - r * per;
+            const int cnt = ccnt[q * SS + r];
+            if (j < cnt) c = cbuf[((size_t)q * SS + r) * Cs + j];   // cnt > Cs: the region holds Cs, and j < per <= Cs
+        }
+        buf[i] = c;
+    }
+    __syncthreads();
+    block_bitonic_sort(buf, cap);
+    cand_t kth = (k <= cap) ? buf[k - 1] : CAND_NONE;   // the same value in every thread
+    __syncthreads();
+    if (per < Cs && kth != CAND_NONE) {
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        for (int r = 0; r < SS; ++r) {
+            int cnt = ccnt[q * SS + r];
+            cnt = cnt > Cs ? Cs : cnt;
+            for (int j = tid; j < cnt; j += 256) {
+                const cand_t c = cbuf[((size_t)q * SS + r) * Cs + j];
+                if (c <= kth) {
+                    const int at = atomicAdd(&s_n, 1);
+                    if (at < maxc) buf[at] = c;
+                }
+            }
+        }
+        __syncthreads();
+        const int m = s_n;
+        if (m >= k && m <= maxc) {
+            int cap2 = 2;
+            while (cap2 < m) cap2 <<= 1;
+            for (int i = m + tid; i < cap2; i += 256) buf[i] = CAND_NONE;
+            __syncthreads();
+            block_bitonic_sort(buf, cap2);
+            kth = buf[k - 1];
         }
     }
-    if (lane == 0) over[q] = 0;
+    return kth == CAND_NONE ? old_bound : next_bound(kth);
 }
 
 // Last step of the collecting scan, one workgroup per query: gather the query's regions into LDS,
@@ -359,7 +454,8 @@ __global__ __launch_bounds__(256) void collect_select_kernel(
     const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int SS, int Cs, int k, int maxc,
     int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
     int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric,
-    const int32_t *__restrict__ only, const int32_t *__restrict__ gate_count, int gate_min)
+    const int32_t *__restrict__ only, const int32_t *__restrict__ gate_count, int gate_min,
+    const cand_t *bounds_in, cand_t *bounds_out /* may be the same array */)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);            // [maxc]
@@ -370,7 +466,10 @@ __global__ __launch_bounds__(256) void collect_select_kernel(
     const int tid = threadIdx.x;
     if (only) {   // second round: queries flagged in the first one, if they were more than gate_min
         if (*gate_count <= gate_min || !only[q]) {
-            if (tid == 0) over[q] = 0;
+            if (tid == 0) {
+                over[q] = 0;
+                if (bounds_out) bounds_out[q] = 0;
+            }
             return;
         }
     }
@@ -397,6 +496,10 @@ __global__ __launch_bounds__(256) void collect_select_kernel(
     const int M = tsum[255];
     if (s_bad || M > maxc || M < k) {
         if (tid == 0) { over[q] = 1; qlist[atomicAdd(qcount, 1)] = (int32_t)q; }
+        if (bounds_out) {
+            const cand_t b = refined_bound(cbuf, ccnt, q, SS, Cs, k, maxc, buf, bounds_in[q]);
+            if (tid == 0) bounds_out[q] = b;
+        }
         return;
     }
     int run = tsum[tid] - local;
@@ -423,80 +526,10 @@ __global__ __launch_bounds__(256) void collect_select_kernel(
     __syncthreads();
     block_bitonic_sort(buf, cap);
     for (int i = tid; i < k; i += 256) emit_result(buf[i], q * k + i, q, ids, dists, qnorms, metric);
-    if (tid == 0) over[q] = 0;
-}
-
-// Tighter bounds for queries whose regions overflowed.  Whatever the scan did collect for such a
-// query are real items, so the k-th best of them bounds the query's final k-th best from above -
-// and far more closely than the seeding pass did, since they all passed its bound.  One workgroup
-// per query: every region gives its first min(count, Cs, maxc / SS) candidates, the workgroup
-// sorts them and writes bounds_out[q] = the candidate right after the k-th best in (key, id)
-// order: the k-th best and everything before it pass, so ties of its key with larger ids do not
-// (a region keeps its FIRST arrivals, the lowest ids among equal keys, which is what makes this
-// converge on codes of few bits).  With fewer than k collected the old bound is kept.  Queries that are
-// not flagged get the bound nothing passes (candidate 0), and so does every query when no more
-// than min_flagged are flagged (then the second scan does not run at all).  Also clears *zero_word.
-__global__ __launch_bounds__(256) void collect_refine_kernel(
-    const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int SS, int Cs, int k, int maxc,
-    const int32_t *__restrict__ over, const int32_t *__restrict__ qcount, int min_flagged,
-    const cand_t *bounds_in, cand_t *bounds_out /* may be the same array */, int32_t *__restrict__ zero_word)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    cand_t *buf = reinterpret_cast<cand_t *>(smem);            // [maxc]
-    const int64_t q = blockIdx.x;
-    const int tid = threadIdx.x;
-    if (q == 0 && tid == 0 && zero_word) *zero_word = 0;
-    if (*qcount <= min_flagged || !over[q]) {
-        if (tid == 0) bounds_out[q] = 0;
-        return;
+    if (tid == 0) {
+        over[q] = 0;
+        if (bounds_out) bounds_out[q] = 0;                     // nothing passes: this query is done
     }
-    const int per = maxc / SS < Cs ? maxc / SS : Cs;           // slots per region, >= 1
-    const int used = SS * per;
-    const int cap = next_pow2(used < 2 ? 2 : used);
-    for (int i = tid; i < cap; i += 256) {
-        cand_t c = CAND_NONE;
-        if (i < used) {
-            const int r = i / per, j = i - r * per;
-            const int cnt = ccnt[q * SS + r];
-            if (j < cnt) c = cbuf[((size_t)q * SS + r) * Cs + j];   // cnt > Cs: the region holds Cs, and j < per <= Cs
-        }
-        buf[i] = c;
-    }
-    __syncthreads();
-    block_bitonic_sort(buf, cap);
-    cand_t kth = (k <= cap) ? buf[k - 1] : CAND_NONE;   // the same value in every thread
-    __syncthreads();
-    // Second pass when the regions hold more than the sort does (per < Cs): every collected
-    // candidate that is no worse than that k-th best goes into the buffer - about k Cs / per of
-    // them - and the k-th best of ALL collected candidates comes out.  (If even those do not fit,
-    // the first estimate stands: it is a valid bound either way.)
-    if (per < Cs && kth != CAND_NONE) {
-        __shared__ int s_n;
-        if (tid == 0) s_n = 0;
-        __syncthreads();
-        for (int r = 0; r < SS; ++r) {
-            int cnt = ccnt[q * SS + r];
-            cnt = cnt > Cs ? Cs : cnt;
-            for (int j = tid; j < cnt; j += 256) {
-                const cand_t c = cbuf[((size_t)q * SS + r) * Cs + j];
-                if (c <= kth) {
-                    const int at = atomicAdd(&s_n, 1);
-                    if (at < maxc) buf[at] = c;
-                }
-            }
-        }
-        __syncthreads();
-        const int m = s_n;
-        if (m >= k && m <= maxc) {
-            const int cap2 = next_pow2(m < 2 ? 2 : m);
-            for (int i = m + tid; i < cap2; i += 256) buf[i] = CAND_NONE;
-            __syncthreads();
-            block_bitonic_sort(buf, cap2);
-            kth = buf[k - 1];
-        }
-    }
-    // the scan passes candidates strictly below its bound: kth itself must pass, later ids with its key need not
-    if (tid == 0) bounds_out[q] = (kth == CAND_NONE) ? bounds_in[q] : kth + 1;
 }
 
 // Merge of lists that are each sorted ascending, for k <= 32 and up to 1024 lists: one workgroup per
@@ -629,41 +662,31 @@ int merge_max_lists(int k) { return 4096 / k - 1; }
 // Lists of k that are each sorted and short (k <= 32): at most 1024 of them, less one for an extra list.
 int merge_max_sorted_lists(int k) { return k > 32 ? merge_max_lists(k) : 1023; }
 
-hipError_t launch_collect_refine(const cand_t *cbuf, const int32_t *ccnt, int64_t nq, int SS, int Cs, int k,
-                                 const int32_t *over, const int32_t *qcount, int min_flagged, const cand_t *bounds_in,
-                                 cand_t *bounds_out, int32_t *zero_word, hipStream_t st)
-{
-    if (nq <= 0) return hipSuccess;
-    const int maxc = 4096;
-    if (SS < 1 || SS > 2048 || Cs < 1 || k > maxc) return hipErrorInvalidValue;
-    collect_refine_kernel<<<(unsigned)nq, 256, (size_t)maxc * sizeof(cand_t), st>>>(cbuf, ccnt, SS, Cs, k, maxc, over, qcount,
-                                                                                   min_flagged, bounds_in, bounds_out, zero_word);
-    return hipGetLastError();
-}
-
 hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_t nq, int SS, int Cs, int k,
                                  int32_t *over, int32_t *qlist, int32_t *qcount, int32_t *ids, int32_t *dists,
                                  const int32_t *qnorms, int metric, hipStream_t st, int expected_candidates,
-                                 const int32_t *only, const int32_t *gate_count, int gate_min)
+                                 const int32_t *only, const int32_t *gate_count, int gate_min, const cand_t *bounds_in,
+                                 cand_t *bounds_out)
 {
     if (nq <= 0) return hipSuccess;
     const int maxc = 4096;
     if (SS < 1 || SS > 2048 || k > maxc) return hipErrorInvalidValue;
     // (k rounds of "smallest in the wave" beat the sorting network only for the shortest lists: k = 1
     // 1.00 against 1.01 ms per search on the benchmark workload, k = 10 1.178 against 1.166, k = 32 1.446 against 1.375)
-    if (!only && expected_candidates > 0 && expected_candidates <= 256 && SS <= 64 && k <= 2) {
+    if (!only && !bounds_out && expected_candidates > 0 && expected_candidates <= 256 && SS <= 64 && k <= 2) {
         collect_select_wave_kernel<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist,
                                                                                  qcount, ids, dists, qnorms, metric);
         return hipGetLastError();
     }
     if (!only && SS <= 64 && k <= 128) {   // one wave per query, sorted in registers
         collect_select_sort_kernel<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist,
-                                                                                 qcount, ids, dists, qnorms, metric);
+                                                                                 qcount, ids, dists, qnorms, metric, bounds_in,
+                                                                                 bounds_out);
         return hipGetLastError();
     }
     const size_t lds = (size_t)maxc * sizeof(cand_t) + (size_t)(SS + 1) * sizeof(int);
     collect_select_kernel<<<(unsigned)nq, 256, lds, st>>>(cbuf, ccnt, SS, Cs, k, maxc, over, qlist, qcount, ids, dists,
-                                                          qnorms, metric, only, gate_count, gate_min);
+                                                          qnorms, metric, only, gate_count, gate_min, bounds_in, bounds_out);
     return hipGetLastError();
 }
 
@@ -680,14 +703,17 @@ hipError_t launch_search_generic(const SearchArgs &a, int64_t row0, int64_t row1
 }
 
 hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const int32_t *qlist,
-                                      const int32_t *qcount, cand_t *lists, hipStream_t st, int max_listed)
+                                      const int32_t *qcount, cand_t *lists, int32_t *flags, int32_t *ids, int32_t *dists,
+                                      const int32_t *qnorms, int metric, hipStream_t st, int max_listed)
 {
     if (a.nq <= 0 || row1 <= row0) return hipSuccess;
+    if ((int64_t)S * a.k > 4096) return hipErrorInvalidValue;   // one workgroup merges a query's lists
     const int cap = next_pow2((2 * a.k > a.k + 2 * GEN_ROWS) ? 2 * a.k : a.k + 2 * GEN_ROWS);
     const int64_t split_rows = round_up(ceil_div(row1 - row0, S), GEN_ROWS);
     const size_t shmem = (size_t)cap * sizeof(cand_t) + (size_t)a.d_pad;
-    search_generic_list_kernel<<<2048, GEN_THREADS, shmem, st>>>(a, row0, row1, S, split_rows, qlist, qcount, lists, cap,
-                                                                 max_listed);
+    const size_t merge = (size_t)next_pow2(S * a.k < 2 ? 2 : S * a.k) * sizeof(cand_t);
+    search_generic_list_kernel<<<2048, GEN_THREADS, shmem > merge ? shmem : merge, st>>>(
+        a, row0, row1, S, split_rows, qlist, qcount, lists, cap, max_listed, flags, ids, dists, qnorms, metric);
     return hipGetLastError();
 }
 

@@ -1180,10 +1180,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
 template <int E>
 __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k,
                                                             cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word,
-                                                            int32_t *__restrict__ kth_out)
+                                                            int32_t *__restrict__ kth_out, int32_t *__restrict__ zero_word2,
+                                                            int zero_more, int64_t zero_stride)
 {
     const int lane = threadIdx.x & 63;
-    if (zero_word && blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0;
+    if (zero_word && blockIdx.x == 0 && threadIdx.x == 0) {
+        *zero_word = 0;
+        for (int i = 0; i < zero_more; ++i) zero_word2[i * zero_stride] = 0;
+    }
     const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (q >= nq) return;                                   // wave-uniform
     int v[E];
@@ -1520,16 +1524,21 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
 }
 
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
-                                int32_t *zero_word, int32_t *kth_out)
+                                int32_t *zero_word, int32_t *kth_out, int32_t *zero_word2, int zero_more, int64_t zero_stride)
 {
     if (nq <= 0) return hipSuccess;
     if (G > 4096) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)ceil_div(nq, (int64_t)4);
-    if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
-    else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
-    else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
-    else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
-    else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out);
+    if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
+                                                                    zero_word2, zero_more, zero_stride);
+    else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
+                                                                    zero_word2, zero_more, zero_stride);
+    else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
+                                                                    zero_word2, zero_more, zero_stride);
+    else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
+                                                                    zero_word2, zero_more, zero_stride);
+    else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
+                                                                    zero_word2, zero_more, zero_stride);
     return hipGetLastError();
 }
 
