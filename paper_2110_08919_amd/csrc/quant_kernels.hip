@@ -959,6 +959,56 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(
     }
 }
 
+// The same for a batch of long rows (queries): one workgroup per row.  The kernel above gives a row to one
+// wave, which walks it 256 columns at a time, each step waiting for its constants; a few hundred rows of
+// 2048 columns leave most of the chip idle that way (1 to 1000 of them: 24 to 30 us, here 7 to 12).
+template <bool VEC>
+__global__ __launch_bounds__(ENC_THREADS) void encode_row_kernel(
+    QuantParams qp, const float *__restrict__ x, int64_t n, int64_t ld, int8_t *__restrict__ codes,
+    int64_t ldc, int zero_pad_to, int32_t *__restrict__ norms)
+{
+    __shared__ int part[ENC_THREADS / 64];
+    const int64_t r = blockIdx.x;
+    const int d = qp.d, half = 1 << (qp.bits - 1), lim = zero_pad_to > d ? zero_pad_to : d;
+    const float lo = (float)(-half), top = (float)(half < 127 ? half : 127);
+    int acc = 0;
+    for (int c0 = 4 * threadIdx.x; c0 < lim; c0 += 4 * ENC_THREADS) {
+        int q[4];
+        float v[4];
+        if (VEC && r < n && c0 + 3 < d) {
+            const float4 t = *reinterpret_cast<const float4 *>(x + r * ld + c0);
+            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = (r < n && c0 + j < d) ? x[r * ld + c0 + j] : 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float k, b, e, m;
+            column_constants(qp, c0 + j, c0 + j < d, k, b, e, m);
+            q[j] = (r < n && c0 + j < d) ? quantize_one(v[j], k, b, e, m, lo, top) : 0;
+            acc += q[j] * q[j];
+        }
+        if (VEC && c0 + 3 < lim) {
+            *reinterpret_cast<uint32_t *>(codes + r * ldc + c0) = (uint32_t)(q[0] & 255) | ((uint32_t)(q[1] & 255) << 8) |
+                                                                  ((uint32_t)(q[2] & 255) << 16) | ((uint32_t)(q[3] & 255) << 24);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c0 + j < lim) codes[r * ldc + c0 + j] = (int8_t)q[j];
+        }
+    }
+    if (!norms) return;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < ENC_THREADS / 64; ++w) acc += part[w];
+        norms[r] = acc;
+    }
+}
+
 // Copy int8 rows into zero-padded rows and compute their norms; 16 lanes per row.
 __global__ __launch_bounds__(256) void repack_i8_kernel(
     const int8_t *__restrict__ src, int64_t n, int64_t ld, int d, int8_t *__restrict__ dst,
@@ -1212,6 +1262,11 @@ hipError_t launch_encode(const QuantParams &qp, const float *x, int64_t n, int64
     int tpr = 1;
     while (tpr < groups && tpr < 64) tpr <<= 1;
     const bool vec = ((uintptr_t)x % 16 == 0) && (ld % 4 == 0) && ((uintptr_t)codes % 4 == 0) && (ldc % 4 == 0);
+    if (lim > 256 && n_out <= 16384) {   // (larger calls fill the chip a wave per row, and reuse a column's constants)
+        if (vec) encode_row_kernel<true><<<(unsigned)n_out, ENC_THREADS, 0, st>>>(qp, x, n, ld, codes, ldc, zero_pad_to, norms);
+        else encode_row_kernel<false><<<(unsigned)n_out, ENC_THREADS, 0, st>>>(qp, x, n, ld, codes, ldc, zero_pad_to, norms);
+        return hipGetLastError();
+    }
     const int rpw = 64 / tpr;
     int64_t waves = ceil_div(n_out, (int64_t)rpw * ENC_UNROLL);
     int64_t blocks = ceil_div(waves, ENC_THREADS / 64);
