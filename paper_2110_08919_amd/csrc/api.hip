@@ -526,12 +526,14 @@ constexpr int WIDE_MIN_BITS = 2;
 constexpr int64_t PACKED_BATCH_MIN = 128;  // packed index: larger batches take one collecting scan instead of tiles of 64 queries
 constexpr int REFINE_ROUNDS = 2;        // further rounds of the collecting scan for queries that overflowed (k > 16)
 
-Plan make_plan(const lpq_index *idx, int64_t nq, int k)
+// compact: the plan for callers with a fixed workspace whose normal plan does not fit - fewer, larger splits
+// (at least 512 rows), no collecting scan where another kernel needs less room.  Slower, the same results.
+Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
 {
     Plan p;
     const int64_t n = idx->size;
     const int64_t want = tune(LPQ_TUNE_PATH);
-    const bool regs = mfma_reg_supported(idx->d_pad, k), stream = !idx->packed && mfma_stream_rows(idx->d_pad);
+    const bool regs = mfma_reg_supported(idx->d_pad, k), stream = !idx->packed && mfma_stream_rows(idx->d_pad) && !(compact && idx->d_pad > 1536);
     const bool coll = stream ? k <= MAX_K : mfma_collect_supported(idx->d_pad, k);
     // Large batches of short rows: the collecting variant with 128 queries per wave beats the
     // register lists at any k it takes (fewer LDS reads and less per-stage overhead per contraction).
@@ -549,7 +551,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
     // Batches of 65 to 256 queries on corpora of up to a million rows: the register lists fill from nothing
     // in every split (10 000 x 128, 100 queries: 0.068 ms against 0.041 collecting; 50 000: 0.043 / 0.039; 300 000,
     // 200 queries: 0.055 / 0.052; even at 1M; 4M x 64, 256 queries: 0.100 / 0.110, left to the lists).
-    const bool few_rows = coll && nq > 64 && n <= 1000000;
+    const bool few_rows = coll && nq > 64 && n <= 1000000 && !compact;
     // Packed rows: the row-split register-list kernel (callers tile the queries by 64), or for large
     // batches the collecting scan over all queries at once; the generic kernel on request.
     // (lists of more than 16 entries: the collecting scan at every batch size; rows of 32 packed
@@ -605,7 +607,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             // candidates of a query stay well inside the 4096 the selection kernel sorts; at most n / 4.
             // (Streamed rows: a sampled row costs d / 128 times as much, a candidate no more.)
             double by_cost = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
-            if (stream) by_cost *= std::sqrt(128.0 / (double)idx->d);
+            if (stream && !compact) by_cost *= std::sqrt(128.0 / (double)idx->d);
             const double by_room = (double)k * (double)n / 1500.0;
             const double want_rows = by_cost > by_room ? by_cost : by_room;
             // (k beyond 512: half the corpus, or the ~4.6 k candidates a quarter lets through would not fit;
@@ -672,7 +674,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
     // queries: 0.104 ms with splits of 512 rows, 0.065 with 256, 0.054 with 128; 100 queries 0.065 -> 0.041;
     // 30 000 x 128, 100 queries, k = 100: 0.127 -> 0.082; 64 rows gain nothing more.
     // (Packed rows: from 64K items on 128 splits are enough, more only spread the candidates thinner.)
-    const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : (idx->packed && n >= 65536 ? 512 : 128);
+    const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : (compact || (idx->packed && n >= 65536) ? 512 : 128);
     if (seed) {
         // group maxima per query: 2 per split and segment (8 when rows are split), at most 2048 (4096 for k > 512)
         // (row-split launches: up to 128 splits; with 256 the 2048 maxima cost the threshold kernel 3 us more
@@ -693,7 +695,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
             seed = (int64_t)p.seed_tiles * 256;
         } else if (gmode) {
             SampleShape shape = {p.S1, ceil_div(seed / 64, p.S1)};
-            if (!p.rsplit && !long_scan) shape = sample_that_covers(n, seed / 64, 8, p.S1);   // runs of 8 rows, see below
+            if (!p.rsplit && !long_scan && !compact) shape = sample_that_covers(n, seed / 64, 8, p.S1);   // runs of 8 rows, see below
             p.S1 = shape.splits;
             p.SEG = mfma_seed_segments(p.S1, k, p.rs_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, p.rs_waves);
@@ -733,13 +735,13 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k)
         const double per_region = 1.15 * (double)k * (double)n / (double)seed / p.SS;
         p.expect = (int)(per_region * p.SS + 1.0);
         int64_t cs = 64;
-        while ((double)cs < 3.0 * per_region && cs < 4096) cs <<= 1;
+        while ((double)cs < (compact && stream ? 1.5 : 3.0) * per_region && cs < 4096) cs <<= 1;
         p.Cs = (int)cs;
         if (tune(LPQ_TUNE_REGION_CAP) > 0) p.Cs = (int)(tune(LPQ_TUNE_REGION_CAP) < 4096 ? tune(LPQ_TUNE_REGION_CAP) : 4096);
         // splits of the redo scan: many, so that a few queries spread over the chip; bounded by the
         // single merge pass and by 256 MB of lists
         p.Sg = merge_max_lists(k) < 128 ? merge_max_lists(k) : 128;
-        while (p.Sg > 4 && (size_t)nq * p.Sg * k * sizeof(cand_t) > (size_t(256) << 20)) p.Sg /= 2;
+        while (p.Sg > 4 && (size_t)nq * p.Sg * k * sizeof(cand_t) > (size_t(compact ? 16 : 256) << 20)) p.Sg /= 2;
     }
 
     size_t o = 0;
@@ -947,20 +949,20 @@ struct PackedPlan {
 };
 constexpr int64_t PACKED_TILE = 64;
 
-PackedPlan make_packed_plan(const lpq_index *idx, int64_t nq, int k)
+PackedPlan make_packed_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
 {
     PackedPlan pp;
     const int64_t full = nq < PACKED_TILE ? nq : PACKED_TILE, last = nq % PACKED_TILE;
-    const Plan a = make_plan(idx, full, k);
+    const Plan a = make_plan(idx, full, k, compact);
     size_t tile = a.total;
     int64_t tail = a.nq_pad;
     if (last) {
-        const Plan b = make_plan(idx, last, k);
+        const Plan b = make_plan(idx, last, k, compact);
         if (b.total > tile) tile = b.total;
         if (b.nq_pad > tail) tail = b.nq_pad;
     }
     pp.nq_pad = ceil_div(nq, PACKED_TILE) * PACKED_TILE + tail;   // every tile may read a whole padded tile
-    const Plan whole = make_plan(idx, nq, k);
+    const Plan whole = make_plan(idx, nq, k, compact);
     if (whole.mode == PLAN_MFMA_COLLECT && !whole.rsplit) {   // large batch: one scan over all queries
         tile = whole.total;
         if (whole.nq_pad > pp.nq_pad) pp.nq_pad = whole.nq_pad;
@@ -976,19 +978,19 @@ PackedPlan make_packed_plan(const lpq_index *idx, int64_t nq, int k)
 }
 
 int search_packed(const lpq_index *idx, const PackedPlan &pp, char *ws, int64_t nq, int k, int metric, int32_t *ids,
-                  int32_t *dist, hipStream_t st)
+                  int32_t *dist, hipStream_t st, bool compact = false)
 {
     int8_t *qperm = reinterpret_cast<int8_t *>(ws + pp.off_qperm);
     int32_t *qadj = reinterpret_cast<int32_t *>(ws + pp.off_qadj);
     HIP_TRY(launch_permute_queries(reinterpret_cast<const int8_t *>(ws + pp.off_qcodes), pp.nq_pad, idx->d_pad,
                                    metric == LPQ_METRIC_L2SQ, qperm, qadj, st));
     const int emit = metric == LPQ_METRIC_L2SQ ? MODE_I8_L2 : MODE_I8_IP_ADJ;
-    const Plan whole = make_plan(idx, nq, k);
+    const Plan whole = make_plan(idx, nq, k, compact);
     if (whole.mode == PLAN_MFMA_COLLECT && !whole.rsplit)
         return search_core(idx, whole, ws + pp.off_tile, qperm, qadj, nq, k, metric, emit, ids, dist, st);
     for (int64_t q0 = 0; q0 < nq; q0 += PACKED_TILE) {
         const int64_t nt = nq - q0 < PACKED_TILE ? nq - q0 : PACKED_TILE;
-        const Plan pt = make_plan(idx, nt, k);
+        const Plan pt = make_plan(idx, nt, k, compact);
         int rc = search_core(idx, pt, ws + pp.off_tile, qperm + q0 * idx->d_pad, qadj + q0, nt, k, metric, emit,
                              ids + q0 * k, dist + q0 * k, st);
         if (rc) return rc;
@@ -1043,19 +1045,19 @@ extern "C" size_t lpq_search_workspace_bytes(const lpq_index *idx, int64_t nq, i
 
 static int search_f32_queries(const lpq_index *idx, const float *q_dev, int64_t nq, int64_t ld, int k, int metric,
                               int32_t *ids_dev, int32_t *dist_dev, void *workspace_dev, size_t workspace_bytes,
-                              hipStream_t st)
+                              hipStream_t st, bool compact = false)
 {
     char *ws = (char *)workspace_dev;
     if ((uintptr_t)workspace_dev % 256) return fail(LPQ_EINVAL, "workspace must be 256-byte aligned");
     if (idx->packed) {
-        const PackedPlan pp = make_packed_plan(idx, nq, k);
+        const PackedPlan pp = make_packed_plan(idx, nq, k, compact);
         if (!workspace_dev || workspace_bytes < pp.total) return fail(LPQ_ERANGE, "workspace of %zu bytes needed", pp.total);
         HIP_TRY(launch_encode(view(idx->params, idx->d, idx->bits), q_dev, nq, ld,
                               reinterpret_cast<int8_t *>(ws + pp.off_qcodes), idx->d_pad, idx->d_pad,
                               reinterpret_cast<int32_t *>(ws + pp.off_qnorms), st, pp.nq_pad));
-        return search_packed(idx, pp, ws, nq, k, metric, ids_dev, dist_dev, st);
+        return search_packed(idx, pp, ws, nq, k, metric, ids_dev, dist_dev, st, compact);
     }
-    const Plan p = make_plan(idx, nq, k);
+    const Plan p = make_plan(idx, nq, k, compact);
     if (!workspace_dev || workspace_bytes < p.total) return fail(LPQ_ERANGE, "workspace of %zu bytes needed", p.total);
     // Padding query rows [nq, nq_pad) are written as zero codes; their results are never written out.
     HIP_TRY(launch_encode(view(idx->params, idx->d, idx->bits), q_dev, nq, ld,
@@ -1110,7 +1112,13 @@ extern "C" int lpq_search_static(const lpq_index *idx, const float *q_dev, int64
     int rc = check_search_args(idx, q_dev, nq, ld, k, metric, ids_dev, dist_dev);
     if (rc) return rc;
     if (nq == 0) return LPQ_OK;
-    const size_t need = idx->packed ? make_packed_plan(idx, nq, k).total : make_plan(idx, nq, k).total;
+    size_t need = 0;
+    bool compact = false;
+    for (int pass = 0; pass < 2; ++pass) {
+        compact = pass != 0;
+        need = idx->packed ? make_packed_plan(idx, nq, k, compact).total : make_plan(idx, nq, k, compact).total;
+        if (need <= (size_t)LPQ_STATIC_WORKSPACE_BYTES) break;
+    }
     if (need > (size_t)LPQ_STATIC_WORKSPACE_BYTES)
         return fail(LPQ_ERANGE, "this search needs %zu bytes of workspace, the built-in one holds %zu: use lpq_search",
                     need, (size_t)LPQ_STATIC_WORKSPACE_BYTES);
@@ -1118,7 +1126,7 @@ extern "C" int lpq_search_static(const lpq_index *idx, const float *q_dev, int64
     rc = scratch_address(&ws);
     if (rc) return rc;
     return search_f32_queries(idx, q_dev, nq, ld, k, metric, ids_dev, dist_dev, ws, (size_t)LPQ_STATIC_WORKSPACE_BYTES,
-                              (hipStream_t)stream);
+                              (hipStream_t)stream, compact);
 }
 
 extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,

@@ -43,3 +43,15 @@ def test_merge_of_sorted_lists_with_few_candidates(lpq, n, k):
     x[: n // 2] = 1.0
     ids, dists = lpq.search_f32(x, x[:3], k, "l2sq")
     assert torch.equal(ids.cpu(), torch.arange(k, dtype=torch.int32).expand(3, k)) and not dists.any()
+
+
+@pytest.mark.parametrize("n,d,nq,k", [(100_000, 256, 256, 10), (10_000, 32, 2000, 10), (5000, 2048, 3000, 10), (50_000, 100, 700, 100)])
+def test_static_search_of_shapes_whose_normal_plan_needs_more(lpq, n, d, nq, k):
+    """The library's own workspace of 64 MiB: a search whose plan does not fit takes one that does."""
+    w = synth.Workload("w", "bimodal", n, d, nq, "l2sq", (k,), "minmax", "global", 7)
+    x, q = w.corpus("cuda"), w.queries("cuda")
+    index = lpq.Index(lpq.Quantizer(d, 8).calibrate(x, "minmax", "global"), n).add_f32(x)
+    assert index.workspace_bytes(nq, k) > lpq.STATIC_WORKSPACE_BYTES
+    want, got = index.search(q, k), index.search_static(q, k)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
