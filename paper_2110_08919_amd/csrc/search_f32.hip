@@ -298,14 +298,33 @@ static size_t f32_lists_bytes(int64_t n, int64_t nq, int d, int k)
     return ((size_t)nq * f32_splits(n, nq, d, k) * k * sizeof(cand_t) + 255) & ~size_t(255);
 }
 
-size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k)
+// Larger batches are searched this many queries at a time, which bounds the workspace (a few hundred
+// megabytes of candidate regions); the tiles are full long before.
+constexpr int64_t F32_BATCH = 16384;
+
+static size_t f32_batch_bytes(int64_t n, int64_t nq, int d, int k)
 {
     return f32_lists_bytes(n, nq, d, k) + f32_filter_plan(n, nq, d, k).total;
+}
+
+size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k)
+{
+    if (nq <= F32_BATCH) return f32_batch_bytes(n, nq, d, k);
+    const size_t full = f32_batch_bytes(n, F32_BATCH, d, k), rest = nq % F32_BATCH ? f32_batch_bytes(n, nq % F32_BATCH, d, k) : 0;
+    return full > rest ? full : rest;
 }
 
 hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
                              int d, int k, int metric, int32_t *ids, float *dists, void *ws, hipStream_t st)
 {
+    if (nq > F32_BATCH) {
+        for (int64_t q0 = 0; q0 < nq; q0 += F32_BATCH) {
+            const hipError_t e = launch_search_f32(x, n, ldx, q + q0 * ldq, nq - q0 < F32_BATCH ? nq - q0 : F32_BATCH, ldq, d, k,
+                                                   metric, ids + q0 * k, dists + q0 * k, ws, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const int S = f32_splits(n, nq, d, k);
     const int qt = f32_query_tile(d, k);
     const int mode = metric == LPQ_METRIC_L2SQ ? MODE_F32_L2 : MODE_F32_IP;

@@ -53,6 +53,7 @@ def _same_bits(got, want):
     ("bimodal", 20_000, 128, 300, 10, "l2sq"),
     ("scaled_unit", 16_385, 24, 64, 1, "ip"),
     ("bimodal", 50_000, 96, 1, 10, "l2sq"),
+    ("scaled_unit", 5000, 24, 16_500, 2, "l2sq"),        # two batches of queries
     ("bimodal", 300_000, 40, 3000, 10, "ip"),            # one or two splits of the corpus per query tile
     ("scaled_unit", 30_001, 33, 65, 100, "l2sq"),
     ("skewed_int", 40_000, 100, 500, 10, "l2sq"),        # integer data: many equal distances
