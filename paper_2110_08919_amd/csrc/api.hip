@@ -677,9 +677,10 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : (compact || (idx->packed && n >= 65536) ? 512 : 128);
     if (seed) {
         // group maxima per query: 2 per split and segment (8 when rows are split), at most 2048 (4096 for k > 512)
-        // (row-split launches: up to 128 splits; with 256 the 2048 maxima cost the threshold kernel 3 us more
-        // than the pass gains)
-        p.S1 = splits_for(seed, tiles_q, min_rows, slots_now, gmode ? (p.rsplit ? 128 : 1024) : merge_max_lists(k));
+        // (row-split launches with register lists: up to 128 splits; with 256 the 2048 maxima cost the
+        // threshold kernel 3 us more than the pass gains.  Longer lists want the tighter bound: 1543 queries,
+        // 97 candidates on 780K x 56 at 4 bits 2.05 ms with 128, 1.93 with 256)
+        p.S1 = splits_for(seed, tiles_q, min_rows, slots_now, gmode ? (p.rsplit ? (p.mode == PLAN_MFMA_REG ? 128 : 256) : 1024) : merge_max_lists(k));
         if (p.stream) {
             // tiles of 256 rows made of runs of 16 rows spread evenly over the corpus
             const int row_waves = mfma_stream_row_waves(nq);

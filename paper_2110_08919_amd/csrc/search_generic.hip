@@ -574,14 +574,30 @@ __global__ __launch_bounds__(256) void merge_sorted_kernel(
         head[j] = l < P ? lists[(q * P + l) * k] : (l < Pt ? extra[q * k] : CAND_NONE);
         mn = head[j] < mn ? head[j] : mn;
     }
-    {
-        cand_t v[1] = {mn};
-        wave_sort<1>(v, lane);                          // lane i: the wave's i-th smallest
-        if (lane < 16 * E) best[wave * 16 * E + lane] = v[0];
-    }
+    // lane i < k of the result: the i-th smallest of the lanes' values (all different, or CAND_NONE); the
+    // shortest lists by k rounds of "smallest", which beat the sorting network up to k = 4
+    auto smallest = [&](cand_t c) -> cand_t {
+        if (k > 4) {
+            cand_t v[1] = {c};
+            wave_sort<1>(v, lane);
+            return v[0];
+        }
+        cand_t out = CAND_NONE;
+        for (int r = 0; r < k; ++r) {
+            const cand_t m = wave_min_cand(c);
+            if (lane == r) out = m;
+            if (c == m) c = CAND_NONE;
+        }
+        return out;
+    };
+    const cand_t wbest = smallest(mn);
+    if (lane < 16 * E) best[wave * 16 * E + lane] = wbest;
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
-    if (wave == 0) {
+    if (wave == 0 && E == 1) {
+        const cand_t c = smallest(best[lane]);
+        if (lane == k - 1) bound = c;
+    } else if (wave == 0) {
         cand_t v[E];
 #pragma unroll
         for (int j = 0; j < E; ++j) v[j] = best[E * lane + j];
@@ -625,7 +641,7 @@ __global__ __launch_bounds__(256) void merge_sorted_kernel(
         for (int j = 0; j < S; ++j) emit(v[j], lane * S + j);
     };
     if (m <= 64) {
-        if (wave == 0) sorted(std::integral_constant<int, 1>{});
+        if (wave == 0) emit(smallest(lane < m ? buf[lane] : CAND_NONE), lane);
     } else if (m <= 128) {
         if (wave == 0) sorted(std::integral_constant<int, 2>{});
     } else if (m <= 256) {
