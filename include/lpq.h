@@ -322,18 +322,17 @@ int lpq_probe_stream(const void *src_dev, size_t bytes, int mode, int reps, doub
 
 /* Diagnostics of the collecting variant: after a search with the same (idx, nq, k, metric) and
  * workspace has finished, the number of queries whose candidates did not fit and that were
- * searched again (up to 64 by the generic kernel, more by a pass of the register-list
- * matrix-core kernel when k <= 16; 0 when the search did not use the collecting variant) and the
+ * searched again (0 when the search did not use the collecting variant) and the
  * largest number of candidates any region received in the last round of the scan.  Synchronises
  * the device. */
 int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,
                               int64_t *redone_queries, int64_t *max_region_fill);
 
-/* For k > 16 more than 16 such queries are not searched again exactly at once: the scan
- * runs again (up to two more rounds) over the query tiles that hold one, with bounds taken from
- * the candidates the round before did collect, and only queries that overflow every time go
- * through the generic kernel.  *left_queries = their number after the last search (0 when the
- * plan has no further rounds or they did not run).  Same arguments and synchronisation as above. */
+/* Where the plan has further rounds (for k > 16, and on rows of more than 256 bytes) such queries are not
+ * searched again exactly at once: the scan runs again (up to two more rounds) over the query tiles that
+ * hold one, with bounds taken from the candidates the round before did collect, and only queries that
+ * overflow every time go through the generic kernel.  *left_queries = their number after the last search
+ * (0 when the plan has no further rounds or they did not run).  Same arguments and synchronisation as above. */
 int lpq_search_overflow_left(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,
                              int64_t *left_queries);
 
