@@ -24,8 +24,9 @@
 // direct kernel instead.
 //
 // Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.5 -> 0.94 ms (the scan 0.81 = 0.97 PFLOP/s
-// of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  The scan is bound by LDS
-// traffic: a k-step of a wave reads eight fragments for twelve matrix instructions.
+// of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  In the scan the
+// matrix pipe is busy 45 % of the time and the LDS 27 %: the two waves of a SIMD split and store their
+// rows in step with each other, and wait a third of their time at the barrier of each stage.
 //
 // Layout: workgroups of eight waves on tiles of 256 items x 64 WQ queries, as in search_mfma_stream.hip;
 // a stage is 32 features.  Items come from HBM in fp32 through registers (one stage ahead), are split

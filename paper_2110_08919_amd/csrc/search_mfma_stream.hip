@@ -14,9 +14,9 @@
 // queries 3.9 ms = 2.1 POP/s.  Stages of 64 bytes (four in the ring) measured 10 % slower: half lines
 // double the requests that the L2 serves.
 //
-// What bounds it (10 000 queries, same box): without the copies the search takes 3.0 ms instead of
-// 3.9, without candidates 3.64; the matrix pipe is busy half of the time and the part is
-// power-limited while it is (codes of few toggling bits run 10 % faster).
+// What bounds it: the matrix pipe is busy 64 % of the scan (1000 queries), the LDS 27 %, and the part is
+// power-limited while it is, at 1.8 GHz (codes of few toggling bits run 10 % faster).  10 000 queries, same
+// box: without the copies the search takes 3.0 ms instead of 3.9, without candidates 3.64.
 //
 // One workgroup barrier per stage, placed in front of its last k-step: by then every wave has read the
 // stage (its reads were waited for), so the ring slot is refilled right behind the barrier, and the
