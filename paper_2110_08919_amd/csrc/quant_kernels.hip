@@ -569,7 +569,7 @@ __global__ void quantile_finish_kernel(int d, int pooled, int cols, const uint32
 // If a rank turns out to lie outside its window, or a list overflows, bit 1 of the flag asks for the
 // radix selection above.  The pass also looks for values that are not finite, so the min/max pass is not
 // needed either.  Bound by the one read of the data: 1M x 128, p = 0.001: 0.117 ms = 4.4 TB/s against five
-// passes of about 0.1 each; calibration and encoding together 0.98 -> 0.50 ms.
+// passes of about 0.1 each; calibration and encoding together 0.96 -> 0.46 ms.
 constexpr int QW_SAMPLE = 4096;   // sorting twice as many costs 40 us more than the narrower windows save
 
 __global__ __launch_bounds__(1024) void quantile_window_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int m,

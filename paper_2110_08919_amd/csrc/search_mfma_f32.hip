@@ -23,7 +23,7 @@
 // tiny next to its norms), vectors beyond 1e30 in square and anything not finite go through the
 // direct kernel instead.
 //
-// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.5 -> 0.94 ms (the scan 0.81 = 0.97 PFLOP/s
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.3 -> 0.88 ms (the scan 0.81 = 0.97 PFLOP/s
 // of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  In the scan the
 // matrix pipe is busy 45 % of the time and the LDS 27 %: the two waves of a SIMD split and store their
 // rows in step with each other, and wait a third of their time at the barrier of each stage.

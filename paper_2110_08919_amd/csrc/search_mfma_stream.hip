@@ -10,7 +10,7 @@
 //
 // Why this shape.  Rows of more than 1536 features had only the dot-product kernel; here the row
 // length does not matter: a k-step of the 256 x 256 tile reads six fragments from LDS for eight matrix
-// instructions.  200 000 x 2048, inner product, k = 10, whole search: 1000 queries 31.2 -> 0.49 ms, 10 000
+// instructions.  200 000 x 2048, inner product, k = 10, whole search: 1000 queries 31.2 -> 0.42 ms, 10 000
 // queries 3.9 ms = 2.1 POP/s.  Stages of 64 bytes (four in the ring) measured 10 % slower: half lines
 // double the requests that the L2 serves.
 //
