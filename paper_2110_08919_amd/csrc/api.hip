@@ -548,10 +548,17 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     // Lists of 11 to 16 entries: the 16-entry register lists cost more per accepted candidate than
     // collecting does; collecting measured 11 to 40 % faster at every batch size (d = 64 to 128).
     const bool long_lists = coll && k > 10;
-    // Batches of 65 to 256 queries on corpora of up to a million rows: the register lists fill from nothing
-    // in every split (10 000 x 128, 100 queries: 0.068 ms against 0.041 collecting; 50 000: 0.043 / 0.039; 300 000,
-    // 200 queries: 0.055 / 0.052; even at 1M; 4M x 64, 256 queries: 0.100 / 0.110, left to the lists).
-    const bool few_rows = coll && nq > 64 && n <= 1000000 && !compact;
+    // Batches of 65 to 256 and 513 to 768 queries (the others are `wide`), lists of 5 to 10: the register lists
+    // fill from nothing in every split, at a cost that grows with the candidates asked for and not with the
+    // corpus, so the collecting scan wins from about one candidate in fifty items on.  Collecting / register
+    // lists in us, 128 features, 8 bits: 5000 items, 65 queries, k = 10 42 / 55, 640 queries 49 / 63; 20 000, 256
+    // queries, k = 10 39 / 45, k = 5 38 / 36; 100 000, 65 queries, k = 10 42 / 35, 640 49 / 51; 300 000, 640 65 / 66,
+    // 256 50 / 50; a million, 65 68 / 62, 640 127 / 125.  k = 4 and less: the lists (50 000, 256 queries, k = 1 38 / 29).
+    // (Codes of few bits tie at the bound and all that tie is collected.  1 bit always keeps the lists: a
+    // million items, 100 queries 2.1 / 0.35 ms.  2 bits beyond 32 768 items too: 20 000, 256 queries 47 / 53 us,
+    // 100 000 53 / 45, a million 114 / 78.  3 bits behave like 8.)
+    const bool few_rows = coll && !compact && nq > 64 && k > 4 && nq * k * 50 >= n &&
+                          idx->bits >= (n <= 32768 ? WIDE_MIN_BITS : 3);
     // Packed rows: the row-split register-list kernel (callers tile the queries by 64), or for large
     // batches the collecting scan over all queries at once; the generic kernel on request.
     // (lists of more than 16 entries: the collecting scan at every batch size; rows of 32 packed
