@@ -273,6 +273,8 @@ struct F32Filter {
            total = 0;
 };
 F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k);
+// The filter's score of an item is within this times (|q|^2 + |x|^2) / 2 of the directly summed one.
+constexpr float f32_filter_constant(int d) { return 0x1p-14f + (float)d * 0x1p-20f; }
 // Rows that may be among the k nearest of each query -> regions cbuf[nq][S2][Cs] (the low half of a
 // candidate holds the row), ccnt[nq][S2]; the counter behind the redo list is cleared.
 hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,

@@ -9,12 +9,15 @@
 //   score       s = q.x - |x|^2 / 2 (L2; larger = nearer) or q.x (inner product)
 //   split       q = qh + ql, x = xh + xl in bf16 (round to nearest), and
 //               acc = qh.xh + qh.xl + ql.xh accumulated in fp32
-//   error       |acc - q.x| <= 3 2^-18 sum |q x|  (what the split drops: ql.xl and the remainders)
-//                            + 3 d 2^-23 (sum |q x| + |x|^2 / 2)  (3 d accumulations, each off by an ulp)
+//   error       |acc - q.x| <= 2^-15 sum |q x|  (what the split drops.  bf16 keeps 8 bits, so |ql| <= 2^-8 |q| and the
+//                              remainder of q is at most 2^-17 |q|: ql.xl 2^-16, the two remainders 2^-17 each;
+//                              1.00391388 squared, just below a tie, is off by 0.994 2^-15)
+//                            + 3 d 2^-23 sum |q x|  (3 d accumulations, each off by an ulp)
 //               |x|^2 is off by d 2^-24 of itself, the directly summed distance by (d / 8 + 8) 2^-24 of
-//               itself, at most (d / 4 + 16) 2^-24 (|q|^2 + |x|^2) on the score's scale;
-//               sum |q x| <= (|q|^2 + |x|^2) / 2, so all of it together stays below
-//               C (|q|^2 + |x|^2) / 2   with   C = 2^-15 + d 2^-20
+//               itself, at most (d / 4 + 16) 2^-24 (|q|^2 + |x|^2) on the score's scale, and the few operations
+//               that form a bound by an ulp of it each; sum |q x| <= (|q|^2 + |x|^2) / 2 = M, so all of it
+//               together is less than  (2^-15 + 2^-18 + d 2^-21) M, and stays below
+//               C (|q|^2 + |x|^2) / 2   with   C = 2^-14 + d 2^-20   (f32_filter_constant)
 //
 // so  acc - |x|^2 / 2 -+ C (|q|^2 + |x|^2) / 2  bounds an item's score from both sides, split into a part
 // per item and a part per query.  A seeding pass over a sample takes, per query, the k-th largest
@@ -502,7 +505,7 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     FilterIo o = {};
     o.x = x; o.n = n; o.ldx = ldx; o.d = d; o.dp = p.dp;
     o.qh = qh; o.ql = ql; o.qn = qn; o.nq = nq; o.qtiles = p.qtiles;
-    o.c = 0x1p-15f + (float)d * 0x1p-20f;
+    o.c = f32_filter_constant(d);
     // seeding pass: lower bounds of the scores of a sample (runs of 16 rows spread over the corpus)
     o.S = p.S1; o.SEG = p.SEG; o.gmax = gmax;
     o.tiles = p.seed_tiles; o.tile_stride = p.run_stride; o.run_gap = (int64_t)p.seed_tiles * p.run_stride;
