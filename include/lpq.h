@@ -195,7 +195,7 @@ int lpq_search_i8(const lpq_index *idx, const int8_t *qcodes_dev, int64_t nq, in
  * a query vector and its candidate buffer in 64 KB of LDS, which bounds d: at most 15 328 features
  * for k <= 256, 12 256 for k = 1024 (in between: (65 408 - 8 c) / 4 rounded down to a multiple of 4,
  * c = the power of two >= max(2 k, k + 256)); beyond that LPQ_ERANGE, and the workspace query
- * returns 0. */
+ * returns 0.  Batches are searched in parts of as many queries as about 256 MB of workspace hold. */
 size_t lpq_search_f32_workspace_bytes(int64_t n, int64_t nq, int d, int k);
 int lpq_search_f32(const float *x_dev, int64_t n, int64_t ldx, const float *q_dev, int64_t nq,
                    int64_t ldq, int d, int k, int metric, int32_t *ids_dev, float *dist_dev,

@@ -298,33 +298,40 @@ static size_t f32_lists_bytes(int64_t n, int64_t nq, int d, int k)
     return ((size_t)nq * f32_splits(n, nq, d, k) * k * sizeof(cand_t) + 255) & ~size_t(255);
 }
 
-// Larger batches are searched this many queries at a time, which bounds the workspace (a few hundred
-// megabytes of candidate regions); the tiles are full long before.
-constexpr int64_t F32_BATCH = 16384;
-
 static size_t f32_batch_bytes(int64_t n, int64_t nq, int d, int k)
 {
     return f32_lists_bytes(n, nq, d, k) + f32_filter_plan(n, nq, d, k).total;
 }
 
-size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k)
+// Queries searched at a time: as many as 256 MB of workspace hold, in parts of about the same size.  (Whole, 8192
+// queries, k = 480 on 1M x 128 took 1.2 GB of candidate regions, where the direct kernel's lists take 31 MB.  A few
+// thousand queries fill the tiles: 10 000, k = 100, 512 MB, 10.22 ms, in four parts of 141 MB 10.40.)
+constexpr size_t F32_WORKSPACE = size_t(256) << 20;
+
+static size_t f32_parts_bytes(int64_t n, int64_t nq, int64_t b, int d, int k)   // the largest part's workspace
 {
-    if (nq <= F32_BATCH) return f32_batch_bytes(n, nq, d, k);
-    const size_t full = f32_batch_bytes(n, F32_BATCH, d, k), rest = nq % F32_BATCH ? f32_batch_bytes(n, nq % F32_BATCH, d, k) : 0;
+    const int64_t last = nq > b ? nq % b : 0;
+    const size_t full = f32_batch_bytes(n, b, d, k), rest = last ? f32_batch_bytes(n, last, d, k) : 0;
     return full > rest ? full : rest;
 }
 
-hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
-                             int d, int k, int metric, int32_t *ids, float *dists, void *ws, hipStream_t st)
+static int64_t f32_batch(int64_t n, int64_t nq, int d, int k)
 {
-    if (nq > F32_BATCH) {
-        for (int64_t q0 = 0; q0 < nq; q0 += F32_BATCH) {
-            const hipError_t e = launch_search_f32(x, n, ldx, q + q0 * ldq, nq - q0 < F32_BATCH ? nq - q0 : F32_BATCH, ldq, d, k,
-                                                   metric, ids + q0 * k, dists + q0 * k, ws, st);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+    if (nq <= 256) return nq;
+    for (int64_t parts = ceil_div(nq, 16384);; parts *= 2) {
+        const int64_t b = parts == 1 ? nq : round_up(ceil_div(nq, parts), 128);
+        if (b <= 256 || f32_parts_bytes(n, nq, b, d, k) <= F32_WORKSPACE) return b;
     }
+}
+
+size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k)
+{
+    return f32_parts_bytes(n, nq, f32_batch(n, nq, d, k), d, k);
+}
+
+static hipError_t launch_f32_batch(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
+                                   int d, int k, int metric, int32_t *ids, float *dists, void *ws, hipStream_t st)
+{
     const int S = f32_splits(n, nq, d, k);
     const int qt = f32_query_tile(d, k);
     const int mode = metric == LPQ_METRIC_L2SQ ? MODE_F32_L2 : MODE_F32_IP;
@@ -369,6 +376,18 @@ hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float
     if (e != hipSuccess) return e;
     return launch_merge(lists, nq, S, k, nullptr, nullptr, nullptr, ids, reinterpret_cast<int32_t *>(dists),
                         nullptr, mode, st, true, only);
+}
+
+hipError_t launch_search_f32(const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
+                             int d, int k, int metric, int32_t *ids, float *dists, void *ws, hipStream_t st)
+{
+    const int64_t b = f32_batch(n, nq, d, k);
+    for (int64_t q0 = 0; q0 < nq; q0 += b) {
+        const hipError_t e = launch_f32_batch(x, n, ldx, q + q0 * ldq, nq - q0 < b ? nq - q0 : b, ldq, d, k, metric,
+                                              ids + q0 * k, dists + q0 * k, ws, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace lpq

@@ -1,0 +1,26 @@
+"""Workspace of the exact fp32 search: large batches are searched in parts.  The sizes need no GPU."""
+import pytest
+import torch
+
+from paper_2110_08919_amd import lpq, synth
+
+
+@pytest.mark.parametrize("n", [5000, 60_000, 447_990, 1_000_000, 50_000_000])
+@pytest.mark.parametrize("d", [16, 128, 771])
+def test_workspace_is_bounded_for_any_batch_and_k(n, d):
+    for k in (1, 10, 100, 480, 505, 1024):
+        for nq in (256, 257, 1000, 8192, 10_000, 16_384, 16_385, 20_580, 100_000, 1_000_000):
+            # 256 MB and the rounding of the query
+            assert 0 < lpq.lib().lpq_search_f32_workspace_bytes(n, nq, d, k) <= (256 << 20) + 256
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,nq,k", [(30_000, 16, 15_001, 100)])
+def test_search_in_parts_equals_the_same_queries_searched_apart(n, d, nq, k):
+    w = synth.Workload("w", "bimodal", n, d, nq, "l2sq", (k,), "minmax", "global", 3)
+    x, q = w.corpus("cuda"), w.queries("cuda")
+    ids, dists = lpq.search_f32(x, q, k, "l2sq")
+    for q0, q1 in ((0, 70), (nq // 2 - 40, nq // 2 + 40), (nq - 50, nq)):
+        i, v = lpq.search_f32(x, q[q0:q1], k, "l2sq")
+        torch.cuda.synchronize()
+        assert torch.equal(ids[q0:q1], i) and torch.equal(dists[q0:q1], v)
