@@ -33,10 +33,10 @@ struct CalibScratch {
     // quantile selection by windows: per target and column
     uint32_t *qwin;              // [2][d][2] first and last key of the window
     uint32_t *qcount;            // [2][d][4] values strictly inside, equal to the first, to the last, outside (below / above)
-    uint32_t *qlist;             // [2][d][window_cap(d)] keys strictly inside
 };
 
-// Keys a window's list holds: 16 MB of lists in all; none beyond 2048 features.
+// Keys a window's list holds ([2][d][window_cap(d)], the keys strictly inside): 16 MB of lists in all; none
+// beyond 2048 features.
 int window_cap(int d)
 {
     if (d > 2048) return 0;
@@ -62,8 +62,7 @@ CalibScratch carve(void *scratch, int d)
     s.qrank = (unsigned long long *)p;  p += sizeof(unsigned long long) * 2 * (size_t)d;
     s.qprefix = (uint32_t *)p;  p += sizeof(uint32_t) * 2 * (size_t)d;
     s.qwin = (uint32_t *)p;     p += sizeof(uint32_t) * 4 * (size_t)d;
-    s.qcount = (uint32_t *)p;   p += sizeof(uint32_t) * 8 * (size_t)d;
-    s.qlist = (uint32_t *)p;
+    s.qcount = (uint32_t *)p;
     return s;
 }
 
@@ -1114,43 +1113,57 @@ size_t calib_scratch_bytes(int d)
 {
     const size_t G = calib_blocks(d) + CAL_EXTRA_ROWS;
     return G * d * (sizeof(double) + 2 * sizeof(float)) + (size_t)d * (3 * sizeof(double) + 2 * sizeof(float)) + 256 +
-           (size_t)d * (512 * sizeof(unsigned long long) + 2 * sizeof(unsigned long long) + 14 * sizeof(uint32_t)) +
-           (size_t)2 * d * window_cap(d) * sizeof(uint32_t);
+           (size_t)d * (512 * sizeof(unsigned long long) + 2 * sizeof(unsigned long long) + 14 * sizeof(uint32_t));
+}
+
+size_t calib_lists_bytes(int64_t n, int d, int mode, int scope, double clip)
+{
+    if (mode != LPQ_CALIB_QUANTILE || scope == LPQ_SCOPE_GLOBAL) return 0;
+    // values a window is expected to hold: twice the sample's deviation and the rank's own share
+    const int m = (int)(n < QW_SAMPLE ? n : QW_SAMPLE), cap = window_cap(d);
+    const double at = clip * m, dev = 5.0 * sqrt(at * (1.0 - clip)) + 5.0;
+    const double expect = ((at < dev ? at : dev) + dev) / m * (double)n;
+    return expect + 8.0 * expect / sqrt(at + dev) < (double)cap ? (size_t)2 * d * cap * sizeof(uint32_t) : 0;
+}
+
+static unsigned long long low_rank(int64_t n, double clip) { return (unsigned long long)floor(clip * (double)(n - 1)); }
+static unsigned long long high_rank(int64_t n, double clip) { return (unsigned long long)ceil((1.0 - clip) * (double)(n - 1)); }
+
+hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, double clip, void *scratch, hipStream_t st)
+{
+    CalibScratch s = carve(scratch, d);
+    const int m = (int)(n < QW_SAMPLE ? n : QW_SAMPLE);
+    quantile_window_kernel<<<d, 1024, (size_t)next_pow2(m) * sizeof(uint32_t), st>>>(x, n, ld, d, m, low_rank(n, clip),
+                                                                                     high_rank(n, clip), s.qwin, s.qcount);
+    return hipGetLastError();
 }
 
 hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bits, int mode, int scope,
                             double sigma_mult, void *scratch, float *params_out, float *params_committed,
-                            int *nonfinite_flag, hipStream_t st, bool windows)
+                            int *nonfinite_flag, hipStream_t st, uint32_t *lists)
 {
     const int G = calib_blocks(d);
     CalibScratch s = carve(scratch, d);
     const int64_t rpb = ceil_div(n, G);
     hipError_t e = hipMemsetAsync(nonfinite_flag, 0, sizeof(int), st);
     if (e != hipSuccess) return e;
-    if (mode == LPQ_CALIB_QUANTILE && scope != LPQ_SCOPE_GLOBAL && windows) {
-        const unsigned long long rl = (unsigned long long)floor(sigma_mult * (double)(n - 1));
-        const unsigned long long rh = (unsigned long long)ceil((1.0 - sigma_mult) * (double)(n - 1));
-        // values a window is expected to hold: twice the sample's deviation and the rank's own share
-        const int m = (int)(n < QW_SAMPLE ? n : QW_SAMPLE), cap = window_cap(d);
-        const double at = sigma_mult * m, dev = 5.0 * sqrt(at * (1.0 - sigma_mult)) + 5.0;
-        const double expect = ((at < dev ? at : dev) + dev) / m * (double)n;
-        if (expect + 8.0 * expect / sqrt(at + dev) < (double)cap) {
-            int lpr = 1;
-            while (4 * lpr < d && lpr < 32) lpr <<= 1;
-            const int64_t tiles = ceil_div(d, 4 * lpr);
-            int64_t rows = round_up(ceil_div(n * tiles, 512), 64);   // two workgroups per CU
-            if (rows < 512) rows = 512;
-            const dim3 grid((unsigned)ceil_div(n, rows), (unsigned)tiles);
-            quantile_window_kernel<<<d, 1024, (size_t)next_pow2(m) * sizeof(uint32_t), st>>>(x, n, ld, d, m, rl, rh, s.qwin, s.qcount);
-            if (d % 4 == 0 && ld % 4 == 0 && (uintptr_t)x % 16 == 0)
-                quantile_gather_kernel<true><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, s.qlist, cap, nonfinite_flag);
-            else
-                quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, s.qlist, cap, nonfinite_flag);
-            quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, s.qwin, s.qcount, s.qlist, cap, s.mn, s.mx, nonfinite_flag);
-            calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out,
-                                                           nonfinite_flag, params_committed);
-            return hipGetLastError();
-        }
+    if (lists) {
+        const unsigned long long rl = low_rank(n, sigma_mult), rh = high_rank(n, sigma_mult);
+        const int cap = window_cap(d);
+        int lpr = 1;
+        while (4 * lpr < d && lpr < 32) lpr <<= 1;
+        const int64_t tiles = ceil_div(d, 4 * lpr);
+        int64_t rows = round_up(ceil_div(n * tiles, 512), 64);   // two workgroups per CU
+        if (rows < 512) rows = 512;
+        const dim3 grid((unsigned)ceil_div(n, rows), (unsigned)tiles);
+        if (d % 4 == 0 && ld % 4 == 0 && (uintptr_t)x % 16 == 0)
+            quantile_gather_kernel<true><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, lists, cap, nonfinite_flag);
+        else
+            quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, lists, cap, nonfinite_flag);
+        quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, s.qwin, s.qcount, lists, cap, s.mn, s.mx, nonfinite_flag);
+        calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out,
+                                                       nonfinite_flag, params_committed);
+        return hipGetLastError();
     }
     // 16-byte loads when the rows allow them; lanes per row: the power of two that covers d / 4
     const bool vec = d % 4 == 0 && ld % 4 == 0 && (uintptr_t)x % 16 == 0;
