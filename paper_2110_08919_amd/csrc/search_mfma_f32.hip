@@ -22,9 +22,10 @@
 // so  acc - |x|^2 / 2 -+ C (|q|^2 + |x|^2) / 2  bounds an item's score from both sides, split into a part
 // per item and a part per query.  A seeding pass over a sample takes, per query, the k-th largest
 // group maximum of the lower bounds (at least k items reach it); the scan collects every item whose
-// upper bound does.  (An absolute 2^-110 covers products that underflow.)  Queries that collect too many (data whose distances are
-// tiny next to its norms), vectors beyond 1e30 in square and anything not finite go through the
-// direct kernel instead.
+// upper bound does.  (An absolute 2^-110 covers products that underflow.)  Queries that collect too many
+// (data whose distances are tiny next to its norms), vectors beyond 1e30 in square and anything not finite go
+// through the direct kernel instead; the scan collects nothing more for a query whose region has overflowed,
+// and a workgroup ends when none of its queries is left.
 //
 // Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.3 -> 0.88 ms (the scan 0.81 = 0.97 PFLOP/s
 // of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  In the scan the
@@ -79,9 +80,13 @@ struct FilterIo {
 };
 
 constexpr int FDUMPS = 32;
+// Control words of a workgroup of the scan, in LDS: queries that are done (their region has overflowed, or the slot holds
+// none), and what wave 0 has said of them.
+enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_WORDS = 64 };
+constexpr int ALL_LOST = 1 << 20;     // in CTL_DONE: a row was seen that the bounds do not hold for
 constexpr size_t filter_lds_bytes(int wq, bool seed)
 {
-    return (size_t)2 * (TILE_ROWS + 64 * wq) * 2 * PB + 4 * TILE_ROWS * 4 + (size_t)64 * wq * 8 + 256 +
+    return (size_t)2 * (TILE_ROWS + 64 * wq) * 2 * PB + 4 * TILE_ROWS * 4 + (size_t)64 * wq * 8 + CTL_WORDS * 4 +
            (seed ? 0 : (size_t)FW * FDUMPS * 80);
 }
 
@@ -138,12 +143,14 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     float *nx = reinterpret_cast<float *>(smem + 2 * STAGE);       // [4][256] squared norms, by tile & 3
     float *thr_l = nx + 4 * TILE_ROWS;                             // [QT]
     int *fill = reinterpret_cast<int *>(thr_l + QT);               // [QT]
-    int *bad = fill + QT;                                          // a row that is not finite, or huge, was seen
-    float *dval = reinterpret_cast<float *>(bad + 64) + wave * (DUMPS * 20);
+    int *ctl = fill + QT;                                          // [CTL_WORDS]
+    float *dval = reinterpret_cast<float *>(ctl + CTL_WORDS) + wave * (DUMPS * 20);
     v4i *dmeta = reinterpret_cast<v4i *>(dval + DUMPS * 16);
     const int64_t q_tile = (int64_t)qt * QT, q_first = q_tile + wq * 64;
 
     if (!SEED) {
+        if (tid < CTL_WORDS) ctl[tid] = 0;
+        __syncthreads();
         for (int i = tid; i < QT; i += FW * 64) {
             float t = NAN;                                         // nothing compares: a slot that never collects
             if (q_tile + i < o.nq && o.qn[q_tile + i] <= HUGE_NORM) {
@@ -151,11 +158,11 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 t = kth == INT32_MIN ? -INFINITY
                                      : sortable_to_float(kth) - o.c * o.qn[q_tile + i] * 1.00001f - 0x1p-110f;
             }
+            if (t != t) atomicAdd(&ctl[CTL_DONE], 1);
             thr_l[i] = t;
             fill[i] = 0;
         }
     }
-    if (tid == 0) *bad = 0;
     __syncthreads();
     float thr[2] = {NAN, NAN}, gm[2] = {-INFINITY, -INFINITY};
     if (!SEED) { thr[0] = thr_l[wq * 64 + col]; thr[1] = thr_l[wq * 64 + 32 + col]; }
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 p += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(p)));
                 p += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(p)));
                 if ((lane & 7) == 0) dst[wave * 32 + i * 8 + lrow] = p;
-                if (!SEED && !(p <= HUGE_NORM)) *bad = 1;
+                if (!SEED && !(p <= HUGE_NORM)) ctl[CTL_DONE] = ALL_LOST;
                 part[i] = 0.0f;
             }
             pk = 0;
@@ -291,7 +298,12 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 const int64_t row = (int64_t)(unsigned)m4[0] + 8 * (r >> 2) + 4 * (m4[1] >> 8) + (r & 3);
                 if (u >= thr_l[ql] && row < o.n) {
                     const int pos = atomicAdd(&fill[ql], 1);
-                    if (pos < o.Cs) cbase[(size_t)ql * qstride + pos] = (cand_t)row;
+                    if (__builtin_expect(pos < o.Cs, 1)) {
+                        cbase[(size_t)ql * qstride + pos] = (cand_t)row;
+                    } else if (__builtin_expect(pos == o.Cs, 0)) {   // the direct kernel takes this query: collect no more for it
+                        thr_l[ql] = NAN;
+                        atomicAdd(&ctl[CTL_DONE], 1);
+                    }
                 }
             }
         }
@@ -336,6 +348,16 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         LPQF_MFMA(1);
         ++t;
     };
+    // For the epilogue of the next tile, read in this one: how many queries are done, and how many wave 0 said are
+    // done in the epilogue before this one.  Everyone has passed the barriers of a tile since, and that word is
+    // written again only behind those of the next, so all threads of the workgroup get the same.
+    int done = 0, said = 0, known = 0, next = 0;
+    auto look = [&]() {
+        done = ctl[CTL_DONE];
+        said = ctl[CTL_SAID + next];
+        next ^= 1;
+    };
+    if (!SEED) look();
 #pragma clang loop unroll(disable)
     for (int tile = 0; tile < nt; ++tile) {
 #pragma unroll
@@ -355,6 +377,17 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         __builtin_amdgcn_sched_barrier(0);        // nothing of the contraction drifts down into the epilogue
         const int64_t row0 = ((int64_t)s + (int64_t)tile * S) * o.tile_stride;
         int dumps = 0;
+        if (!SEED) {
+            const int now = __builtin_amdgcn_readfirstlane(said);
+            if (__builtin_expect(now != known, 0)) {
+                if (now >= QT) break;            // nothing left to collect
+                known = now;
+                thr[0] = thr_l[wq * 64 + col];
+                thr[1] = thr_l[wq * 64 + 32 + col];
+            }
+            if (tid == 0) ctl[CTL_SAID + (next ^ 1)] = done;
+            look();                              // (here, not behind the epilogue: the next stage waits for all LDS reads at once)
+        }
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             const float *np = nx + (tile & 3) * TILE_ROWS + (wr * RB + i) * 32 + 4 * half;
@@ -406,10 +439,12 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 #undef LPQF_ORDER
 
     if (!SEED) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (left early: the query copies on their way land before the LDS is given back)
         __syncthreads();
         // a row the bounds do not hold for: all queries of the tile overflow
+        const bool lost = ctl[CTL_DONE] >= ALL_LOST;
         for (int i = tid; i < QT; i += FW * 64)
-            if (q_tile + i < o.nq) o.ccnt[(size_t)(q_tile + i) * S + s] = *bad ? o.Cs + 1 : fill[i];
+            if (q_tile + i < o.nq) o.ccnt[(size_t)(q_tile + i) * S + s] = lost ? o.Cs + 1 : fill[i];
     }
 }
 
