@@ -526,6 +526,7 @@ struct Plan {
     int Sg = 0;             // PLAN_MFMA_COLLECT: splits of the generic kernel for overflowed queries
     int Sr = 0;             // PLAN_MFMA_COLLECT: splits of the register-list kernel for many overflowed queries (0 = none)
     int rounds = 0;         // PLAN_MFMA_COLLECT: further rounds of the collecting scan, with tighter bounds, for overflowed queries
+    int few = 0;            // ... unless no more than this many overflowed, which the generic kernel takes
     int wave_queries = 64;  // PLAN_MFMA_COLLECT: queries per wave of the scan
     bool stream = false;    // PLAN_MFMA_COLLECT: the scan that streams both operands (search_mfma_stream.hip)
     int seed_tiles = 0;     // ... its seeding pass: tiles of 256 rows, in runs of 16 rows
@@ -799,6 +800,12 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
         }
         // longer lists: a second collecting scan of the flagged queries, bounded by what the first collected
         if (!p.Sr) {
+            // A round takes as long as the scan of the whole batch, the generic kernel as long as the corpus over Sg
+            // splits - fewer for longer lists - once, and up to twice that for 16 queries.  1 / 8 / 16 flagged, ms above a search with
+            // none, generic kernel against rounds: 10 000 queries on 500K x 768, k = 10 0.8 / 1.0 / 1.7 against 3.7;
+            // on 1M x 128, k = 32 0.63 / 0.72 / 0.75 against 1.15; 4000 queries there, k = 20 0.37 / 0.42 / 0.72 against 0.65;
+            // 2048 on 500K x 768, k = 10 0.54 / 0.63 / 1.25 against 0.90; 1000 on 1M x 128, k = 100 0.72 against 0.20.
+            if (k <= 32 && nq >= 2048) p.few = nq >= 8192 ? 16 : 8;
             p.rounds = p.rsplit ? 1 : REFINE_ROUNDS;   // few queries: every launch counts, and their many regions rarely overflow twice
             p.off_bounds2 = o; o = align256(o + (size_t)p.nq_pad * sizeof(cand_t));
             p.off_over2 = o;   o = align256(o + (size_t)p.rounds * nq * sizeof(int32_t));
@@ -910,30 +917,31 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         // by the generic kernel, many (a corpus full of duplicates or ties) by a pass of the register-list
         // kernel over the query tiles that hold one; both are launched and the count on the device decides.
         if (p.Sr)
-            HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist, qcount, lists2, over, ids, dist, qnorms, emit_mode, st,
-                                               REDO_GENERIC_MAX));
+            HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, {qlist, qcount, over}, REDO_GENERIC_MAX, {}, lists2, ids, dist,
+                                               qnorms, emit_mode, st));
         // Otherwise the selection has also left a bound per flagged query, taken from what the scan did
         // collect for it, and the scan runs again over the query tiles that hold one, up to p.rounds times
         // (what a round collects is the FIRST candidates of each region in scan order, not the best, so one
         // round may still leave too many: each cuts the number that pass by about k / (candidates the regions
-        // hold)).  What overflows even then goes through the generic kernel.  All of it returns at once when
-        // nothing is flagged, so the number of these launches is what a search pays: scan and selection per
-        // round and one more (with the bounds and the merge in launches of their own and the generic kernel in
+        // hold)).  What overflows even then goes through the generic kernel, and so does at once what is flagged first
+        // where no more than p.few queries are: a round takes as long as the scan of the whole batch, however few
+        // they are.  All of it returns at once when nothing is flagged, so the number of these launches is what a
+        // search pays: scan and selection per round and one more (with the bounds and the merge in launches of their own and the generic kernel in
         // front, ten instead of five, 1000 queries on 500K x 768 took 15 us longer).
         const int32_t *over_prev = over, *count_prev = qcount;
         for (int r = 0; r < p.rounds; ++r) {
             int32_t *over_r = reinterpret_cast<int32_t *>(ws + p.off_over2) + (size_t)r * nq;
             int32_t *qlist_r = reinterpret_cast<int32_t *>(ws + p.off_qlist2) + (size_t)r * (nq + 1), *count_r = qlist_r + nq;
             SearchArgs ar = a;
-            ar.redo_flags = over_prev; ar.redo_count = count_prev; ar.redo_min = 0;
+            ar.redo_flags = over_prev; ar.redo_count = count_prev; ar.redo_min = r ? 0 : p.few;
             HIP_TRY(collect(ar, bounds2));
             const bool last = r + 1 == p.rounds;
             HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over_r, qlist_r, count_r, ids, dist, qnorms,
-                                          emit_mode, st, 0, over_prev, count_prev, 0, bounds2, last ? nullptr : bounds2));
+                                          emit_mode, st, 0, over_prev, count_prev, ar.redo_min, bounds2, last ? nullptr : bounds2));
             over_prev = over_r; count_prev = count_r;
             if (last)
-                HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, qlist_r, count_r, lists2, over_r, ids, dist, qnorms,
-                                                   emit_mode, st));
+                HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, {qlist, qcount, over}, p.few, {qlist_r, count_r, over_r}, lists2,
+                                                   ids, dist, qnorms, emit_mode, st));
         }
         if (p.Sr) {
             cand_t *lists_r = reinterpret_cast<cand_t *>(ws + p.off_redo);

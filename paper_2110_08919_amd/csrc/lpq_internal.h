@@ -162,13 +162,18 @@ constexpr int REDO_GENERIC_MAX = 64;
 // Writes lists[(q * S + s) * k + r], sorted ascending, CAND_NONE-filled.
 hipError_t launch_search_generic(const SearchArgs &a, int64_t row0, int64_t row1, int S,
                                  const cand_t *seeds, cand_t *lists, hipStream_t st);
-// The same for the *qcount queries listed in qlist (device memory, written by an earlier kernel): a fixed
-// grid shares out the (query, split) pairs, and a query's lists are merged into its final result (S k <=
-// 4096).  flags[q] is 1 for a listed query and stays non-zero.  Does nothing if more than max_listed
-// queries are listed.
-hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const int32_t *qlist,
-                                      const int32_t *qcount, cand_t *lists, int32_t *flags, int32_t *ids, int32_t *dists,
-                                      const int32_t *qnorms, int metric, hipStream_t st, int max_listed = INT32_MAX);
+// Queries to be searched again: their number and numbers, written by an earlier kernel, and a flag per query of
+// the batch, 1 for a listed one.
+struct RedoList {
+    const int32_t *queries, *count;
+    int32_t *flags;
+};
+// The same for the queries of `first`, or of `last` if first lists more than first_max (without last nothing is
+// done then): a fixed grid shares out the (query, split) pairs, and a query's lists are merged into its final
+// result (S k <= 4096).  The flags of the queries searched stay non-zero.
+hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const RedoList &first,
+                                      int first_max, const RedoList &last, cand_t *lists, int32_t *ids, int32_t *dists,
+                                      const int32_t *qnorms, int metric, hipStream_t st);
 
 // Matrix-core kernels.  search_mfma.hip keeps the k best of a query in registers (k <= 16) and
 // has a seeding pass; search_mfma_lds.hip keeps them in LDS (larger k).  launch_search_mfma

@@ -126,38 +126,48 @@ __device__ __forceinline__ cand_t next_bound(cand_t c) { return c + 1; }
 // The same scan for a LIST of queries (the ones a collecting scan could not finish): the
 // workgroups of a fixed-size grid share out the (listed query, split) pairs, so a handful of
 // queries is spread over the whole chip and an empty list costs one tiny launch.  The workgroup that
-// finishes a query's last split merges its lists: flags[q], 1 when listed, counts the finished ones (and
+// finishes a query's last split merges its lists: the flag of a query, 1 when listed, counts the finished ones (and
 // stays non-zero), so no second launch is needed, and none waits for another.
+// The merge takes no more LDS than eight workgroups of a CU have room for (with 32 KB to sort 4096 at once, 16 of 4000
+// queries, k = 20, on 1M x 128 took 0.87 ms here, with 16 KB 0.72).
+constexpr int LIST_MERGE_CAP = 2048;
 __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
-    SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, const int32_t *__restrict__ qlist,
-    const int32_t *__restrict__ qcount, cand_t *lists, int cap, int max_listed, int32_t *flags, int32_t *__restrict__ ids,
-    int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
+    SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, RedoList first, int first_max, RedoList last,
+    cand_t *lists, int cap, int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms,
+    int metric)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);
     uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
     __shared__ int s_count, s_last;
     __shared__ cand_t s_thr;
-    if (*qcount > max_listed) return;                       // too many for this path: another kernel takes them
-    const int64_t items = (int64_t)(*qcount) * S;           // same for every thread of the grid
+    const bool many = *first.count > first_max;             // same for every thread of the grid
+    if (many && !last.queries) return;                      // another kernel takes them
+    const RedoList work = many ? last : first;
+    const int64_t items = (int64_t)(*work.count) * S;
     for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const int64_t q = qlist[item / S];
+        const int64_t q = work.queries[item / S];
         const int s = (int)(item % S);
         const int64_t rs = row0 + (int64_t)s * split_rows;
         const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
         generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
         __threadfence();                                    // this thread's part of the list is visible to the chip
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&flags[q], 1) == S;
+        if (threadIdx.x == 0) s_last = atomicAdd(&work.flags[q], 1) == S;
         __syncthreads();
         if (s_last) {                                       // the same answer in every thread of the workgroup
             __threadfence();
-            const int m = S * a.k;
-            int mcap = 2;
-            while (mcap < m) mcap <<= 1;
-            for (int i = threadIdx.x; i < mcap; i += GEN_THREADS) buf[i] = i < m ? lists[q * m + i] : CAND_NONE;
-            __syncthreads();
-            block_bitonic_sort(buf, mcap);
+            const int m = S * a.k;                          // up to 4096, sorted in two or three parts
+            for (int from = 0, kept = 0; from < m; kept = a.k) {
+                const int take = m - from < LIST_MERGE_CAP - kept ? m - from : LIST_MERGE_CAP - kept;
+                int mcap = 2;
+                while (mcap < kept + take) mcap <<= 1;
+                for (int i = kept + threadIdx.x; i < mcap; i += GEN_THREADS)
+                    buf[i] = i < kept + take ? lists[q * m + from + (i - kept)] : CAND_NONE;
+                __syncthreads();
+                block_bitonic_sort(buf, mcap);
+                from += take;
+            }
             for (int i = threadIdx.x; i < a.k; i += GEN_THREADS) emit_result(buf[i], q * a.k + i, q, ids, dists, qnorms, metric);
             __syncthreads();
         }
@@ -295,110 +305,6 @@ __device__ __forceinline__ void wave_sort(cand_t (&v)[E], int lane)
     }
 }
 
-// Last step of the collecting scan for k <= 128 and at most 64 R regions, one WAVE per query and no
-// LDS: lane r holds the counts of regions R r .. R r + R - 1; the wave loads up to 512 candidates (2, 4 or 8
-// per lane as needed, each found by a search over the prefix counts), sorts them in registers and keeps the
-// best 128 in its first 16 lanes; further candidates come in 384 at a time through the other 48 lanes.  Any number
-// of candidates the regions hold is handled; a query with an overflowed region or fewer than k
-// candidates is flagged in over[] instead, and gets a tighter bound for the next round where bounds_out
-// is given (see next_bound; zero for the others).  (R = 4: 1000 queries with 256 regions take 9 us
-// against 13 with a workgroup per query.)
-template <int R>
-__global__ __launch_bounds__(256) void collect_select_sort_kernel(
-    const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t nq, int SS, int Cs, int k,
-    int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
-    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric,
-    const cand_t *__restrict__ bounds_in, cand_t *__restrict__ bounds_out)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 4 + wave;
-    if (q >= nq) return;                                   // wave-uniform
-    bool bad = false;
-    int upto[R], mine = 0;                                 // candidates of this lane's regions 0 .. j together
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int offered = (R * lane + j < SS) ? ccnt[q * SS + R * lane + j] : 0;
-        bad |= offered > Cs || offered < 0;
-        mine += offered < 0 ? 0 : (offered < Cs ? offered : Cs);   // what the region holds
-        upto[j] = mine;
-    }
-    int incl = mine;                                       // inclusive prefix sum over the lanes
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    const int total = __shfl(incl, 63, 64);
-    const bool flagged = __ballot(bad) || total < k;       // wave-uniform
-    if (flagged) {
-        if (lane == 0) { over[q] = 1; qlist[atomicAdd(qcount, 1)] = (int32_t)q; }
-        if (!bounds_out) return;
-        if (total < k) {                                   // nothing better than the old bound
-            if (lane == 0) bounds_out[q] = bounds_in[q];
-            return;
-        }
-    }
-    const int excl = incl - mine;                          // index of the first candidate of this lane's regions
-    const cand_t *base = cbuf + (size_t)q * SS * Cs;
-    // candidate number i of the query sits with the first lane whose inclusive count exceeds i, there in the
-    // first region that ends beyond it
-    auto fetch = [&](int i) -> cand_t {
-        int r = 0;
-#pragma unroll
-        for (int step = 32; step >= 1; step >>= 1)
-            if (__shfl(incl, r + step - 1, 64) <= i) r += step;
-        r = r > 63 ? 63 : r;
-        int at = i - __shfl(excl, r, 64), region = R * r, before = 0;
-#pragma unroll
-        for (int j = 0; j + 1 < R; ++j) {
-            const int end = __shfl(upto[j], r, 64);
-            if (at >= end) { region = R * r + j + 1; before = end; }
-        }
-        return i < total ? base[(size_t)region * Cs + (at - before)] : CAND_NONE;
-    };
-    auto put = [&](cand_t v, int e) {                      // the e-th best
-        if (flagged) {
-            if (e == k - 1) bounds_out[q] = next_bound(v);
-        } else if (e < k) {
-            emit_result(v, q * k + e, q, ids, dists, qnorms, metric);
-        }
-    };
-    // few candidates: a smaller network (2 or 4 per lane) does
-    auto small = [&](auto tag) {
-        constexpr int E = decltype(tag)::value;
-        cand_t v[E];
-#pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = fetch(j * 64 + lane);
-        wave_sort<E>(v, lane);
-#pragma unroll
-        for (int j = 0; j < E; ++j) put(v[j], lane * E + j);
-    };
-    if (total <= 128) {                                    // wave-uniform
-        small(std::integral_constant<int, 2>{});
-    } else if (total <= 256) {
-        small(std::integral_constant<int, 4>{});
-    } else {
-        cand_t v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = fetch(j * 64 + lane);
-        wave_sort<8>(v, lane);
-        for (int done = 512; done < total; done += 384) {  // wave-uniform: the best 128 stay in lanes 0 .. 15
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const cand_t n = fetch(done + j * 48 + (lane - 16));   // (every lane takes part in the shuffles)
-                if (lane >= 16) v[j] = n;
-            }
-            wave_sort<8>(v, lane);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) put(v[j], lane * 8 + j);
-    }
-    if (lane == 0 && !flagged) {
-        over[q] = 0;
-        if (bounds_out) bounds_out[q] = 0;
-    }
-}
-
 // A query whose regions overflowed: whatever the scan did collect for it are real items, so the k-th
 // best of them bounds its final k-th best from above - and far more closely than the seeding pass did,
 // since they all passed its bound.  The scan passes candidates strictly below a bound, and the k-th best
@@ -436,15 +342,13 @@ __device__ cand_t refined_bound(const cand_t *cbuf, const int32_t *ccnt, int64_t
     if (per < Cs && kth != CAND_NONE) {
         if (tid == 0) s_n = 0;
         __syncthreads();
-        for (int r = 0; r < SS; ++r) {
-            int cnt = ccnt[q * SS + r];
-            cnt = cnt > Cs ? Cs : cnt;
-            for (int j = tid; j < cnt; j += 256) {
-                const cand_t c = cbuf[((size_t)q * SS + r) * Cs + j];
-                if (c <= kth) {
-                    const int at = atomicAdd(&s_n, 1);
-                    if (at < maxc) buf[at] = c;
-                }
+#pragma unroll 4
+        for (int i = tid; i < SS * Cs; i += 256) {
+            const int r = i / Cs;
+            const cand_t c = i - r * Cs < ccnt[q * SS + r] ? cbuf[(size_t)q * SS * Cs + i] : CAND_NONE;
+            if (c <= kth) {
+                const int at = atomicAdd(&s_n, 1);
+                if (at < maxc) buf[at] = c;
             }
         }
         __syncthreads();
@@ -459,6 +363,119 @@ __device__ cand_t refined_bound(const cand_t *cbuf, const int32_t *ccnt, int64_t
         }
     }
     return kth == CAND_NONE ? old_bound : next_bound(kth);
+}
+
+// One query of the kernel below by one wave: writes its result, or returns true if it has to be flagged.
+template <int R>
+__device__ bool collect_select_one(const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t q, int SS, int Cs,
+                                   int k, int32_t *__restrict__ ids, int32_t *__restrict__ dists,
+                                   const int32_t *__restrict__ qnorms, int metric)
+{
+    const int lane = threadIdx.x & 63;
+    bool bad = false;
+    int upto[R], mine = 0;                                 // candidates of this lane's regions 0 .. j together
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int offered = (R * lane + j < SS) ? ccnt[q * SS + R * lane + j] : 0;
+        bad |= offered > Cs || offered < 0;
+        mine += offered < 0 ? 0 : (offered < Cs ? offered : Cs);   // what the region holds
+        upto[j] = mine;
+    }
+    int incl = mine;                                       // inclusive prefix sum over the lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+    }
+    const int total = __shfl(incl, 63, 64);
+    if (__ballot(bad) || total < k) return true;           // wave-uniform
+    const int excl = incl - mine;                          // index of the first candidate of this lane's regions
+    const cand_t *base = cbuf + (size_t)q * SS * Cs;
+    // candidate number i of the query sits with the first lane whose inclusive count exceeds i, there in the
+    // first region that ends beyond it
+    auto fetch = [&](int i) -> cand_t {
+        int r = 0;
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1)
+            if (__shfl(incl, r + step - 1, 64) <= i) r += step;
+        r = r > 63 ? 63 : r;
+        int at = i - __shfl(excl, r, 64), region = R * r, before = 0;
+#pragma unroll
+        for (int j = 0; j + 1 < R; ++j) {
+            const int end = __shfl(upto[j], r, 64);
+            if (at >= end) { region = R * r + j + 1; before = end; }
+        }
+        return i < total ? base[(size_t)region * Cs + (at - before)] : CAND_NONE;
+    };
+    auto put = [&](cand_t v, int e) {                      // the e-th best
+        if (e < k) emit_result(v, q * k + e, q, ids, dists, qnorms, metric);
+    };
+    // few candidates: a smaller network (2 or 4 per lane) does
+    auto small = [&](auto tag) {
+        constexpr int E = decltype(tag)::value;
+        cand_t v[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = fetch(j * 64 + lane);
+        wave_sort<E>(v, lane);
+#pragma unroll
+        for (int j = 0; j < E; ++j) put(v[j], lane * E + j);
+    };
+    if (total <= 128) {                                    // wave-uniform
+        small(std::integral_constant<int, 2>{});
+    } else if (total <= 256) {
+        small(std::integral_constant<int, 4>{});
+    } else {
+        cand_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = fetch(j * 64 + lane);
+        wave_sort<8>(v, lane);
+        for (int done = 512; done < total; done += 384) {  // wave-uniform: the best 128 stay in lanes 0 .. 15
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const cand_t n = fetch(done + j * 48 + (lane - 16));   // (every lane takes part in the shuffles)
+                if (lane >= 16) v[j] = n;
+            }
+            wave_sort<8>(v, lane);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) put(v[j], lane * 8 + j);
+    }
+    return false;
+}
+
+// Last step of the collecting scan for k <= 128 and at most 64 R regions, one WAVE per query: lane r holds the counts of regions R r .. R r + R - 1; the wave loads up to 512 candidates (2, 4 or 8
+// per lane as needed, each found by a search over the prefix counts), sorts them in registers and keeps the
+// best 128 in its first 16 lanes; further candidates come in 384 at a time through the other 48 lanes.  Any number
+// of candidates the regions hold is handled; a query with an overflowed region or fewer than k
+// candidates is flagged in over[] instead, and gets a tighter bound for the next round where bounds_out
+// is given (zero for the others): by all four waves, as its regions hold thousands of candidates (one wave sorting
+// them 384 at a time took 0.24 ms for 16 384).  (R = 4: 1000 queries with 256 regions take 9 us
+// against 13 with a workgroup per query.)
+constexpr int SORT_BOUND_BUF = 2048;   // of refined_bound: 16 KB, which leaves ten workgroups to a CU
+template <int R>
+__global__ __launch_bounds__(256) void collect_select_sort_kernel(
+    const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t nq, int SS, int Cs, int k,
+    int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
+    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric,
+    const cand_t *__restrict__ bounds_in, cand_t *__restrict__ bounds_out)
+{
+    __shared__ cand_t buf[SORT_BOUND_BUF];
+    __shared__ int s_flagged[4];
+    const int64_t first = (int64_t)blockIdx.x * 4;
+    const bool flagged = first + (threadIdx.x >> 6) < nq &&
+                         collect_select_one<R>(cbuf, ccnt, first + (threadIdx.x >> 6), SS, Cs, k, ids, dists, qnorms, metric);
+    if ((threadIdx.x & 63) == 0) s_flagged[threadIdx.x >> 6] = flagged;
+    __syncthreads();
+    for (int j = 0; j < 4 && first + j < nq; ++j) {        // the same in every thread
+        const int64_t q = first + j;
+        if (threadIdx.x == 0) {
+            over[q] = s_flagged[j];
+            if (s_flagged[j]) qlist[atomicAdd(qcount, 1)] = (int32_t)q;
+        }
+        if (!bounds_out) continue;
+        const cand_t bound = s_flagged[j] ? refined_bound(cbuf, ccnt, q, SS, Cs, k, SORT_BOUND_BUF, buf, bounds_in[q]) : 0;
+        if (threadIdx.x == 0) bounds_out[q] = bound;
+    }
 }
 
 // Last step of the collecting scan, one workgroup per query: gather the query's regions into LDS,
@@ -732,18 +749,19 @@ hipError_t launch_search_generic(const SearchArgs &a, int64_t row0, int64_t row1
     return hipGetLastError();
 }
 
-hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const int32_t *qlist,
-                                      const int32_t *qcount, cand_t *lists, int32_t *flags, int32_t *ids, int32_t *dists,
-                                      const int32_t *qnorms, int metric, hipStream_t st, int max_listed)
+hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const RedoList &first,
+                                      int first_max, const RedoList &last, cand_t *lists, int32_t *ids, int32_t *dists,
+                                      const int32_t *qnorms, int metric, hipStream_t st)
 {
     if (a.nq <= 0 || row1 <= row0) return hipSuccess;
     if ((int64_t)S * a.k > 4096) return hipErrorInvalidValue;   // one workgroup merges a query's lists
     const int cap = next_pow2((2 * a.k > a.k + 2 * GEN_ROWS) ? 2 * a.k : a.k + 2 * GEN_ROWS);
     const int64_t split_rows = round_up(ceil_div(row1 - row0, S), GEN_ROWS);
     const size_t shmem = (size_t)cap * sizeof(cand_t) + (size_t)a.d_pad;
-    const size_t merge = (size_t)next_pow2(S * a.k < 2 ? 2 : S * a.k) * sizeof(cand_t);
+    const int merged = S * a.k < 2 ? 2 : (S * a.k < LIST_MERGE_CAP ? S * a.k : LIST_MERGE_CAP);
+    const size_t merge = (size_t)next_pow2(merged) * sizeof(cand_t);
     search_generic_list_kernel<<<2048, GEN_THREADS, shmem > merge ? shmem : merge, st>>>(
-        a, row0, row1, S, split_rows, qlist, qcount, lists, cap, max_listed, flags, ids, dists, qnorms, metric);
+        a, row0, row1, S, split_rows, first, first_max, last, lists, cap, ids, dists, qnorms, metric);
     return hipGetLastError();
 }
 
