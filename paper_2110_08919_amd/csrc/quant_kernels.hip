@@ -1275,7 +1275,10 @@ hipError_t launch_encode(const QuantParams &qp, const float *x, int64_t n, int64
     int tpr = 1;
     while (tpr < groups && tpr < 64) tpr <<= 1;
     const bool vec = ((uintptr_t)x % 16 == 0) && (ld % 4 == 0) && ((uintptr_t)codes % 4 == 0) && (ldc % 4 == 0);
-    if (lim > 256 && n_out <= 16384) {   // (larger calls fill the chip a wave per row, and reuse a column's constants)
+    // Larger calls fill the chip a wave per row, and reuse a column's constants.  Row kernel / the other, us: 512 columns,
+    // 4000 rows 12.4 / 16.7, 8000 17.5 / 16.8; 768, 4000 13.7 / 16.7, 8000 24.7 / 17.5; 1024, 4000 17.5 / 17.7; 2048, 1000
+    // 12.5 / 25.7, 4000 32.2 / 29.7; 4096, 1000 17.3 / 48.4, 4000 61 / 54.
+    if (lim > 256 && n_out * lim <= (int64_t)(lim < 1024 ? 3 : 4) << 20) {
         if (vec) encode_row_kernel<true><<<(unsigned)n_out, ENC_THREADS, 0, st>>>(qp, x, n, ld, codes, ldc, zero_pad_to, norms);
         else encode_row_kernel<false><<<(unsigned)n_out, ENC_THREADS, 0, st>>>(qp, x, n, ld, codes, ldc, zero_pad_to, norms);
         return hipGetLastError();

@@ -23,3 +23,9 @@ def test_encode_long_rows(oracle, n, d, bits, ld_codes):
     oq = oracle.Quantizer(d, bits).set_params(k, k - s, k + s)
     ocodes, onorms = oq.encode(x, with_norms=True)
     assert np.array_equal(codes.cpu().numpy(), ocodes) and np.array_equal(norms.cpu().numpy(), onorms)
+
+
+# the last call that takes a workgroup per row and the first that does not
+@pytest.mark.parametrize("n,d", [(12_098, 260), (12_099, 260), (4096, 1024), (4097, 1024)])
+def test_encode_on_both_sides_of_the_rule(oracle, n, d):
+    test_encode_long_rows(oracle, n, d, 8, None)
