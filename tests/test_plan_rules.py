@@ -40,6 +40,16 @@ def test_small_batches_collect_on_small_corpora_only(bits, n, nq, k, mode):
     assert _plan(128, bits, n, nq, k)[0] == mode
 
 
+@pytest.mark.parametrize("d", [513, 1024, 2048, 4096])
+@pytest.mark.parametrize("n", [4096, 4097, 8000, 10_000, 20_000, 60_001])
+def test_streamed_rows_have_a_tile_for_every_split(d, n):
+    """Splits and regions (7 and 10 of the plan) that no tile of 256 rows falls to."""
+    for nq in (1, 64, 100, 300, 1000, 10_000):
+        for k in (1, 10, 30):
+            p = lpq.search_plan_info(d, 8, False, n, nq, k)
+            assert p[0] != COLLECTING or (p[7] <= -(-n // 256) and p[10] == p[7])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits,n,nq,k,calib,scope", [
     (1, 40_000, 300, 10, "minmax", "per_feature"), (1, 40_000, 700, 10, "absmax", "global"),
