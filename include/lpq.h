@@ -174,9 +174,9 @@ int lpq_search(const lpq_index *idx, const float *q_dev, int64_t nq, int64_t ld,
  * on every GPU the library is used on, held until the process ends.  The call allocates nothing
  * (no hipMalloc / hipFree, no allocating library routine) and is kernel launches only, after one
  * hipGetSymbolAddress per device on the first call there.  A search whose plan needs more than
- * LPQ_STATIC_WORKSPACE_BYTES (lpq_search_workspace_bytes tells) returns LPQ_ERANGE and launches
- * nothing: the limit is meant for small batches (e.g. 1M x 128: up to 256 queries at k = 10, 48 at
- * k = 100).  All calls on one GPU share the array, which keeps the previous call's contents (every
+ * LPQ_STATIC_WORKSPACE_BYTES (lpq_search_workspace_bytes tells) takes a slower one that needs less; if
+ * that does not fit either the call returns LPQ_ERANGE and launches nothing: it is meant for small
+ * batches (1M x 128: the usual plan fits up to 256 queries at k = 10, 57 at k = 100).  All calls on one GPU share the array, which keeps the previous call's contents (every
  * counter in it is cleared by the kernels that precede its use): calls that overlap on one GPU -
  * different streams, or different threads - race; serialise them on one stream. */
 #define LPQ_STATIC_WORKSPACE_BYTES (64u << 20)

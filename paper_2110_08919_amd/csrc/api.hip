@@ -1147,21 +1147,36 @@ extern "C" int lpq_search_static(const lpq_index *idx, const float *q_dev, int64
     int rc = check_search_args(idx, q_dev, nq, ld, k, metric, ids_dev, dist_dev);
     if (rc) return rc;
     if (nq == 0) return LPQ_OK;
-    size_t need = 0;
+    const size_t limit = (size_t)LPQ_STATIC_WORKSPACE_BYTES;
     bool compact = false;
-    for (int pass = 0; pass < 2; ++pass) {
-        compact = pass != 0;
-        need = idx->packed ? make_packed_plan(idx, nq, k, compact).total : make_plan(idx, nq, k, compact).total;
-        if (need <= (size_t)LPQ_STATIC_WORKSPACE_BYTES) break;
+    auto bytes = [&](int64_t queries) {
+        return idx->packed ? make_packed_plan(idx, queries, k, compact).total : make_plan(idx, queries, k, compact).total;
+    };
+    size_t need = bytes(nq);
+    if (need > limit) {
+        compact = true;
+        need = bytes(nq);
     }
-    if (need > (size_t)LPQ_STATIC_WORKSPACE_BYTES)
-        return fail(LPQ_ERANGE, "this search needs %zu bytes of workspace, the built-in one holds %zu: use lpq_search",
-                    need, (size_t)LPQ_STATIC_WORKSPACE_BYTES);
+    // Rows beyond 1536 features are padded for the streaming scan, which the compact plan does not take; where only that
+    // padding of the queries' codes is too much, half of them are searched at a time.
+    int64_t part = nq;
+    const size_t padding = idx->d_pad > 1536 ? (size_t)round_up(nq, 512) * (idx->d_pad - round_up(idx->d, 32)) : 0;
+    if (need > limit && need - padding <= limit) {
+        part = round_up(ceil_div(nq, 2), 512);
+        need = bytes(part < nq ? part : nq);
+    }
+    if (need > limit)
+        return fail(LPQ_ERANGE, "this search needs %zu bytes of workspace, the built-in one holds %zu: use lpq_search", need, limit);
     void *ws = nullptr;
     rc = scratch_address(&ws);
     if (rc) return rc;
-    return search_f32_queries(idx, q_dev, nq, ld, k, metric, ids_dev, dist_dev, ws, (size_t)LPQ_STATIC_WORKSPACE_BYTES,
-                              (hipStream_t)stream, compact);
+    for (int64_t q0 = 0; q0 < nq; q0 += part) {
+        const int64_t take = nq - q0 < part ? nq - q0 : part;
+        rc = search_f32_queries(idx, q_dev + q0 * ld, take, ld, k, metric, ids_dev + q0 * k, dist_dev + q0 * k, ws, limit,
+                                (hipStream_t)stream, compact);
+        if (rc) return rc;
+    }
+    return LPQ_OK;
 }
 
 extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,

@@ -116,3 +116,14 @@ def test_search_streamed_rows_corpus_sorted_by_cluster(lpq):
     index = lpq.Index(gq, n).add_i8(x)
     for metric in ("l2sq", "ip"):
         _same(index.search(q, k, metric), _generic(lpq, index, q, k, metric))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,nq,k", [(32, 3511, 17_478, 10), (3, 4248, 15_190, 3), (3000, 1805, 5041, 700)])
+def test_static_search_of_batches_that_row_padding_pushes_over_the_limit(lpq, n, d, nq, k):
+    """The codes of these queries fit the built-in workspace with rows padded to 32 bytes, but not to 128."""
+    w = synth.Workload("w", "bimodal", n, d, nq, "l2sq", (k,), "minmax", "global", 7)
+    x, q = w.corpus("cuda"), w.queries("cuda")
+    index = lpq.Index(lpq.Quantizer(d, 8).calibrate(x, "minmax", "global"), n).add_f32(x)
+    want, got = index.search(q, k), index.search_static(q, k)
+    _same(got, want)
