@@ -151,12 +151,15 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
         const int64_t rs = row0 + (int64_t)s * split_rows;
         const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
         generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
-        __threadfence();                                    // this thread's part of the list is visible to the chip
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's part of the list has reached the L2 ...
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&work.flags[q], 1) == S;
+        if (threadIdx.x == 0) {
+            __threadfence();                                // ... and is visible to the chip, by one write-back for all
+            s_last = atomicAdd(&work.flags[q], 1) == S;
+            if (s_last) __threadfence();                    // the other lists are read as they are now
+        }
         __syncthreads();
         if (s_last) {                                       // the same answer in every thread of the workgroup
-            __threadfence();
             const int m = S * a.k;                          // up to 4096, sorted in two or three parts
             for (int from = 0, kept = 0; from < m; kept = a.k) {
                 const int take = m - from < LIST_MERGE_CAP - kept ? m - from : LIST_MERGE_CAP - kept;
