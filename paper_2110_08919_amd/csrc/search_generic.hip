@@ -728,7 +728,10 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
                                                                                  qcount, ids, dists, qnorms, metric);
         return hipGetLastError();
     }
-    if (!only && k <= 128 && SS <= (nq >= 64 ? 256 : 64)) {   // one wave per query, sorted in registers
+    // (Beyond 64 regions only for batches that fill the chip that way: one wave takes 5 us for every 384 candidates, which is
+    // long where thousands tie at the bound: 1694 queries in tiles of 64 on 6216 x 20 at 3 bits, k = 21, 5.2 against 3.7 ms;
+    // without ties, 300 on 6000 x 60, k = 30 0.168 against 0.181.)
+    if (!only && k <= 128 && SS <= (nq > 64 ? 256 : 64)) {   // one wave per query, sorted in registers
         auto kern = SS <= 64 ? collect_select_sort_kernel<1> : collect_select_sort_kernel<4>;
         kern<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
                                                                 metric, bounds_in, bounds_out);

@@ -37,3 +37,20 @@ def test_a_few_queries_are_searched_again(n, d, nq, k, flagged):
         finally:
             lpq.set_tuning(lpq.TUNE_PATH, 0)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("n,d,nq,k,bits", [(6216, 20, 200, 21, 3), (8000, 60, 64, 30, 3), (8300, 60, 65, 12, 4)])
+def test_packed_tiles_with_thousands_of_ties(n, d, nq, k, bits):
+    """Tiles of 64 queries with up to and beyond 256 regions, most items equal at the bound."""
+    w = synth.Workload("w", "skewed_int", n, d, nq, "ip", (k,), "absmax", "per_feature", 1)
+    x, q = w.corpus("cuda"), w.queries("cuda")
+    index = lpq.Index(lpq.Quantizer(d, bits).calibrate(x, "absmax", "per_feature"), n, packed=True).add_f32(x)
+    got = index.search(q, k, "ip")
+    torch.cuda.synchronize()
+    lpq.set_tuning(lpq.TUNE_PATH, 1)
+    try:
+        want = index.search(q, k, "ip")
+        torch.cuda.synchronize()
+    finally:
+        lpq.set_tuning(lpq.TUNE_PATH, 0)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
