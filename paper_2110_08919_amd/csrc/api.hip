@@ -187,9 +187,10 @@ struct lpq_quantizer {
     bool ready = false;
     float *params = nullptr;   // device [4][d]: k, S_b, S_e, m
     float *staging = nullptr;  // device [4][d]: calibration result before it is committed
-    void *scratch = nullptr;   // calibration partials
     int *flag = nullptr;       // device: non-finite value seen
+    void *windows = nullptr;   // of a quantile calibration
     void *block = nullptr;     // the allocation all of these lie in
+    void *scratch = nullptr;   // calibration partials, from the first calibration that is not by windows on
 };
 
 static QuantParams view(const float *params, int d, int bits)
@@ -204,6 +205,7 @@ extern "C" void lpq_quantizer_destroy(lpq_quantizer *q)
 {
     if (!q) return;
     (void)hipFree(q->block);
+    (void)hipFree(q->scratch);
     delete q;
 }
 
@@ -216,10 +218,10 @@ extern "C" int lpq_quantizer_create(lpq_quantizer **out, int d, int bits)
     lpq_quantizer *q = new (std::nothrow) lpq_quantizer;
     if (!q) return fail(LPQ_ENOMEM, "host allocation failed");
     q->d = d; q->bits = bits;
-    // One allocation for everything: an allocation and its release cost tens of microseconds each,
-    // which a program that calibrates often pays every time.
+    // One allocation: each and its release cost tens of microseconds, which a program that calibrates often pays
+    // every time.
     const size_t set = ((size_t)4 * d * sizeof(float) + 255) & ~size_t(255);
-    const hipError_t e = hipMalloc(&q->block, 256 + 2 * set + calib_scratch_bytes(d));
+    const hipError_t e = hipMalloc(&q->block, 256 + 2 * set + calib_windows_bytes(d));
     if (e != hipSuccess) {
         lpq_quantizer_destroy(q);
         return fail(e == hipErrorOutOfMemory ? LPQ_ENOMEM : LPQ_EDEVICE, "hipMalloc: %s", hipGetErrorString(e));
@@ -228,7 +230,7 @@ extern "C" int lpq_quantizer_create(lpq_quantizer **out, int d, int bits)
     q->flag = reinterpret_cast<int *>(p);
     q->params = reinterpret_cast<float *>(p + 256);
     q->staging = reinterpret_cast<float *>(p + 256 + set);
-    q->scratch = p + 256 + 2 * set;
+    q->windows = p + 256 + 2 * set;
     *out = q;
     return LPQ_OK;
 }
@@ -244,29 +246,38 @@ extern "C" int lpq_quantizer_calibrate(lpq_quantizer *q, const float *x_dev, int
     if (scope != LPQ_SCOPE_PER_FEATURE && scope != LPQ_SCOPE_GLOBAL && scope != LPQ_SCOPE_SHARED_WIDTH) return fail(LPQ_EINVAL, "unknown scope %d", scope);
     if (mode == LPQ_CALIB_GAUSS && !(sigma_mult > 0.0f)) return fail(LPQ_EINVAL, "sigma_mult must be > 0");
     hipStream_t st = (hipStream_t)stream;
-    // Lists of a quantile's windows, 16 MB at most, are held during the call only: a quantizer lives as long as its
-    // index does, and most never see this mode.  Without the room for them the general path does.  (Allocated while the
-    // sample is taken; 1M x 128, create to destroy, 253 us against 241 with lists held for good.)
-    uint32_t *lists = nullptr;
+    // A quantile's windows come with lists of 16 MB at most.  They are held during the call only, a quantizer lives as
+    // long as its index does; allocated, with the partials, while the sample is taken (1M x 128, create to
+    // destroy, 255 us with both held for good, 240 so; a second calibration 218 and 237).  Without the room for them
+    // the general path does.
+    char *temp = nullptr;
     const size_t lists_bytes = calib_lists_bytes(n, q->d, mode, scope, (double)sigma_mult);
+    const size_t scratch_bytes = (calib_scratch_bytes(q->d) + 255) & ~size_t(255);
     if (lists_bytes) {
-        HIP_TRY(launch_calib_windows(x_dev, n, ld, q->d, (double)sigma_mult, q->scratch, st));
-        if (hipMalloc(&lists, lists_bytes) != hipSuccess) {
-            lists = nullptr;
+        HIP_TRY(launch_calib_windows(x_dev, n, ld, q->d, (double)sigma_mult, q->windows, st));
+        if (hipMalloc(&temp, scratch_bytes + lists_bytes) != hipSuccess) {
+            temp = nullptr;
             (void)hipGetLastError();
         }
     }
+    if (!temp && !q->scratch) {
+        const hipError_t e = hipMalloc(&q->scratch, scratch_bytes);
+        if (e != hipSuccess) {
+            q->scratch = nullptr;
+            return fail(e == hipErrorOutOfMemory ? LPQ_ENOMEM : LPQ_EDEVICE, "hipMalloc: %s", hipGetErrorString(e));
+        }
+    }
     int bad = 0;
-    auto attempt = [&](uint32_t *with) -> hipError_t {
-        hipError_t e = launch_calibrate(x_dev, n, ld, q->d, q->bits, mode, scope, (double)sigma_mult, q->scratch, q->staging,
-                                        q->params, q->flag, st, with);
+    auto attempt = [&](uint32_t *lists) -> hipError_t {
+        hipError_t e = launch_calibrate(x_dev, n, ld, q->d, q->bits, mode, scope, (double)sigma_mult, temp ? temp : q->scratch,
+                                        q->staging, q->params, q->flag, st, q->windows, lists);
         if (e == hipSuccess) e = hipMemcpyAsync(&bad, q->flag, sizeof(int), hipMemcpyDeviceToHost, st);
-        const hipError_t w = hipStreamSynchronize(st);   // in any case: what was launched may still use the lists
+        const hipError_t w = hipStreamSynchronize(st);   // in any case: what was launched may still use the memory
         return e != hipSuccess ? e : w;
     };
-    hipError_t e = attempt(lists);
-    if (e == hipSuccess && lists && bad == 2) e = attempt(nullptr);   // a window missed its quantile
-    if (lists) (void)hipFree(lists);
+    hipError_t e = attempt(temp ? reinterpret_cast<uint32_t *>(temp + scratch_bytes) : nullptr);
+    if (e == hipSuccess && temp && bad == 2) e = attempt(nullptr);   // a window missed its quantile
+    if (temp) (void)hipFree(temp);
     HIP_TRY(e);
     if (bad & 1) return fail(LPQ_ENONFINITE, "calibration data holds a NaN or an infinity");
     q->ready = true;

@@ -90,19 +90,20 @@ struct QuantParams {
 
 // ---- quantizer kernels (quant_kernels.hip) ---------------------------------------
 // Calibration scratch layout is private to quant_kernels.hip; the API allocates
-// calib_scratch_bytes(d) bytes once per quantizer.
+// calib_scratch_bytes(d) bytes.
 size_t calib_scratch_bytes(int d);
 // Bytes of the lists with which a quantile calibration takes one pass over the data; 0 where it takes the
 // general path.
 size_t calib_lists_bytes(int64_t n, int d, int mode, int scope, double clip);
-// The windows that the lists are for, from a sample of the data.
-hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, double clip, void *scratch, hipStream_t st);
+// The windows that the lists are for, from a sample of the data: calib_windows_bytes(d) bytes of device memory.
+size_t calib_windows_bytes(int d);
+hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, double clip, void *windows, hipStream_t st);
 // lists: that many bytes of device memory (launch_calib_windows comes first), or null for the general path.
 // *flag: bit 0 a value is not finite; bit 1 (only with lists) a quantile lies outside the window its
 // sample gave, and the call has to be repeated without lists.
 hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bits, int mode,
                             int scope, double sigma_mult, void *scratch, float *params_out, float *params_committed,
-                            int *flag, hipStream_t st, uint32_t *lists);   // committed: written only if *flag stays 0
+                            int *flag, hipStream_t st, void *windows, uint32_t *lists);   // committed: written only if *flag stays 0
 hipError_t launch_derive_m(float *params, int d, int bits, hipStream_t st);
 // Equation 1 on n rows.  zero_pad_to > d additionally writes zero bytes for columns
 // d .. zero_pad_to-1 of each row; n_out > n additionally writes rows n .. n_out-1 as zero codes

@@ -30,10 +30,14 @@ struct CalibScratch {
     unsigned long long *qhist;   // [d][2][256] counts of the current byte among the still matching values
     unsigned long long *qrank;   // [2][d] rank still to go inside the matching values
     uint32_t *qprefix;           // [2][d] the bytes of the answer decided so far (sortable image)
-    // quantile selection by windows: per target and column
-    uint32_t *qwin;              // [2][d][2] first and last key of the window
-    uint32_t *qcount;            // [2][d][4] values strictly inside, equal to the first, to the last, outside (below / above)
 };
+
+// Quantile selection by windows: per target and column (calib_windows_bytes).
+struct CalibWindows {
+    uint32_t *win;               // [2][d][2] first and last key of the window
+    uint32_t *count;             // [2][d][4] values strictly inside, equal to the first, to the last, outside (below / above)
+};
+CalibWindows carve_windows(void *windows, int d) { return {(uint32_t *)windows, (uint32_t *)windows + 4 * (size_t)d}; }
 
 // Keys a window's list holds ([2][d][window_cap(d)], the keys strictly inside): 16 MB of lists in all; none
 // beyond 2048 features.
@@ -60,9 +64,7 @@ CalibScratch carve(void *scratch, int d)
     p = (char *)(((uintptr_t)p + 15) & ~uintptr_t(15));
     s.qhist = (unsigned long long *)p;  p += sizeof(unsigned long long) * 512 * (size_t)d;
     s.qrank = (unsigned long long *)p;  p += sizeof(unsigned long long) * 2 * (size_t)d;
-    s.qprefix = (uint32_t *)p;  p += sizeof(uint32_t) * 2 * (size_t)d;
-    s.qwin = (uint32_t *)p;     p += sizeof(uint32_t) * 4 * (size_t)d;
-    s.qcount = (uint32_t *)p;
+    s.qprefix = (uint32_t *)p;
     return s;
 }
 
@@ -1113,8 +1115,10 @@ size_t calib_scratch_bytes(int d)
 {
     const size_t G = calib_blocks(d) + CAL_EXTRA_ROWS;
     return G * d * (sizeof(double) + 2 * sizeof(float)) + (size_t)d * (3 * sizeof(double) + 2 * sizeof(float)) + 256 +
-           (size_t)d * (512 * sizeof(unsigned long long) + 2 * sizeof(unsigned long long) + 14 * sizeof(uint32_t));
+           (size_t)d * (512 * sizeof(unsigned long long) + 2 * sizeof(unsigned long long) + 2 * sizeof(uint32_t));
 }
+
+size_t calib_windows_bytes(int d) { return (size_t)d * 12 * sizeof(uint32_t); }
 
 size_t calib_lists_bytes(int64_t n, int d, int mode, int scope, double clip)
 {
@@ -1129,18 +1133,18 @@ size_t calib_lists_bytes(int64_t n, int d, int mode, int scope, double clip)
 static unsigned long long low_rank(int64_t n, double clip) { return (unsigned long long)floor(clip * (double)(n - 1)); }
 static unsigned long long high_rank(int64_t n, double clip) { return (unsigned long long)ceil((1.0 - clip) * (double)(n - 1)); }
 
-hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, double clip, void *scratch, hipStream_t st)
+hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, double clip, void *windows, hipStream_t st)
 {
-    CalibScratch s = carve(scratch, d);
+    const CalibWindows w = carve_windows(windows, d);
     const int m = (int)(n < QW_SAMPLE ? n : QW_SAMPLE);
     quantile_window_kernel<<<d, 1024, (size_t)next_pow2(m) * sizeof(uint32_t), st>>>(x, n, ld, d, m, low_rank(n, clip),
-                                                                                     high_rank(n, clip), s.qwin, s.qcount);
+                                                                                     high_rank(n, clip), w.win, w.count);
     return hipGetLastError();
 }
 
 hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bits, int mode, int scope,
                             double sigma_mult, void *scratch, float *params_out, float *params_committed,
-                            int *nonfinite_flag, hipStream_t st, uint32_t *lists)
+                            int *nonfinite_flag, hipStream_t st, void *windows, uint32_t *lists)
 {
     const int G = calib_blocks(d);
     CalibScratch s = carve(scratch, d);
@@ -1148,6 +1152,7 @@ hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bi
     hipError_t e = hipMemsetAsync(nonfinite_flag, 0, sizeof(int), st);
     if (e != hipSuccess) return e;
     if (lists) {
+        const CalibWindows w = carve_windows(windows, d);
         const unsigned long long rl = low_rank(n, sigma_mult), rh = high_rank(n, sigma_mult);
         const int cap = window_cap(d);
         int lpr = 1;
@@ -1157,10 +1162,10 @@ hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bi
         if (rows < 512) rows = 512;
         const dim3 grid((unsigned)ceil_div(n, rows), (unsigned)tiles);
         if (d % 4 == 0 && ld % 4 == 0 && (uintptr_t)x % 16 == 0)
-            quantile_gather_kernel<true><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, lists, cap, nonfinite_flag);
+            quantile_gather_kernel<true><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, w.win, w.count, lists, cap, nonfinite_flag);
         else
-            quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, s.qwin, s.qcount, lists, cap, nonfinite_flag);
-        quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, s.qwin, s.qcount, lists, cap, s.mn, s.mx, nonfinite_flag);
+            quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, w.win, w.count, lists, cap, nonfinite_flag);
+        quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, w.win, w.count, lists, cap, s.mn, s.mx, nonfinite_flag);
         calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out,
                                                        nonfinite_flag, params_committed);
         return hipGetLastError();
