@@ -149,7 +149,9 @@ int lpq_index_data(const lpq_index *idx, const int8_t **codes_dev, int64_t *ld_c
 /* --------------------------------------------------------------------- search ---- */
 
 /* Bytes of device workspace lpq_search / lpq_search_i8 need for nq queries and k results
- * (0 on invalid arguments).  The workspace needs 256-byte alignment. */
+ * (0 on invalid arguments).  The workspace needs 256-byte alignment.  It grows with the batch and
+ * with k (1M x 128: 10 000 queries 247 MB at k = 10, 315 at k = 100; about 4 GB for 100 000 queries on long
+ * rows): where that is too much, search a batch in parts. */
 size_t lpq_search_workspace_bytes(const lpq_index *idx, int64_t nq, int k, int metric);
 
 /* k nearest items of each of nq queries q_dev[nq][ld] (fp32; encoded with the index's
@@ -329,7 +331,7 @@ int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metri
                               int64_t *redone_queries, int64_t *max_region_fill);
 
 /* Where the plan has further rounds (for k > 16, and on rows of more than 256 bytes) such queries are not
- * searched again exactly at once: the scan runs again (up to two more rounds) over the query tiles that
+ * searched again exactly at once (but for a few of a large batch with k <= 32): the scan runs again (up to two more rounds) over the query tiles that
  * hold one, with bounds taken from the candidates the round before did collect, and only queries that
  * overflow every time go through the generic kernel.  *left_queries = their number after the last search
  * (0 when the plan has no further rounds or they did not run).  Same arguments and synchronisation as above. */

@@ -27,7 +27,7 @@
 // through the direct kernel instead; the scan collects nothing more for a query whose region has overflowed,
 // and a workgroup ends when none of its queries is left.
 //
-// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.3 -> 0.88 ms (the scan 0.81 = 0.97 PFLOP/s
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.3 -> 0.89 ms (the scan 0.82 = 0.97 PFLOP/s
 // of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  In the scan the
 // matrix pipe is busy 45 % of the time and the LDS 27 %: the two waves of a SIMD split and store their
 // rows in step with each other, and wait a third of their time at the barrier of each stage.
