@@ -446,14 +446,14 @@ __device__ bool collect_select_one(const cand_t *__restrict__ cbuf, const int32_
     return false;
 }
 
-// Last step of the collecting scan for k <= 128 and at most 64 R regions, one WAVE per query: lane r holds the counts of regions R r .. R r + R - 1; the wave loads up to 512 candidates (2, 4 or 8
-// per lane as needed, each found by a search over the prefix counts), sorts them in registers and keeps the
-// best 128 in its first 16 lanes; further candidates come in 384 at a time through the other 48 lanes.  Any number
-// of candidates the regions hold is handled; a query with an overflowed region or fewer than k
-// candidates is flagged in over[] instead, and gets a tighter bound for the next round where bounds_out
-// is given (zero for the others): by all four waves, as its regions hold thousands of candidates (one wave sorting
-// them 384 at a time took 0.24 ms for 16 384).  (R = 4: 1000 queries with 256 regions take 9 us
-// against 13 with a workgroup per query.)
+// Last step of the collecting scan for k <= 128 and at most 64 R regions, one WAVE per query: lane r holds the
+// counts of regions R r .. R r + R - 1; the wave loads up to 512 candidates (2, 4 or 8 per lane as needed, each
+// found by a search over the prefix counts), sorts them in registers and keeps the best 128 in its first 16 lanes;
+// further candidates come in 384 at a time through the other 48 lanes.  Any number of candidates the regions hold
+// is handled; a query with an overflowed region or fewer than k candidates is flagged in over[] instead, and gets a
+// tighter bound for the next round where bounds_out is given (zero for the others): by all four waves, as its
+// regions hold thousands of candidates (one wave sorting them 384 at a time took 0.24 ms for 16 384).  (R = 4:
+// 1000 queries with 256 regions take 9 us against 13 with a workgroup per query.)
 constexpr int SORT_BOUND_BUF = 2048;   // of refined_bound: 16 KB, which leaves ten workgroups to a CU
 template <int R>
 __global__ __launch_bounds__(256) void collect_select_sort_kernel(
