@@ -239,12 +239,20 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
                                  // the k-th best of what was collected for a flagged query (bounds_in[q] if that was fewer
                                  // than k), for any other query the bound that nothing passes
                                  const cand_t *bounds_in = nullptr, cand_t *bounds_out = nullptr);
+// Maxima that are images of floats (fp32 filter): flags[q / 128] is set for a query with more than `most` maxima within
+// c qn[q] + cx *nxsum of its k-th largest.
+struct HardQueries {
+    const float *qn = nullptr, *nxsum = nullptr;
+    float c = 0.0f, cx = 0.0f;
+    int most = 0;
+    int32_t *flags = nullptr;         // null: nothing is done
+};
 // zero_word (optional): one int the kernel also sets to 0 (the counter of the redo list), and zero_more further
 // ones, the i-th at zero_word2 + i * zero_stride.
 // kth_out (optional): the k-th largest maximum itself per query, INT32_MIN where there is none (seeds may then be null).
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
                                 int32_t *zero_word = nullptr, int32_t *kth_out = nullptr, int32_t *zero_word2 = nullptr,
-                                int zero_more = 0, int64_t zero_stride = 0);
+                                int zero_more = 0, int64_t zero_stride = 0, const HardQueries &hq = HardQueries());
 
 // Merge P lists of k candidates per query into one (merge.hip).  If ids/dists are given the
 // result is final: ids, and dist = key + qnorm (L2SQ) or -key/2 (IP).  Otherwise the merged
@@ -279,14 +287,17 @@ hipError_t launch_rerank_f32(const float *x, int64_t n, int64_t ldx, const float
 // Matrix-core filter in front of the direct sums: plan of its passes and where its buffers lie.
 struct F32Filter {
     bool use = false;         // the direct kernel alone otherwise
-    int wq = 0, qtiles = 0, dp = 0, S1 = 0, S2 = 0, SEG = 0, G = 0, seed_tiles = 0, Cs = 0;
+    bool half = false;        // a first scan in fp16
+    int wq = 0, qtiles = 0, wq_half = 0, qtiles_half = 0, dp = 0, S1 = 0, S2 = 0, SEG = 0, G = 0, seed_tiles = 0, Cs = 0;
     int64_t nq_pad = 0, run_stride = 0;
-    size_t off_qh = 0, off_ql = 0, off_qn = 0, off_gmax = 0, off_kth = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_list = 0,
+    size_t off_qh = 0, off_ql = 0, off_qf = 0, off_qn = 0, off_qe = 0, off_hard = 0, off_again = 0, off_gmax = 0, off_kth = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_list = 0,
            total = 0;
 };
 F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k);
 // The filter's score of an item is within this times (|q|^2 + |x|^2) / 2 of the directly summed one.
 constexpr float f32_filter_constant(int d) { return 0x1p-14f + (float)d * 0x1p-20f; }
+// The same of its first scan, one product of operands rounded to fp16.
+constexpr float f32_half_filter_constant(int d) { return 0x1p-10f + 0x1p-15f + (float)d * 0x1p-21f; }
 // Rows that may be among the k nearest of each query -> regions cbuf[nq][S2][Cs] (the low half of a
 // candidate holds the row), ccnt[nq][S2]; the counter behind the redo list is cleared.
 hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,

@@ -1181,7 +1181,7 @@ template <int E>
 __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k,
                                                             cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word,
                                                             int32_t *__restrict__ kth_out, int32_t *__restrict__ zero_word2,
-                                                            int zero_more, int64_t zero_stride)
+                                                            int zero_more, int64_t zero_stride, HardQueries hq)
 {
     const int lane = threadIdx.x & 63;
     if (zero_word && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1240,6 +1240,14 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
     // at least k items have E >= kth, hence key <= -2 kth
     if (lane == 0 && seeds) seeds[q] = (G < k || kth == INT32_MIN) ? CAND_NONE : make_cand(-2 * kth, 0xFFFFFFFFu);
     if (lane == 0 && kth_out) kth_out[q] = G < k ? INT32_MIN : kth;
+    if (hq.flags) {
+        const float at = sortable_to_float(kth) - hq.c * hq.qn[q] - hq.cx * *hq.nxsum;
+        const int line = at > -INFINITY ? float_to_sortable(at) : INT32_MIN;   // (also where at is not a number)
+        int within = k <= 24 ? k : 0;                      // (the k largest were taken out above)
+#pragma unroll
+        for (int e = 0; e < E; ++e) within += __popcll(__ballot(e * 64 + lane < G && v[e] >= line));
+        if (lane == 0 && (G < k || kth == INT32_MIN || line == INT32_MIN || within > hq.most)) hq.flags[q >> 7] = 1;
+    }
 }
 
 size_t lds_bytes(int ks, bool seed, int nw, bool rsplit, int nb, bool pack, bool big = false)
@@ -1524,21 +1532,22 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
 }
 
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
-                                int32_t *zero_word, int32_t *kth_out, int32_t *zero_word2, int zero_more, int64_t zero_stride)
+                                int32_t *zero_word, int32_t *kth_out, int32_t *zero_word2, int zero_more, int64_t zero_stride,
+                                const HardQueries &hq)
 {
     if (nq <= 0) return hipSuccess;
     if (G > 4096) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)ceil_div(nq, (int64_t)4);
     if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride);
+                                                                    zero_word2, zero_more, zero_stride, hq);
     else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride);
+                                                                    zero_word2, zero_more, zero_stride, hq);
     else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride);
+                                                                    zero_word2, zero_more, zero_stride, hq);
     else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride);
+                                                                    zero_word2, zero_more, zero_stride, hq);
     else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride);
+                                                                    zero_word2, zero_more, zero_stride, hq);
     return hipGetLastError();
 }
 

@@ -27,15 +27,32 @@
 // through the direct kernel instead; the scan collects nothing more for a query whose region has overflowed,
 // and a workgroup ends when none of its queries is left.
 //
-// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 8.3 -> 0.89 ms (the scan 0.82 = 0.97 PFLOP/s
-// of bf16), 10 000 queries 8.9 ms; one query on 10 000 x 128 0.23 -> 0.036 ms.  In the scan the
-// matrix pipe is busy 45 % of the time and the LDS 27 %: the two waves of a SIMD split and store their
-// rows in step with each other, and wait a third of their time at the barrier of each stage.
+// Two scans follow the seeding pass.  The first forms ONE product, of operands rounded to fp16: a third of the matrix
+// work, half the LDS and half the vector work of the split, and a tile of 256 queries instead of 128.
+//
+//   error       |acc - q.x| <= 2 (2^-11 + 2^-23) sum |q x| + d 2^-23 sum |q x|, everything else as above, so
+//               C = 2^-10 + 2^-15 + d 2^-21   (f32_half_filter_constant)
+//   range       a query is scaled by a power of two to a norm of 1 to 2, the rows of a tile by the mean of its queries'
+//               scales (not at all where that lies near one), so that fp16 holds both; what is too small for its
+//               normal range is off by 2^-25, sqrt(d) 2^-25 (|q| + |x|) in all: the first part is in the threshold
+//               (sqrt(d) 2^-22), the second in C's slack.  Rows beyond 2^15 after scaling, and queries 2^24 away from
+//               the others, go to the second scan.
+//
+// On ordinary data the wider bound lets through a tenth more (1M x 128, k = 10: 281 items instead of 261 a query).
+// The second scan, with C and the split, takes query tiles where the seeding pass has more than twice k groups within
+// the first one's error (hard), and queries that overflowed in the first.  1M x 128 shifted by 30 or 100 (inner
+// product, all hard) 0.90 / 1.00 -> 0.88 / 0.97 ms.
+//
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 0.91 -> 0.46 ms (with the split alone; 8.3 with the direct
+// kernel alone), 64 queries 0.156 -> 0.147, 256 0.30 -> 0.19; 1M x 96, 1000 0.75 -> 0.46; 300 000 x 771, 1000
+// 2.53 -> 1.01; 200 000 x 128, 10 000 2.03 -> 1.06; 2M x 24, 2000 1.81 -> 1.05.
 //
 // Layout: workgroups of eight waves on tiles of 256 items x 64 WQ queries, as in search_mfma_stream.hip;
-// a stage is 32 features.  Items come from HBM in fp32 through registers (one stage ahead), are split
-// and written to LDS as two bf16 planes, their squared norms summed on the way; the queries, split
-// once per search, are copied asynchronously.
+// a stage is 32 features.  Items come from HBM in fp32 through registers (two stages ahead), are rounded or split
+// and written to LDS as one fp16 or two bf16 planes, their squared norms summed on the way; the queries, rounded or
+// split once per search, are copied asynchronously.  Bound by the vector work that the two waves of a SIMD do in step
+// (rounding and norms between the matrix instructions of a stage's first half, the epilogue of a tile behind its last:
+// 34 % of the first scan's cycles, next to 30 % with the matrix pipe busy) and by the barrier of each stage.
 #include <cmath>
 #include <type_traits>
 
@@ -48,8 +65,12 @@ namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 v4b __attribute__((ext_vector_type(4)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 constexpr int FW = 8;                 // waves per workgroup
 constexpr int TILE_ROWS = 256;
@@ -57,12 +78,18 @@ constexpr int KF = 32;                // features per stage
 constexpr int PB = KF * 2;            // bytes of a row in one plane of a stage
 constexpr int RUN = 16;               // a tile is 16 runs of 16 rows
 constexpr float HUGE_NORM = 1e30f;
-
+constexpr float HALF_NORM = 0x1p30f;  // squared norm of a scaled row up to which its values are far from overflowing in fp16
+constexpr int HALF_RANGE = 24;        // powers of two by which a query's norm may differ from those of its tile
+constexpr int NO_SCALE = INT32_MIN;   // in FilterIo::qe: the query counts as zero (or is a padding row)
+constexpr int ZERO_SCALE = 12;        // ... which holds up to this scale of its tile
+constexpr int NEAR_ONE_LO = -10, NEAR_ONE_HI = 6;   // scales of a tile that rows do without: fp16 holds norms of 2^-6 to 2^10 well
+enum { AGAIN = 1, DIRECT = 2 };       // bits of FilterIo::again
 
 struct FilterIo {
     const float *x;
     int64_t n, ldx;
-    int d, dp;                // dp: d rounded up to whole stages
+    int d, dp;                // dp: d rounded up to pairs of stages
+    int kst;                  // stages to a tile: what holds d, an even number of them in fp16
     const __bf16 *qh, *ql;    // [nq_pad][dp] the queries' two planes
     const float *qn;          // [nq_pad] squared norms
     int64_t nq;
@@ -73,20 +100,27 @@ struct FilterIo {
     float c;                  // C above
     int32_t *gmax;            // seeding pass: [nq_pad][G] group maxima (order-preserving images), G = S * SEG * 2 * (8 / WQ)
     int SEG;
+    float *nxsum;             // seeding pass: the sampled rows' squared norms together, eight times over for each query tile
+    const _Float16 *qf;       // first scan: [nq_pad][dp] the queries in fp16, each scaled to a norm of 1 to 2
+    const int32_t *qe;        // ... by two to this power
+    float ch;                 // ... and the constant of its error
+    const int32_t *hard;      // scans: [nq_pad / 128] set where only the second scan can resolve the queries
+    int32_t *again;           // [nq_pad] AGAIN: the first scan could not; DIRECT: neither can the second
     const int32_t *kth;       // scan: [nq] k-th largest group maximum
     cand_t *cbuf;             // [nq][S][Cs] rows that may belong (the key half is filled in later)
     int32_t *ccnt;            // [nq][S]
     int Cs;
 };
 
+#define LPQF_INLINE __attribute__((always_inline))
 constexpr int FDUMPS = 32;
 // Control words of a workgroup of the scan, in LDS: queries that are done (their region has overflowed, or the slot holds
-// none), and what wave 0 has said of them.
-enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_WORDS = 64 };
+// none), what wave 0 has said of them, whether rows were lost to the first scan or to both, and the sum and number of the queries' scales.
+enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_LOST = 3, CTL_HUGE = 4, CTL_SCALES = 5, CTL_SCALED = 6, CTL_WORDS = 64 };
 constexpr int ALL_LOST = 1 << 20;     // in CTL_DONE: a row was seen that the bounds do not hold for
-constexpr size_t filter_lds_bytes(int wq, bool seed)
+constexpr size_t filter_lds_bytes(int wq, bool seed, bool fp16)
 {
-    return (size_t)2 * (TILE_ROWS + 64 * wq) * 2 * PB + 4 * TILE_ROWS * 4 + (size_t)64 * wq * 8 + CTL_WORDS * 4 +
+    return (size_t)2 * (TILE_ROWS + 64 * wq) * (fp16 ? 1 : 2) * PB + 4 * TILE_ROWS * 4 + (size_t)64 * wq * 12 + CTL_WORDS * 4 +
            (seed ? 0 : (size_t)FW * FDUMPS * 80);
 }
 
@@ -99,10 +133,13 @@ __device__ __forceinline__ void split4(v4f v, v4b &hi, v4b &lo)
     }
 }
 
-// One wave per query row: its two planes (zero beyond d and for rows beyond nq) and its squared norm.
+// One wave per query row: its two planes (zero beyond d and for rows beyond nq), its squared norm and its fp16 image.
+// Clears the words that the passes behind it set.
 __global__ __launch_bounds__(256) void split_queries_kernel(const float *__restrict__ q, int64_t ldq, int64_t nq, int64_t rows,
                                                             int d, int dp, __bf16 *__restrict__ qh, __bf16 *__restrict__ ql,
-                                                            float *__restrict__ qn)
+                                                            float *__restrict__ qn, _Float16 *__restrict__ qf,
+                                                            int32_t *__restrict__ qe, int32_t *__restrict__ hard,
+                                                            int32_t *__restrict__ again, float *__restrict__ nxsum)
 {
     const int lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -117,17 +154,31 @@ __global__ __launch_bounds__(256) void split_queries_kernel(const float *__restr
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-    if (lane == 0) qn[r] = ss;
+    // |q| 2^e lies in [1, 2); norms below 2^-50 count as zero
+    const int e = ss >= 0x1p-100f && ss <= HUGE_NORM ? -(ilogbf(ss) >> 1) : NO_SCALE;
+    for (int c = lane; c < dp; c += 64) {
+        const float v = (r < nq && c < d && e != NO_SCALE) ? q[r * ldq + c] : 0.0f;
+        qf[r * dp + c] = (_Float16)ldexpf(v, e == NO_SCALE ? 0 : e);
+    }
+    if (lane == 0) {
+        qn[r] = ss;
+        qe[r] = e;
+        again[r] = 0;
+        if (r % 128 == 0) hard[r / 128] = 0;
+        if (r == 0) *nxsum = 0.0f;
+    }
 }
 
-template <bool SEED, int WQ, bool VEC>
+template <bool SEED, int WQ, bool WIDE, bool FP16, bool EVEN>
 __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int WR = FW / WQ, RB = WQ, QT = 64 * WQ;
+    constexpr int NP = FP16 ? 1 : 2;                      // planes
     constexpr int AP = TILE_ROWS * PB, BP = QT * PB;      // bytes of a plane: items, queries
-    constexpr int STAGE = 2 * AP + 2 * BP;                // xh, xl, qh, ql
-    constexpr int BC = 2 * BP / 1024;                     // query copies per stage: 16 rows of one plane each
+    constexpr int STAGE = NP * (AP + BP);                 // xh, xl, qh, ql
+    constexpr int BC = NP * BP / 1024;                    // query copies per stage: 16 rows of one plane each
+    using frag_t = std::conditional_t<FP16, v8h, v8b>;
     constexpr int DUMPS = FDUMPS;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -142,8 +193,9 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 
     float *nx = reinterpret_cast<float *>(smem + 2 * STAGE);       // [4][256] squared norms, by tile & 3
     float *thr_l = nx + 4 * TILE_ROWS;                             // [QT]
-    int *fill = reinterpret_cast<int *>(thr_l + QT);               // [QT]
-    int *ctl = fill + QT;                                          // [CTL_WORDS]
+    int *fill = reinterpret_cast<int *>(thr_l + QT);               // [QT]; below 0: not a query of this scan
+    float *h_l = reinterpret_cast<float *>(fill + QT);             // [QT] FP16: what a scaled norm is multiplied by
+    int *ctl = fill + 2 * QT;                                      // [CTL_WORDS]
     float *dval = reinterpret_cast<float *>(ctl + CTL_WORDS) + wave * (DUMPS * 20);
     v4i *dmeta = reinterpret_cast<v4i *>(dval + DUMPS * 16);
     const int64_t q_tile = (int64_t)qt * QT, q_first = q_tile + wq * 64;
@@ -151,86 +203,173 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     if (!SEED) {
         if (tid < CTL_WORDS) ctl[tid] = 0;
         __syncthreads();
+    }
+    // FP16: the tile's rows are scaled by two to the mean of its queries' scales
+    int xe = 0;
+    if (!SEED && FP16) {
         for (int i = tid; i < QT; i += FW * 64) {
+            const int e = o.qe[q_tile + i];
+            if (e != NO_SCALE) { atomicAdd(&ctl[CTL_SCALES], e); atomicAdd(&ctl[CTL_SCALED], 1); }
+        }
+        __syncthreads();
+        const int scaled = ctl[CTL_SCALED];
+        xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
+        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI) xe = 0;
+    }
+    const float xscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, xe))));
+    if (!SEED) {
+        for (int i = tid; i < QT; i += FW * 64) {
+            const int64_t q = q_tile + i;
             float t = NAN;                                         // nothing compares: a slot that never collects
-            if (q_tile + i < o.nq && o.qn[q_tile + i] <= HUGE_NORM) {
-                const int32_t kth = o.kth[q_tile + i];
-                t = kth == INT32_MIN ? -INFINITY
-                                     : sortable_to_float(kth) - o.c * o.qn[q_tile + i] * 1.00001f - 0x1p-110f;
+            const bool hard = q < o.nq && o.hard[q >> 7];
+            bool mine = q < o.nq && (FP16 ? !hard : hard || o.again[q] == AGAIN);
+            if (mine && o.qn[q] <= HUGE_NORM) {
+                const int32_t kth = o.kth[q];
+                const float bound = kth == INT32_MIN ? -INFINITY : sortable_to_float(kth);
+                if (FP16) {
+                    // (a norm of up to 2^-50 taken as zero is off by 2^-50 |x| <= 2^(-35 - xe), scaled by 2^2 xe)
+                    const bool zero = o.qe[q] == NO_SCALE;
+                    const int e = zero ? xe : o.qe[q];
+                    if (e - xe > HALF_RANGE || xe - e > HALF_RANGE || (zero && xe > ZERO_SCALE)) {
+                        mine = false;
+                        atomicOr(&o.again[q], AGAIN);
+                    } else {
+                        t = ldexpf(bound - 0.5f * (o.c + o.ch) * o.qn[q] * 1.00001f - 0x1p-110f, xe + e) - sqrtf((float)o.d) * 0x1p-22f;
+                        h_l[i] = ldexpf(o.h, e - xe);
+                    }
+                } else {
+                    t = bound - o.c * o.qn[q] * 1.00001f - 0x1p-110f;
+                }
             }
             if (t != t) atomicAdd(&ctl[CTL_DONE], 1);
             thr_l[i] = t;
-            fill[i] = 0;
+            fill[i] = mine ? 0 : -1;
         }
     }
     __syncthreads();
-    float thr[2] = {NAN, NAN}, gm[2] = {-INFINITY, -INFINITY};
-    if (!SEED) { thr[0] = thr_l[wq * 64 + col]; thr[1] = thr_l[wq * 64 + 32 + col]; }
+    // Nothing to collect (to the second scan: the first has resolved all of them)?  The next barrier comes before any row
+    // can be found lost, which is written to the same word.
+    const bool none = !SEED && ctl[CTL_DONE] >= QT;
+    __syncthreads();
+    float gm[2] = {-INFINITY, -INFINITY};
 
-    const int nt = (o.tiles > s) ? (o.tiles - s + S - 1) / S : 0;
-    const int kst = o.dp / KF, T = nt * kst;
+    const int nt = (!none && o.tiles > s) ? (o.tiles - s + S - 1) / S : 0;
+    const int kst = o.kst, T = nt * kst;
 
     // ---- items: registers -> two planes in LDS --------------------------------------------------
     // Eight lanes share a row of a stage (16 bytes each); a wave loads rows wave * 32 + 8 i + lane / 8.
     // Chunk c (16 bytes of a plane) of row r sits in slot c ^ ((r >> 2) & 3).
     const int lrow = lane >> 3, lcol = (lane & 7) * 4;
     v4f pre[2][4];                    // stages on their way, stage t in set t & 1
+    // a lane's four rows: where they start in the tile's rows (the scan, whose tiles lie together), or in memory
     const float *src[4];
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    const float *tile_rows = o.x;
+    unsigned src_off[4];
+    float part[4] = {0.f, 0.f, 0.f, 0.f}, sum = 0.0f;
     int ft = 0, fk = 0;               // tile (of this split) and stage of the tile that is fetched next
     int pt = 0, pk = 0;               // ... and that goes to LDS next
-    auto fetch_tile = [&]() {
+    auto fetch_tile = [&]() LPQF_INLINE {
         const int64_t t0 = ((int64_t)s + (int64_t)ft * S) * o.tile_stride;
+        const int last = (int)(o.n - 1 - t0 < TILE_ROWS ? o.n - 1 - t0 : TILE_ROWS);   // rows past the end: any row, rejected later
+        if (!SEED) tile_rows = o.x + t0 * o.ldx;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            int64_t row = t0 + (int64_t)(wave * 2 + (i >> 1)) * o.run_gap + (i & 1) * 8 + lrow;
-            row = row < o.n ? row : o.n - 1;     // rows past the end: any row, rejected later
-            src[i] = o.x + row * o.ldx + lcol;
+            if (SEED) {
+                int64_t row = t0 + (int64_t)(wave * 2 + (i >> 1)) * o.run_gap + (i & 1) * 8 + lrow;
+                src[i] = o.x + (row < o.n ? row : o.n - 1) * o.ldx;
+            } else {
+                const int r = wave * 32 + i * 8 + lrow;
+                src_off[i] = (unsigned)(r < last ? r : last) * (unsigned)o.ldx;
+            }
         }
     };
-    auto fetch = [&](v4f (&to)[4]) {  // loads of stage (ft, fk); at least four of them
-        const int k0 = fk * KF;
-        if (VEC && k0 + KF <= o.d) {
+    // Loads of stage (ft, fk), LOADS of them on every path: only then does the compiler wait for one stage's loads
+    // without waiting for those issued after them.  (With a branch between them, and with a stage that fetched
+    // nothing, it waited for all, a memory round trip per stage.)  What lies past a row's end is loaded from its
+    // last four values and put right in fix; past the last stage the last tile's are fetched again.
+    constexpr int LOADS = WIDE ? 4 : 16;
+    auto fetch = [&](v4f (&to)[4]) LPQF_INLINE {
+        const int c = fk * KF + lcol;
+        if (WIDE) {
+            const int at = c < o.d - 4 ? c : o.d - 4;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) to[i] = *reinterpret_cast<const v4f *>(src[i] + k0);
+            for (int i = 0; i < 4; ++i)
+                to[i] = *reinterpret_cast<const v4f_any *>(SEED ? src[i] + at : tile_rows + (src_off[i] + (unsigned)at));
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) to[i][e] = (k0 + lcol + e < o.d) ? src[i][k0 + e] : 0.0f;
+                for (int e = 0; e < 4; ++e) {
+                    const int at = c + e < o.d ? c + e : 0;
+                    to[i][e] = SEED ? src[i][at] : tile_rows[src_off[i] + (unsigned)at];
+                }
         }
         if (++fk == kst) {
             fk = 0;
-            if (++ft < nt) fetch_tile();
+            if (ft + 1 < nt) { ++ft; fetch_tile(); }
         }
     };
-    auto put = [&](const v4f (&from)[4], int slot) {   // a fetched stage goes to LDS
+    auto fix = [&](v4f v) LPQF_INLINE {           // the last stage of a row, and rows that are scaled
+        const int left = o.d - (pk * KF + lcol);
+        if (WIDE && left < 4) {
+            v = left == 3 ? v4f{v[1], v[2], v[3], 0.f} : left == 2 ? v4f{v[2], v[3], 0.f, 0.f} : v4f{v[3], 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < left ? (FP16 ? v[e] * xscale : v[e]) : 0.0f;
+        return v;
+    };
+    auto fix_stage = [&](v4f (&from)[4]) LPQF_INLINE {
+        if ((pk + 1) * KF > o.d || (FP16 && xe != 0)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) from[i] = fix(from[i]);
+        }
+    };
+    auto put = [&](v4f (&from)[4], int slot) LPQF_INLINE {   // a fetched stage goes to LDS (fix_stage comes first)
         unsigned char *base = smem + slot * STAGE;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = wave * 32 + i * 8 + lrow;
             const int at = r * PB + (((lane & 7) >> 1) ^ ((r >> 2) & 3)) * 16 + (lane & 1) * 8;
-            v4b hi, lo;
-            split4(from[i], hi, lo);
-            *reinterpret_cast<v4b *>(base + at) = hi;
-            *reinterpret_cast<v4b *>(base + AP + at) = lo;
+            v4f v = from[i];
+            if constexpr (FP16) {
+                v4h f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part[i] = fmaf(from[i][e], from[i][e], part[i]);
+                for (int e = 0; e < 4; ++e) f[e] = (_Float16)v[e];
+                *reinterpret_cast<v4h *>(base + at) = f;
+            } else {
+                v4b hi, lo;
+                split4(v, hi, lo);
+                *reinterpret_cast<v4b *>(base + at) = hi;
+                *reinterpret_cast<v4b *>(base + AP + at) = lo;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[i] = fmaf(v[e], v[e], part[i]);
         }
     };
-    auto put_done = [&]() {           // ... and, at the end of a tile, its rows' norms
+    auto put_done = [&]() LPQF_INLINE {           // ... and, at the end of a tile, its rows' norms
         if (++pk == kst) {
-            float *dst = nx + (pt & 3) * TILE_ROWS;
+            constexpr float LIMIT = FP16 ? HALF_NORM : HUGE_NORM;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float p = part[i];
-                p += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(p)));
-                p += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(p)));
-                p += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(p)));
-                if ((lane & 7) == 0) dst[wave * 32 + i * 8 + lrow] = p;
-                if (!SEED && !(p <= HUGE_NORM)) ctl[CTL_DONE] = ALL_LOST;
-                part[i] = 0.0f;
+                part[i] += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(part[i])));
+                part[i] += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(part[i])));
+                part[i] += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(part[i])));
+                if (SEED) sum += part[i];
             }
+            const int i = lane & 3;              // lanes 0 to 3 of the eight that share a row write the four rows' norms
+            float p = part[0];
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+                const float pe = part[e];
+                p = i == e ? pe : p;
+            }
+            if ((lane & 4) == 0) nx[(pt & 3) * TILE_ROWS + wave * 32 + i * 8 + lrow] = p;
+            if (!SEED && !(p <= LIMIT)) {
+                ctl[CTL_DONE] = ALL_LOST;
+                if (FP16) ctl[ldexpf(p, -2 * xe) <= HUGE_NORM ? CTL_LOST : CTL_HUGE] = 1;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[e] = 0.0f;
             pk = 0;
             ++pt;
         }
@@ -241,41 +380,47 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     const unsigned lds0 = lds_offset(smem);
     const unsigned q_off = (unsigned)(((lane >> 2) * o.dp) * 2 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16));
     int qk = 0;
-    auto copy_queries = [&](int slot) {
+    auto copy_queries = [&](int slot) LPQF_INLINE {
 #pragma unroll
         for (int e = 0; e < (BC + FW - 1) / FW; ++e) {
             const int i = wave + e * FW, plane = i / (QT / 16), r16 = i % (QT / 16);
-            const __bf16 *base = (plane ? o.ql : o.qh) + (q_tile + r16 * 16) * o.dp + qk * KF;
-            const unsigned dst = lds0 + slot * STAGE + 2 * AP + plane * BP + r16 * 1024;
+            if (BC % FW != 0 && i >= BC) break;
+            const void *base = (FP16 ? (const char *)o.qf : (const char *)(plane ? o.ql : o.qh)) +
+                               2 * ((q_tile + r16 * 16) * o.dp + qk * KF);
+            const unsigned dst = lds0 + slot * STAGE + NP * AP + plane * BP + r16 * 1024;
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(q_off), "s"(base) : "memory");
         }
         qk = qk + 1 == kst ? 0 : qk + 1;
     };
-    static_assert(BC % FW == 0, "every wave copies the same number of times");
 
     // ---- fragments ------------------------------------------------------------------------------
     const int sw = (half ^ ((col >> 2) & 3)) * 16;
-    const int a_off = (wr * RB * 32 + col) * PB + sw, b_off = 2 * AP + (wq * 64 + col) * PB + sw;
-    v8b A[2][2][RB], B[2][2][2];      // [k-step][plane][block]
+    const int a_off = (wr * RB * 32 + col) * PB + sw, b_off = NP * AP + (wq * 64 + col) * PB + sw;
+    frag_t A[2][NP][RB], B[2][NP][2]; // [k-step][plane][block]
 #define LPQF_LOAD(SLOT, KSTEP, F)                                                                       \
     do {                                                                                                \
         const unsigned char *sb_ = smem + (SLOT) * STAGE;                                               \
         const unsigned char *pa_ = sb_ + (a_off ^ ((KSTEP) * 32)), *pb_ = sb_ + (b_off ^ ((KSTEP) * 32)); \
-        _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                 \
-            _Pragma("unroll") for (int j = 0; j < 2; ++j) B[F][p][j] = *reinterpret_cast<const v8b *>(pb_ + p * BP + j * 32 * PB); \
-            _Pragma("unroll") for (int i = 0; i < RB; ++i) A[F][p][i] = *reinterpret_cast<const v8b *>(pa_ + p * AP + i * 32 * PB); \
+        _Pragma("unroll") for (int p = 0; p < NP; ++p) {                                                \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j) B[F][p][j] = *reinterpret_cast<const frag_t *>(pb_ + p * BP + j * 32 * PB); \
+            _Pragma("unroll") for (int i = 0; i < RB; ++i) A[F][p][i] = *reinterpret_cast<const frag_t *>(pa_ + p * AP + i * 32 * PB); \
         }                                                                                               \
     } while (0)
-    v16f acc[RB][2];
-#define LPQF_MFMA(F)                                                                                    \
-    _Pragma("unroll") for (int pp = 0; pp < 3; ++pp)   /* xh qh, xh ql, xl qh */                        \
+    v16f acc[RB][2];                  // (a tile's first matrix instructions start from zero)
+    constexpr v16f ZERO = {};
+    auto mfma = [](frag_t a, frag_t b, v16f c) LPQF_INLINE {
+        if constexpr (FP16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    };
+#define LPQF_MFMA(F, FIRST)                                                                                  \
+    _Pragma("unroll") for (int pp = 0; pp < 2 * NP - 1; ++pp)   /* xh qh, xh ql, xl qh */               \
         _Pragma("unroll") for (int i = 0; i < RB; ++i)                                                  \
             _Pragma("unroll") for (int j = 0; j < 2; ++j)                                               \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[F][pp == 2][i], B[F][pp == 1][j], acc[i][j], 0, 0, 0)
+                acc[i][j] = mfma(A[F][pp == 2][i], B[F][pp == 1][j], (FIRST) && pp == 0 ? ZERO : acc[i][j])
 
 #define LPQF_ORDER() __builtin_amdgcn_sched_barrier(0)
     const int G = S * o.SEG * 2 * WR;
-    auto flush_segment = [&](int seg) {
+    auto flush_segment = [&](int seg) LPQF_INLINE {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             o.gmax[(size_t)(q_first + j * 32 + col) * G + (((size_t)s * o.SEG + seg) * WR + wr) * 2 + half] = float_to_sortable(gm[j]);
@@ -287,7 +432,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     }
     cand_t *cbase = SEED ? nullptr : o.cbuf + ((size_t)q_tile * S + s) * o.Cs;
     const size_t qstride = (size_t)S * o.Cs;
-    auto drain = [&](int dumps) {     // queued scores that reach their query's threshold go to its region
+    auto drain = [&](int dumps) LPQF_INLINE {     // queued scores that reach their query's threshold go to its region
         wave_lds_sync();
         for (int base = 0; base < dumps * 16; base += 64) {
             const int at = base + lane;
@@ -314,76 +459,74 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         fetch_tile();
         fetch(pre[0]);
         copy_queries(0);
+        fix_stage(pre[0]);
         put(pre[0], 0);
         put_done();
         if (T > 1) copy_queries(1);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        if (T > 1) fetch(pre[1]);
-        if (T > 2) fetch(pre[0]);
+        fetch(pre[1]);
+        fetch(pre[0]);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
         LPQF_LOAD(0, 0, 0);
     }
-    int t = 0, seg = 0, partial = 0;
+    int t = 0, tile = 0, seg = 0, partial = 0;
     // Stage t, whose parity P is a constant: the sets of registers cannot be indexed at run time.
-    auto stage = [&](auto parity) {
+    auto stage = [&](auto parity, auto first) LPQF_INLINE {
         constexpr int P = decltype(parity)::value;
+        constexpr bool FIRST = decltype(first)::value;
+        fix_stage(pre[P ^ 1]);                // (a branch: not among what the matrix instructions cover)
         __builtin_amdgcn_s_waitcnt(0xC07F);   // the first k-step's fragments are there; do not wait for the second's below
         LPQF_LOAD(P, 1, 1);
-        LPQF_MFMA(0);
+        LPQF_MFMA(0, FIRST);
         // stage t + 1 goes into the other slot, which was read out before the last barrier (after the
         // last stage: stale values that nobody reads)
         put(pre[P ^ 1], P ^ 1);
+        if (FP16) {   // the second k-step's fragments first, then the vector work of the split between the matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 + RB, 0);
+#pragma unroll
+            for (int i = 0; i < 2 * RB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 48 / (2 * RB), 0);
+            }
+        }
         LPQF_ORDER();
         if (t + 1 < T) put_done();
         // My reads of stage t, my writes and my query copies of stage t + 1 are complete; of the vector
-        // memory operations only the four or more loads of stage t + 2 may be newer than those copies.
-        if (t + 2 < T) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        // memory operations only the loads of stage t + 2 are newer than those copies.
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
         LPQF_LOAD(P ^ 1, 0, 0);               // (after the last stage: whatever the slot holds, unused)
         if (t + 2 < T) copy_queries(P);
-        if (t + 3 < T) fetch(pre[P ^ 1]);
-        LPQF_MFMA(1);
+        fetch(pre[P ^ 1]);
+        LPQF_MFMA(1, false);
         ++t;
     };
     // For the epilogue of the next tile, read in this one: how many queries are done, and how many wave 0 said are
     // done in the epilogue before this one.  Everyone has passed the barriers of a tile since, and that word is
     // written again only behind those of the next, so all threads of the workgroup get the same.
     int done = 0, said = 0, known = 0, next = 0;
-    auto look = [&]() {
+    auto look = [&]() LPQF_INLINE {
         done = ctl[CTL_DONE];
         said = ctl[CTL_SAID + next];
         next ^= 1;
     };
     if (!SEED) look();
-#pragma clang loop unroll(disable)
-    for (int tile = 0; tile < nt; ++tile) {
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        int k = kst;
-        if (t & 1) { stage(std::integral_constant<int, 1>{}); --k; }
-#pragma clang loop unroll(disable)
-        for (; k >= 2; k -= 2) {
-            stage(std::integral_constant<int, 0>{});
-            stage(std::integral_constant<int, 1>{});
-        }
-        if (k) stage(std::integral_constant<int, 0>{});
+    // The end of a tile; false when nothing is left to do.
+    auto finish_tile = [&]() LPQF_INLINE -> bool {
         __builtin_amdgcn_sched_barrier(0);        // nothing of the contraction drifts down into the epilogue
         const int64_t row0 = ((int64_t)s + (int64_t)tile * S) * o.tile_stride;
         int dumps = 0;
+        float thr[2], hq[2] = {o.h, o.h};        // (read here: registers are what the contraction is short of)
         if (!SEED) {
+            thr[0] = thr_l[wq * 64 + col];
+            thr[1] = thr_l[wq * 64 + 32 + col];
+            if (FP16) { hq[0] = h_l[wq * 64 + col]; hq[1] = h_l[wq * 64 + 32 + col]; }
             const int now = __builtin_amdgcn_readfirstlane(said);
             if (__builtin_expect(now != known, 0)) {
-                if (now >= QT) break;            // nothing left to collect
+                if (now >= QT) return false;     // nothing left to collect
                 known = now;
-                thr[0] = thr_l[wq * 64 + col];
-                thr[1] = thr_l[wq * 64 + 32 + col];
             }
             if (tid == 0) ctl[CTL_SAID + (next ^ 1)] = done;
             look();                              // (here, not behind the epilogue: the next stage waits for all LDS reads at once)
@@ -398,7 +541,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
             for (int j = 0; j < 2; ++j) {
                 v16f v = acc[i][j];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = fmaf(-o.h, nv[e >> 2][e & 3], v[e]);
+                for (int e = 0; e < 16; ++e) v[e] = fmaf(-hq[j], nv[e >> 2][e & 3], v[e]);
                 float m = v[0];
 #pragma unroll
                 for (int e = 1; e < 16; ++e) m = fmaxf(m, v[e]);
@@ -433,6 +576,36 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
             if (partial >= nt || tile + 1 == nt) flush_segment(seg);
             for (; partial >= nt; partial -= nt) ++seg;
         }
+        return ++tile < nt;
+    };
+    constexpr std::integral_constant<int, 0> P0;
+    constexpr std::integral_constant<int, 1> P1;
+    bool more = T > 0;
+#pragma clang loop unroll(disable)
+    while (more) {
+        if constexpr (EVEN) {         // an even number of stages to a tile: the parities alternate in the code, too
+            stage(P0, std::true_type());
+            stage(P1, std::false_type());
+#pragma clang loop unroll(disable)
+            for (int k = 2; k < kst; k += 2) {
+                stage(P0, std::false_type());
+                stage(P1, std::false_type());
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = ZERO;
+            int k = kst;
+            if (t & 1) { stage(P1, std::false_type()); --k; }
+#pragma clang loop unroll(disable)
+            for (; k >= 2; k -= 2) {
+                stage(P0, std::false_type());
+                stage(P1, std::false_type());
+            }
+            if (k) stage(P0, std::false_type());
+        }
+        more = finish_tile();
     }
 #undef LPQF_LOAD
 #undef LPQF_MFMA
@@ -443,24 +616,45 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         __syncthreads();
         // a row the bounds do not hold for: all queries of the tile overflow
         const bool lost = ctl[CTL_DONE] >= ALL_LOST;
-        for (int i = tid; i < QT; i += FW * 64)
-            if (q_tile + i < o.nq) o.ccnt[(size_t)(q_tile + i) * S + s] = lost ? o.Cs + 1 : fill[i];
+        for (int i = tid; i < QT; i += FW * 64) {
+            const int64_t q = q_tile + i;
+            if (q >= o.nq || (!FP16 && fill[i] < 0)) continue;
+            const int have = fill[i] < 0 ? 0 : (lost ? o.Cs + 1 : fill[i]);
+            o.ccnt[(size_t)q * S + s] = have;
+            if (FP16 && have > o.Cs) atomicOr(&o.again[q], lost && ctl[CTL_HUGE] ? DIRECT : AGAIN);
+        }
+    }
+    if (SEED) {
+#pragma unroll
+        for (int o_ = 32; o_ > 0; o_ >>= 1) sum += __shfl_xor(sum, o_, 64);
+        __syncthreads();                          // (nobody reads the norms any more)
+        if (lane == 0) nx[wave] = sum;
+        __syncthreads();
+        if (tid == 0) {                           // one atomic operation per workgroup: they all go to one word
+#pragma unroll
+            for (int i = 1; i < FW; ++i) sum += nx[i];
+            atomicAdd(o.nxsum, sum);
+        }
     }
 }
 
-template <bool SEED, int WQ>
+template <bool SEED, int WQ, bool FP16>
 hipError_t launch_filter(const FilterIo &o, hipStream_t st)
 {
-    const bool vec = ((uintptr_t)o.x % 16 == 0) && (o.ldx % 4 == 0);
-    auto kern = vec ? filter_f32_kernel<SEED, WQ, true> : filter_f32_kernel<SEED, WQ, false>;
-    static bool attr_set[2] = {false, false};
-    if (!attr_set[vec]) {
+    const bool wide = o.d >= 4;       // (16-byte loads need no more than the rows' own alignment of 4)
+    const bool even = o.kst % 2 == 0;
+    if (FP16 && !even) return hipErrorInvalidValue;
+    auto kern = !wide ? filter_f32_kernel<SEED, WQ, false, FP16, FP16>
+                      : (even ? filter_f32_kernel<SEED, WQ, true, FP16, true> : filter_f32_kernel<SEED, WQ, true, FP16, FP16>);
+    static bool attr_set[3] = {false, false, false};
+    const int which = wide ? 1 + even : 0;
+    if (!attr_set[which]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
-        attr_set[vec] = true;
+        attr_set[which] = true;
     }
-    kern<<<(unsigned)(o.qtiles * o.S), FW * 64, filter_lds_bytes(WQ, SEED), st>>>(o);
+    kern<<<(unsigned)(o.qtiles * o.S), FW * 64, filter_lds_bytes(WQ, SEED, FP16), st>>>(o);
     return hipGetLastError();
 }
 
@@ -477,8 +671,13 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     p.wq = nq <= 64 ? 1 : 2;
     const int qt = 64 * p.wq, row_waves = FW / p.wq;
     p.qtiles = (int)ceil_div(nq, qt);
-    p.nq_pad = round_up(nq, 128);
-    p.dp = (int)round_up(d, KF);
+    // The first scan pays for its launch from about 4e9 multiplications on (20 000 x 100, 50 queries 42 us without it and
+    // 45 with it, 10 000 x 64, 2000 queries 48 and 52; 1M x 128, 128 queries 197 and 159).
+    p.half = (double)n * (double)round_up(nq, 64) * (double)round_up(d, 2 * KF) >= 4e9;
+    p.wq_half = !p.half ? p.wq : nq <= 64 ? 1 : (nq <= 128 ? 2 : 4);
+    p.qtiles_half = (int)ceil_div(nq, 64 * p.wq_half);
+    p.nq_pad = round_up(nq, 256);
+    p.dp = (int)round_up(d, 2 * KF);
     // The sample costs a contraction per row and query (or, for few queries, the bytes of its rows), each
     // item it lets through - about k n / rows per query - the bytes of a row: least at rows ~ sqrt(k n)
     // (~ sqrt(nq k n); the factors are measured, 1M x 128: one query 0.16 ms with 19 000 rows, 0.18 with 8300).
@@ -504,7 +703,7 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
     if (p.G < k || p.G > 4096) return p;
     const int64_t tiles = ceil_div(n, TILE_ROWS);
-    int64_t s2 = slots / p.qtiles;
+    int64_t s2 = slots / p.qtiles_half;
     if (s2 > tiles) s2 = tiles;
     p.S2 = (int)(s2 < 1 ? 1 : s2);
     const double expect = 1.5 * (double)k * (double)n / ((double)p.seed_tiles * TILE_ROWS);
@@ -515,7 +714,11 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     size_t o = 0;
     p.off_qh = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
     p.off_ql = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
+    p.off_qf = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
     p.off_qn = o;   o = align256(o + (size_t)p.nq_pad * 4);
+    p.off_qe = o;   o = align256(o + (size_t)p.nq_pad * 4);
+    p.off_hard = o; o = align256(o + (size_t)p.nq_pad / 128 * 4 + 4);
+    p.off_again = o; o = align256(o + (size_t)p.nq_pad * 4);
     p.off_gmax = o; o = align256(o + (size_t)p.nq_pad * p.G * 4);
     p.off_kth = o;  o = align256(o + (size_t)nq * 4);
     p.off_cbuf = o; o = align256(o + (size_t)nq * p.S2 * p.Cs * sizeof(cand_t));
@@ -534,28 +737,48 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     float *qn = reinterpret_cast<float *>(ws + p.off_qn);
     int32_t *gmax = reinterpret_cast<int32_t *>(ws + p.off_gmax), *kth = reinterpret_cast<int32_t *>(ws + p.off_kth);
     int32_t *count = reinterpret_cast<int32_t *>(ws + p.off_list) + nq;
-    split_queries_kernel<<<(unsigned)ceil_div(p.nq_pad, (int64_t)4), 256, 0, st>>>(q, ldq, nq, p.nq_pad, d, p.dp, qh, ql, qn);
+    _Float16 *qf = reinterpret_cast<_Float16 *>(ws + p.off_qf);
+    int32_t *qe = reinterpret_cast<int32_t *>(ws + p.off_qe), *hard = reinterpret_cast<int32_t *>(ws + p.off_hard);
+    float *nxsum = reinterpret_cast<float *>(hard + p.nq_pad / 128);
+    int32_t *again = reinterpret_cast<int32_t *>(ws + p.off_again);
+    split_queries_kernel<<<(unsigned)ceil_div(p.nq_pad, (int64_t)4), 256, 0, st>>>(q, ldq, nq, p.nq_pad, d, p.dp, qh, ql, qn, qf, qe,
+                                                                                   hard, again, nxsum);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     FilterIo o = {};
     o.x = x; o.n = n; o.ldx = ldx; o.d = d; o.dp = p.dp;
+    o.kst = (int)ceil_div(d, (int64_t)KF);
     o.qh = qh; o.ql = ql; o.qn = qn; o.nq = nq; o.qtiles = p.qtiles;
     o.c = f32_filter_constant(d);
+    o.ch = f32_half_filter_constant(d);
+    o.qf = qf; o.qe = qe; o.hard = hard; o.again = again; o.nxsum = nxsum;
     // seeding pass: lower bounds of the scores of a sample (runs of 16 rows spread over the corpus)
     o.S = p.S1; o.SEG = p.SEG; o.gmax = gmax;
     o.tiles = p.seed_tiles; o.tile_stride = p.run_stride; o.run_gap = (int64_t)p.seed_tiles * p.run_stride;
     if (p.run_stride < RUN || ((int64_t)16 * p.seed_tiles - 1) * p.run_stride + RUN > n) return hipErrorInvalidValue;
     o.h = l2 ? 0.5f * (1.0f + o.c) : 0.5f * o.c;
-    e = p.wq == 1 ? launch_filter<true, 1>(o, st) : launch_filter<true, 2>(o, st);
+    e = p.wq == 1 ? launch_filter<true, 1, false>(o, st) : launch_filter<true, 2, false>(o, st);
     if (e != hipSuccess) return e;
-    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, count, kth);
+    // Groups within the first scan's error of the bound, for a row of the sample's mean norm: beyond twice k and a few, the
+    // query is left to the second scan (regions hold three times what the sample lets expect, so it would overflow).
+    const float c2 = 0.5f * (o.c + o.ch) * 1.00001f;
+    const HardQueries hq = {qn, nxsum, c2, c2 / (8.0f * TILE_ROWS * (float)p.seed_tiles * (float)p.qtiles), p.half ? 2 * k + 8 : 0, hard};
+    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, count, kth, nullptr, 0, 0, hq);
     if (e != hipSuccess) return e;
-    // scan: every item whose upper bound reaches the k-th lower bound
+    // scans: every item whose upper bound reaches the k-th lower bound
     o.S = p.S2; o.kth = kth;
     o.cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf); o.ccnt = reinterpret_cast<int32_t *>(ws + p.off_ccnt); o.Cs = p.Cs;
     o.tiles = (int)ceil_div(n, (int64_t)TILE_ROWS); o.tile_stride = TILE_ROWS; o.run_gap = RUN;
+    if (p.half) {
+        o.h = l2 ? 0.5f * (1.0f - o.ch) : -0.5f * o.ch;
+        o.qtiles = p.qtiles_half; o.kst = p.dp / KF;
+        e = p.wq_half == 1 ? launch_filter<false, 1, true>(o, st)
+                           : (p.wq_half == 2 ? launch_filter<false, 2, true>(o, st) : launch_filter<false, 4, true>(o, st));
+        if (e != hipSuccess) return e;
+    }
     o.h = l2 ? 0.5f * (1.0f - o.c) : -0.5f * o.c;
-    return p.wq == 1 ? launch_filter<false, 1>(o, st) : launch_filter<false, 2>(o, st);
+    o.qtiles = p.qtiles; o.kst = (int)ceil_div(d, (int64_t)KF);
+    return p.wq == 1 ? launch_filter<false, 1, false>(o, st) : launch_filter<false, 2, false>(o, st);
 }
 
 }  // namespace lpq
