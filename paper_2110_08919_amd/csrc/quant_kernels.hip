@@ -569,38 +569,101 @@ __global__ void quantile_finish_kernel(int d, int pooled, int cols, const uint32
 // and counts those outside; the answer is then selected among the collected ones and its rank is exact.
 // If a rank turns out to lie outside its window, or a list overflows, bit 1 of the flag asks for the
 // radix selection above.  The pass also looks for values that are not finite, so the min/max pass is not
-// needed either.  Bound by the one read of the data: 1M x 128, p = 0.001: 0.117 ms = 4.4 TB/s against five
-// passes of about 0.1 each; calibration and encoding together 0.96 -> 0.46 ms.
-constexpr int QW_SAMPLE = 4096;   // sorting twice as many costs 40 us more than the narrower windows save
+// needed either.  Bound by the one read of the data: 1M x 128, p = 0.001: 0.113 ms = 4.5 TB/s (0.122 while every value
+// went through the tests of both windows) against five passes of about 0.1 each; calibration and encoding together
+// 0.96 -> 0.40 ms.
+constexpr int QW_SAMPLE = 4096;   // twice as many: narrower windows save less than the longer selection costs
+constexpr int QW_THREADS = 1024;
 
-__global__ __launch_bounds__(1024) void quantile_window_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int m,
+// Counts of one digit of up to 11 bits.  A lane of the wave that looks for a bin owns 32 of them; one word between
+// those of two lanes keeps its reads out of each other's banks.
+constexpr int QW_DIGIT = 11;
+constexpr int QW_HIST = (1 << QW_DIGIT) + 64;
+__device__ __forceinline__ uint32_t qw_slot(uint32_t bin) { return bin + (bin >> 5); }
+
+// The bin that holds the value of this rank, and its rank among the values of that bin; the rank lies below the
+// histogram's total.  A whole wave works together.
+__device__ __forceinline__ uint32_t qw_find_bin(const uint32_t *hist, uint32_t rank, int lane, uint32_t &rest)
+{
+    auto scan = [&](uint32_t v) {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t up = __shfl_up(v, o, 64);
+            if (lane >= o) v += up;
+        }
+        return v;
+    };
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) mine += hist[33 * lane + j];
+    uint32_t incl = scan(mine);
+    const int owner = __ffsll((unsigned long long)__ballot(rank < incl)) - 1;
+    rank -= __shfl(incl - mine, owner, 64);
+    mine = lane < 32 ? hist[33 * owner + lane] : 0u;
+    incl = scan(mine);
+    const int at = __ffsll((unsigned long long)__ballot(rank < incl)) - 1;
+    rest = rank - __shfl(incl - mine, at, 64);
+    return (uint32_t)(32 * owner + at);
+}
+
+// The windows of a column's two ranks: four order statistics of its sample, by radix selection with digits of 11, 11
+// and 10 bits for all four together, the sample in registers.  (Sorting the sample: 78 steps of an LDS network with a
+// barrier each, 40 us at 128 columns; here 15.)
+__global__ __launch_bounds__(QW_THREADS) void quantile_window_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int m,
                                                                unsigned long long rank_lo, unsigned long long rank_hi,
                                                                uint32_t *__restrict__ qwin, uint32_t *__restrict__ qcount)
 {
-    extern __shared__ uint32_t qs[];                 // [next_pow2(m)]
-    const int c = blockIdx.x, tid = threadIdx.x;
-    int cap = 1;
-    while (cap < m) cap <<= 1;
-    for (int i = tid; i < cap; i += 1024)
-        qs[i] = i < m ? float_sortable_u32(x[(int64_t)((double)i * (double)n / (double)m) * ld + c]) : 0xFFFFFFFFu;
-    __syncthreads();
-    for (int size = 2; size <= cap; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < (cap >> 1); i += 1024) {
-                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-                const uint32_t a = qs[lo], b = qs[hi];
-                if ((a > b) == ((lo & size) == 0)) { qs[lo] = b; qs[hi] = a; }
-            }
-            __syncthreads();
-        }
-    if (tid < 2) {
-        const double rank = (double)(tid ? rank_hi : rank_lo), f = rank / (double)n, at = f * m;
-        const double w = 5.0 * sqrt((double)m * f * (1.0 - f)) + 4.0;
-        const double lo = floor(at - w), hi = ceil(at + w);
-        uint32_t *win = qwin + 2 * ((size_t)tid * d + c);
-        win[0] = lo < 0.0 ? 0u : qs[(int)lo];
-        win[1] = hi >= (double)m ? 0xFFFFFFFFu : qs[(int)hi];
+    constexpr int PER = QW_SAMPLE / QW_THREADS;
+    __shared__ uint32_t hist[4][QW_HIST], s_prefix[4], s_rank[4];
+    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = tid + j * QW_THREADS;
+        key[j] = i < m ? float_sortable_u32(x[(int64_t)((double)i * (double)n / (double)m) * ld + c]) : 0u;
     }
+    if (tid < 4) {                                   // statistic tid: first or last key of the window of target tid / 2
+        const double rank = (double)(tid >> 1 ? rank_hi : rank_lo), f = rank / (double)n, at = f * m;
+        const double w = 5.0 * sqrt((double)m * f * (1.0 - f)) + 4.0;
+        const double pos = tid & 1 ? ceil(at + w) : floor(at - w);
+        // beyond the sample: the window is open on that side (marked by a rank that no sample has)
+        s_rank[tid] = pos < 0.0 || pos >= (double)m ? 0xFFFFFFFFu : (uint32_t)pos;
+        s_prefix[tid] = 0u;
+    }
+    for (int hi = 32; hi > 0;) {                     // bits below hi are undecided
+        const int bits = hi >= QW_DIGIT ? QW_DIGIT : hi, shift = hi - bits, hists = hi == 32 ? 1 : 4;
+        for (int i = tid; i < hists * QW_HIST; i += QW_THREADS) (&hist[0][0])[i] = 0u;
+        __syncthreads();
+        uint32_t prefix[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) prefix[t] = s_prefix[t];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (tid + j * QW_THREADS < m) {
+                const uint32_t slot = qw_slot((key[j] >> shift) & ((1u << bits) - 1u));
+                if (hi == 32) {                      // nothing decided: the four share a histogram
+                    atomicAdd(&hist[0][slot], 1u);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (((key[j] ^ prefix[t]) >> hi) == 0u) atomicAdd(&hist[t][slot], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        if (wave < 4) {
+            const uint32_t rank = s_rank[wave];
+            if (rank != 0xFFFFFFFFu) {
+                uint32_t rest;
+                const uint32_t bin = qw_find_bin(hist[hi == 32 ? 0 : wave], rank, lane, rest);
+                if (lane == 0) { s_prefix[wave] |= bin << shift; s_rank[wave] = rest; }
+            }
+        }
+        hi = shift;
+        __syncthreads();
+    }
+    if (tid < 4)
+        qwin[2 * ((size_t)(tid >> 1) * d + c) + (tid & 1)] = s_rank[tid] == 0xFFFFFFFFu ? (tid & 1 ? 0xFFFFFFFFu : 0u) : s_prefix[tid];
     if (tid < 8) qcount[4 * ((size_t)(tid >> 2) * d + c) + (tid & 3)] = 0u;
 }
 
@@ -609,28 +672,34 @@ __global__ __launch_bounds__(1024) void quantile_window_kernel(const float *__re
 // column and target, to the column's list.
 constexpr int QW_LOCAL = 32;
 template <bool VEC>
-__global__ __launch_bounds__(1024) void quantile_gather_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int lpr,
+__global__ __launch_bounds__(1024, 8) void quantile_gather_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int lpr,
                                                                int64_t rows_per_block, const uint32_t *__restrict__ qwin,
                                                                uint32_t *__restrict__ qcount, uint32_t *__restrict__ qlist,
                                                                int cap, int *__restrict__ flag)
 {
     __shared__ uint32_t s_cnt[256][4];               // per target and column of the tile: inside, first, last, outside
     __shared__ uint32_t s_buf[256][QW_LOCAL];
+    __shared__ uint32_t s_win[256][2];               // ... its window: first key, width
     const int tid = threadIdx.x, jl = tid & (lpr - 1), rl = tid / lpr, rstep = 1024 / lpr;
-    for (int i = tid; i < 1024; i += 1024) s_cnt[i >> 2][i & 3] = 0u;
-    __syncthreads();
     const int tile = 4 * lpr, cb = blockIdx.y * tile, c0 = cb + 4 * jl;
-    uint32_t lo[2][4], wid[2][4], outside[2][4];
+    for (int i = tid; i < 1024; i += 1024) s_cnt[i >> 2][i & 3] = 0u;
+    if (tid < 256) {
+        const int c = cb + (tid & 127) < d ? cb + (tid & 127) : d - 1;
+        const uint32_t *win = qwin + 2 * ((size_t)(tid >> 7) * d + c);
+        s_win[tid][0] = win[0];
+        s_win[tid][1] = win[1] - win[0];
+    }
+    __syncthreads();
     bool bad = false;
+    // What lies between the two windows of its column, almost every value, needs nothing: two compares, in which a value
+    // that is not a number fails, as everything does against the open end of a window.  The others are worked off one per
+    // lane at a time, whichever each lane's next one is.
+    float mid_lo[4], mid_hi[4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = c0 + e < d ? c0 + e : d - 1;
-            lo[t][e] = qwin[2 * ((size_t)t * d + c)];
-            wid[t][e] = qwin[2 * ((size_t)t * d + c) + 1] - lo[t][e];
-            outside[t][e] = 0u;
-        }
+    for (int e = 0; e < 4; ++e) {
+        mid_lo[e] = sortable_u32_float(s_win[4 * jl + e][0] + s_win[4 * jl + e][1]);
+        mid_hi[e] = sortable_u32_float(s_win[128 + 4 * jl + e][0]);
+    }
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r1 = (r0 + rows_per_block < n) ? r0 + rows_per_block : n;
     constexpr int U = 4;
@@ -649,47 +718,46 @@ __global__ __launch_bounds__(1024) void quantile_gather_kernel(const float *__re
                 for (int e = 0; e < 4; ++e) v[u][e] = c0 + e < d ? src[e] : 0.0f;
             }
         }
+        uint32_t rest = 0u;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (r + (int64_t)u * rstep >= r1) break;
+        for (int i = 0; i < 4 * U; ++i) {
+            const bool plain = v[i >> 2][i & 3] > mid_lo[i & 3] && v[i >> 2][i & 3] < mid_hi[i & 3];
+            rest = 2u * rest + (plain ? 0u : 1u);                          // value i in bit 4 U - 1 - i
+        }
+        while (rest) {
+            const int i = __clz((int)rest) - (32 - 4 * U);
+            rest &= ~(1u << (4 * U - 1 - i));
+            const int e = i & 3;
+            if (r + (int64_t)(i >> 2) * rstep >= r1 || (!VEC && c0 + e >= d)) continue;
+            float f = v[0][0];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (!VEC && c0 + e >= d) break;
-                bad |= !isfinite(v[u][e]);
-                const uint32_t key = float_sortable_u32(v[u][e]);
-                const uint32_t a0 = key - lo[0][e], a1 = key - lo[1][e];
-                outside[0][e] += key < lo[0][e];                       // below the low window
-                outside[1][e] += key > lo[1][e] + wid[1][e];           // above the high one
-                if (a0 <= wid[0][e] || a1 <= wid[1][e]) {
+            for (int j = 1; j < 4 * U; ++j) f = i == j ? v[j >> 2][j & 3] : f;
+            bad |= !isfinite(f);
+            const uint32_t key = float_sortable_u32(f);
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const uint32_t a = t ? a1 : a0;
-                        if (a <= wid[t][e]) {
-                            const int slot = t * 128 + 4 * jl + e;
-                            if (a == 0u) atomicAdd(&s_cnt[slot][1], 1u);
-                            else if (a == wid[t][e]) atomicAdd(&s_cnt[slot][2], 1u);
-                            else {
-                                const uint32_t at = atomicAdd(&s_cnt[slot][0], 1u);
-                                if (at < (uint32_t)QW_LOCAL) {
-                                    s_buf[slot][at] = key;
-                                } else {                               // the local list is full
-                                    const size_t col = (size_t)t * d + c0 + e;
-                                    const uint32_t g = atomicAdd(&qcount[4 * col], 1u);
-                                    if (g < (uint32_t)cap) qlist[col * cap + g] = key;
-                                }
-                            }
-                        }
+            for (int t = 0; t < 2; ++t) {
+                const int slot = t * 128 + 4 * jl + e;
+                const uint32_t first = s_win[slot][0], wid = s_win[slot][1], a = key - first;
+                if (a > wid) {                                             // below the low window, above the high one
+                    if (t ? key > first : key < first) atomicAdd(&s_cnt[slot][3], 1u);
+                } else if (a == 0u) {
+                    atomicAdd(&s_cnt[slot][1], 1u);
+                } else if (a == wid) {
+                    atomicAdd(&s_cnt[slot][2], 1u);
+                } else {
+                    const uint32_t at = atomicAdd(&s_cnt[slot][0], 1u);
+                    if (at < (uint32_t)QW_LOCAL) {
+                        s_buf[slot][at] = key;
+                    } else {                                               // the local list is full
+                        const size_t col = (size_t)t * d + c0 + e;
+                        const uint32_t g = atomicAdd(&qcount[4 * col], 1u);
+                        if (g < (uint32_t)cap) qlist[col * cap + g] = key;
                     }
                 }
             }
         }
     }
     if (bad) atomicOr(flag, 1);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (outside[t][e]) atomicAdd(&s_cnt[t * 128 + 4 * jl + e][3], outside[t][e]);
     __syncthreads();
     if (tid < 256) {
         const int t = tid >> 7, lc = tid & 127;
@@ -708,12 +776,15 @@ __global__ __launch_bounds__(1024) void quantile_gather_kernel(const float *__re
 }
 
 // One workgroup per (column, target): the order statistic inside its window, by radix selection on the list.
-__global__ __launch_bounds__(256) void quantile_select_kernel(int d, int64_t n, unsigned long long rank_lo, unsigned long long rank_hi,
+// Digits of 11 bits of a key's distance from the window's first, from the window's highest bit down: two passes for most
+// windows, whose keys spread over the bins (with bytes of the keys themselves four, and in the first two all keys met in
+// one or two bins).  128 columns of a million rows, 4400 keys each: 23 us then, 14 now.
+__global__ __launch_bounds__(QW_THREADS) void quantile_select_kernel(int d, int64_t n, unsigned long long rank_lo, unsigned long long rank_hi,
                                                               const uint32_t *__restrict__ qwin, const uint32_t *__restrict__ qcount,
                                                               const uint32_t *__restrict__ qlist, int cap,
                                                               float *__restrict__ mn, float *__restrict__ mx, int *__restrict__ flag)
 {
-    __shared__ uint32_t hist[256], s_prefix, s_rank;
+    __shared__ uint32_t hist[QW_HIST], s_prefix, s_rank;
     const int c = blockIdx.x >> 1, t = blockIdx.x & 1, tid = threadIdx.x;
     const size_t col = (size_t)t * d + c;
     const int64_t inside = qcount[4 * col], first = qcount[4 * col + 1], last = qcount[4 * col + 2], out = qcount[4 * col + 3];
@@ -729,39 +800,27 @@ __global__ __launch_bounds__(256) void quantile_select_kernel(int d, int64_t n, 
         return;
     }
     const uint32_t *list = qlist + col * cap;
+    const uint32_t base = qwin[2 * col], wid = qwin[2 * col + 1] - base;   // the keys lie strictly inside, wid is at least 2
     if (tid == 0) { s_prefix = 0u; s_rank = (uint32_t)(r - first); }
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0u;
+    for (int hi = 32 - __clz((int)wid); hi > 0;) {       // bits of the distance below hi are undecided
+        const int bits = hi >= QW_DIGIT ? QW_DIGIT : hi, shift = hi - bits;
+        for (int i = tid; i < QW_HIST; i += QW_THREADS) hist[i] = 0u;
         __syncthreads();
-        const uint32_t keep = shift == 24 ? 0u : (0xFFFFFFFFu << (shift + 8)), prefix = s_prefix, rank = s_rank;
-        for (int64_t i = tid; i < inside; i += 256) {
-            const uint32_t key = list[i];
-            if (((key ^ prefix) & keep) == 0u) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+        const uint32_t prefix = s_prefix, rank = s_rank;
+        for (int64_t i = tid; i < inside; i += QW_THREADS) {
+            const uint32_t a = list[i] - base;
+            if (((uint64_t)(a ^ prefix) >> hi) == 0u) atomicAdd(&hist[qw_slot((a >> shift) & ((1u << bits) - 1u))], 1u);
         }
         __syncthreads();
-        if (tid < 64) {                                  // one wave finds the bin, as quantile_pick_kernel does
-            uint32_t v[4], mine = 0u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = hist[4 * tid + j]; mine += v[j]; }
-            uint32_t incl = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = __shfl_up(incl, o, 64);
-                if (tid >= o) incl += up;
-            }
-            const unsigned long long has = __ballot(rank < incl);
-            if (has && tid == __ffsll(has) - 1) {
-                uint32_t before = incl - mine;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (rank < before + v[j]) { s_prefix = prefix | ((uint32_t)(4 * tid + j) << shift); s_rank = rank - before; break; }
-                    before += v[j];
-                }
-            }
+        if (tid < 64) {
+            uint32_t rest;
+            const uint32_t bin = qw_find_bin(hist, rank, tid, rest);
+            if (tid == 0) { s_prefix = prefix | bin << shift; s_rank = rest; }
         }
+        hi = shift;
         __syncthreads();
     }
-    if (tid == 0) dst[c] = sortable_u32_float(s_prefix);
+    if (tid == 0) dst[c] = sortable_u32_float(base + s_prefix);
 }
 
 __device__ inline float derive_m(float sb, float se, int bits)
@@ -1137,8 +1196,7 @@ hipError_t launch_calib_windows(const float *x, int64_t n, int64_t ld, int d, do
 {
     const CalibWindows w = carve_windows(windows, d);
     const int m = (int)(n < QW_SAMPLE ? n : QW_SAMPLE);
-    quantile_window_kernel<<<d, 1024, (size_t)next_pow2(m) * sizeof(uint32_t), st>>>(x, n, ld, d, m, low_rank(n, clip),
-                                                                                     high_rank(n, clip), w.win, w.count);
+    quantile_window_kernel<<<d, QW_THREADS, 0, st>>>(x, n, ld, d, m, low_rank(n, clip), high_rank(n, clip), w.win, w.count);
     return hipGetLastError();
 }
 
@@ -1165,7 +1223,7 @@ hipError_t launch_calibrate(const float *x, int64_t n, int64_t ld, int d, int bi
             quantile_gather_kernel<true><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, w.win, w.count, lists, cap, nonfinite_flag);
         else
             quantile_gather_kernel<false><<<grid, 1024, 0, st>>>(x, n, ld, d, lpr, rows, w.win, w.count, lists, cap, nonfinite_flag);
-        quantile_select_kernel<<<2 * d, 256, 0, st>>>(d, n, rl, rh, w.win, w.count, lists, cap, s.mn, s.mx, nonfinite_flag);
+        quantile_select_kernel<<<2 * d, QW_THREADS, 0, st>>>(d, n, rl, rh, w.win, w.count, lists, cap, s.mn, s.mx, nonfinite_flag);
         calib_params_kernel<<<1, CAL_THREADS, 0, st>>>(d, n, bits, mode, scope, sigma_mult, s.mn, s.mx, s.mu, s.css, params_out,
                                                        nonfinite_flag, params_committed);
         return hipGetLastError();

@@ -62,3 +62,14 @@ def test_window_quantiles_reject_values_that_are_not_finite(lpq):
             q.calibrate(y, "quantile", "per_feature", 0.01)
         assert e.value.code == lpq.ENONFINITE
     assert all(np.array_equal(a, b) for a, b in zip(before, q.get_params()))
+
+
+# windows as wide as the whole range of floats, lists longer than the sample, and half of all values outside both windows
+@pytest.mark.parametrize("n,d,p", [(3000, 2, 0.0), (1_000_000, 5, 0.001), (700_001, 4, 0.0), (250_000, 8, 0.25)])
+def test_window_quantiles_over_the_whole_range_of_floats(lpq, n, d, p):
+    g = torch.Generator(device="cuda").manual_seed(d)
+    bits = torch.randint(-2 ** 31, 2 ** 31, (n, d), generator=g, device="cuda", dtype=torch.int64).int()
+    x = bits.view(torch.float32)
+    x = torch.where(torch.isfinite(x), x, torch.zeros_like(x))
+    x[:, 1] = torch.randn(n, generator=g, device="cuda") * 1e-39          # subnormal
+    _check(lpq, x, p)
