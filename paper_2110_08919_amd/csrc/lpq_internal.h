@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -290,16 +291,18 @@ struct F32Filter {
     bool half = false;        // a first scan in fp16
     int wq = 0, qtiles = 0, wq_half = 0, qtiles_half = 0, dp = 0, S1 = 0, S2 = 0, SEG = 0, G = 0, seed_tiles = 0, Cs = 0;
     int64_t nq_pad = 0, run_stride = 0;
-    size_t off_qh = 0, off_ql = 0, off_qf = 0, off_qn = 0, off_qe = 0, off_hard = 0, off_again = 0, off_gmax = 0, off_kth = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_list = 0,
-           total = 0;
+    size_t off_qh = 0, off_ql = 0, off_qf = 0, off_qn = 0, off_qe = 0, off_qx = 0, off_hard = 0, off_again = 0, off_gmax = 0, off_kth = 0,
+           off_cbuf = 0, off_ccnt = 0, off_over = 0, total = 0;
 };
 F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k);
 // The filter's score of an item is within this times (|q|^2 + |x|^2) / 2 of the directly summed one.
 constexpr float f32_filter_constant(int d) { return 0x1p-14f + (float)d * 0x1p-20f; }
 // The same of its first scan, one product of operands rounded to fp16.
 constexpr float f32_half_filter_constant(int d) { return 0x1p-10f + 0x1p-15f + (float)d * 0x1p-21f; }
-// Rows that may be among the k nearest of each query -> regions cbuf[nq][S2][Cs] (the low half of a
-// candidate holds the row), ccnt[nq][S2]; the counter behind the redo list is cleared.
+// ... and what values too small for fp16's normal range may add to a scaled score.
+inline __host__ __device__ float f32_half_filter_small(int d) { return sqrtf((float)d) * 0x1p-22f; }
+// Rows that may be among the k nearest of each query, and the upper bounds of their scores -> regions cbuf[nq][S2][Cs],
+// ccnt[nq][S2].
 hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int64_t ldx, const float *q, int64_t nq, int64_t ldq,
                              int d, int k, bool l2, char *ws, hipStream_t st);
 size_t f32_workspace_bytes(int64_t n, int64_t nq, int d, int k);

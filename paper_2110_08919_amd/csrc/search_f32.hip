@@ -184,70 +184,290 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
     }
 }
 
-// Directly summed distances of the rows the filter collected: eight lanes per row, each with the same
-// chunks of four features in the same order, the eight partial sums added in the same pairs, as in the
-// kernel above, so a distance comes out with the same bits.  `share` workgroups per query; the key half
-// of every collected candidate is written in place.  Bound by the gathered rows (4 KB each at 1024 features).
-constexpr int DIST_REGIONS = 256;   // regions whose counts the kernel lists in LDS
-template <bool VEC>
-__global__ __launch_bounds__(F32_THREADS) void f32_distances_kernel(const float *__restrict__ x, int64_t ldx,
-                                                                    const float *__restrict__ qv, int64_t ldq, int d, bool l2,
-                                                                    int SS, int Cs, int share, const int32_t *__restrict__ ccnt,
-                                                                    cand_t *__restrict__ cbuf)
+// The k nearest of the rows the filter collected, one workgroup per query.  A candidate comes with the upper bound of
+// its score: the k and a few with the highest are summed directly, the k-th of those distances says which upper bounds
+// still matter, and only those rows are summed too: some 30 of 280 (1M x 128, k = 10), each 4 d bytes from far apart.
+// Up to FIN_FEW candidates, almost always, nothing is sorted: a histogram of the bounds gives the highest, and the rank of
+// a distance is the number of those before it, counted by the thread that holds it.  Beyond, bounds and distances are
+// sorted.  Directly summed: eight lanes per row, each with the same chunks of four features in the same order, the eight
+// partial sums added in the same pairs, as in the kernel above, so a distance comes out with the same bits.
+// Bound by barriers and the latency of the rows.  1000 queries on 1M x 128, k = 10: 13 us, where summing all candidates
+// took 37 and selecting among them 29 (sorting the bounds here: 37); k = 100, 700 candidates each: 28.
+constexpr int FIN_CAP = 4096;       // candidates in LDS; of more, the best half is kept while the rest passes by
+constexpr int FIN_FEW = FIN_CAP / 2, FIN_RANKED = 2 * F32_THREADS, FIN_BINS = F32_THREADS;
+constexpr int FIN_REGIONS = F32_THREADS;
+struct FinishIo {
+    const float *x, *q;
+    int64_t ldx, ldq;
+    int d, k, SS, Cs;
+    const int32_t *ccnt;            // [nq][SS]
+    const cand_t *cbuf;             // [nq][SS][Cs] (~ image of the score's upper bound without the query's part, row)
+    const float *qn;                // [nq] squared norms
+    const int32_t *hard, *again;    // which scan a query's candidates are from
+    const int32_t *qx;              // ... and by which power of two the first has scaled their scores
+    float c, ch;                    // ... and the constants of their bounds
+    int32_t *over;                  // [nq] set to 1 where the direct kernel has to search, else to 0
+    int32_t *ids;
+    float *dists;
+};
+template <bool VEC, bool L2>
+__global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    float *qs = reinterpret_cast<float *>(smem);              // the query, zero beyond d
-    __shared__ int s_end[DIST_REGIONS];                       // candidates of regions 0 .. r together
-    const int64_t q = blockIdx.x / share;
-    const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3, chunks = (d + 3) >> 2;
-    for (int i = tid; i < 4 * chunks; i += F32_THREADS) qs[i] = i < d ? qv[q * ldq + i] : 0.0f;
-    int mine = 0;
-    if (tid < SS) {
-        const int have = ccnt[q * SS + tid];
-        mine = have > Cs ? 0 : have;                          // overflowed: searched again anyway
+    cand_t *buf = reinterpret_cast<cand_t *>(smem);           // [FIN_CAP]
+    float *qs = reinterpret_cast<float *>(buf + FIN_CAP);     // the query, zero beyond d
+    __shared__ int s_end[FIN_REGIONS];                        // candidates of regions 0 .. r together
+    __shared__ int s_more, s_hist[FIN_BINS], s_wave[F32_THREADS / 64], s_cut;
+    __shared__ float s_lo[F32_THREADS / 64], s_hi[F32_THREADS / 64];
+    __shared__ cand_t s_kth;
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3, chunks = (o.d + 3) >> 2, k = o.k;
+    for (int i = tid; i < 4 * chunks; i += F32_THREADS) qs[i] = i < o.d ? o.q[q * o.ldq + i] : 0.0f;
+    int mine = 0, lost = 0;
+    if (tid < o.SS) {
+        mine = o.ccnt[q * o.SS + tid];
+        lost = mine > o.Cs;
     }
-    s_end[tid] = mine;
-    __syncthreads();
-    for (int o = 1; o < F32_THREADS; o <<= 1) {
-        const int v = tid >= o ? s_end[tid - o] : 0;
-        __syncthreads();
-        s_end[tid] += v;
-        __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6;
+    auto scan = [&](int v) {                                  // inclusive sums over the lanes of a wave
+#pragma unroll
+        for (int w = 1; w < 64; w <<= 1) {
+            const int up = __shfl_up(v, w, 64);
+            if (lane >= w) v += up;
+        }
+        return v;
+    };
+    const int upto = scan(mine);
+    if (lane == 63) s_wave[wave] = upto;
+    if (tid == 0) s_more = 0;
+    s_hist[tid] = 0;
+    lost = __syncthreads_or(lost);
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < F32_THREADS / 64; ++w) {
+        before += w < wave ? s_wave[w] : 0;
+        total += s_wave[w];
     }
-    const int total = s_end[F32_THREADS - 1];
-    for (int i = (int)(blockIdx.x % share) * F32_ROWS + grp; i < total; i += share * F32_ROWS) {
-        int lo = 0, hi = SS - 1;                              // first region that ends beyond i
+    s_end[tid] = before + upto;
+    if (lost || total < k) {                                  // the same in every thread
+        if (tid == 0) o.over[q] = 1;
+        return;
+    }
+    const cand_t *regions = o.cbuf + (size_t)q * o.SS * o.Cs;
+    auto candidate = [&](int i) {
+        int lo = 0, hi = o.SS - 1;                            // first region that ends beyond i
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (s_end[mid] > i) hi = mid; else lo = mid + 1;
         }
-        cand_t *at = cbuf + ((size_t)q * SS + lo) * Cs + (i - (lo ? s_end[lo - 1] : 0));
-        const uint32_t row = cand_id(*at);
-        const float *xr = x + (int64_t)row * ldx;
-        float acc = 0.0f;
+        return regions[(size_t)lo * o.Cs + (i - (lo ? s_end[lo - 1] : 0))];
+    };
+    auto pow2 = [](int v) { return v <= 32 ? 32 : 1 << (32 - __clz(v - 1)); };
+    auto sort = [&](int count) {                              // of buf[0 .. count), and fills up to a power of two behind it
+        const int size = pow2(count);
+        for (int i = count + tid; i < size; i += F32_THREADS) buf[i] = CAND_NONE;
+        __syncthreads();
+        block_bitonic_sort(buf, size);
+    };
+    auto sum_directly = [&](cand_t *buf, int from, int to) {  // key halves of buf[from .. to) become the distances' images
+        for (int i = from + grp; i < to; i += F32_ROWS) {
+            const cand_t at = buf[i];
+            if (at == CAND_NONE) continue;
+            const uint32_t row = cand_id(at);
+            const float *xr = o.x + (int64_t)row * o.ldx;
+            float acc = 0.0f;
 #pragma unroll 4
-        for (int c = sub; c < chunks; c += 8) {
-            float xa[4];
-            if (VEC && 4 * c + 3 < d) {
-                const float4 t = *reinterpret_cast<const float4 *>(xr + 4 * c);
-                xa[0] = t.x; xa[1] = t.y; xa[2] = t.z; xa[3] = t.w;
-            } else {
+            for (int c = sub; c < chunks; c += 8) {
+                float xa[4];
+                if (VEC && 4 * c + 3 < o.d) {
+                    const float4 t = *reinterpret_cast<const float4 *>(xr + 4 * c);
+                    xa[0] = t.x; xa[1] = t.y; xa[2] = t.z; xa[3] = t.w;
+                } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) xa[e] = 4 * c + e < d ? xr[4 * c + e] : 0.0f;
+                    for (int e = 0; e < 4; ++e) xa[e] = 4 * c + e < o.d ? xr[4 * c + e] : 0.0f;
+                }
+                const float4 qq = *reinterpret_cast<const float4 *>(qs + 4 * c);
+                const float qa[4] = {qq.x, qq.y, qq.z, qq.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (L2) { const float t = qa[e] - xa[e]; acc = fmaf(t, t, acc); }
+                    else acc = fmaf(qa[e], xa[e], acc);
+                }
             }
-            const float4 qq = *reinterpret_cast<const float4 *>(qs + 4 * c);
-            const float qa[4] = {qq.x, qq.y, qq.z, qq.w};
+            acc += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(acc)));
+            acc += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(acc)));
+            acc += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(acc)));
+            if (sub == 0) buf[i] = make_cand(float_to_sortable(L2 ? acc : -acc), row);
+        }
+        __syncthreads();
+    };
+
+    // A row among the k nearest has a directly summed score of at least that of the k-th of some rows; its upper bound
+    // is less than (C |q|^2) / 2 below that, C the constant of its scan.  The norm and the conversion of a distance
+    // into a score are off by less than the split's constant allows.
+    const bool half = !o.hard[q >> 7] && !o.again[q];
+    const float qn = o.qn[q], c = half ? o.ch : o.c;
+    auto limit_of = [&](cand_t kth_row) {
+        const float kth = sortable_to_float(cand_key(kth_row));
+        const float at = L2 ? 0.5f * (qn - kth) - 0.5f * (c + o.c) * qn * 1.00001f - 0.5f * o.c * kth - 0x1p-110f
+                            : -kth - 0.5f * c * qn * 1.00001f - 0x1p-20f * fabsf(kth) - 0x1p-110f;
+        return make_cand(~float_to_sortable(half ? ldexpf(at, o.qx[q]) - f32_half_filter_small(o.d) : at), 0xFFFFFFFFu);
+    };
+    auto emit = [&](cand_t best, int i) {
+        const float v = sortable_to_float(cand_key(best));
+        o.ids[q * k + i] = (int32_t)cand_id(best);
+        o.dists[q * k + i] = L2 ? v : -v;
+    };
+
+    if (total <= FIN_FEW) {
+        cand_t *few = buf + FIN_FEW;                          // the rows that are summed
+        auto bound = [](cand_t cand) { return sortable_to_float(~cand_key(cand)); };
+        float lo = INFINITY, hi = -INFINITY;
+        for (int i = 0; i < mine; ++i) {
+            const cand_t cand = regions[(size_t)tid * o.Cs + i];
+            buf[before + upto - mine + i] = cand;
+            lo = fminf(lo, bound(cand));
+            hi = fmaxf(hi, bound(cand));
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (l2) { const float t = qa[e] - xa[e]; acc = fmaf(t, t, acc); }
-                else acc = fmaf(qa[e], xa[e], acc);
+        for (int w = 32; w > 0; w >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, w, 64));
+            hi = fmaxf(hi, __shfl_xor(hi, w, 64));
+        }
+        if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < F32_THREADS / 64; ++w) {
+            lo = fminf(lo, s_lo[w]);
+            hi = fmaxf(hi, s_hi[w]);
+        }
+        const float scale = (FIN_BINS - 1) / fmaxf(hi - lo, 0x1p-100f);
+        auto bin = [&](cand_t cand) {                         // from the highest down
+            const float at = (hi - bound(cand)) * scale;
+            return at < (float)(FIN_BINS - 1) ? (int)at : FIN_BINS - 1;
+        };
+        for (int i = tid; i < total; i += F32_THREADS) atomicAdd(&s_hist[bin(buf[i])], 1);
+        __syncthreads();
+        if (wave == 0) {                                      // the bin up to which k and a few are
+            const int want = k + k / 4 + 6 < total ? k + k / 4 + 6 : total;
+            int v[4], sum = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = s_hist[4 * lane + j]; sum += v[j]; }
+            const int incl = scan(sum);
+            if (lane == __ffsll((unsigned long long)__ballot(incl >= want)) - 1) {
+                int at = incl - sum, j = 0;
+                while (j < 3 && at + v[j] < want) at += v[j++];
+                s_cut = 4 * lane + j;
             }
         }
-        acc += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(acc)));
-        acc += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(acc)));
-        acc += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(acc)));
-        if (sub == 0) *at = make_cand(float_to_sortable(l2 ? acc : -acc), row);
+        __syncthreads();
+        const int cut = s_cut;
+        for (int i = tid; i < total; i += F32_THREADS)
+            if (bin(buf[i]) <= cut) few[atomicAdd(&s_more, 1)] = buf[i];
+        __syncthreads();
+        const int first = s_more;
+        sum_directly(few, 0, first);
+        // threads' first two: the rank of a distance among all
+        auto rank = [&](int i, int count) {
+            const cand_t me = few[i];
+            int r = 0;
+            for (int j = 0; j < count; ++j) r += few[j] < me;
+            return r;
+        };
+        if (first <= FIN_RANKED) {
+            for (int i = tid; i < first; i += F32_THREADS)
+                if (rank(i, first) == k - 1) s_kth = few[i];
+            __syncthreads();
+        } else {
+            for (int i = first + tid; i < pow2(first); i += F32_THREADS) few[i] = CAND_NONE;
+            __syncthreads();
+            block_bitonic_sort(few, pow2(first));
+            if (tid == 0) s_kth = few[k - 1];
+            __syncthreads();
+        }
+        const cand_t limit = limit_of(s_kth);
+        for (int i = tid; i < total; i += F32_THREADS) {
+            const cand_t cand = buf[i];
+            if (bin(cand) > cut && cand <= limit) few[atomicAdd(&s_more, 1)] = cand;
+        }
+        __syncthreads();
+        const int all = s_more;
+        sum_directly(few, first, all);
+        if (all <= FIN_RANKED) {
+            for (int i = tid; i < all; i += F32_THREADS) {
+                const int r = rank(i, all);
+                if (r < k) emit(few[i], r);
+            }
+        } else {
+            for (int i = all + tid; i < pow2(all); i += F32_THREADS) few[i] = CAND_NONE;
+            __syncthreads();
+            block_bitonic_sort(few, pow2(all));
+            for (int i = tid; i < k; i += F32_THREADS) emit(few[i], i);
+        }
+        if (tid == 0) o.over[q] = 0;
+        return;
     }
+    __syncthreads();                                          // the ends of the regions are there
+
+    // the candidates (at least the FIN_CAP / 2 best) by their upper bounds, the highest first
+    int kept = 0;
+    for (int pos = 0; pos < total;) {
+        const int take = total - pos < FIN_CAP - kept ? total - pos : FIN_CAP - kept;
+        for (int i = tid; i < take; i += F32_THREADS) buf[kept + i] = candidate(pos + i);
+        sort(kept + take);
+        pos += take;
+        kept = pos < total || total > FIN_CAP ? FIN_CAP / 2 : kept + take;
+    }
+    const int first = pow2(k);                                // at most FIN_CAP / 2; beyond the candidates: CAND_NONE
+    const cand_t last = buf[first - 1];
+    __syncthreads();
+    sum_directly(buf, 0, first);
+    block_bitonic_sort(buf, first);
+    const cand_t limit = limit_of(buf[k - 1]);
+    if (total <= FIN_CAP) {                                   // sorted: those behind the first
+        for (int i = first + tid; i < total; i += F32_THREADS)
+            if (buf[i] <= limit && (i + 1 == total || buf[i + 1] > limit)) s_more = i + 1 - first;
+        __syncthreads();
+    } else {
+        __syncthreads();                                      // (kth has been read by all)
+        for (int i = tid; i < total; i += F32_THREADS) {
+            const cand_t cand = candidate(i);
+            if (cand > last && cand <= limit) {
+                const int at_ = first + atomicAdd(&s_more, 1);
+                if (at_ < FIN_CAP) buf[at_] = cand;
+            }
+        }
+        __syncthreads();
+    }
+    const int all = first + s_more;
+    if (all > FIN_CAP) {
+        if (tid == 0) o.over[q] = 1;
+        return;
+    }
+    if (all > first) {
+        sum_directly(buf, first, all);
+        sort(all);
+    }
+    for (int i = tid; i < k; i += F32_THREADS) emit(buf[i], i);
+    if (tid == 0) o.over[q] = 0;
+}
+
+hipError_t launch_finish(bool vec, bool l2, int64_t nq, const FinishIo &o, hipStream_t st)
+{
+    auto kern = vec ? (l2 ? f32_finish_kernel<true, true> : f32_finish_kernel<true, false>)
+                    : (l2 ? f32_finish_kernel<false, true> : f32_finish_kernel<false, false>);
+    static bool attr_set[4] = {false, false, false, false};
+    const int which = 2 * vec + l2;
+    if (!attr_set[which]) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set[which] = true;
+    }
+    const size_t lds = FIN_CAP * sizeof(cand_t) + (size_t)((o.d + 3) / 4) * 16;
+    if (o.SS > FIN_REGIONS || 2 * next_pow2(o.k) > FIN_CAP || lds > 128 * 1024) return hipErrorInvalidValue;
+    kern<<<(unsigned)nq, F32_THREADS, lds, st>>>(o);
+    return hipGetLastError();
 }
 
 int f32_cap(int k) { return next_pow2((2 * k > k + 2 * F32_STEP) ? 2 * k : k + 2 * F32_STEP); }
@@ -349,21 +569,20 @@ static hipError_t launch_f32_batch(const float *x, int64_t n, int64_t ldx, const
     const int32_t *only = nullptr;
     if (fp.use) {
         char *fws = (char *)ws + f32_lists_bytes(n, nq, d, k);
-        cand_t *cbuf = reinterpret_cast<cand_t *>(fws + fp.off_cbuf);
-        int32_t *ccnt = reinterpret_cast<int32_t *>(fws + fp.off_ccnt), *over = reinterpret_cast<int32_t *>(fws + fp.off_over);
-        int32_t *list = reinterpret_cast<int32_t *>(fws + fp.off_list);
         e = launch_f32_filter(fp, x, n, ldx, q, nq, ldq, d, k, mode == MODE_F32_L2, fws, st);
         if (e != hipSuccess) return e;
-        static_assert(DIST_REGIONS == F32_THREADS, "a thread per region");
-        if (fp.S2 > DIST_REGIONS) return hipErrorInvalidValue;
-        const int share = nq >= 2048 ? 1 : (int)(2048 / nq < 16 ? 2048 / nq : 16);   // workgroups per query: fill the chip
-        (vec ? f32_distances_kernel<true> : f32_distances_kernel<false>)<<<(unsigned)(nq * share), F32_THREADS,
-                                                                         (size_t)((d + 3) / 4) * 16, st>>>(
-            x, ldx, q, ldq, d, mode == MODE_F32_L2, fp.S2, fp.Cs, share, ccnt, cbuf);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        e = launch_collect_select(cbuf, ccnt, nq, fp.S2, fp.Cs, k, over, list, list + nq, ids, reinterpret_cast<int32_t *>(dists),
-                                  nullptr, mode, st);
+        FinishIo o = {};
+        o.x = x; o.q = q; o.ldx = ldx; o.ldq = ldq; o.d = d; o.k = k; o.SS = fp.S2; o.Cs = fp.Cs;
+        o.ccnt = reinterpret_cast<const int32_t *>(fws + fp.off_ccnt);
+        o.cbuf = reinterpret_cast<const cand_t *>(fws + fp.off_cbuf);
+        o.qn = reinterpret_cast<const float *>(fws + fp.off_qn);
+        o.hard = reinterpret_cast<const int32_t *>(fws + fp.off_hard);
+        o.again = reinterpret_cast<const int32_t *>(fws + fp.off_again);
+        o.qx = reinterpret_cast<const int32_t *>(fws + fp.off_qx);
+        o.c = f32_filter_constant(d); o.ch = f32_half_filter_constant(d);
+        int32_t *over = reinterpret_cast<int32_t *>(fws + fp.off_over);
+        o.over = over; o.ids = ids; o.dists = dists;
+        e = launch_finish(vec, mode == MODE_F32_L2, nq, o, st);
         if (e != hipSuccess) return e;
         only = over;
     }

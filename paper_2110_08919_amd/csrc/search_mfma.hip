@@ -1177,7 +1177,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
 // seed threshold.  Each lane keeps E of the values in registers.  Small k: k times the wave takes
 // the largest value left and the first lane holding it drops one copy.  Larger k: bisection on
 // the value with wave-wide counts.
-template <int E>
+template <int E, bool HARD>
 __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k,
                                                             cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word,
                                                             int32_t *__restrict__ kth_out, int32_t *__restrict__ zero_word2,
@@ -1240,7 +1240,7 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
     // at least k items have E >= kth, hence key <= -2 kth
     if (lane == 0 && seeds) seeds[q] = (G < k || kth == INT32_MIN) ? CAND_NONE : make_cand(-2 * kth, 0xFFFFFFFFu);
     if (lane == 0 && kth_out) kth_out[q] = G < k ? INT32_MIN : kth;
-    if (hq.flags) {
+    if (HARD) {
         const float at = sortable_to_float(kth) - hq.c * hq.qn[q] - hq.cx * *hq.nxsum;
         const int line = at > -INFINITY ? float_to_sortable(at) : INT32_MIN;   // (also where at is not a number)
         int within = k <= 24 ? k : 0;                      // (the k largest were taken out above)
@@ -1538,16 +1538,13 @@ hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, c
     if (nq <= 0) return hipSuccess;
     if (G > 4096) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)ceil_div(nq, (int64_t)4);
-    if (G <= 256) seed_finalize_kernel<4><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride, hq);
-    else if (G <= 512) seed_finalize_kernel<8><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride, hq);
-    else if (G <= 1024) seed_finalize_kernel<16><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride, hq);
-    else if (G <= 2048) seed_finalize_kernel<32><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride, hq);
-    else seed_finalize_kernel<64><<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out,
-                                                                    zero_word2, zero_more, zero_stride, hq);
+    auto launch = [&](auto kern) { kern<<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out, zero_word2, zero_more, zero_stride, hq); };
+    const bool hard = hq.flags != nullptr;
+    if (G <= 256) launch(hard ? seed_finalize_kernel<4, true> : seed_finalize_kernel<4, false>);
+    else if (G <= 512) launch(hard ? seed_finalize_kernel<8, true> : seed_finalize_kernel<8, false>);
+    else if (G <= 1024) launch(hard ? seed_finalize_kernel<16, true> : seed_finalize_kernel<16, false>);
+    else if (G <= 2048) launch(hard ? seed_finalize_kernel<32, true> : seed_finalize_kernel<32, false>);
+    else launch(hard ? seed_finalize_kernel<64, true> : seed_finalize_kernel<64, false>);
     return hipGetLastError();
 }
 

@@ -2,7 +2,8 @@
 //
 // The exact search sums (q - x)^2 (or q x) directly in fp32, one multiply-add per value on the vector
 // units.  Almost all of that work rejects items that are nowhere near: this file does the rejecting on
-// the matrix cores and leaves the direct sums to the few items that may be among the k nearest.  The
+// the matrix cores and leaves the direct sums to the few items that may be among the k nearest (f32_finish_kernel
+// narrows them down once more).  The
 // results are the ones of the direct kernel bit for bit, because the final distances are formed by the
 // same operations in the same order (search_f32.hip) and the filter never loses an item that belongs:
 //
@@ -35,17 +36,17 @@
 //   range       a query is scaled by a power of two to a norm of 1 to 2, the rows of a tile by the mean of its queries'
 //               scales (not at all where that lies near one), so that fp16 holds both; what is too small for its
 //               normal range is off by 2^-25, sqrt(d) 2^-25 (|q| + |x|) in all: the first part is in the threshold
-//               (sqrt(d) 2^-22), the second in C's slack.  Rows beyond 2^15 after scaling, and queries 2^24 away from
+//               (sqrt(d) 2^-22: f32_half_filter_small), the second in C's slack.  Rows beyond 2^15 after scaling, and queries 2^24 away from
 //               the others, go to the second scan.
 //
 // On ordinary data the wider bound lets through a tenth more (1M x 128, k = 10: 281 items instead of 261 a query).
 // The second scan, with C and the split, takes query tiles where the seeding pass has more than twice k groups within
 // the first one's error (hard), and queries that overflowed in the first.  1M x 128 shifted by 30 or 100 (inner
-// product, all hard) 0.90 / 1.00 -> 0.88 / 0.97 ms.
+// product, all hard) 0.90 / 1.00 -> 0.86 / 0.92 ms.
 //
-// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 0.91 -> 0.46 ms (with the split alone; 8.3 with the direct
-// kernel alone), 64 queries 0.156 -> 0.147, 256 0.30 -> 0.19; 1M x 96, 1000 0.75 -> 0.46; 300 000 x 771, 1000
-// 2.53 -> 1.01; 200 000 x 128, 10 000 2.03 -> 1.06; 2M x 24, 2000 1.81 -> 1.05.
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 0.91 -> 0.44 ms (with the split alone; 8.3 with the direct
+// kernel alone), 64 queries 0.156 -> 0.139, 256 0.29 -> 0.18; 1M x 96, 1000 0.75 -> 0.42; 300 000 x 771, 1000
+// 2.53 -> 0.89; 200 000 x 128, 10 000 2.03 -> 1.04; 2M x 24, 2000 1.81 -> 1.00.
 //
 // Layout: workgroups of eight waves on tiles of 256 items x 64 WQ queries, as in search_mfma_stream.hip;
 // a stage is 32 features.  Items come from HBM in fp32 through registers (two stages ahead), are rounded or split
@@ -104,10 +105,11 @@ struct FilterIo {
     const _Float16 *qf;       // first scan: [nq_pad][dp] the queries in fp16, each scaled to a norm of 1 to 2
     const int32_t *qe;        // ... by two to this power
     float ch;                 // ... and the constant of its error
+    int32_t *qx;              // [nq_pad] ... which leaves here what its scores are scaled by, two to this power
     const int32_t *hard;      // scans: [nq_pad / 128] set where only the second scan can resolve the queries
     int32_t *again;           // [nq_pad] AGAIN: the first scan could not; DIRECT: neither can the second
     const int32_t *kth;       // scan: [nq] k-th largest group maximum
-    cand_t *cbuf;             // [nq][S][Cs] rows that may belong (the key half is filled in later)
+    cand_t *cbuf;             // [nq][S][Cs] rows that may belong: (~ image of acc - h |x|^2, row)
     int32_t *ccnt;            // [nq][S]
     int Cs;
 };
@@ -234,8 +236,9 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                         mine = false;
                         atomicOr(&o.again[q], AGAIN);
                     } else {
-                        t = ldexpf(bound - 0.5f * (o.c + o.ch) * o.qn[q] * 1.00001f - 0x1p-110f, xe + e) - sqrtf((float)o.d) * 0x1p-22f;
+                        t = ldexpf(bound - 0.5f * (o.c + o.ch) * o.qn[q] * 1.00001f - 0x1p-110f, xe + e) - f32_half_filter_small(o.d);
                         h_l[i] = ldexpf(o.h, e - xe);
+                        if (s == 0) o.qx[q] = xe + e;
                     }
                 } else {
                     t = bound - o.c * o.qn[q] * 1.00001f - 0x1p-110f;
@@ -444,7 +447,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 if (u >= thr_l[ql] && row < o.n) {
                     const int pos = atomicAdd(&fill[ql], 1);
                     if (__builtin_expect(pos < o.Cs, 1)) {
-                        cbase[(size_t)ql * qstride + pos] = (cand_t)row;
+                        cbase[(size_t)ql * qstride + pos] = make_cand(~float_to_sortable(u), (uint32_t)row);
                     } else if (__builtin_expect(pos == o.Cs, 0)) {   // the direct kernel takes this query: collect no more for it
                         thr_l[ql] = NAN;
                         atomicAdd(&ctl[CTL_DONE], 1);
@@ -717,6 +720,7 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     p.off_qf = o;   o = align256(o + (size_t)p.nq_pad * p.dp * 2);
     p.off_qn = o;   o = align256(o + (size_t)p.nq_pad * 4);
     p.off_qe = o;   o = align256(o + (size_t)p.nq_pad * 4);
+    p.off_qx = o;   o = align256(o + (size_t)p.nq_pad * 4);
     p.off_hard = o; o = align256(o + (size_t)p.nq_pad / 128 * 4 + 4);
     p.off_again = o; o = align256(o + (size_t)p.nq_pad * 4);
     p.off_gmax = o; o = align256(o + (size_t)p.nq_pad * p.G * 4);
@@ -724,7 +728,6 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     p.off_cbuf = o; o = align256(o + (size_t)nq * p.S2 * p.Cs * sizeof(cand_t));
     p.off_ccnt = o; o = align256(o + (size_t)nq * p.S2 * 4);
     p.off_over = o; o = align256(o + (size_t)nq * 4);
-    p.off_list = o; o = align256(o + ((size_t)nq + 1) * 4);
     p.total = o;
     p.use = true;
     return p;
@@ -736,7 +739,6 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     __bf16 *qh = reinterpret_cast<__bf16 *>(ws + p.off_qh), *ql = reinterpret_cast<__bf16 *>(ws + p.off_ql);
     float *qn = reinterpret_cast<float *>(ws + p.off_qn);
     int32_t *gmax = reinterpret_cast<int32_t *>(ws + p.off_gmax), *kth = reinterpret_cast<int32_t *>(ws + p.off_kth);
-    int32_t *count = reinterpret_cast<int32_t *>(ws + p.off_list) + nq;
     _Float16 *qf = reinterpret_cast<_Float16 *>(ws + p.off_qf);
     int32_t *qe = reinterpret_cast<int32_t *>(ws + p.off_qe), *hard = reinterpret_cast<int32_t *>(ws + p.off_hard);
     float *nxsum = reinterpret_cast<float *>(hard + p.nq_pad / 128);
@@ -751,7 +753,7 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     o.qh = qh; o.ql = ql; o.qn = qn; o.nq = nq; o.qtiles = p.qtiles;
     o.c = f32_filter_constant(d);
     o.ch = f32_half_filter_constant(d);
-    o.qf = qf; o.qe = qe; o.hard = hard; o.again = again; o.nxsum = nxsum;
+    o.qf = qf; o.qe = qe; o.qx = reinterpret_cast<int32_t *>(ws + p.off_qx); o.hard = hard; o.again = again; o.nxsum = nxsum;
     // seeding pass: lower bounds of the scores of a sample (runs of 16 rows spread over the corpus)
     o.S = p.S1; o.SEG = p.SEG; o.gmax = gmax;
     o.tiles = p.seed_tiles; o.tile_stride = p.run_stride; o.run_gap = (int64_t)p.seed_tiles * p.run_stride;
@@ -763,7 +765,7 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     // query is left to the second scan (regions hold three times what the sample lets expect, so it would overflow).
     const float c2 = 0.5f * (o.c + o.ch) * 1.00001f;
     const HardQueries hq = {qn, nxsum, c2, c2 / (8.0f * TILE_ROWS * (float)p.seed_tiles * (float)p.qtiles), p.half ? 2 * k + 8 : 0, hard};
-    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, count, kth, nullptr, 0, 0, hq);
+    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, nullptr, kth, nullptr, 0, 0, hq);
     if (e != hipSuccess) return e;
     // scans: every item whose upper bound reaches the k-th lower bound
     o.S = p.S2; o.kth = kth;
