@@ -481,6 +481,143 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
     }
 }
 
+// The same for k beyond 16, one workgroup per query, SS <= 256: nothing is sorted while the regions hold no more than
+// RANK_FEW candidates.  A histogram of the keys between the best and the worst gives the few (k and the rest of a bin)
+// that can belong, and the rank of each is the number of better ones, counted by the thread that holds it.  More
+// candidates are sorted RANK_FEW at a time, the k best kept.  (A wave per query sorting 512 candidates in registers, k =
+// 100: 1000 queries 20 us, 10 000 on 1M x 128 73, on 4M x 256 107; here FIGURES.  At k = 10, 90 candidates, it is the
+// faster one: 10 000 queries 21 us.)
+constexpr int RANK_FROM_K = 16, RANK_FEW = 2048, RANK_COUNTED = 512, RANK_BINS = 256;
+__global__ __launch_bounds__(256) void collect_select_rank_kernel(
+    const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int SS, int Cs, int k,
+    int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
+    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric,
+    const cand_t *__restrict__ bounds_in, cand_t *__restrict__ bounds_out)
+{
+    __shared__ cand_t buf[RANK_FEW], few[RANK_COUNTED];
+    __shared__ int s_end[256], s_hist[RANK_BINS], s_wave[4], s_cut, s_more;
+    __shared__ uint32_t s_lo[4], s_hi[4];
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto scan = [&](int v) {                                   // inclusive sums over the lanes of a wave
+#pragma unroll
+        for (int w = 1; w < 64; w <<= 1) {
+            const int up = __shfl_up(v, w, 64);
+            if (lane >= w) v += up;
+        }
+        return v;
+    };
+    const int mine = tid < SS ? ccnt[q * SS + tid] : 0;
+    const int bad = mine > Cs || mine < 0;
+    const int upto = scan(bad ? 0 : mine);
+    if (lane == 63) s_wave[wave] = upto;
+    s_hist[tid] = 0;
+    if (tid == 0) s_more = 0;
+    const int lost = __syncthreads_or(bad);
+    int end = upto, total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        end += w < wave ? s_wave[w] : 0;
+        total += s_wave[w];
+    }
+    const bool flagged = lost || total < k;                    // the same in every thread
+    if (tid == 0) {
+        over[q] = flagged;
+        if (flagged) qlist[atomicAdd(qcount, 1)] = (int32_t)q;
+    }
+    if (bounds_out) {
+        const cand_t bound = flagged ? refined_bound(cbuf, ccnt, q, SS, Cs, k, RANK_FEW, buf, bounds_in[q]) : 0;
+        if (tid == 0) bounds_out[q] = bound;
+    }
+    if (flagged) return;
+    const cand_t *regions = cbuf + (size_t)q * SS * Cs;
+    if (total > RANK_FEW) {
+        s_end[tid] = end;
+        __syncthreads();
+        int kept = 0;
+        for (int pos = 0; pos < total;) {
+            const int take = total - pos < RANK_FEW - kept ? total - pos : RANK_FEW - kept;
+            for (int i = tid; i < RANK_FEW - kept; i += 256) {
+                cand_t c = CAND_NONE;
+                if (i < take) {
+                    int lo = 0, hi = SS - 1;                   // first region that ends beyond it
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (s_end[mid] > pos + i) hi = mid; else lo = mid + 1;
+                    }
+                    c = regions[(size_t)lo * Cs + (pos + i - (lo ? s_end[lo - 1] : 0))];
+                }
+                buf[kept + i] = c;
+            }
+            __syncthreads();
+            block_bitonic_sort(buf, RANK_FEW);
+            pos += take;
+            kept = k;
+        }
+        for (int i = tid; i < k; i += 256) emit_result(buf[i], q * k + i, q, ids, dists, qnorms, metric);
+        return;
+    }
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    for (int i = 0; i < mine; ++i) {
+        const cand_t c = regions[(size_t)tid * Cs + i];
+        buf[end - mine + i] = c;
+        const uint32_t key = (uint32_t)(c >> 32);
+        lo = key < lo ? key : lo;
+        hi = key > hi ? key : hi;
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const uint32_t l = __shfl_xor(lo, w, 64), h = __shfl_xor(hi, w, 64);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+    }
+    if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        lo = s_lo[w] < lo ? s_lo[w] : lo;
+        hi = s_hi[w] > hi ? s_hi[w] : hi;
+    }
+    const int wide = 32 - __clz((int)(hi - lo)), shift = wide > 8 ? wide - 8 : 0;
+    auto bin = [&](cand_t c) { return (int)(((uint32_t)(c >> 32) - lo) >> shift); };
+    for (int i = tid; i < total; i += 256) atomicAdd(&s_hist[bin(buf[i])], 1);
+    __syncthreads();
+    if (wave == 0) {                                           // the bin that holds the k-th
+        int v[4], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[j] = s_hist[4 * lane + j]; sum += v[j]; }
+        const int incl = scan(sum);
+        if (lane == __ffsll((unsigned long long)__ballot(incl >= k)) - 1) {
+            int at = incl - sum, j = 0;
+            while (j < 3 && at + v[j] < k) at += v[j++];
+            s_cut = 4 * lane + j;
+        }
+    }
+    __syncthreads();
+    const int cut = s_cut;
+    for (int i = tid; i < total; i += 256)
+        if (bin(buf[i]) <= cut) {
+            const int at = atomicAdd(&s_more, 1);
+            if (at < RANK_COUNTED) few[at] = buf[i];
+        }
+    __syncthreads();
+    const int count = s_more;
+    if (count <= RANK_COUNTED) {
+        for (int i = tid; i < count; i += 256) {
+            const cand_t me = few[i];
+            int r = 0;
+            for (int j = 0; j < count; ++j) r += few[j] < me;
+            if (r < k) emit_result(me, q * k + r, q, ids, dists, qnorms, metric);
+        }
+        return;
+    }
+    const int cap = next_pow2(total);                          // many in the last bin: sort
+    for (int i = total + tid; i < cap; i += 256) buf[i] = CAND_NONE;
+    __syncthreads();
+    block_bitonic_sort(buf, cap);
+    for (int i = tid; i < k; i += 256) emit_result(buf[i], q * k + i, q, ids, dists, qnorms, metric);
+}
+
 // Last step of the collecting scan, one workgroup per query: gather the query's regions into LDS,
 // sort, write the k best.  A query with an overflowed region, more than `maxc` candidates or fewer
 // than k is flagged in over[] instead and left to the generic kernel.
@@ -731,7 +868,13 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
     // (Beyond 64 regions only for batches that fill the chip that way: one wave takes 5 us for every 384 candidates, which is
     // long where thousands tie at the bound: 1694 queries in tiles of 64 on 6216 x 20 at 3 bits, k = 21, 5.2 against 3.7 ms;
     // without ties, 300 on 6000 x 60, k = 30 0.168 against 0.181.)
-    if (!only && k <= 128 && SS <= (nq > 64 ? 256 : 64)) {   // one wave per query, sorted in registers
+    if (!only && k <= 128 && SS <= (nq > 64 ? 256 : 64)) {
+        if (k > RANK_FROM_K) {
+            collect_select_rank_kernel<<<(unsigned)nq, 256, 0, st>>>(cbuf, ccnt, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
+                                                                     metric, bounds_in, bounds_out);
+            return hipGetLastError();
+        }
+        // one wave per query, sorted in registers
         auto kern = SS <= 64 ? collect_select_sort_kernel<1> : collect_select_sort_kernel<4>;
         kern<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
                                                                 metric, bounds_in, bounds_out);
