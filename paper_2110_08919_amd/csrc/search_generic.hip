@@ -481,13 +481,16 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
     }
 }
 
-// The same for k beyond 16, one workgroup per query, SS <= 256: nothing is sorted while the regions hold no more than
+// The same with one workgroup per query, SS <= 256: nothing is sorted while the regions hold no more than
 // RANK_FEW candidates.  A histogram of the keys between the best and the worst gives the few (k and the rest of a bin)
 // that can belong, and the rank of each is the number of better ones, counted by the thread that holds it.  More
-// candidates are sorted RANK_FEW at a time, the k best kept.  (A wave per query sorting 512 candidates in registers, k =
-// 100: 1000 queries 20 us, 10 000 on 1M x 128 73, on 4M x 256 107; here FIGURES.  At k = 10, 90 candidates, it is the
-// faster one: 10 000 queries 21 us.)
-constexpr int RANK_FROM_K = 16, RANK_FEW = 2048, RANK_COUNTED = 512, RANK_BINS = 256;
+// candidates are sorted RANK_FEW at a time, the k best kept.  Against a wave per query that sorts in registers: k = 100,
+// 450 candidates, 1000 queries 20 -> 11 us, 10 000 on 1M x 128 73 -> 47, on 4M x 256 107 -> 57; k = 10, 1000 queries on
+// 1.2M x 100 9.8 -> 6.7, on 500 000 x 768 10.7 -> 7.6, on 200 000 x 2048 (350 candidates) 19.6 -> 7.8, 100 on 10 000 x 128
+// 6.0 -> 4.3.  Large batches with few candidates stay with the wave, a quarter of a workgroup per query: 10 000 queries,
+// k = 10, 90 candidates 21 us against 29 here.
+constexpr int RANK_FROM_K = 16, RANK_TO_NQ = 4096, RANK_FROM_EXPECTED = 192;
+constexpr int RANK_FEW = 2048, RANK_COUNTED = 512, RANK_BINS = 256;
 __global__ __launch_bounds__(256) void collect_select_rank_kernel(
     const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int SS, int Cs, int k,
     int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
@@ -869,7 +872,7 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
     // long where thousands tie at the bound: 1694 queries in tiles of 64 on 6216 x 20 at 3 bits, k = 21, 5.2 against 3.7 ms;
     // without ties, 300 on 6000 x 60, k = 30 0.168 against 0.181.)
     if (!only && k <= 128 && SS <= (nq > 64 ? 256 : 64)) {
-        if (k > RANK_FROM_K) {
+        if (k > RANK_FROM_K || nq <= RANK_TO_NQ || expected_candidates > RANK_FROM_EXPECTED) {
             collect_select_rank_kernel<<<(unsigned)nq, 256, 0, st>>>(cbuf, ccnt, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
                                                                      metric, bounds_in, bounds_out);
             return hipGetLastError();
