@@ -228,8 +228,9 @@ hipError_t launch_stream_collect(const SearchArgs &a, int S, const cand_t *seeds
                                  hipStream_t st);
 // Per query: if no region overflowed and at most 4096 candidates were collected, sort them, write
 // the k best as the final result and set over[q] = 0; otherwise set over[q] = 1 and write nothing.
-// Up to k = 128 and 64 regions (256 in batches of more than 64 queries) a wave per query sorts any number of candidates the
-// regions hold, or for k <= 2 and few expected_candidates (per query, 0 = unknown) extracts them without sorting.
+// Up to k = 128 and 64 regions (256 in batches of more than 64 queries) any number of candidates the regions hold is handled:
+// a workgroup per query counts ranks, in large batches with few expected_candidates (per query, 0 = unknown) a wave per
+// query sorts, or for k <= 2 extracts them without sorting.
 // Flagged queries are also appended to qlist[atomicAdd(qcount, 1)] (qcount must be zero before).
 hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_t nq, int SS, int Cs, int k,
                                  int32_t *over, int32_t *qlist, int32_t *qcount, int32_t *ids, int32_t *dists,

@@ -369,21 +369,14 @@ __device__ cand_t refined_bound(const cand_t *cbuf, const int32_t *ccnt, int64_t
 }
 
 // One query of the kernel below by one wave: writes its result, or returns true if it has to be flagged.
-template <int R>
 __device__ bool collect_select_one(const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t q, int SS, int Cs,
                                    int k, int32_t *__restrict__ ids, int32_t *__restrict__ dists,
                                    const int32_t *__restrict__ qnorms, int metric)
 {
     const int lane = threadIdx.x & 63;
-    bool bad = false;
-    int upto[R], mine = 0;                                 // candidates of this lane's regions 0 .. j together
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int offered = (R * lane + j < SS) ? ccnt[q * SS + R * lane + j] : 0;
-        bad |= offered > Cs || offered < 0;
-        mine += offered < 0 ? 0 : (offered < Cs ? offered : Cs);   // what the region holds
-        upto[j] = mine;
-    }
+    const int count = lane < SS ? ccnt[q * SS + lane] : 0;
+    const bool bad = count > Cs || count < 0;
+    const int mine = bad ? 0 : count;
     int incl = mine;                                       // inclusive prefix sum over the lanes
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -392,23 +385,17 @@ __device__ bool collect_select_one(const cand_t *__restrict__ cbuf, const int32_
     }
     const int total = __shfl(incl, 63, 64);
     if (__ballot(bad) || total < k) return true;           // wave-uniform
-    const int excl = incl - mine;                          // index of the first candidate of this lane's regions
+    const int excl = incl - mine;                          // index of the first candidate of this lane's region
     const cand_t *base = cbuf + (size_t)q * SS * Cs;
-    // candidate number i of the query sits with the first lane whose inclusive count exceeds i, there in the
-    // first region that ends beyond it
+    // candidate number i of the query sits in the region of the first lane whose inclusive count exceeds i
     auto fetch = [&](int i) -> cand_t {
         int r = 0;
 #pragma unroll
         for (int step = 32; step >= 1; step >>= 1)
             if (__shfl(incl, r + step - 1, 64) <= i) r += step;
         r = r > 63 ? 63 : r;
-        int at = i - __shfl(excl, r, 64), region = R * r, before = 0;
-#pragma unroll
-        for (int j = 0; j + 1 < R; ++j) {
-            const int end = __shfl(upto[j], r, 64);
-            if (at >= end) { region = R * r + j + 1; before = end; }
-        }
-        return i < total ? base[(size_t)region * Cs + (at - before)] : CAND_NONE;
+        const int at = i - __shfl(excl, r, 64);
+        return i < total ? base[(size_t)r * Cs + at] : CAND_NONE;
     };
     auto put = [&](cand_t v, int e) {                      // the e-th best
         if (e < k) emit_result(v, q * k + e, q, ids, dists, qnorms, metric);
@@ -446,16 +433,14 @@ __device__ bool collect_select_one(const cand_t *__restrict__ cbuf, const int32_
     return false;
 }
 
-// Last step of the collecting scan for k <= 128 and at most 64 R regions, one WAVE per query: lane r holds the
-// counts of regions R r .. R r + R - 1; the wave loads up to 512 candidates (2, 4 or 8 per lane as needed, each
+// Last step of the collecting scan for k <= 128 and at most 64 regions, one WAVE per query: lane r holds the
+// count of region r; the wave loads up to 512 candidates (2, 4 or 8 per lane as needed, each
 // found by a search over the prefix counts), sorts them in registers and keeps the best 128 in its first 16 lanes;
 // further candidates come in 384 at a time through the other 48 lanes.  Any number of candidates the regions hold
 // is handled; a query with an overflowed region or fewer than k candidates is flagged in over[] instead, and gets a
 // tighter bound for the next round where bounds_out is given (zero for the others): by all four waves, as its
-// regions hold thousands of candidates (one wave sorting them 384 at a time took 0.24 ms for 16 384).  (R = 4:
-// 1000 queries with 256 regions take 9 us against 13 with a workgroup per query.)
+// regions hold thousands of candidates (one wave sorting them 384 at a time took 0.24 ms for 16 384).
 constexpr int SORT_BOUND_BUF = 2048;   // of refined_bound: 16 KB, which leaves ten workgroups to a CU
-template <int R>
 __global__ __launch_bounds__(256) void collect_select_sort_kernel(
     const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int64_t nq, int SS, int Cs, int k,
     int32_t *__restrict__ over, int32_t *__restrict__ qlist, int32_t *__restrict__ qcount,
@@ -466,7 +451,7 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
     __shared__ int s_flagged[4];
     const int64_t first = (int64_t)blockIdx.x * 4;
     const bool flagged = first + (threadIdx.x >> 6) < nq &&
-                         collect_select_one<R>(cbuf, ccnt, first + (threadIdx.x >> 6), SS, Cs, k, ids, dists, qnorms, metric);
+                         collect_select_one(cbuf, ccnt, first + (threadIdx.x >> 6), SS, Cs, k, ids, dists, qnorms, metric);
     if ((threadIdx.x & 63) == 0) s_flagged[threadIdx.x >> 6] = flagged;
     __syncthreads();
     for (int j = 0; j < 4 && first + j < nq; ++j) {        // the same in every thread
@@ -868,19 +853,14 @@ hipError_t launch_collect_select(const cand_t *cbuf, const int32_t *ccnt, int64_
                                                                                  qcount, ids, dists, qnorms, metric);
         return hipGetLastError();
     }
-    // (Beyond 64 regions only for batches that fill the chip that way: one wave takes 5 us for every 384 candidates, which is
-    // long where thousands tie at the bound: 1694 queries in tiles of 64 on 6216 x 20 at 3 bits, k = 21, 5.2 against 3.7 ms;
-    // without ties, 300 on 6000 x 60, k = 30 0.168 against 0.181.)
     if (!only && k <= 128 && SS <= (nq > 64 ? 256 : 64)) {
-        if (k > RANK_FROM_K || nq <= RANK_TO_NQ || expected_candidates > RANK_FROM_EXPECTED) {
+        if (k > RANK_FROM_K || nq <= RANK_TO_NQ || expected_candidates > RANK_FROM_EXPECTED || SS > 64)
             collect_select_rank_kernel<<<(unsigned)nq, 256, 0, st>>>(cbuf, ccnt, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
                                                                      metric, bounds_in, bounds_out);
-            return hipGetLastError();
-        }
-        // one wave per query, sorted in registers
-        auto kern = SS <= 64 ? collect_select_sort_kernel<1> : collect_select_sort_kernel<4>;
-        kern<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist, qcount, ids, dists, qnorms,
-                                                                metric, bounds_in, bounds_out);
+        else   // one wave per query, sorted in registers
+            collect_select_sort_kernel<<<(unsigned)ceil_div(nq, (int64_t)4), 256, 0, st>>>(cbuf, ccnt, nq, SS, Cs, k, over, qlist,
+                                                                                         qcount, ids, dists, qnorms, metric,
+                                                                                         bounds_in, bounds_out);
         return hipGetLastError();
     }
     const size_t lds = (size_t)maxc * sizeof(cand_t) + (size_t)(SS + 1) * sizeof(int);

@@ -69,7 +69,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 v4b __attribute__((ext_vector_type(4)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
