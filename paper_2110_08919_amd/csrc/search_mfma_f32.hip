@@ -684,7 +684,12 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     // item it lets through - about k n / rows per query - the bytes of a row: least at rows ~ sqrt(k n)
     // (~ sqrt(nq k n); the factors are measured, 1M x 128: one query 0.16 ms with 19 000 rows, 0.18 with 8300).
     const double per = 1.5 * std::sqrt((double)nq);
-    const double by_cost = (per < 6.0 ? 6.0 : (per < 13.0 ? per : 13.0)) * std::sqrt((double)k * (double)n);
+    // Behind the fp16 scan an item let through costs little that grows with d, a sampled row d: the most goes with
+    // sqrt(1 / d) (with 13 for all: 100 000 x 1024, 2000 queries, k = 50 0.99 ms, with 5 0.84; 300 000 x 771 0.89 and
+    // 0.85; 2M x 24, 2000 queries 0.99, with 20 0.98).
+    const double by_d = 13.0 * std::sqrt(128.0 / (double)d);
+    const double most = !p.half ? 13.0 : (by_d < 5.0 ? 5.0 : (by_d < 20.0 ? by_d : 20.0)), least = most < 6.0 ? most : 6.0;
+    const double by_cost = (per < least ? least : (per < most ? per : most)) * std::sqrt((double)k * (double)n);
     const double by_room = (double)k * (double)n / 1200.0;
     int64_t seed = (int64_t)(by_cost > by_room ? by_cost : by_room);
     if (seed > n / 4) seed = n / 4;
