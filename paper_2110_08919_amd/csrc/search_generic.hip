@@ -473,8 +473,9 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
 // 450 candidates, 1000 queries 20 -> 11 us, 10 000 on 1M x 128 73 -> 47, on 4M x 256 107 -> 57; k = 10, 1000 queries on
 // 1.2M x 100 9.8 -> 6.7, on 500 000 x 768 10.7 -> 7.6, on 200 000 x 2048 (350 candidates) 19.6 -> 7.8, 100 on 10 000 x 128
 // 6.0 -> 4.3.  Large batches with few candidates stay with the wave, a quarter of a workgroup per query: 10 000 queries,
-// k = 10, 90 candidates 21 us against 29 here.
-constexpr int RANK_FROM_K = 16, RANK_TO_NQ = 4096, RANK_FROM_EXPECTED = 192;
+// k = 10, 90 candidates 21 us against 29 here; whole searches of 400 000 x 128, k = 10: 2100 and 3000 queries the same, 4000
+// 243 against 248, 6000 346 against 352.
+constexpr int RANK_FROM_K = 16, RANK_TO_NQ = 2048, RANK_FROM_EXPECTED = 192;
 constexpr int RANK_FEW = 2048, RANK_COUNTED = 512, RANK_BINS = 256;
 __global__ __launch_bounds__(256) void collect_select_rank_kernel(
     const cand_t *__restrict__ cbuf, const int32_t *__restrict__ ccnt, int SS, int Cs, int k,
