@@ -296,6 +296,8 @@ struct F32Filter {
            off_cbuf = 0, off_ccnt = 0, off_over = 0, total = 0;
 };
 F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k);
+// Largest distance of rows, in values, the filter takes: its scans reach the 256 rows of a tile by 32-bit offsets.
+constexpr int64_t f32_filter_max_ld(int d) { return ((int64_t(1) << 32) - d) / 255; }
 // The filter's score of an item is within this times (|q|^2 + |x|^2) / 2 of the directly summed one.
 constexpr float f32_filter_constant(int d) { return 0x1p-14f + (float)d * 0x1p-20f; }
 // The same of its first scan, one product of operands rounded to fp16.

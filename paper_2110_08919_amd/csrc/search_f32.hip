@@ -567,7 +567,7 @@ static hipError_t launch_f32_batch(const float *x, int64_t n, int64_t ldx, const
     // then only works on query tiles that hold a query whose candidates did not fit.
     const F32Filter fp = f32_filter_plan(n, nq, d, k);
     const int32_t *only = nullptr;
-    if (fp.use) {
+    if (fp.use && ldx <= f32_filter_max_ld(d)) {
         char *fws = (char *)ws + f32_lists_bytes(n, nq, d, k);
         e = launch_f32_filter(fp, x, n, ldx, q, nq, ldq, d, k, mode == MODE_F32_L2, fws, st);
         if (e != hipSuccess) return e;

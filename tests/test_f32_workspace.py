@@ -1,7 +1,11 @@
-"""Workspace of the exact fp32 search: large batches are searched in parts.  The sizes need no GPU."""
+"""Workspace of the exact fp32 search: large batches are searched in parts; rows too far apart for its filter's offsets.
+The sizes need no GPU."""
+import subprocess
+
 import pytest
 import torch
 
+from paper_2110_08919_amd import build as lpq_build
 from paper_2110_08919_amd import lpq, synth
 
 
@@ -12,6 +16,18 @@ def test_workspace_is_bounded_for_any_batch_and_k(n, d):
         for nq in (256, 257, 1000, 8192, 10_000, 16_384, 16_385, 20_580, 100_000, 1_000_000):
             # 256 MB and the rounding of the query
             assert 0 < lpq.lib().lpq_search_f32_workspace_bytes(n, nq, d, k) <= (256 << 20) + 256
+
+
+def test_rows_of_a_tile_lie_within_32_bit_offsets(tmp_path):
+    """Rows any further apart (4096 of them span 276 GB) are left to the direct kernel, whose offsets have 64 bits."""
+    src, exe = tmp_path / "c.hip", str(tmp_path / "c")
+    src.write_text('#include <cstdio>\n#include "lpq_internal.h"\n'
+                   'int main() { for (int d : {1, 4, 128, 16384}) std::printf("%d %lld\\n", d, (long long)lpq::f32_filter_max_ld(d)); }\n')
+    subprocess.run([lpq_build.HIPCC, *lpq_build.FLAGS, str(src), "-o", exe], check=True)
+    for line in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines():
+        d, ld = map(int, line.split())
+        last = 255 * ld + d - 1                      # last value of a tile's last row
+        assert last < 2 ** 32 <= last + 255 + d
 
 
 @pytest.mark.gpu
