@@ -36,8 +36,9 @@
 //   range       a query is scaled by a power of two to a norm of 1 to 2, the rows of a tile by the mean of its queries'
 //               scales (not at all where that lies near one), so that fp16 holds both; what is too small for its
 //               normal range is off by 2^-25, sqrt(d) 2^-25 (|q| + |x|) in all: the first part is in the threshold
-//               (sqrt(d) 2^-22: f32_half_filter_small), the second in C's slack.  Rows beyond 2^15 after scaling, and queries 2^24 away from
-//               the others, go to the second scan.
+//               (sqrt(d) 2^-22: f32_half_filter_small), the second in C's slack.  Rows beyond 2^15 after scaling are set
+//               aside, up to 16 of a wave, and summed in fp32 at the workgroup's end; where there are more, and queries
+//               2^24 away from the others, go to the second scan.
 //
 // On ordinary data the wider bound lets through a tenth more (1M x 128, k = 10: 281 items instead of 261 a query).
 // The second scan, with C and the split, takes query tiles where the seeding pass has more than twice k groups within
@@ -83,6 +84,9 @@ constexpr int HALF_RANGE = 24;        // powers of two by which a query's norm m
 constexpr int NO_SCALE = INT32_MIN;   // in FilterIo::qe: the query counts as zero (or is a padding row)
 constexpr int ZERO_SCALE = 12;        // ... which holds up to this scale of its tile
 constexpr int NEAR_ONE_LO = -10, NEAR_ONE_HI = 6;   // scales of a tile that rows do without: fp16 holds norms of 2^-6 to 2^10 well
+constexpr float NEAR_ONE_ROWS = 0x1p21f;   // ... where their mean squared norm is at most this: one row in 512 beyond HALF_NORM
+constexpr int ASIDE = 16;             // rows beyond HALF_NORM that a wave of the first scan sets aside
+constexpr float LONG_NORM = 0x1p90f;  // ... up to this squared norm: what is formed of it stays finite
 enum { AGAIN = 1, DIRECT = 2 };       // bits of FilterIo::again
 
 struct FilterIo {
@@ -101,6 +105,7 @@ struct FilterIo {
     int32_t *gmax;            // seeding pass: [nq_pad][G] group maxima (order-preserving images), G = S * SEG * 2 * (8 / WQ)
     int SEG;
     float *nxsum;             // seeding pass: the sampled rows' squared norms together, eight times over for each query tile
+    float nxper;              // ... times this is their mean
     const _Float16 *qf;       // first scan: [nq_pad][dp] the queries in fp16, each scaled to a norm of 1 to 2
     const int32_t *qe;        // ... by two to this power
     float ch;                 // ... and the constant of its error
@@ -116,8 +121,10 @@ struct FilterIo {
 #define LPQF_INLINE __attribute__((always_inline))
 constexpr int FDUMPS = 32;
 // Control words of a workgroup of the scan, in LDS: queries that are done (their region has overflowed, or the slot holds
-// none), what wave 0 has said of them, whether rows were lost to the first scan or to both, and the sum and number of the queries' scales.
-enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_LOST = 3, CTL_HUGE = 4, CTL_SCALES = 5, CTL_SCALED = 6, CTL_WORDS = 64 };
+// none), what wave 0 has said of them, whether a row is lost to both scans, the sum and number of the queries' scales,
+// and how many rows each wave of the first scan has set aside and which.
+enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_HUGE = 3, CTL_SCALES = 4, CTL_SCALED = 5, CTL_ASIDE = 8 /* [FW] */,
+       CTL_ROWS = CTL_ASIDE + FW /* [FW][ASIDE] */, CTL_WORDS = CTL_ROWS + FW * ASIDE };
 constexpr int ALL_LOST = 1 << 20;     // in CTL_DONE: a row was seen that the bounds do not hold for
 constexpr size_t filter_lds_bytes(int wq, bool seed, bool fp16)
 {
@@ -215,7 +222,8 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         __syncthreads();
         const int scaled = ctl[CTL_SCALED];
         xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
-        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI) xe = 0;
+        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && *o.nxsum * o.nxper <= NEAR_ONE_ROWS) xe = 0;
+        xe = __builtin_amdgcn_readfirstlane(xe);
     }
     const float xscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, xe))));
     if (!SEED) {
@@ -270,6 +278,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     float part[4] = {0.f, 0.f, 0.f, 0.f}, sum = 0.0f;
     int ft = 0, fk = 0;               // tile (of this split) and stage of the tile that is fetched next
     int pt = 0, pk = 0;               // ... and that goes to LDS next
+    int aside = 0;                    // rows this wave has come upon that are set aside
     auto fetch_tile = [&]() LPQF_INLINE {
         const int64_t t0 = ((int64_t)s + (int64_t)ft * S) * o.tile_stride;
         const int last = (int)(o.n - 1 - t0 < TILE_ROWS ? o.n - 1 - t0 : TILE_ROWS);   // rows past the end: any row, rejected later
@@ -365,11 +374,22 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 const float pe = part[e];
                 p = i == e ? pe : p;
             }
-            if ((lane & 4) == 0) nx[(pt & 3) * TILE_ROWS + wave * 32 + i * 8 + lrow] = p;
-            if (!SEED && !(p <= LIMIT)) {
+            if (FP16) {
+                // set aside: without a norm no score of the row reaches a threshold
+                const bool far = !(p <= LIMIT);
+                if (far) p = NAN;
+                unsigned long long mask = __ballot(far) & 0x0F0F0F0F0F0F0F0Full;
+                for (; __builtin_expect(mask != 0, 0); mask &= mask - 1) {
+                    const int l = __ffsll(mask) - 1, at = wave * 32 + (l & 3) * 8 + (l >> 3);
+                    if (((int64_t)s + (int64_t)pt * S) * TILE_ROWS + at >= o.n) continue;   // a copy of the last row
+                    if (aside < ASIDE) ctl[CTL_ROWS + wave * ASIDE + aside] = pt * TILE_ROWS + at;
+                    else ctl[CTL_DONE] = ALL_LOST;
+                    ++aside;
+                }
+            } else if (!SEED && !(p <= LIMIT)) {
                 ctl[CTL_DONE] = ALL_LOST;
-                if (FP16) ctl[ldexpf(p, -2 * xe) <= HUGE_NORM ? CTL_LOST : CTL_HUGE] = 1;
             }
+            if ((lane & 4) == 0) nx[(pt & 3) * TILE_ROWS + wave * 32 + i * 8 + lrow] = p;
 #pragma unroll
             for (int e = 0; e < 4; ++e) part[e] = 0.0f;
             pk = 0;
@@ -614,16 +634,54 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 #undef LPQF_ORDER
 
     if (!SEED) {
+        if (FP16) ctl[CTL_ASIDE + wave] = aside;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (left early: the query copies on their way land before the LDS is given back)
         __syncthreads();
+        // The rows set aside, summed in fp32 (off by less than the constant lets the rounded rows be): eight lanes to a row
+        // and query, eight values each at a time.  1M x 128, 1000 queries, one such row: 0.45 ms (L2) and 0.52 in all, as
+        // without it (the split's scan alone: 0.92; the first given up for it and the split's behind: 1.27).
+#pragma clang loop unroll(disable)
+        for (int w = 0; FP16 && w < FW; ++w) {
+            const int rows = ctl[CTL_ASIDE + w] < ASIDE ? ctl[CTL_ASIDE + w] : ASIDE, sub = tid & 7;
+            for (int at = tid >> 3; at < QT * rows; at += FW * 8) {
+                const int i = at % QT, tr = ctl[CTL_ROWS + w * ASIDE + at / QT];
+                const int64_t row = ((int64_t)s + (int64_t)(tr / TILE_ROWS) * S) * TILE_ROWS + tr % TILE_ROWS;
+                const _Float16 *qr = o.qf + (q_tile + i) * o.dp;
+                const float *xr = o.x + row * o.ldx;
+                float u = 0.0f, p = 0.0f;
+#pragma clang loop unroll(disable)
+                for (int c = 8 * sub; c < o.d; c += 64) {
+                    const v8h qv = *reinterpret_cast<const v8h *>(qr + c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float v = c + e < o.d ? xr[c + e] * xscale : 0.0f;
+                        u = fmaf((float)qv[e], v, u);
+                        p = fmaf(v, v, p);
+                    }
+                }
+#pragma unroll
+                for (int m = 1; m < 8; m <<= 1) {
+                    u += __shfl_xor(u, m, 64);
+                    p += __shfl_xor(p, m, 64);
+                }
+                if (!(p <= LONG_NORM)) ctl[CTL_DONE] = ALL_LOST;
+                if (!(ldexpf(p, -2 * xe) <= HUGE_NORM)) ctl[CTL_HUGE] = 1;
+                u = fmaf(-h_l[i], p, u);
+                if (sub == 0 && u >= thr_l[i]) {
+                    const int pos = atomicAdd(&fill[i], 1);
+                    if (pos < o.Cs) cbase[(size_t)i * qstride + pos] = make_cand(~float_to_sortable(u), (uint32_t)row);
+                }
+            }
+        }
+        if (FP16) __syncthreads();
         // a row the bounds do not hold for: all queries of the tile overflow
-        const bool lost = ctl[CTL_DONE] >= ALL_LOST;
+        const bool lost = ctl[CTL_DONE] >= ALL_LOST || ctl[CTL_HUGE];
         for (int i = tid; i < QT; i += FW * 64) {
             const int64_t q = q_tile + i;
             if (q >= o.nq || (!FP16 && fill[i] < 0)) continue;
             const int have = fill[i] < 0 ? 0 : (lost ? o.Cs + 1 : fill[i]);
             o.ccnt[(size_t)q * S + s] = have;
-            if (FP16 && have > o.Cs) atomicOr(&o.again[q], lost && ctl[CTL_HUGE] ? DIRECT : AGAIN);
+            if (FP16 && have > o.Cs) atomicOr(&o.again[q], ctl[CTL_HUGE] ? DIRECT : AGAIN);
         }
     }
     if (SEED) {
@@ -762,13 +820,14 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     o.S = p.S1; o.SEG = p.SEG; o.gmax = gmax;
     o.tiles = p.seed_tiles; o.tile_stride = p.run_stride; o.run_gap = (int64_t)p.seed_tiles * p.run_stride;
     if (p.run_stride < RUN || ((int64_t)16 * p.seed_tiles - 1) * p.run_stride + RUN > n) return hipErrorInvalidValue;
+    o.nxper = 1.0f / (8.0f * TILE_ROWS * (float)p.seed_tiles * (float)p.qtiles);
     o.h = l2 ? 0.5f * (1.0f + o.c) : 0.5f * o.c;
     e = p.wq == 1 ? launch_filter<true, 1, false>(o, st) : launch_filter<true, 2, false>(o, st);
     if (e != hipSuccess) return e;
     // Groups within the first scan's error of the bound, for a row of the sample's mean norm: beyond twice k and a few, the
     // query is left to the second scan (regions hold three times what the sample lets expect, so it would overflow).
     const float c2 = 0.5f * (o.c + o.ch) * 1.00001f;
-    const HardQueries hq = {qn, nxsum, c2, c2 / (8.0f * TILE_ROWS * (float)p.seed_tiles * (float)p.qtiles), p.half ? 2 * k + 8 : 0, hard};
+    const HardQueries hq = {qn, nxsum, c2, c2 * o.nxper, p.half ? 2 * k + 8 : 0, hard};
     e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, nullptr, kth, nullptr, 0, 0, hq);
     if (e != hipSuccess) return e;
     // scans: every item whose upper bound reaches the k-th lower bound

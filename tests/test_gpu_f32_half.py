@@ -83,3 +83,28 @@ def test_rows_and_queries_the_first_scan_leaves_to_the_second():
     dup[20_000:60_000] = dup[0]             # more equal rows than a region holds, found by few queries
     q[7] = dup[0]
     _check(dup, q, 10, "l2sq")
+
+
+# one row, as many as a wave of the scan sets aside (all of them in the rows of the same wave) and more, and rows that only
+# scaled rows can hold
+@pytest.mark.gpu
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("norm,long,factor,resolved", [
+    (1.0, [77_777], 3e4, True), (85.0, [3, 255, 256, 129_999], 60.0, True), (85.0, [129_999], 1e4, True),
+    (85.0, range(7, 16 * 256, 256), 50.0, True), (40.0, range(0, 129_999, 256), 2000.0, None),
+    (85.0, range(5, 129_999, 50), 60.0, None), (1e-9, [500], 1e7, True), (1e3, [9], 1e12, False)])
+def test_rows_of_large_norm_cost_only_themselves(metric, norm, long, factor, resolved):
+    """A row that fp16 cannot hold is set aside: the first scan still resolves the queries of its tile."""
+    import f32_plan
+    from paper_2110_08919_amd import lpq
+    from test_gpu_f32_filter import _direct, _same_bits
+    x, q = _rows(130_000, 128, 300, 3)
+    x, q = x * norm, q * norm
+    x[list(long)] *= factor
+    got, p, ws = f32_plan.search(x, q, 10, metric)
+    _same_bits(got, _direct(lpq, x, q, 10, metric))
+    again, hard = f32_plan.words(p, ws, "off_again", 300), f32_plan.words(p, ws, "off_hard", p["nq_pad"] // 128)
+    assert p["half"]
+    if resolved is not None:
+        left = (again != 0) | (hard[torch.arange(300, device="cuda") // 128] != 0)
+        assert bool(left.any()) != resolved
