@@ -8,7 +8,7 @@ import tempfile
 
 from paper_2110_08919_amd import build as lpq_build
 
-FIELDS = ("use", "half", "wq_half", "qtiles", "qtiles_half", "S2", "Cs", "nq_pad", "off_hard", "off_again", "off_ccnt", "total")
+FIELDS = ("use", "half", "wq_half", "qtiles", "qtiles_half", "S2", "Cs", "nq_pad", "off_hard", "off_again", "off_cbuf", "off_ccnt", "total")
 
 
 @functools.lru_cache(None)

@@ -4,6 +4,7 @@ Needs a real MI355X."""
 import pytest
 import torch
 
+import f32_plan
 from paper_2110_08919_amd import lpq
 from test_gpu_f32_filter import _direct, _same_bits
 
@@ -37,6 +38,19 @@ def test_rows_that_are_not_finite_or_huge(metric, n, d, nq, k):
             xs = x.clone()
             xs[list(rows), n // 3 % d] = value
             _same_bits(lpq.search_f32(xs, q, k, metric), _direct(lpq, xs, q, k, metric))
+
+
+def test_a_second_round_of_workgroups_leaves_out_what_the_first_has_given_up():
+    """1000 queries take 512 workgroups, twice what the GPU holds at a time."""
+    n, d, nq, k = 200_000, 64, 1000, 10
+    x, q = _data(n, d, nq, 5)
+    x, q = x + 3000.0, q + 3000.0
+    got, p, ws = f32_plan.search(x, q, k, "l2sq")
+    _same_bits(got, _direct(lpq, x, q, k, "l2sq"))
+    assert p["half"] and p["qtiles"] * p["S2"] == 512
+    given_up = f32_plan.words(p, ws, "off_ccnt", nq * p["S2"]) > p["Cs"]
+    empty = f32_plan.words(p, ws, "off_cbuf", nq * p["S2"] * p["Cs"] * 2).view(-1, p["Cs"] * 2)[:, :2].eq(0).all(dim=1)
+    assert bool(given_up.all()) and float(empty.float().mean()) > 0.25
 
 
 def test_giving_up_costs_a_fraction_of_the_direct_kernel():
