@@ -473,8 +473,10 @@ __global__ __launch_bounds__(256) void collect_select_sort_kernel(
 // 450 candidates, 1000 queries 20 -> 11 us, 10 000 on 1M x 128 73 -> 47, on 4M x 256 107 -> 57; k = 10, 1000 queries on
 // 1.2M x 100 9.8 -> 6.7, on 500 000 x 768 10.7 -> 7.6, on 200 000 x 2048 (350 candidates) 19.6 -> 7.8, 100 on 10 000 x 128
 // 6.0 -> 4.3.  Large batches with few candidates stay with the wave, a quarter of a workgroup per query: 10 000 queries,
-// k = 10, 90 candidates 21 us against 29 here; whole searches of 400 000 x 128, k = 10: 2100 and 3000 queries the same, 4000
-// 243 against 248, 6000 346 against 352.
+// k = 10, 90 candidates 21 us against 29 here.  RANK_TO_NQ is the line where there are 64 regions or fewer; on short rows that
+// is from some 3600 queries on, where the wave is ahead (whole searches, k = 10, wave and here: 100 000 x 64, 3600 queries 92
+// and 95 us, 50 000 778 and 816; 400 000 x 128, 4000 216 and 217, 10 000 485 and 492), so that the number decides for long rows
+// alone, where the two hardly differ (500 000 x 768, 2600 queries 993 and 985, 6000 2144 and 2136; 1M x 256, 3000 671 and 670).
 constexpr int RANK_FROM_K = 16, RANK_TO_NQ = 2048, RANK_FROM_EXPECTED = 192;
 constexpr int RANK_FEW = 2048, RANK_COUNTED = 512, RANK_BINS = 256;
 __global__ __launch_bounds__(256) void collect_select_rank_kernel(
@@ -496,9 +498,13 @@ __global__ __launch_bounds__(256) void collect_select_rank_kernel(
         }
         return v;
     };
-    const int mine = tid < SS ? ccnt[q * SS + tid] : 0;
+    // The lanes of a region share its candidates, 256 lanes where there is one region.  (With a thread to a region whole
+    // searches on 1M x 128, k = 100 took: 50 000 queries, 5 regions 7.9 ms, 100 000, 2 regions 19.7, 300 000, one 69.0;
+    // 7.7, 19.1 and 65.5 now, and a wave's sort 7.9, 19.3 and 65.9.)
+    const int share = __clz(SS - 1) - 24, per = 1 << share, region = tid >> share, sub = tid & (per - 1);
+    const int mine = region < SS ? ccnt[q * SS + region] : 0;
     const int bad = mine > Cs || mine < 0;
-    const int upto = scan(bad ? 0 : mine);
+    const int upto = scan(bad || sub ? 0 : mine);
     if (lane == 63) s_wave[wave] = upto;
     s_hist[tid] = 0;
     if (tid == 0) s_more = 0;
@@ -521,7 +527,7 @@ __global__ __launch_bounds__(256) void collect_select_rank_kernel(
     if (flagged) return;
     const cand_t *regions = cbuf + (size_t)q * SS * Cs;
     if (total > RANK_FEW) {
-        s_end[tid] = end;
+        if (sub == 0) s_end[region] = end;
         __syncthreads();
         int kept = 0;
         for (int pos = 0; pos < total;) {
@@ -547,8 +553,8 @@ __global__ __launch_bounds__(256) void collect_select_rank_kernel(
         return;
     }
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-    for (int i = 0; i < mine; ++i) {
-        const cand_t c = regions[(size_t)tid * Cs + i];
+    for (int i = sub; i < mine; i += per) {
+        const cand_t c = regions[(size_t)region * Cs + i];
         buf[end - mine + i] = c;
         const uint32_t key = (uint32_t)(c >> 32);
         lo = key < lo ? key : lo;
