@@ -8,7 +8,8 @@ import tempfile
 
 from paper_2110_08919_amd import build as lpq_build
 
-FIELDS = ("use", "half", "wq_half", "qtiles", "qtiles_half", "S2", "Cs", "nq_pad", "off_hard", "off_again", "off_cbuf", "off_ccnt", "total")
+FIELDS = ("use", "half", "wq_half", "qtiles", "qtiles_half", "S2", "Cs", "nq_pad", "off_hard", "off_again", "off_cbuf", "off_ccnt", "off_over",
+          "total")
 
 
 @functools.lru_cache(None)
@@ -52,3 +53,17 @@ def words(p, ws, name, count):
     """`count` words of the workspace from offset `name` of the plan on."""
     at = p[name] // 4
     return ws[at:at + count]
+
+
+def best_ms(fn):
+    """Shortest of six calls."""
+    import torch
+    times = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
