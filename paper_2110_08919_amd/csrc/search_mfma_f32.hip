@@ -122,8 +122,8 @@ struct FilterIo {
 constexpr int FDUMPS = 32;
 // Control words of a workgroup of the scan, in LDS: queries that are done (their region has overflowed, or the slot holds
 // none), what wave 0 has said of them, whether a row is lost to both scans, the sum and number of the queries' scales,
-// and how many rows each wave of the first scan has set aside and which.
-enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_HUGE = 3, CTL_SCALES = 4, CTL_SCALED = 5, CTL_ASIDE = 8 /* [FW] */,
+// and whether rows were set aside, how many by each wave of the first scan, and which.
+enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_HUGE = 3, CTL_SCALES = 4, CTL_SCALED = 5, CTL_ANY = 6, CTL_ASIDE = 8 /* [FW] */,
        CTL_ROWS = CTL_ASIDE + FW /* [FW][ASIDE] */, CTL_WORDS = CTL_ROWS + FW * ASIDE };
 constexpr int ALL_LOST = 1 << 20;     // in CTL_DONE: a row was seen that the bounds do not hold for
 constexpr size_t filter_lds_bytes(int wq, bool seed, bool fp16)
@@ -215,6 +215,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     // FP16: the tile's rows are scaled by two to the mean of its queries' scales
     int xe = 0;
     if (!SEED && FP16) {
+        const float mean = *o.nxsum * o.nxper;
         for (int i = tid; i < QT; i += FW * 64) {
             const int e = o.qe[q_tile + i];
             if (e != NO_SCALE) { atomicAdd(&ctl[CTL_SCALES], e); atomicAdd(&ctl[CTL_SCALED], 1); }
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
         __syncthreads();
         const int scaled = ctl[CTL_SCALED];
         xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
-        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && *o.nxsum * o.nxper <= NEAR_ONE_ROWS) xe = 0;
+        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && mean <= NEAR_ONE_ROWS) xe = 0;
         xe = __builtin_amdgcn_readfirstlane(xe);
     }
     const float xscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, xe))));
@@ -281,7 +282,6 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     float part[4] = {0.f, 0.f, 0.f, 0.f}, sum = 0.0f;
     int ft = 0, fk = 0;               // tile (of this split) and stage of the tile that is fetched next
     int pt = 0, pk = 0;               // ... and that goes to LDS next
-    int aside = 0;                    // rows this wave has come upon that are set aside
     auto fetch_tile = [&]() LPQF_INLINE {
         const int64_t t0 = ((int64_t)s + (int64_t)ft * S) * o.tile_stride;
         const int last = (int)(o.n - 1 - t0 < TILE_ROWS ? o.n - 1 - t0 : TILE_ROWS);   // rows past the end: any row, rejected later
@@ -299,7 +299,8 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     };
     // Loads of stage (ft, fk), LOADS of them on every path: only then does the compiler wait for one stage's loads
     // without waiting for those issued after them.  (With a branch between them, and with a stage that fetched
-    // nothing, it waited for all, a memory round trip per stage.)  What lies past a row's end is loaded from its
+    // nothing, it waited for all, a memory round trip per stage.  It still does where stages of either parity merge: in the
+    // sample and the second scan of an odd number of stages.)  What lies past a row's end is loaded from its
     // last four values and put right in fix; past the last stage the last tile's are fetched again.
     constexpr int LOADS = WIDE ? 4 : 16;
     auto fetch = [&](v4f (&to)[4]) LPQF_INLINE {
@@ -379,15 +380,19 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
             }
             if (FP16) {
                 // set aside: without a norm no score of the row reaches a threshold
-                const bool far = !(p <= LIMIT);
-                if (far) p = NAN;
-                unsigned long long mask = __ballot(far) & 0x0F0F0F0F0F0F0F0Full;
-                for (; __builtin_expect(mask != 0, 0); mask &= mask - 1) {
-                    const int l = __ffsll(mask) - 1, at = wave * 32 + (l & 3) * 8 + (l >> 3);
-                    if (((int64_t)s + (int64_t)pt * S) * TILE_ROWS + at >= o.n) continue;   // a copy of the last row
-                    if (aside < ASIDE) ctl[CTL_ROWS + wave * ASIDE + aside] = pt * TILE_ROWS + at;
-                    else ctl[CTL_DONE] = ALL_LOST;
-                    ++aside;
+                const unsigned long long far = __ballot(!(p <= LIMIT));
+                p = p <= LIMIT ? p : NAN;
+                if (__builtin_expect(far != 0, 0)) {
+                    int lane_ = lane;                                 // (as in drain)
+                    asm volatile("" : "+v"(lane_));
+                    const int at = wave * 32 + (lane_ & 3) * 8 + (lane_ >> 3);
+                    const unsigned row = ((unsigned)s + (unsigned)(pt * S)) * TILE_ROWS + (unsigned)at;
+                    if (((far >> lane_) & 1) && (lane_ & 4) == 0 && row < (unsigned)o.n) {   // (not a copy of the last row)
+                        const int pos = atomicAdd(&ctl[CTL_ASIDE + wave], 1);
+                        ctl[CTL_ANY] = 1;
+                        if (pos < ASIDE) ctl[CTL_ROWS + wave * ASIDE + pos] = pt * TILE_ROWS + at;
+                        else ctl[CTL_DONE] = ALL_LOST;
+                    }
                 }
             } else if (!SEED && !(p <= LIMIT)) {
                 ctl[CTL_DONE] = ALL_LOST;
@@ -460,16 +465,20 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     auto drain = [&](int dumps) LPQF_INLINE {     // queued scores that reach their query's threshold go to its region
         wave_lds_sync();
         for (int base = 0; base < dumps * 16; base += 64) {
-            const int at = base + lane;
+            // (Nothing formed of the lane is kept for the whole scan: no register is left for it in tiles of 256 queries, and
+            // a reload from scratch waited for both stages on their way, at nearly every tile.)
+            int lane_ = lane;
+            asm volatile("" : "+v"(lane_));
+            const int at = base + lane_;
             if (at < dumps * 16) {
                 const float u = dval[at];
                 const v4i m4 = dmeta[at >> 4];
                 const int ql = m4[1] & 255, r = at & 15;
-                const int64_t row = (int64_t)(unsigned)m4[0] + 8 * (r >> 2) + 4 * (m4[1] >> 8) + (r & 3);
-                if (u >= thr_l[ql] && row < o.n) {
+                const unsigned row = (unsigned)m4[0] + 8 * (r >> 2) + 4 * (m4[1] >> 8) + (r & 3);
+                if (u >= thr_l[ql] && row < (unsigned)o.n) {
                     const int pos = atomicAdd(&fill[ql], 1);
                     if (__builtin_expect(pos < o.Cs, 1)) {
-                        cbase[(size_t)ql * qstride + pos] = make_cand(~float_to_sortable(u), (uint32_t)row);
+                        cbase[(size_t)ql * qstride + pos] = make_cand(~float_to_sortable(u), row);
                     } else if (__builtin_expect(pos == o.Cs, 0)) {   // the direct kernel takes this query: collect no more for it
                         thr_l[ql] = NAN;
                         atomicAdd(&ctl[CTL_DONE], 1);
@@ -637,14 +646,14 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 #undef LPQF_ORDER
 
     if (!SEED) {
-        if (FP16) ctl[CTL_ASIDE + wave] = aside;
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (left early: the query copies on their way land before the LDS is given back)
         __syncthreads();
         // The rows set aside, summed in fp32 (off by less than the constant lets the rounded rows be): eight lanes to a row
         // and query, eight values each at a time.  1M x 128, 1000 queries, one such row: 0.45 ms (L2) and 0.52 in all, as
         // without it (the split's scan alone: 0.92; the first given up for it and the split's behind: 1.27).
+        const bool any = FP16 && ctl[CTL_ANY];
 #pragma clang loop unroll(disable)
-        for (int w = 0; FP16 && w < FW; ++w) {
+        for (int w = 0; any && w < FW; ++w) {
             const int rows = ctl[CTL_ASIDE + w] < ASIDE ? ctl[CTL_ASIDE + w] : ASIDE, sub = tid & 7;
             for (int at = tid >> 3; at < QT * rows; at += FW * 8) {
                 const int i = at % QT, tr = ctl[CTL_ROWS + w * ASIDE + at / QT];
@@ -676,7 +685,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                 }
             }
         }
-        if (FP16) __syncthreads();
+        if (any) __syncthreads();                     // (the same in every thread)
         // a row the bounds do not hold for: all queries of the tile overflow
         const bool lost = ctl[CTL_DONE] >= ALL_LOST || ctl[CTL_HUGE];
         for (int i = tid; i < QT; i += FW * 64) {

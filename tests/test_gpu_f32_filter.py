@@ -2,6 +2,7 @@
 returns for the same queries on slices of the corpus too small for the filter, merged, and agree with
 the CPU oracle.  Needs a real MI355X, but for the check of the compiled instruction order."""
 import os
+import re
 
 import numpy as np
 import pytest
@@ -15,6 +16,14 @@ def test_no_read_of_a_matrix_result_sooner_than_the_wait_states_it_needs():
     lpq_build.build()
     bad = _closest_reads(lpq_build.device_asm(os.path.join(lpq_build.CSRC, "search_mfma_f32.hip")))
     assert not bad, f"{len(bad)} reads of matrix results within {NEED} issue slots, e.g. {sorted(bad, key=lambda b: b[1])[:3]}"
+
+
+def test_nothing_is_kept_in_scratch():
+    """A reload from scratch waits for all loads of the stages on their way."""
+    lpq_build.build()
+    asm = open(lpq_build.device_asm(os.path.join(lpq_build.CSRC, "search_mfma_f32.hip"))).read()
+    spills = dict(re.findall(r"\.name: +(\S*filter_f32_kernel\S*)\n(?:.*\n)*?.*\.vgpr_spill_count: (\d+)", asm))
+    assert len(spills) == 18 and not any(map(int, spills.values())), spills
 
 
 @pytest.fixture(scope="module")
