@@ -187,13 +187,13 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
 // The k nearest of the rows the filter collected, one workgroup per query.  A candidate comes with the upper bound of
 // its score: the k and a few with the highest are summed directly, the k-th of those distances says which upper bounds
 // still matter, and only those rows are summed too: some 30 of 280 (1M x 128, k = 10), each 4 d bytes from far apart.
-// Up to FIN_FEW candidates, almost always, nothing is sorted: a histogram of the bounds gives the highest, and the rank of
-// a distance is the number of those before it, counted by the thread that holds it.  Beyond, bounds and distances are
-// sorted.  Directly summed: eight lanes per row, each with the same chunks of four features in the same order, the eight
-// partial sums added in the same pairs, as in the kernel above, so a distance comes out with the same bits.
-// Bound by barriers and the latency of the rows.  1000 queries on 1M x 128, k = 10: 13 us, where summing all candidates
+// Nothing is sorted on the way: a histogram of the bounds gives the highest, digit by digit where there are more than FIN_FEW
+// candidates, and the rank of a distance is the number of those before it, counted by the thread that holds it (sorted are
+// more than FIN_RANKED distances).  Directly summed: eight lanes per row, each with the same chunks of four features in the
+// same order, the eight partial sums added in the same pairs, as in the kernel above, so a distance comes out with the same
+// bits.  Bound by barriers and the latency of the rows.  1000 queries on 1M x 128, k = 10: 13 us, where summing all candidates
 // took 37 and selecting among them 29 (sorting the bounds here: 37); k = 100, 700 candidates each: 28.
-constexpr int FIN_CAP = 4096;       // candidates in LDS; of more, the best half is kept while the rest passes by
+constexpr int FIN_CAP = 4096;       // candidates in LDS
 constexpr int FIN_FEW = FIN_CAP / 2, FIN_RANKED = 2 * F32_THREADS, FIN_BINS = F32_THREADS;
 constexpr int FIN_REGIONS = F32_THREADS;
 struct FinishIo {
@@ -216,8 +216,7 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);           // [FIN_CAP]
     float *qs = reinterpret_cast<float *>(buf + FIN_CAP);     // the query, zero beyond d
-    __shared__ int s_end[FIN_REGIONS];                        // candidates of regions 0 .. r together
-    __shared__ int s_more, s_hist[FIN_BINS], s_wave[F32_THREADS / 64], s_cut;
+    __shared__ int s_more, s_hist[FIN_BINS], s_wave[F32_THREADS / 64], s_cut, s_before;
     __shared__ float s_lo[F32_THREADS / 64], s_hi[F32_THREADS / 64];
     __shared__ cand_t s_kth;
     const int64_t q = blockIdx.x;
@@ -249,26 +248,16 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
         before += w < wave ? s_wave[w] : 0;
         total += s_wave[w];
     }
-    if (part == 0) s_end[region] = before + upto;
     if (lost || total < k) {                                  // the same in every thread
         if (tid == 0) o.over[q] = 1;
         return;
     }
     const cand_t *regions = o.cbuf + (size_t)q * o.SS * o.Cs;
-    auto candidate = [&](int i) {
-        int lo = 0, hi = o.SS - 1;                            // first region that ends beyond i
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (s_end[mid] > i) hi = mid; else lo = mid + 1;
-        }
-        return regions[(size_t)lo * o.Cs + (i - (lo ? s_end[lo - 1] : 0))];
-    };
     auto pow2 = [](int v) { return v <= 32 ? 32 : 1 << (32 - __clz(v - 1)); };
-    auto sort = [&](int count) {                              // of buf[0 .. count), and fills up to a power of two behind it
-        const int size = pow2(count);
-        for (int i = count + tid; i < size; i += F32_THREADS) buf[i] = CAND_NONE;
+    auto sort = [&](cand_t *buf, int count) {                 // fills up to a power of two behind it
+        for (int i = count + tid; i < pow2(count); i += F32_THREADS) buf[i] = CAND_NONE;
         __syncthreads();
-        block_bitonic_sort(buf, size);
+        block_bitonic_sort(buf, pow2(count));
     };
     auto sum_directly = [&](cand_t *buf, int from, int to) {  // key halves of buf[from .. to) become the distances' images
         for (int i = from + grp; i < to; i += F32_ROWS) {
@@ -320,10 +309,47 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
         o.dists[q * k + i] = L2 ? v : -v;
     };
 
-    if (total <= FIN_FEW) {
-        cand_t *few = buf + FIN_FEW;                          // the rows that are summed
-        auto bound = [](cand_t cand) { return sortable_to_float(~cand_key(cand)); };
-        float lo = INFINITY, hi = -INFINITY;
+    // up to FIN_FEW candidates are kept in LDS, more are read again from their regions
+    const bool kept = total <= FIN_FEW;
+    cand_t *few = kept ? buf + FIN_FEW : buf;                 // the rows that are summed
+    const int room = kept ? FIN_FEW : FIN_CAP, want = k + k / 4 + 6 < total ? k + k / 4 + 6 : total;
+    auto each = [&](auto f) {
+        if (kept) { for (int i = tid; i < total; i += F32_THREADS) f(buf[i]); }
+        else for (int i = part; i < mine; i += 4 * per) {     // four on their way at a time
+            cand_t c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = regions[(size_t)region * o.Cs + (i + u * per < mine ? i + u * per : i)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) if (i + u * per < mine) f(c[u]);
+        }
+    };
+    auto find_cut = [&](int want) {                           // the bin up to which that many are, how many before it
+        if (wave == 0) {
+            int v[4], sum = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = s_hist[4 * lane + j]; sum += v[j]; }
+            const int incl = scan(sum);
+            if (lane == __ffsll((unsigned long long)__ballot(incl >= want)) - 1) {
+                int at = incl - sum, j = 0;
+                while (j < 3 && at + v[j] < want) at += v[j++];
+                s_cut = 4 * lane + j;
+                s_before = at;
+            }
+        }
+        __syncthreads();
+    };
+    // near(candidate): one of the highest
+    float hi = -INFINITY, scale = 0.0f;
+    int cut = 0;
+    uint32_t last = 0u;
+    auto bound = [](cand_t cand) { return sortable_to_float(~cand_key(cand)); };
+    auto bin = [&](cand_t cand) {                             // from the highest down
+        const float at = (hi - bound(cand)) * scale;
+        return at < (float)(FIN_BINS - 1) ? (int)at : FIN_BINS - 1;
+    };
+    auto near = [&](cand_t cand) { return kept ? bin(cand) <= cut : (uint32_t)(cand >> 32) <= last; };
+    if (kept) {
+        float lo = INFINITY;
         for (int i = part; i < mine; i += per) {
             const cand_t cand = regions[(size_t)region * o.Cs + i];
             buf[before + upto - mine + i] = cand;
@@ -342,114 +368,86 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
             lo = fminf(lo, s_lo[w]);
             hi = fmaxf(hi, s_hi[w]);
         }
-        const float scale = (FIN_BINS - 1) / fmaxf(hi - lo, 0x1p-100f);
-        auto bin = [&](cand_t cand) {                         // from the highest down
-            const float at = (hi - bound(cand)) * scale;
-            return at < (float)(FIN_BINS - 1) ? (int)at : FIN_BINS - 1;
-        };
-        for (int i = tid; i < total; i += F32_THREADS) atomicAdd(&s_hist[bin(buf[i])], 1);
+        scale = (FIN_BINS - 1) / fmaxf(hi - lo, 0x1p-100f);
+        each([&](cand_t cand) { atomicAdd(&s_hist[bin(cand)], 1); });
         __syncthreads();
-        if (wave == 0) {                                      // the bin up to which k and a few are
-            const int want = k + k / 4 + 6 < total ? k + k / 4 + 6 : total;
-            int v[4], sum = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = s_hist[4 * lane + j]; sum += v[j]; }
-            const int incl = scan(sum);
-            if (lane == __ffsll((unsigned long long)__ballot(incl >= want)) - 1) {
-                int at = incl - sum, j = 0;
-                while (j < 3 && at + v[j] < want) at += v[j++];
-                s_cut = 4 * lane + j;
-            }
-        }
-        __syncthreads();
-        const int cut = s_cut;
-        for (int i = tid; i < total; i += F32_THREADS)
-            if (bin(buf[i]) <= cut) few[atomicAdd(&s_more, 1)] = buf[i];
-        __syncthreads();
-        const int first = s_more;
-        sum_directly(few, 0, first);
-        // threads' first two: the rank of a distance among all
-        auto rank = [&](int i, int count) {
-            const cand_t me = few[i];
-            int r = 0;
-            for (int j = 0; j < count; ++j) r += few[j] < me;
-            return r;
-        };
-        if (first <= FIN_RANKED) {
-            for (int i = tid; i < first; i += F32_THREADS)
-                if (rank(i, first) == k - 1) s_kth = few[i];
-            __syncthreads();
-        } else {
-            for (int i = first + tid; i < pow2(first); i += F32_THREADS) few[i] = CAND_NONE;
-            __syncthreads();
-            block_bitonic_sort(few, pow2(first));
-            if (tid == 0) s_kth = few[k - 1];
-            __syncthreads();
-        }
-        const cand_t limit = limit_of(s_kth);
-        for (int i = tid; i < total; i += F32_THREADS) {
-            const cand_t cand = buf[i];
-            if (bin(cand) > cut && cand <= limit) few[atomicAdd(&s_more, 1)] = cand;
-        }
-        __syncthreads();
-        const int all = s_more;
-        sum_directly(few, first, all);
-        if (all <= FIN_RANKED) {
-            for (int i = tid; i < all; i += F32_THREADS) {
-                const int r = rank(i, all);
-                if (r < k) emit(few[i], r);
-            }
-        } else {
-            for (int i = all + tid; i < pow2(all); i += F32_THREADS) few[i] = CAND_NONE;
-            __syncthreads();
-            block_bitonic_sort(few, pow2(all));
-            for (int i = tid; i < k; i += F32_THREADS) emit(few[i], i);
-        }
-        if (tid == 0) o.over[q] = 0;
-        return;
-    }
-    __syncthreads();                                          // the ends of the regions are there
-
-    // the candidates (at least the FIN_CAP / 2 best) by their upper bounds, the highest first
-    int kept = 0;
-    for (int pos = 0; pos < total;) {
-        const int take = total - pos < FIN_CAP - kept ? total - pos : FIN_CAP - kept;
-        for (int i = tid; i < take; i += F32_THREADS) buf[kept + i] = candidate(pos + i);
-        sort(kept + take);
-        pos += take;
-        kept = pos < total || total > FIN_CAP ? FIN_CAP / 2 : kept + take;
-    }
-    const int first = pow2(k);                                // at most FIN_CAP / 2; beyond the candidates: CAND_NONE
-    const cand_t last = buf[first - 1];
-    __syncthreads();
-    sum_directly(buf, 0, first);
-    block_bitonic_sort(buf, first);
-    const cand_t limit = limit_of(buf[k - 1]);
-    if (total <= FIN_CAP) {                                   // sorted: those behind the first
-        for (int i = first + tid; i < total; i += F32_THREADS)
-            if (buf[i] <= limit && (i + 1 == total || buf[i + 1] > limit)) s_more = i + 1 - first;
-        __syncthreads();
+        find_cut(want);
+        cut = s_cut;
     } else {
-        __syncthreads();                                      // (kth has been read by all)
-        for (int i = tid; i < total; i += F32_THREADS) {
-            const cand_t cand = candidate(i);
-            if (cand > last && cand <= limit) {
-                const int at_ = first + atomicAdd(&s_more, 1);
-                if (at_ < FIN_CAP) buf[at_] = cand;
+        // (Sorting them FIN_CAP at a time took 0.36 ms for 10 000 a query, 64 queries, before too many were found to be left.)
+        int rest = want;
+        for (int shift = 24; shift >= 0; shift -= 8) {
+            if (shift < 24) {
+                s_hist[tid] = 0;
+                __syncthreads();
             }
+            each([&](cand_t cand) {
+                const uint32_t key = (uint32_t)(cand >> 32);
+                if (shift == 24 || (key ^ last) >> (shift + 8) == 0u) atomicAdd(&s_hist[(key >> shift) & 255u], 1);
+            });
+            __syncthreads();
+            find_cut(rest);
+            last |= (uint32_t)s_cut << shift;
+            rest -= s_before;
         }
-        __syncthreads();
     }
-    const int all = first + s_more;
-    if (all > FIN_CAP) {
+    auto take = [&](cand_t cand) {
+        const int at = atomicAdd(&s_more, 1);
+        if (at < room) few[at] = cand;
+    };
+    each([&](cand_t cand) { if (near(cand)) take(cand); });
+    __syncthreads();
+    const int first = s_more;
+    if (first > room) {                                       // (equal bounds)
         if (tid == 0) o.over[q] = 1;
         return;
     }
-    if (all > first) {
-        sum_directly(buf, first, all);
-        sort(all);
+    sum_directly(few, 0, first);
+    // threads' first two: the rank of a distance among all
+    auto rank = [&](int i, int count) {
+        const cand_t me = few[i];
+        int r = 0;
+        for (int j = 0; j < count; ++j) r += few[j] < me;
+        return r;
+    };
+    if (first <= FIN_RANKED) {
+        for (int i = tid; i < first; i += F32_THREADS)
+            if (rank(i, first) == k - 1) s_kth = few[i];
+        __syncthreads();
+    } else {
+        sort(few, first);
+        if (tid == 0) s_kth = few[k - 1];
+        __syncthreads();
     }
-    for (int i = tid; i < k; i += F32_THREADS) emit(buf[i], i);
+    const cand_t limit = limit_of(s_kth);
+    each([&](cand_t cand) { if (!near(cand) && cand <= limit) take(cand); });
+    __syncthreads();
+    int all = s_more;
+    if (all > room) {
+        if (tid == 0) o.over[q] = 1;
+        return;
+    }
+    sum_directly(few, first, all);
+    if (all > FIN_RANKED) {                                   // first without those beyond the k-th of before
+        cand_t c[FIN_CAP / F32_THREADS];
+#pragma unroll
+        for (int u = 0; u < FIN_CAP / F32_THREADS; ++u) c[u] = tid + u * F32_THREADS < all ? few[tid + u * F32_THREADS] : CAND_NONE;
+        if (tid == 0) s_more = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < FIN_CAP / F32_THREADS; ++u) if (c[u] <= s_kth) take(c[u]);
+        __syncthreads();
+        all = s_more;
+    }
+    if (all <= FIN_RANKED) {
+        for (int i = tid; i < all; i += F32_THREADS) {
+            const int r = rank(i, all);
+            if (r < k) emit(few[i], r);
+        }
+    } else {
+        sort(few, all);
+        for (int i = tid; i < k; i += F32_THREADS) emit(few[i], i);
+    }
     if (tid == 0) o.over[q] = 0;
 }
 

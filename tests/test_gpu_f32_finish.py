@@ -38,3 +38,33 @@ def test_equal_distances():
     q = torch.randint(0, 3, (100, 9), generator=g, device="cuda").float()
     for metric in ("l2sq", "ip"):
         _check(x, q, 10, metric)
+
+
+# bounds of the first scan, scaled by the powers of two of rows and queries, of shifted data: more candidates than are kept in
+# LDS (2048), more than 512 rows to rank, and a few
+@pytest.mark.parametrize("metric,k,shift,scale,least", [("l2sq", 400, 4.0, 1e-6, 2500), ("l2sq", 500, 4.0, 300.0, 3000), ("ip", 500, 15.0, 1e-6, 2600),
+                                                        ("ip", 500, 15.0, 1e4, 2600), ("l2sq", 10, 2.0, 1e-6, 150), ("ip", 10, 15.0, 1.0, 150)])
+def test_candidates_of_the_first_scan(metric, k, shift, scale, least):
+    import f32_plan
+    from paper_2110_08919_amd import lpq
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, q = torch.randn((200_000, 64), generator=g, device="cuda"), torch.randn((400, 64), generator=g, device="cuda")
+    x, q = scale * (x + shift), scale * (q + shift)
+    got, p, ws = f32_plan.search(x, q, k, metric)
+    _same_bits(got, _direct(lpq, x, q, k, metric))
+    counts = f32_plan.words(p, ws, "off_ccnt", 400 * p["S2"]).view(400, -1).sum(1)
+    again, hard, over = (f32_plan.words(p, ws, name, m) for name, m in (("off_again", 400), ("off_hard", 4), ("off_over", 400)))
+    assert p["half"] and not bool(again.any() or hard.any() or over.any()) and int(counts.max()) >= least
+
+
+def test_giving_up_on_candidates_costs_a_fraction_of_the_direct_kernel():
+    """Some 10 000 rows of a query within the error of their bounds, in regions that hold them.  With all of them sorted
+    the search took 1.7 times as long as the direct kernel alone."""
+    from paper_2110_08919_amd import lpq
+    from f32_plan import best_ms
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x, q = torch.randn((1_000_000, 128), generator=g, device="cuda"), torch.randn((1, 128), generator=g, device="cuda")
+    x[::100] *= 1e4
+    bad = x.clone()
+    bad[:, 0] = float("nan")               # to the direct kernel, nothing collected
+    assert best_ms(lambda: lpq.search_f32(x, q, 10, "ip")) <= 1.35 * best_ms(lambda: lpq.search_f32(bad, q, 10, "ip"))
