@@ -197,7 +197,10 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     // each XCD gets a contiguous range of (split, query tile) pairs: the query tiles of a split share its L2
     const int S = o.S, total = o.qtiles * S, per = total / 8, b = blockIdx.x;
     const int wk = (b < per * 8) ? (b % 8) * per + b / 8 : b;
-    const int s = wk / o.qtiles, qt = wk % o.qtiles;
+    // ... in another order for each split: the second scan has work for some of the tiles only, and workgroups go to the
+    // shader engines in turn, free or not (1M x 128, 1000 queries, 3 of 8 tiles hard: 743 us
+    // with the same order for all, as long as for 6 tiles; 482 now)
+    const int s = wk / o.qtiles, qt = (wk + s) % o.qtiles;
 
     float *nx = reinterpret_cast<float *>(smem + 2 * STAGE);       // [4][256] squared norms, by tile & 3
     float *thr_l = nx + 4 * TILE_ROWS;                             // [QT]
