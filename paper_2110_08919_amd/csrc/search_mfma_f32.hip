@@ -122,8 +122,8 @@ struct FilterIo {
 constexpr int FDUMPS = 32;
 // Control words of a workgroup of the scan, in LDS: queries that are done (their region has overflowed, or the slot holds
 // none), what wave 0 has said of them, whether a row is lost to both scans, the sum and number of the queries' scales,
-// and whether rows were set aside, how many by each wave of the first scan, and which.
-enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_HUGE = 3, CTL_SCALES = 4, CTL_SCALED = 5, CTL_ANY = 6, CTL_ASIDE = 8 /* [FW] */,
+// whether rows were set aside, the number of hard tiles, and how many rows each wave of the first scan has set aside, and which.
+enum { CTL_DONE = 0, CTL_SAID = 1 /* [2] */, CTL_HUGE = 3, CTL_SCALES = 4, CTL_SCALED = 5, CTL_ANY = 6, CTL_HARD = 7, CTL_ASIDE = 8 /* [FW] */,
        CTL_ROWS = CTL_ASIDE + FW /* [FW][ASIDE] */, CTL_WORDS = CTL_ROWS + FW * ASIDE };
 constexpr int ALL_LOST = 1 << 20;     // in CTL_DONE: a row was seen that the bounds do not hold for
 constexpr size_t filter_lds_bytes(int wq, bool seed, bool fp16)
@@ -217,13 +217,20 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     }
     // FP16: the tile's rows are scaled by two to the mean of its queries' scales
     int xe = 0;
+    // More than a quarter of the tiles are hard: the others are left to the second scan, too, which takes two rounds of
+    // workgroups for all.  Up to a quarter one round is enough, beyond, it may be two behind the first scan: 1M x 128, some tiles hard and
+    // all, ms: 3000 queries, 6 of 24 2.3, 8 2.2 or 3.4, 10 3.6, all 2.8; 5000, 10 of 40 4.1, 12 4.0 or 6.1, all 4.6.
+    bool leave = false;
     if (!SEED && FP16) {
         const float mean = *o.nxsum * o.nxper;
         for (int i = tid; i < QT; i += FW * 64) {
             const int e = o.qe[q_tile + i];
             if (e != NO_SCALE) { atomicAdd(&ctl[CTL_SCALES], e); atomicAdd(&ctl[CTL_SCALED], 1); }
         }
+        for (int64_t i = tid; 128 * i < o.nq; i += FW * 64)
+            if (o.hard[i]) atomicAdd(&ctl[CTL_HARD], 1);
         __syncthreads();
+        leave = 4 * ctl[CTL_HARD] > (o.nq + 127) >> 7;
         const int scaled = ctl[CTL_SCALED];
         xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
         if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && mean <= NEAR_ONE_ROWS) xe = 0;
@@ -246,7 +253,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
                     // (a norm of up to 2^-50 taken as zero is off by 2^-50 |x| <= 2^(-35 - xe), scaled by 2^2 xe)
                     const bool zero = o.qe[q] == NO_SCALE;
                     const int e = zero ? xe : o.qe[q];
-                    if (e - xe > HALF_RANGE || xe - e > HALF_RANGE || (zero && xe > ZERO_SCALE)) {
+                    if (e - xe > HALF_RANGE || xe - e > HALF_RANGE || (zero && xe > ZERO_SCALE) || leave) {
                         mine = false;
                         atomicOr(&o.again[q], AGAIN);
                     } else {

@@ -121,10 +121,25 @@ def _some_hard(rows):
 
 @pytest.mark.gpu
 def test_a_few_hard_queries_cost_no_more_than_the_second_scan_of_all():
-    """A few of 1000 queries hard, in 3 or 4 of 8 tiles: 1.36 times as long as with all of them hard when the workgroups with
-    work met on half of the shader engines, 0.95 now."""
+    """A few of 1000 queries hard, in 3 of 8 tiles: 1.36 times as long as with all of them hard when the workgroups with work met
+    on half of the shader engines."""
     import f32_plan
     from paper_2110_08919_amd import lpq
     x, few = _some_hard(range(64, 1000, 128))
     _, every = _some_hard(range(1000))
     assert f32_plan.best_ms(lambda: lpq.search_f32(x, few, 10, "l2sq")) <= 1.15 * f32_plan.best_ms(lambda: lpq.search_f32(x, every, 10, "l2sq"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tiles,left", [((3,), 0), ((0, 7), 0), ((1, 2, 6), 616), ((0, 1, 2, 3, 4, 6), 232), (range(8), 0)])
+def test_queries_beside_many_hard_tiles_are_left_to_the_second_scan(tiles, left):
+    import f32_plan
+    from paper_2110_08919_amd import lpq
+    from test_gpu_f32_filter import _direct, _same_bits
+    x, q = _some_hard([128 * t + i for t in tiles for i in range(40)])
+    x = x[:260_000].contiguous()
+    got, p, ws = f32_plan.search(x, q, 10, "l2sq")
+    _same_bits(got, _direct(lpq, x, q, 10, "l2sq"))
+    hard = f32_plan.words(p, ws, "off_hard", 8)
+    assert hard.nonzero().flatten().tolist() == list(tiles)
+    assert int((f32_plan.words(p, ws, "off_again", 1000) != 0).sum()) == left
