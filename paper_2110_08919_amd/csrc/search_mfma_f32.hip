@@ -45,7 +45,7 @@
 // the first one's error (hard), and queries that overflowed in the first.  1M x 128 shifted by 30 or 100 (inner
 // product, all hard) 0.90 / 1.00 -> 0.86 / 0.92 ms.
 //
-// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 0.91 -> 0.44 ms (with the split alone; 8.3 with the direct
+// Measured (whole search, k = 10, L2): 1M x 128, 1000 queries 0.91 -> 0.43 ms (with the split alone; 8.3 with the direct
 // kernel alone), 64 queries 0.156 -> 0.139, 256 0.29 -> 0.18; 1M x 96, 1000 0.75 -> 0.42; 300 000 x 771, 1000
 // 2.53 -> 0.89; 200 000 x 128, 10 000 2.03 -> 1.04; 2M x 24, 2000 1.81 -> 1.00.
 //
@@ -54,7 +54,7 @@
 // and written to LDS as one fp16 or two bf16 planes, their squared norms summed on the way; the queries, rounded or
 // split once per search, are copied asynchronously.  Bound by the vector work that the two waves of a SIMD do in step
 // (rounding and norms between the matrix instructions of a stage's first half, the epilogue of a tile behind its last:
-// 34 % of the first scan's cycles, next to 30 % with the matrix pipe busy) and by the barrier of each stage.
+// 34 % of the first scan's cycles, next to 33 % with the matrix pipe busy) and by the barrier of each stage.
 #include <cmath>
 #include <type_traits>
 
