@@ -22,19 +22,31 @@ __device__ inline void block_bitonic_sort(cand_t *buf, int cap)
     }
 }
 
-// Compacts a candidate buffer that may overflow on the next step: sort, keep the best k,
-// tighten the threshold to the k-th best.  Must be reached by all threads of the block;
-// `need` is the largest number of appends one step can make.
-__device__ inline void block_compact_if_full(cand_t *buf, int cap, int k, int need, int *s_count, cand_t *s_thr)
+// A buffer that all threads of a block append to, in steps with one barrier each.  Behind the barrier every thread has to
+// come to the same answer whether the buffer is compacted, while faster waves may already append in the next step: even and
+// odd steps have a counter each, which is read before the next barrier and written again behind it only.  Neither is ever
+// cleared; `before` is what the step's counter stood at, `after` the other one.
+struct AppendSteps {
+    int held = 0, turn = 0, before = 0, after = 0;
+    __device__ __forceinline__ void step_done(int count)      // the step's counter, read behind its barrier
+    {
+        held += count - before;
+        before = after;
+        after = count;
+        turn ^= 1;
+    }
+};
+
+// Compacts such a buffer if the next step could overflow it: sort, keep the best k, tighten the threshold to the k-th best.
+// Must be reached by all threads of the block; `held` candidates are in it, the same number in every thread, and `need` is
+// the largest number of appends one step can make.
+__device__ inline void block_compact_if_full(cand_t *buf, int cap, int k, int need, int &held, cand_t *s_thr)
 {
-    if (*s_count + need > cap) {  // uniform: the count is stable after the caller's barrier
+    if (held + need > cap) {
         block_bitonic_sort(buf, cap);
-        const int cnt = *s_count < k ? *s_count : k;
-        for (int i = cnt + threadIdx.x; i < cap; i += blockDim.x) buf[i] = CAND_NONE;
-        if (threadIdx.x == 0) {
-            if (cnt == k && buf[k - 1] < *s_thr) *s_thr = buf[k - 1];
-            *s_count = cnt;
-        }
+        held = held < k ? held : k;
+        for (int i = held + threadIdx.x; i < cap; i += blockDim.x) buf[i] = CAND_NONE;
+        if (threadIdx.x == 0 && held == k && buf[k - 1] < *s_thr) *s_thr = buf[k - 1];
         __syncthreads();
     }
 }

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);                 // [QT][cap]
     float *qs = reinterpret_cast<float *>(buf + (size_t)QT * cap);  // [QT][dp]
-    __shared__ int s_count[QT];
+    __shared__ int s_count[2][QT];
     __shared__ cand_t s_thr[QT];
 
     // Workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of (split,
@@ -77,10 +77,17 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
         qs[i] = (c < d && q0 + j < nq) ? qv[(q0 + j) * ldq + c] : 0.0f;
     }
     for (int i = threadIdx.x; i < QT * cap; i += F32_THREADS) buf[i] = CAND_NONE;
-    if (threadIdx.x < QT) { s_count[threadIdx.x] = 0; s_thr[threadIdx.x] = CAND_NONE; }
+    if (threadIdx.x < QT) s_thr[threadIdx.x] = CAND_NONE;
+    if (threadIdx.x < 2 * QT) s_count[0][threadIdx.x] = 0;
     __syncthreads();
 
     const int sub = threadIdx.x & 7, grp = threadIdx.x >> 3;
+    // which of the finished sums below are this lane's: all of one query's, whose buffer `at` is about
+    constexpr int NACC = QT * F32_R;
+    constexpr int PER = NACC >= 8 ? NACC / 8 : 1;
+    static_assert(F32_R % PER == 0 && 8 % QT == 0, "a lane's sums are one query's, and every query has lanes of the eight");
+    const int first = NACC >= 8 ? sub * PER : (sub >> 1), jl = first / F32_R;
+    AppendSteps at;
     for (int64_t base = rs; base < re; base += F32_STEP) {
         float acc[QT][F32_R];
 #pragma unroll
@@ -144,8 +151,6 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
         // exchange costs QT * F32_R - 1 shuffles in all (not 3 per sum) and the finished sums end up
         // spread over the lanes: lane `sub` owns sums [sub * PER, sub * PER + PER) in (query, row)
         // order, and tests them against its queries' thresholds.
-        constexpr int NACC = QT * F32_R;
-        constexpr int PER = NACC >= 8 ? NACC / 8 : 1;
         float red[NACC];
 #pragma unroll
         for (int j = 0; j < QT; ++j)
@@ -156,24 +161,28 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
         halve_sums<(NACC > 3 ? NACC / 4 : 1), DPP_XOR1>(red, (sub & 1) != 0);
         // NACC >= 8: lane sub holds sums sub * PER + i.  NACC = 4 (one query): after the two halving
         // steps lanes 2p and 2p + 1 both hold sum p; the even lane acts.
-        const int first = NACC >= 8 ? sub * PER : (sub >> 1);
         const bool acts = NACC >= 8 || (sub & 1) == 0;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int idx = first + i, j = idx / F32_R, r = idx % F32_R;
+            const int r = (first + i) % F32_R;
             const int64_t row = base + r * F32_ROWS + grp;
             if (acts && row < re) {
                 const float a = red[i];
                 const cand_t c = make_cand(float_to_sortable(l2 ? a : -a), (uint32_t)row);
-                if (c < s_thr[j]) {
-                    const int pos = atomicAdd(&s_count[j], 1);
-                    buf[(size_t)j * cap + pos] = c;
+                if (c < s_thr[jl]) {
+                    const int pos = at.held - at.before + atomicAdd(&s_count[at.turn][jl], 1);
+                    buf[(size_t)jl * cap + pos] = c;
                 }
             }
         }
         __syncthreads();
+        at.step_done(s_count[at.turn][jl]);
 #pragma unroll
-        for (int j = 0; j < QT; ++j) block_compact_if_full(buf + (size_t)j * cap, cap, k, F32_STEP, &s_count[j], &s_thr[j]);
+        for (int j = 0; j < QT; ++j) {
+            int h = __builtin_amdgcn_readlane(at.held, j * (8 / QT));   // of a lane of query j
+            block_compact_if_full(buf + (size_t)j * cap, cap, k, F32_STEP, h, &s_thr[j]);
+            at.held = jl == j ? h : at.held;
+        }
     }
     for (int j = 0; j < QT; ++j) {
         block_bitonic_sort(buf + (size_t)j * cap, cap);

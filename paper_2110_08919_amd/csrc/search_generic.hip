@@ -30,11 +30,10 @@ __device__ __forceinline__ void generic_scan(const SearchArgs &a, int64_t rs, in
     const int xchunks = a.packed ? chunks >> 1 : chunks;
     const int64_t row_bytes = a.packed ? a.d_pad >> 1 : a.d_pad;
     for (int i = threadIdx.x; i < cap; i += GEN_THREADS) buf[i] = CAND_NONE;
-    if (threadIdx.x == 0) {
-        *s_count = 0;
-        *s_thr = seeds ? seeds[q] : CAND_NONE;
-    }
+    if (threadIdx.x < 2) s_count[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *s_thr = seeds ? seeds[q] : CAND_NONE;
     __syncthreads();
+    AppendSteps at;
 
     const int sub = threadIdx.x & 7, grp = threadIdx.x >> 3;
     for (int64_t base = rs; base < re; base += GEN_ROWS) {
@@ -72,12 +71,13 @@ __device__ __forceinline__ void generic_scan(const SearchArgs &a, int64_t rs, in
             const int32_t key = (l2 ? a.norms[row] : 0) - 2 * dot;  // see cand_t
             const cand_t c = make_cand(key, (uint32_t)row);
             if (c < *s_thr) {
-                const int pos = atomicAdd(s_count, 1);
+                const int pos = at.held - at.before + atomicAdd(&s_count[at.turn], 1);
                 buf[pos] = c;
             }
         }
         __syncthreads();
-        block_compact_if_full(buf, cap, a.k, GEN_ROWS, s_count, s_thr);
+        at.step_done(__builtin_amdgcn_readfirstlane(s_count[at.turn]));
+        block_compact_if_full(buf, cap, a.k, GEN_ROWS, at.held, s_thr);
     }
     block_bitonic_sort(buf, cap);
     for (int i = threadIdx.x; i < a.k; i += GEN_THREADS) out[i] = buf[i];
@@ -91,13 +91,13 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);
     uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
-    __shared__ int s_count;
+    __shared__ int s_count[2];
     __shared__ cand_t s_thr;
     const int64_t q = blockIdx.x / S;
     const int s = blockIdx.x % S;
     const int64_t rs = row0 + (int64_t)s * split_rows;
     const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
-    generic_scan(a, rs, re, q, seeds, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
+    generic_scan(a, rs, re, q, seeds, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, s_count, &s_thr);
 }
 
 // 64-bit minimum over the wave; every lane gets the result.
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);
     uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
-    __shared__ int s_count, s_last;
+    __shared__ int s_count[2], s_last;
     __shared__ cand_t s_thr;
     const bool many = *first.count > first_max;             // same for every thread of the grid
     if (many && !last.queries) return;                      // another kernel takes them
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
         const int s = (int)(item % S);
         const int64_t rs = row0 + (int64_t)s * split_rows;
         const int64_t re = (rs + split_rows < row1) ? rs + split_rows : row1;
-        generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, &s_count, &s_thr);
+        generic_scan(a, rs, re, q, nullptr, lists + ((int64_t)q * S + s) * a.k, cap, buf, qs, s_count, &s_thr);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's part of the list has reached the L2 ...
         __syncthreads();
         if (threadIdx.x == 0) {
