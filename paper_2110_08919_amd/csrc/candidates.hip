@@ -8,6 +8,8 @@
 // rerank_f32_kernel: second stage that recovers the recall lost to quantization (the 2-6 % of
 // Section 5.3): exact distances of each query's kc candidates on the original fp32 vectors,
 // accumulated in binary64, sorted by (distance, id), the k best written out.
+#include <type_traits>
+
 #include "lpq_internal.h"
 
 namespace lpq {
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(GD_THREADS) void gather_dist_kernel(
 }
 
 // ---------------------------------------------------------------------- re-rank ----
-constexpr int RR_THREADS = 256, RR_ROWS = 4;
+constexpr int RR_THREADS = 256, RR_ROWS = 4, RR_COUNTED = 128, RR_SHORT = 16;
 
 __device__ __forceinline__ unsigned long long double_to_sortable(double v)
 {
@@ -110,6 +112,9 @@ __device__ __forceinline__ double sortable_to_double(unsigned long long u)
     return __longlong_as_double((long long)u);
 }
 
+// SHORT: rows of up to RR_SHORT features, one at a time and sorted: fewer registers let more workgroups run at a time (with
+// four rows 1565 queries of 109 candidates, d = 13, took 19 us, 13 so; their distances tie, too), and there is little to be gained.
+template <bool SHORT>
 __global__ __launch_bounds__(RR_THREADS) void rerank_f32_kernel(
     const float *__restrict__ x, int64_t n, int64_t ldx, const float *__restrict__ q, int64_t ldq, int d,
     const int32_t *__restrict__ cand, int kc, int cap, int k, int metric, int32_t *__restrict__ ids,
@@ -122,17 +127,18 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_f32_kernel(
     const float *qr = q + qi * ldq;
     const bool l2 = metric == LPQ_METRIC_L2SQ;
     const int sub = threadIdx.x & 7, grp = threadIdx.x >> 3;
-    // Eight lanes per row, every eighth value each in ascending order; RR_ROWS rows and four values of each at a time
+    // Eight lanes per row, every eighth value each in ascending order; up to RR_ROWS rows and four values of each at a time
     // (with one value of one row in flight, and a sorting network of 28 steps behind, 1000 queries of 100 candidates, d = 128,
     // took 28 us; 22 now, most of it two trips to rows far apart in memory).
-    for (int j0 = grp; j0 < cap; j0 += RR_ROWS * (RR_THREADS / 8)) {
-        const float *xr[RR_ROWS];
-        int32_t id[RR_ROWS];
-        bool live[RR_ROWS];
-        double s[RR_ROWS];
+    auto sums = [&](int j0, auto rows) {
+        constexpr int ROWS = decltype(rows)::value;
+        const float *xr[ROWS];
+        int32_t id[ROWS];
+        bool live[ROWS];
+        double s[ROWS];
 #pragma unroll
-        for (int r = 0; r < RR_ROWS; ++r) {
-            const int j = j0 + r * (RR_THREADS / 8);
+        for (int r = 0; r < ROWS; ++r) {
+            const int j = j0 + r * (RR_THREADS / 8) + grp;
             id[r] = (j < kc) ? cand[qi * kc + j] : -1;
             live[r] = id[r] >= 0 && (int64_t)id[r] < n;
             xr[r] = live[r] ? x + (int64_t)id[r] * ldx : qr;      // (nothing there: any row)
@@ -145,35 +151,43 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_f32_kernel(
         };
         int t = sub;
         for (; t + 24 < d; t += 32) {
-            float qv[4], xv[RR_ROWS][4];
+            float qv[4], xv[ROWS][4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) qv[u] = qr[t + 8 * u];
 #pragma unroll
-            for (int r = 0; r < RR_ROWS; ++r)
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) xv[r][u] = xr[r][t + 8 * u];
 #pragma unroll
-            for (int r = 0; r < RR_ROWS; ++r)
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) add(r, qv[u], xv[r][u]);
         }
         for (; t < d; t += 8) {
             const float qv = qr[t];
 #pragma unroll
-            for (int r = 0; r < RR_ROWS; ++r) add(r, qv, xr[r][t]);
+            for (int r = 0; r < ROWS; ++r) add(r, qv, xr[r][t]);
         }
 #pragma unroll
-        for (int r = 0; r < RR_ROWS; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             s[r] += __shfl_xor(s[r], 4, 64);
             s[r] += __shfl_xor(s[r], 2, 64);
             s[r] += __shfl_xor(s[r], 1, 64);
-            const int j = j0 + r * (RR_THREADS / 8);
-            if (sub == 0 && j < cap) {
+            const int j = j0 + r * (RR_THREADS / 8) + grp;
+            if (sub == 0 && j < kc) {
                 key[j] = live[r] ? double_to_sortable(l2 ? s[r] : -s[r]) : ~0ull;
                 idv[j] = live[r] ? id[r] : INT32_MAX;   // absent entries sort last
             }
         }
+        return j0 + ROWS * (RR_THREADS / 8);
+    };
+    for (int j0 = 0; SHORT && j0 < kc;) j0 = sums(j0, std::integral_constant<int, 1>());
+    for (int j0 = 0; !SHORT && j0 < kc;) {
+        const int left = (kc - j0 + RR_THREADS / 8 - 1) / (RR_THREADS / 8);
+        j0 = left > 2 ? sums(j0, std::integral_constant<int, RR_ROWS>())
+                             : (left == 2 ? sums(j0, std::integral_constant<int, 2>()) : sums(j0, std::integral_constant<int, 1>()));
     }
+    for (int j = kc + threadIdx.x; j < cap; j += RR_THREADS) { key[j] = ~0ull; idv[j] = INT32_MAX; }
     __syncthreads();
     auto emit = [&](int r, bool have, unsigned long long kr, int32_t ir) {
         ids[qi * k + r] = have ? ir : -1;
@@ -181,20 +195,26 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_f32_kernel(
         if (have) { const double s = sortable_to_double(kr); v = (float)(l2 ? s : -s); }
         dists[qi * k + r] = v;
     };
-    if (kc <= RR_THREADS) {   // a thread per candidate counts those before it: one barrier instead of 28 for 128
+    // A thread per candidate counts those before it by the upper halves of the keys, one barrier instead of 28 for 128, unless
+    // two agree in them.  (Beyond RR_COUNTED the sort is faster: 4964 queries of 198 candidates, d = 105, 74 us, counted 95; 3000
+    // of 250, d = 40, 46 and 71.)
+    if (!SHORT && kc <= RR_COUNTED) {
         const int i = threadIdx.x;
+        const uint32_t *upper = reinterpret_cast<const uint32_t *>(key) + 1, mine = i < kc ? upper[2 * i] : 0u;
+        int r = 0, equal = 0;
         if (i < kc) {
-            const unsigned long long me = key[i];
-            const int32_t mine = idv[i];
-            int r = 0;
+#pragma unroll 8
             for (int j = 0; j < kc; ++j) {
-                const unsigned long long other = key[j];
-                r += other < me || (other == me && (idv[j] < mine || (idv[j] == mine && j < i)));
+                const uint32_t other = upper[2 * j];
+                r += other < mine;
+                equal += other == mine;
             }
-            if (r < k) emit(r, me != ~0ull, me, mine);
         }
-        for (int r = kc + threadIdx.x; r < k; r += RR_THREADS) emit(r, false, 0ull, 0);
-        return;
+        if (!__syncthreads_or(equal > 1)) {
+            if (i < kc && r < k) emit(r, key[i] != ~0ull, key[i], idv[i]);
+            for (r = kc + i; r < k; r += RR_THREADS) emit(r, false, 0ull, 0);
+            return;
+        }
     }
     // ascending bitonic sort of (key, id) pairs
     for (int size = 2; size <= cap; size <<= 1)
@@ -235,8 +255,8 @@ hipError_t launch_rerank_f32(const float *x, int64_t n, int64_t ldx, const float
     if (nq <= 0) return hipSuccess;
     const int cap = next_pow2(kc < 32 ? 32 : kc);   // a whole number of 32-candidate passes
     if (cap > 4096) return hipErrorInvalidValue;
-    rerank_f32_kernel<<<(unsigned)nq, RR_THREADS, (size_t)cap * 12, st>>>(x, n, ldx, q, ldq, d, cand, kc, cap, k, metric,
-                                                                         ids, dists);
+    auto kern = d <= RR_SHORT ? rerank_f32_kernel<true> : rerank_f32_kernel<false>;
+    kern<<<(unsigned)nq, RR_THREADS, (size_t)cap * 12, st>>>(x, n, ldx, q, ldq, d, cand, kc, cap, k, metric, ids, dists);
     return hipGetLastError();
 }
 
