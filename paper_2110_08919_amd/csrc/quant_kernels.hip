@@ -671,7 +671,7 @@ __global__ __launch_bounds__(QW_THREADS) void quantile_window_kernel(const float
 // what falls into a window goes to a short list in LDS first and from there, with one global atomic per
 // column and target, to the column's list.
 constexpr int QW_LOCAL = 32;
-constexpr int QW_MANY = 8;        // of a lane's 16 values, where its wave looks for equal ones
+constexpr int QW_MANY = 8;        // of a lane's 16 values, from where its wave looks for those that no list takes
 template <bool VEC>
 __global__ __launch_bounds__(1024, 8) void quantile_gather_kernel(const float *__restrict__ x, int64_t n, int64_t ld, int d, int lpr,
                                                                int64_t rows_per_block, const uint32_t *__restrict__ qwin,
@@ -694,9 +694,10 @@ __global__ __launch_bounds__(1024, 8) void quantile_gather_kernel(const float *_
     bool bad = false;
     // What lies between the two windows of its column, almost every value, needs nothing: two compares, in which a value
     // that is not a number fails, as everything does against the open end of a window.  The others are worked off one per
-    // lane at a time, whichever each lane's next one is; but many equal values at the ends of what lies between (zeros, for
-    // one) are counted beforehand, four of a column at a time.  (One at a time, 1M x 128 with 90 % zeros: the call 0.36 ms, with
-    // two compares per value in every pass 0.27, now 0.21; half zeros 0.31, 0.25 and 0.21.)
+    // lane at a time, whichever each lane's next one is; but where some lane has many of them, those that no list
+    // takes are counted beforehand, four of a column at a time: outside both windows, or equal to an end of what lies between
+    // (zeros, for one).  (One at a time, clip 0.001, 1M x 128 with 90 % zeros: the call 0.36 ms, with two compares per value in
+    // every pass 0.27, now 0.23; half zeros 0.31, 0.25 and 0.23; clip 0.4, 3578 x 101 158, 146 and 140 us.)
     float mid_lo[4], mid_hi[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -728,30 +729,27 @@ __global__ __launch_bounds__(1024, 8) void quantile_gather_kernel(const float *_
             rest = 2u * rest + (plain ? 0u : 1u);                          // value i in bit 4 U - 1 - i
         }
         if (__ballot(__popc(rest) >= QW_MANY)) {
-            uint32_t ties = 0u;
 #pragma unroll
-            for (int i = 0; i < 4 * U; ++i) {
-                const float f = v[i >> 2][i & 3];
-                ties = 2u * ties + (f == mid_lo[i & 3] || f == mid_hi[i & 3] ? 1u : 0u);
-            }
-            if (__ballot(__popc(ties) >= QW_MANY / 2)) {
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t *const low = s_win[4 * jl + e], *const high = s_win[128 + 4 * jl + e];
+                const uint32_t first = low[0], last = low[0] + low[1], first1 = high[0], last1 = high[0] + high[1];
+                uint32_t below = 0u, at_last = 0u, at_first1 = 0u, above = 0u;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t *const cnt = s_cnt[4 * jl + e], *const win = s_win[4 * jl + e];
-                    const uint32_t last = win[0] + win[1], first = s_win[128 + 4 * jl + e][0];
-                    uint32_t at_last = 0u, at_first = 0u;                  // of the low window, of the high one
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const uint32_t bit = 1u << (4 * (U - u) - 1 - e), key = float_sortable_u32(v[u][e]);
-                        if (!(ties & bit) || key < last || key > first || r + (int64_t)u * rstep >= r1 || (!VEC && c0 + e >= d) ||
-                            !isfinite(v[u][e])) continue;                  // (between the two: one zero next to the other)
-                        rest &= ~bit;
-                        at_last += key == last;
-                        at_first += key == first;
-                    }
-                    if (at_last) atomicAdd(&cnt[win[1] == 0u ? 1 : 2], at_last);
-                    if (at_first) atomicAdd(&s_cnt[128 + 4 * jl + e][1], at_first);
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t bit = 1u << (4 * (U - u) - 1 - e), key = float_sortable_u32(v[u][e]);
+                    const bool lower = key < first && key < first1, upper = key > last1 && key > last, mid = key >= last && key <= first1;
+                    if (!(rest & bit) || !(lower || upper || mid) || r + (int64_t)u * rstep >= r1 || (!VEC && c0 + e >= d) ||
+                        !isfinite(v[u][e])) continue;
+                    rest &= ~bit;
+                    below += lower;
+                    above += upper;
+                    at_last += mid && key == last;
+                    at_first1 += mid && key == first1;
                 }
+                if (below) atomicAdd(&s_cnt[4 * jl + e][3], below);
+                if (at_last) atomicAdd(&s_cnt[4 * jl + e][first == last ? 1 : 2], at_last);
+                if (at_first1) atomicAdd(&s_cnt[128 + 4 * jl + e][1], at_first1);
+                if (above) atomicAdd(&s_cnt[128 + 4 * jl + e][3], above);
             }
         }
         while (rest) {
