@@ -40,3 +40,10 @@ def test_search_in_parts_equals_the_same_queries_searched_apart(n, d, nq, k):
         i, v = lpq.search_f32(x, q[q0:q1], k, "l2sq")
         torch.cuda.synchronize()
         assert torch.equal(ids[q0:q1], i) and torch.equal(dists[q0:q1], v)
+
+
+def test_regions_have_room_for_uneven_filling():
+    """Regions of the fp32 filter that a query is expected to fill by more than half hold 128 candidates, not 64."""
+    import f32_plan
+    assert f32_plan.plan(1_357_103, 9019, 37, 2)["Cs"] == 128
+    assert f32_plan.plan(1_000_000, 1000, 128, 10)["Cs"] == 64
