@@ -203,12 +203,17 @@ __global__ __launch_bounds__(F32_THREADS) void search_f32_kernel(
 // bits.  Bound by barriers and the latency of the rows.  1000 queries on 1M x 128, k = 10: 13 us, where summing all candidates
 // took 37 and selecting among them 29 (sorting the bounds here: 37); k = 100, 700 candidates each: 28.
 constexpr int FIN_CAP = 4096;       // candidates in LDS
-constexpr int FIN_FEW = FIN_CAP / 2, FIN_RANKED = 2 * F32_THREADS, FIN_BINS = F32_THREADS;
+// (ranks of 470 rows, two to a thread, took 16 us, their sort takes 5)
+constexpr int FIN_FEW = FIN_CAP / 2, FIN_RANKED = F32_THREADS, FIN_BINS = F32_THREADS;
 constexpr int FIN_REGIONS = F32_THREADS;
+// A few short rows cost less than finding out which of them matter (8076 x 4, 3764 queries, k = 2 23 us, 13 now; of 500
+// candidates they cost more: 1M x 16, 1000 queries, k = 10, the search 291 us and 302).
+constexpr int FIN_SHORT = 16, FIN_ALL = 128;
 struct FinishIo {
     const float *x, *q;
     int64_t ldx, ldq;
     int d, k, SS, Cs;
+    int cap;                        // FIN_CAP, or as much as the regions can fill: twice a power of two of at least 32
     const int32_t *ccnt;            // [nq][SS]
     const cand_t *cbuf;             // [nq][SS][Cs] (~ image of the score's upper bound without the query's part, row)
     const float *qn;                // [nq] squared norms
@@ -223,8 +228,8 @@ template <bool VEC, bool L2>
 __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    cand_t *buf = reinterpret_cast<cand_t *>(smem);           // [FIN_CAP]
-    float *qs = reinterpret_cast<float *>(buf + FIN_CAP);     // the query, zero beyond d
+    cand_t *buf = reinterpret_cast<cand_t *>(smem);           // [cap]
+    float *qs = reinterpret_cast<float *>(buf + o.cap);       // the query, zero beyond d
     __shared__ int s_more, s_hist[FIN_BINS], s_wave[F32_THREADS / 64], s_cut, s_before;
     __shared__ float s_lo[F32_THREADS / 64], s_hi[F32_THREADS / 64];
     __shared__ cand_t s_kth;
@@ -319,9 +324,11 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
     };
 
     // up to FIN_FEW candidates are kept in LDS, more are read again from their regions
-    const bool kept = total <= FIN_FEW;
-    cand_t *few = kept ? buf + FIN_FEW : buf;                 // the rows that are summed
-    const int room = kept ? FIN_FEW : FIN_CAP, want = k + k / 4 + 6 < total ? k + k / 4 + 6 : total;
+    const int half_cap = o.cap / 2;
+    const bool kept = total <= half_cap;
+    const bool every = total <= FIN_ALL && o.d <= FIN_SHORT;  // all candidates are summed at once
+    cand_t *few = kept && !every ? buf + half_cap : buf;      // the rows that are summed
+    const int room = kept ? half_cap : o.cap, want = k + k / 4 + 6 < total ? k + k / 4 + 6 : total;
     auto each = [&](auto f) {
         if (kept) { for (int i = tid; i < total; i += F32_THREADS) f(buf[i]); }
         else for (int i = part; i < mine; i += 4 * per) {     // four on their way at a time
@@ -332,6 +339,33 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
             for (int u = 0; u < 4; ++u) if (i + u * per < mine) f(c[u]);
         }
     };
+    // the rank of a distance among all
+    auto rank = [&](int i, int count) {
+        const cand_t me = few[i];
+        int r = 0;
+#pragma unroll 8
+        for (int j = 0; j < count; ++j) r += few[j] < me;
+        return r;
+    };
+    auto emit_best = [&](int count) {
+        if (count <= FIN_RANKED) {
+            for (int i = tid; i < count; i += F32_THREADS) {
+                const int r = rank(i, count);
+                if (r < k) emit(few[i], r);
+            }
+        } else {
+            sort(few, count);
+            for (int i = tid; i < k; i += F32_THREADS) emit(few[i], i);
+        }
+    };
+    if (every) {
+        for (int i = part; i < mine; i += per) few[before + upto - mine + i] = regions[(size_t)region * o.Cs + i];
+        __syncthreads();
+        sum_directly(few, 0, total);
+        emit_best(total);
+        if (tid == 0) o.over[q] = 0;
+        return;
+    }
     auto find_cut = [&](int want) {                           // the bin up to which that many are, how many before it
         if (wave == 0) {
             int v[4], sum = 0;
@@ -412,13 +446,6 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
         return;
     }
     sum_directly(few, 0, first);
-    // threads' first two: the rank of a distance among all
-    auto rank = [&](int i, int count) {
-        const cand_t me = few[i];
-        int r = 0;
-        for (int j = 0; j < count; ++j) r += few[j] < me;
-        return r;
-    };
     if (first <= FIN_RANKED) {
         for (int i = tid; i < first; i += F32_THREADS)
             if (rank(i, first) == k - 1) s_kth = few[i];
@@ -448,15 +475,7 @@ __global__ __launch_bounds__(F32_THREADS) void f32_finish_kernel(FinishIo o)
         __syncthreads();
         all = s_more;
     }
-    if (all <= FIN_RANKED) {
-        for (int i = tid; i < all; i += F32_THREADS) {
-            const int r = rank(i, all);
-            if (r < k) emit(few[i], r);
-        }
-    } else {
-        sort(few, all);
-        for (int i = tid; i < k; i += F32_THREADS) emit(few[i], i);
-    }
+    emit_best(all);
     if (tid == 0) o.over[q] = 0;
 }
 
@@ -472,7 +491,7 @@ hipError_t launch_finish(bool vec, bool l2, int64_t nq, const FinishIo &o, hipSt
         if (e != hipSuccess) return e;
         attr_set[which] = true;
     }
-    const size_t lds = FIN_CAP * sizeof(cand_t) + (size_t)((o.d + 3) / 4) * 16;
+    const size_t lds = o.cap * sizeof(cand_t) + (size_t)((o.d + 3) / 4) * 16;
     if (o.SS > FIN_REGIONS || 2 * next_pow2(o.k) > FIN_CAP || lds > 128 * 1024) return hipErrorInvalidValue;
     kern<<<(unsigned)nq, F32_THREADS, lds, st>>>(o);
     return hipGetLastError();
@@ -587,6 +606,10 @@ static hipError_t launch_f32_batch(const float *x, int64_t n, int64_t ldx, const
         o.hard = reinterpret_cast<const int32_t *>(fws + fp.off_hard);
         o.again = reinterpret_cast<const int32_t *>(fws + fp.off_again);
         o.qx = reinterpret_cast<const int32_t *>(fws + fp.off_qx);
+        // (LDS for no more than there can be lets more workgroups run at a time: 100 000 x 64, 10 000
+        // queries, k = 10, six regions of 128: the search 451 -> 427 us)
+        const int64_t most = (int64_t)fp.S2 * fp.Cs;
+        o.cap = most >= FIN_FEW ? FIN_CAP : 2 * next_pow2(most < 32 ? 32 : (int)most);
         o.c = f32_filter_constant(d); o.ch = f32_half_filter_constant(d);
         int32_t *over = reinterpret_cast<int32_t *>(fws + fp.off_over);
         o.over = over; o.ids = ids; o.dists = dists;
