@@ -129,7 +129,7 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_f32_kernel(
     const int sub = threadIdx.x & 7, grp = threadIdx.x >> 3;
     // Eight lanes per row, every eighth value each in ascending order; up to RR_ROWS rows and four values of each at a time
     // (with one value of one row in flight, and a sorting network of 28 steps behind, 1000 queries of 100 candidates, d = 128,
-    // took 28 us; 22 now, most of it two trips to rows far apart in memory).
+    // took 28 us; 20 now, most of it two trips to rows far apart in memory).
     auto sums = [&](int j0, auto rows) {
         constexpr int ROWS = decltype(rows)::value;
         const float *xr[ROWS];
