@@ -523,6 +523,7 @@ struct Plan {
     int mode = PLAN_GENERIC;
     int64_t nq_pad = 0;
     int64_t seed_rows = 0;  // rows of the threshold-seeding pass (0 = none)
+    int rank = 0;           // PLAN_MFMA_COLLECT: the bound of the first scan is the rank-th largest group maximum
     int S1 = 0, S2 = 0;     // corpus splits of the seeding pass and of the main pass
     int SEG = 0;            // PLAN_MFMA_REG: segments per split in the seeding pass
     int G = 0;              // PLAN_MFMA_REG: group maxima per query
@@ -553,6 +554,19 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 constexpr int WIDE_MIN_BITS = 2;
 constexpr int64_t PACKED_BATCH_MIN = 128;  // packed index: larger batches take one collecting scan instead of tiles of 64 queries
 constexpr int REFINE_ROUNDS = 2;        // further rounds of the collecting scan for queries that overflowed (k > 16)
+
+// The bound of a collecting scan is the rank-th largest maximum of its sample.  With rank = k it is certain that k items
+// reach it.  But the k nearest items are in a sample of a share s of the corpus in number like k draws that hit with
+// probability s, and fewer than k items reach the bound only if rank of them or more are: the rank here is that number's
+// mean and as many standard deviations (with the term of its skew) as make it happen in about one batch of a hundred.
+// Such a query is found by its count and searched again, as one whose region overflows is.
+int seed_rank(int64_t n, int64_t rows, int64_t nq, int k)
+{
+    const double s = (double)rows / (double)n, mean = k * s;
+    const double z = 0.905 * std::sqrt(2.0 * std::log(100.0 * (double)(nq > 1 ? nq : 1)));
+    const double r = std::ceil(mean + z * std::sqrt(mean * (1.0 - s)) + (z * z - 1.0) / 6.0 * (1.0 - 2.0 * s) + 1.0);
+    return r < (double)k ? (int)r : k;
+}
 
 // compact: the plan for callers with a fixed workspace whose normal plan does not fit - fewer, larger splits
 // (at least 512 rows), no collecting scan where another kernel needs less room.  Slower, the same results.
@@ -636,19 +650,33 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
             const int64_t by_k = n / 400 * k, least = n / 16, most = k > 512 ? n / 2 : (k > 256 ? n / 4 : n / 8);
             seed = by_k < least ? least : (by_k > most ? most : by_k);
         } else if (p.mode == PLAN_MFMA_COLLECT) {
-            // The sample costs time in proportion to its rows, the candidates it lets through in
-            // proportion to k n / rows: the sum is least at rows ~ sqrt(k n) (coefficient measured:
-            // 125 000 rows at n = 1M, k = 10).  At least k n / 1500, so that the ~1.15 k n / rows
-            // candidates of a query stay well inside the 4096 the selection kernel sorts; at most n / 4.
-            // (Streamed rows: a sampled row costs d / 128 times as much, a candidate no more.)
-            double by_cost = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
-            if (stream && !compact) by_cost *= std::sqrt(128.0 / (double)idx->d);
-            const double by_room = (double)k * (double)n / 1500.0;
-            const double want_rows = by_cost > by_room ? by_cost : by_room;
-            // (k beyond 512: half the corpus, or the ~4.6 k candidates a quarter lets through would not fit;
-            // streamed rows up to two fifths: 33 527 x 904, 7013 queries, k = 76: 0.482 -> 0.450 ms)
+            // The sample costs time in proportion to its rows, the rank n / rows candidates it lets through in proportion
+            // to their number, one as much as 1200 sampled rows of 128 bytes (with 800 and 1700 within 1 % of that on 1M x 128
+            // and 4M x 256, 10 000 queries, k = 10 and 100; with 300 and 2400 2 to 6 % slower).  No more than 1500 candidates
+            // where that can be had, so that they stay well inside the 4096 the selection sorts; at most n / 4.
+            // (k beyond 512: half the corpus; streamed rows up to two fifths: 33 527 x 904, 7013 queries, k = 76: 0.482 -> 0.450 ms)
             const int64_t most = k > 512 ? n / 2 : (stream ? n / 5 * 2 : n / 4);
+            // What is best for the k-th largest maximum goes with sqrt(k n): compact plans keep it, others take no smaller
+            // a sample than lets three quarters more candidates through (the regions would take more memory).
+            double by_k = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
+            if (stream && !compact) by_k *= std::sqrt(128.0 / (double)idx->d);
+            const double by_room = (double)k * (double)n / 1500.0;
+            const double want_rows = by_k > by_room ? by_k : by_room;
             seed = want_rows > (double)most ? most : (int64_t)want_rows;
+            const double per_candidate = 1200.0 * 128.0 / (double)idx->d_pad;
+            const double room = 1.75 * (double)k * (double)n / (double)(seed > 1 ? seed : 1);
+            double best = INFINITY;
+            for (double share = 0.5; !compact && share > 1.0 / 80.0; share *= 0.86) {
+                const int64_t rows = (int64_t)((double)n * share);
+                if (rows > most) continue;
+                if (rows < lo) break;
+                const double candidates = (double)seed_rank(n, rows, nq, k) / share;
+                const double cost = (double)rows + per_candidate * (candidates > 1500.0 ? 100.0 : 1.0) * candidates;
+                if (cost < best && candidates <= room) { best = cost; seed = rows; }
+            }
+            // Codes of few bits tie at the bound, and all that tie are collected: the sample that was best for the
+            // k-th largest maximum (1M x 128, 1000 queries, k = 10, 2 bits: 159 us, 238 with the smaller one).
+            if (idx->bits < 4 && (double)seed < want_rows) seed = want_rows > (double)most ? most : (int64_t)want_rows;
         }
     }
     seed = seed / 256 * 256;
@@ -710,7 +738,12 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     // 30 000 x 128, 100 queries, k = 100: 0.127 -> 0.082; 64 rows gain nothing more.
     // (Packed rows: from 64K items on 128 splits are enough, more only spread the candidates thinner.)
     const int64_t min_rows = p.mode == PLAN_GENERIC ? 2048 : (compact || (idx->packed && n >= 65536) ? 512 : 128);
+    // (A sample of a size asked for keeps the certain bound, and so do row-split launches: the number of candidates is not
+    // what takes their time, and a query too few items pass for costs one of their rounds; and compact plans.)
+    const bool by_rank = p.mode == PLAN_MFMA_COLLECT && !compact && !mfma_row_split(nq, idx->d_pad, idx->packed) &&
+                         tune(LPQ_TUNE_SEED_ROWS) == 0;
     if (seed) {
+        const int rank = by_rank ? seed_rank(n, seed, nq, k) : k;   // of the sample as asked for; it comes out a little larger or smaller
         // group maxima per query: 2 per split and segment (8 when rows are split), at most 2048 (4096 for k > 512)
         // (row-split launches with register lists: up to 128 splits; with 256 the 2048 maxima cost the
         // threshold kernel 3 us more than the pass gains.  Longer lists want the tighter bound: 1543 queries,
@@ -723,7 +756,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
             if (p.S1 > most) p.S1 = most;
             const SampleShape shape = sample_that_covers(n, ceil_div(seed, 256), 16, p.S1);
             p.S1 = shape.splits;
-            p.SEG = mfma_seed_segments(p.S1, k, row_waves);
+            p.SEG = mfma_seed_segments(p.S1, k, rank, row_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
             p.seed_tiles = (int)shape.per_split * p.S1;
             if ((int64_t)p.seed_tiles * 256 > n) p.seed_tiles = (int)(seed / 256);
@@ -733,7 +766,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
             SampleShape shape = {p.S1, ceil_div(seed / 64, p.S1)};
             if (!p.rsplit && !long_scan && !compact) shape = sample_that_covers(n, seed / 64, 8, p.S1);   // runs of 8 rows, see below
             p.S1 = shape.splits;
-            p.SEG = mfma_seed_segments(p.S1, k, p.rs_waves);
+            p.SEG = mfma_seed_segments(p.S1, k, rank, p.rs_waves);
             p.G = mfma_seed_groups(p.S1, p.SEG, p.rs_waves);
             // systematic sample: one stage every seed_stride rows, shared out over the S1 splits
             const int64_t stage_rows = p.rsplit ? 32 * p.rs_waves : (long_scan ? mfma_long_stage_rows(idx->d_pad, nq) : 64);
@@ -759,6 +792,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
         }
     }
     p.seed_rows = seed;
+    p.rank = by_rank ? seed_rank(n, seed, nq, k) : k;
     p.S2 = splits_for(gmode ? n : n - seed, tiles_q, min_rows, slots_now,
                       p.mode == PLAN_MFMA_COLLECT ? (p.rsplit ? 512 : 2048)
                                                   : (p.rsplit ? one_pass : max_lists));   // few queries: one merge pass
@@ -771,7 +805,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
         // least 64, which leaves room for bounds several times looser than expected (a corpus stored
         // in sorted order).  Overflow is caught per query and redone exactly.
         p.SS = mfma_collect_regions(p.S2, p.rs_waves);
-        const double per_region = 1.15 * (double)k * (double)n / (double)seed / p.SS;
+        const double per_region = 1.15 * (double)p.rank * (double)n / (double)seed / p.SS;
         p.expect = (int)(per_region * p.SS + 1.0);
         int64_t cs = 64;
         while ((double)cs < (compact && stream ? 1.5 : 3.0) * per_region && cs < 4096) cs <<= 1;
@@ -871,6 +905,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
     cand_t *lists1 = reinterpret_cast<cand_t *>(ws + p.off_lists1);
     cand_t *seedlist = reinterpret_cast<cand_t *>(ws + p.off_seedlist);
     cand_t *seeds = reinterpret_cast<cand_t *>(ws + p.off_seeds);
+    cand_t *certain = p.mode == PLAN_MFMA_COLLECT ? seedlist : nullptr;   // bounds that k items are sure to reach, one per query
     cand_t *lists2 = reinterpret_cast<cand_t *>(ws + p.off_lists2);
     int32_t *gmax = reinterpret_cast<int32_t *>(ws + p.off_gmax);
 
@@ -903,8 +938,9 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         }
         // (it also clears the counters of the redo lists)
         const bool coll = p.mode == PLAN_MFMA_COLLECT;
-        return launch_seed_finalize(gmax, nq, p.G, k, seeds, st, coll ? reinterpret_cast<int32_t *>(ws + p.off_qlist) + nq : nullptr,
-                                    nullptr, coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
+        return launch_seed_finalize(gmax, nq, p.G, k, coll ? p.rank : k, seeds, certain, st,
+                                    coll ? reinterpret_cast<int32_t *>(ws + p.off_qlist) + nq : nullptr, nullptr,
+                                    coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
                                     coll ? p.rounds : 0, nq + 1);
     };
     if (p.mode == PLAN_MFMA_COLLECT) {
@@ -926,7 +962,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         int32_t *qlist = reinterpret_cast<int32_t *>(ws + p.off_qlist), *qcount = qlist + nq;
         cand_t *bounds2 = p.rounds ? reinterpret_cast<cand_t *>(ws + p.off_bounds2) : nullptr;
         HIP_TRY(launch_collect_select(cbuf, ccnt, nq, p.SS, p.Cs, k, over, qlist, qcount, ids, dist, qnorms, emit_mode, st,
-                                      p.expect, nullptr, nullptr, 0, seeds, bounds2));
+                                      p.expect, nullptr, nullptr, 0, certain, bounds2));
         // Queries whose candidates did not fit are searched again, exactly.  Short lists on short rows: a few
         // by the generic kernel, many (a corpus full of duplicates or ties) by a pass of the register-list
         // kernel over the query tiles that hold one; both are launched and the count on the device decides.
@@ -963,7 +999,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
             ar.rsplit = false;
             ar.wave_queries = 64;
             ar.redo_flags = over; ar.redo_count = qcount; ar.redo_min = REDO_GENERIC_MAX;
-            HIP_TRY(launch_search_mfma(ar, 0, a.n, p.Sr, seeds, lists_r, st));
+            HIP_TRY(launch_search_mfma(ar, 0, a.n, p.Sr, certain, lists_r, st));
             HIP_TRY(launch_merge(lists_r, nq, p.Sr, k, nullptr, nullptr, nullptr, ids, dist, qnorms, emit_mode, st, false,
                                  over, qcount, REDO_GENERIC_MAX + 1, INT32_MAX));
         }

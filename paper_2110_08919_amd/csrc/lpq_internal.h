@@ -188,8 +188,8 @@ hipError_t launch_search_mfma(const SearchArgs &a, int64_t row0, int64_t row1, i
 hipError_t launch_search_mfma_lds(const SearchArgs &a, int64_t row0, int64_t row1, int S, const cand_t *seeds,
                                   cand_t *lists, hipStream_t st);
 // Seeding pass: group maxima gmax[nq_pad][G], G = mfma_seed_groups(S, SEG, rsplit), over the sampled
-// rows (all of them real items), then seeds[q] = bound from the k-th largest group maximum.
-int mfma_seed_segments(int S, int k, int rs_waves);   // rs_waves: waves of a row-split workgroup, 0 = not row-split
+// rows (all of them real items), then seeds[q] = bound from the rank-th largest group maximum.
+int mfma_seed_segments(int S, int k, int rank, int rs_waves);   // rs_waves: waves of a row-split workgroup, 0 = not row-split
 int mfma_seed_groups(int S, int SEG, int rs_waves);      // = G, entries per query in gmax
 int mfma_queries_per_workgroup(int64_t nq, int d_pad, bool wide = false);   // query tile; wide: 128 queries per wave
 bool mfma_collect_wide(int64_t nq, int d_pad);           // collecting mode may use 128 queries per wave
@@ -252,7 +252,8 @@ struct HardQueries {
 // zero_word (optional): one int the kernel also sets to 0 (the counter of the redo list), and zero_more further
 // ones, the i-th at zero_word2 + i * zero_stride.
 // kth_out (optional): the k-th largest maximum itself per query, INT32_MIN where there is none (seeds may then be null).
-hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
+// seeds come from the rank-th largest maximum (rank <= k), certain (optional) from the k-th.
+hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, int rank, cand_t *seeds, cand_t *certain, hipStream_t st,
                                 int32_t *zero_word = nullptr, int32_t *kth_out = nullptr, int32_t *zero_word2 = nullptr,
                                 int zero_more = 0, int64_t zero_stride = 0, const HardQueries &hq = HardQueries());
 

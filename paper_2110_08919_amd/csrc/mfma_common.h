@@ -41,6 +41,14 @@ __device__ __forceinline__ unsigned lds_offset(const void *p)
     return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
+// A systematic sample takes one unit of rows out of every so many; this moves unit number `unit` by 0 .. room rows
+// inside its stretch, so that a corpus stored with a period (the rows of an image, one class after another) is not
+// sampled at the same places of every period.
+__device__ __forceinline__ int64_t sample_shift(unsigned unit, int64_t room)
+{
+    return (int64_t)__umulhi(unit * 0x9E3779B1u, (unsigned)room + 1u);
+}
+
 // s_waitcnt vmcnt(n) with n a run-time value in 0..63 (other counters untouched).  The count is
 // an immediate, split over bits 3:0 and 15:14 of the operand.
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }   // operand of s_waitcnt vmcnt(n)

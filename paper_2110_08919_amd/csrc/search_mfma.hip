@@ -34,10 +34,10 @@
 // Collecting mode (KCAP = 0, for k beyond what fits in registers).  The threshold of a query stays
 // at its seed for the whole scan and a drain appends every exact candidate that beats it to a
 // region of global memory owned by this (query, split[, wave]): no lists, no atomics outside the
-// wave's LDS counters.  The seed threshold is reached by at least k items, so the k best are among
-// the collected ones; a later kernel selects them (or flags a query whose region overflowed for an
-// exact redo: by the generic kernel, or, when many are flagged, by a launch of this kernel in list
-// mode that skips query tiles without a flagged query).  With short rows and many queries a wave
+// wave's LDS counters.  Where at least k items were collected the k best are among them; a later kernel
+// selects them (or flags a query with fewer - its seed was closer than is certain to do, see seed_rank in
+// api.hip - or whose region overflowed for an exact redo: by the generic kernel, or, when many are flagged,
+// by a launch of this kernel in list mode that skips query tiles without a flagged query).  With short rows and many queries a wave
 // holds 128 queries (NB = 4 blocks of 32) instead of 64.
 //
 // Row-split launches (RSPLIT, at most 64 queries).  The four waves (two on rows of more than 128
@@ -442,6 +442,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     constexpr bool CAN_PIECES = SEED && !RSPLIT;
     const bool pieces = CAN_PIECES && o.piece_stride > 0;
     const int64_t piece_gap = pieces ? (int64_t)S * o.piece_stride : 0;   // rows between the pieces of a stage
+    const int64_t shift_room = pieces ? o.piece_stride - 8 : (o.stage_stride ? o.stage_stride - RS : 0);
     int src_off[IPW];   // byte offset of the lane's source chunk relative to the first row of a stage (of its piece)
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -464,8 +465,9 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         int lane_ = lane;                                                                               \
         if (REFORM) LPQ_OPAQUE(lane_);                                                                  \
         const int64_t cin_off = pieces ? (int64_t)(lane_ >> 3) * piece_gap + (lane_ & 7) : (int64_t)wave * 64 + lane_; \
-        const int64_t r0_ = pieces ? ((int64_t)s + (int64_t)S * 8 * st_) * o.piece_stride                \
-                                   : rs + (int64_t)(LPQ_DRY(a) == 7 ? (st_ & 1) : st_) * sstride;       \
+        int64_t r0_ = pieces ? ((int64_t)s + (int64_t)S * 8 * st_) * o.piece_stride                      \
+                             : rs + (int64_t)(LPQ_DRY(a) == 7 ? (st_ & 1) : st_) * sstride;             \
+        if (CAN_PIECES) r0_ += sample_shift((unsigned)(s + S * st_), shift_room);                        \
         const int ring_slot_ = st_ % NST;                                                               \
         const int8_t *src_ = a.codes + r0_ * ROWB;                                                      \
         _Pragma("unroll") for (int j = 0; j < IPW; ++j) {                                               \
@@ -944,7 +946,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
 #define LPQL_ISSUE(ST, SLOT)                                                                            \
     do {                                                                                                \
         const int st_ = (ST), slot_ = (SLOT);                                                           \
-        const int64_t r0_ = rs + (int64_t)st_ * bstride;                                                \
+        int64_t r0_ = rs + (int64_t)st_ * bstride;                                                      \
+        if (SEED) r0_ += sample_shift((unsigned)(s + S * st_), o.stage_stride ? o.stage_stride - RS : 0); \
         const int8_t *src_ = a.codes + r0_ * ROWB;                                                      \
         _Pragma("unroll") for (int j = 0; j < IPW; ++j)                                                 \
             if (NI % NW == 0 || j < mine) {                                                             \
@@ -1173,13 +1176,15 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void search_long_kernel(
     }
 }
 
-// One wave per query: the k-th largest of its G group maxima (duplicates counted) becomes the
-// seed threshold.  Each lane keeps E of the values in registers.  Small k: k times the wave takes
+// One wave per query: the rank-th largest of its G group maxima (duplicates counted) becomes the
+// seed threshold, the k-th the one that is certain to let k items pass.  Bisection for the second starts from the
+// first, and both are few steps on the 200 maxima that k = 100 asks for (10 000 queries 17 us; 39 on 600).  Each lane keeps E of the values in registers.  Small k: k times the wave takes
 // the largest value left and the first lane holding it drops one copy.  Larger k: bisection on
 // the value with wave-wide counts.
 template <int E, bool HARD>
-__global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k,
-                                                            cand_t *__restrict__ seeds, int32_t *__restrict__ zero_word,
+__global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__restrict__ gmax, int64_t nq, int G, int k, int rank,
+                                                            cand_t *__restrict__ seeds, cand_t *__restrict__ certain,
+                                                            int32_t *__restrict__ zero_word,
                                                             int32_t *__restrict__ kth_out, int32_t *__restrict__ zero_word2,
                                                             int zero_more, int64_t zero_stride, HardQueries hq)
 {
@@ -1196,7 +1201,7 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
         const int i = e * 64 + lane;
         v[e] = (i < G) ? gmax[q * G + i] : INT32_MIN;
     }
-    int kth = INT32_MIN;
+    int kth = INT32_MIN, ranked = INT32_MIN;
     if (k <= 24) {
         for (int r = 0; r < k; ++r) {
             int mx = v[0];
@@ -1204,6 +1209,7 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
             for (int e = 1; e < E; ++e) mx = v[e] > mx ? v[e] : mx;
             const int wmx = wave_max_i32(mx);
             kth = wmx;
+            if (r + 1 == rank) ranked = wmx;
             const int win = __ffsll((unsigned long long)__ballot(mx == wmx)) - 1;
             bool done = lane != win;
 #pragma unroll
@@ -1227,18 +1233,24 @@ __global__ __launch_bounds__(256) void seed_finalize_kernel(const int32_t *__res
             mn = a < mn ? a : mn;
             mx = b > mx ? b : mx;
         }
-        long long lo = mn, hi = mx;        // #{v >= lo} = all >= k; the answer lies in [lo, hi]
-        while (lo < hi) {                  // wave-uniform
-            const long long mid = lo + (hi - lo + 1) / 2;
-            int cnt = 0;
+        auto largest = [&](long long lo, int wanted) {   // #{v >= lo} >= wanted; the answer lies in [lo, mx]
+            long long hi = mx;
+            while (lo < hi) {                  // wave-uniform
+                const long long mid = lo + (hi - lo + 1) / 2;
+                int cnt = 0;
 #pragma unroll
-            for (int e = 0; e < E; ++e) cnt += __popcll(__ballot(v[e] >= (int)mid));
-            if (cnt >= k) lo = mid; else hi = mid - 1;
-        }
-        kth = (int)lo;
+                for (int e = 0; e < E; ++e) cnt += __popcll(__ballot(v[e] >= (int)mid));
+                if (cnt >= wanted) lo = mid; else hi = mid - 1;
+            }
+            return (int)lo;
+        };
+        kth = largest(mn, k);
+        ranked = rank < k ? largest(kth, rank) : kth;
     }
     // at least k items have E >= kth, hence key <= -2 kth
-    if (lane == 0 && seeds) seeds[q] = (G < k || kth == INT32_MIN) ? CAND_NONE : make_cand(-2 * kth, 0xFFFFFFFFu);
+    auto bound = [&](int at) { return (G < k || at == INT32_MIN) ? CAND_NONE : make_cand(-2 * at, 0xFFFFFFFFu); };
+    if (lane == 0 && seeds) seeds[q] = bound(ranked);
+    if (lane == 0 && certain) certain[q] = bound(kth);
     if (lane == 0 && kth_out) kth_out[q] = G < k ? INT32_MIN : kth;
     if (HARD) {
         const float at = sortable_to_float(kth) - hq.c * hq.qn[q] - hq.cx * *hq.nxsum;
@@ -1494,11 +1506,13 @@ int mfma_collect_regions(int S, int rs_waves) { return S * (rs_waves ? rs_waves 
 
 int mfma_seed_groups(int S, int SEG, int rs_waves) { return S * SEG * (rs_waves ? 2 * rs_waves : 2); }
 
-int mfma_seed_segments(int S, int k, int rs_waves)
+int mfma_seed_segments(int S, int k, int rank, int rs_waves)
 {
     const int per = rs_waves ? 2 * rs_waves : 2;   // groups a split contributes per segment
-    int seg = (int)ceil_div(6 * k, per * S);   // >= 6k groups: the k-th largest is then close to
-    if (seg < 1) seg = 1;                      // the k-th best item of the seeded rows
+    // >= 6 rank groups: the rank-th largest is then close to the rank-th best item of the sampled rows; >= 2 k: a looser
+    // k-th largest (about the 1.4 k-th best item) does for the queries whose rank-th let too few items pass
+    int seg = (int)ceil_div(6 * rank > 2 * k ? 6 * rank : 2 * k, per * S);
+    if (seg < 1) seg = 1;
     const int most = k > 512 ? 4096 : 2048;    // (k beyond 512: with 2048 groups or fewer the k-th largest
     while (per * S * seg > most && seg > 1) --seg;   // maximum sits far below the k-th best sampled item)
     return seg;
@@ -1531,14 +1545,14 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
     return launch_any(a, row0, row1, S, o, st);
 }
 
-hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, cand_t *seeds, hipStream_t st,
+hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, int rank, cand_t *seeds, cand_t *certain, hipStream_t st,
                                 int32_t *zero_word, int32_t *kth_out, int32_t *zero_word2, int zero_more, int64_t zero_stride,
                                 const HardQueries &hq)
 {
     if (nq <= 0) return hipSuccess;
     if (G > 4096) return hipErrorInvalidValue;
     const unsigned blocks = (unsigned)ceil_div(nq, (int64_t)4);
-    auto launch = [&](auto kern) { kern<<<blocks, 256, 0, st>>>(gmax, nq, G, k, seeds, zero_word, kth_out, zero_word2, zero_more, zero_stride, hq); };
+    auto launch = [&](auto kern) { kern<<<blocks, 256, 0, st>>>(gmax, nq, G, k, rank, seeds, certain, zero_word, kth_out, zero_word2, zero_more, zero_stride, hq); };
     const bool hard = hq.flags != nullptr;
     if (G <= 256) launch(hard ? seed_finalize_kernel<4, true> : seed_finalize_kernel<4, false>);
     else if (G <= 512) launch(hard ? seed_finalize_kernel<8, true> : seed_finalize_kernel<8, false>);

@@ -786,7 +786,7 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     while ((int64_t)p.seed_tiles * TILE_ROWS > n) p.seed_tiles -= p.S1;
     if (p.seed_tiles < 1) return p;
     p.run_stride = n / (16 * (int64_t)p.seed_tiles);
-    p.SEG = mfma_seed_segments(p.S1, k, row_waves);
+    p.SEG = mfma_seed_segments(p.S1, k, k, row_waves);
     p.G = mfma_seed_groups(p.S1, p.SEG, row_waves);
     if (p.G < k || p.G > 4096) return p;
     const int64_t tiles = ceil_div(n, TILE_ROWS);
@@ -853,7 +853,7 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
     // query is left to the second scan (regions hold three times what the sample lets expect, so it would overflow).
     const float c2 = 0.5f * (o.c + o.ch) * 1.00001f;
     const HardQueries hq = {qn, nxsum, c2, c2 * o.nxper, p.half ? 2 * k + 8 : 0, hard};
-    e = launch_seed_finalize(gmax, nq, p.G, k, nullptr, st, nullptr, kth, nullptr, 0, 0, hq);
+    e = launch_seed_finalize(gmax, nq, p.G, k, k, nullptr, nullptr, st, nullptr, kth, nullptr, 0, 0, hq);
     if (e != hipSuccess) return e;
     // scans: every item whose upper bound reaches the k-th lower bound
     o.S = p.S2; o.kth = kth;

@@ -149,7 +149,11 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
     const unsigned off_wave = (wave & 1) ? off_odd : off_even;
     const int8_t *qsrc = a.qcodes + (q_tile + 8 * BPW * wave) * a.d_pad;
     int it = 0, ik = 0, islot = 0;     // the next stage to issue: tile (of this split), stage of the tile, ring slot
-    int64_t irow = (int64_t)s * o.tile_stride;
+    auto first_row = [&](int t) {      // of the split's t-th tile
+        const int64_t r = ((int64_t)s + (int64_t)S * t) * o.tile_stride;
+        return SEED ? r + sample_shift((unsigned)(s + S * t), o.tile_stride - RUN) : r;
+    };
+    int64_t irow = first_row(0);
     auto issue = [&]() {
         if (L2 && ik == 0) {           // a tile's first stage brings its accumulator seeds and parity words
             const unsigned dst = aux_lds + (it & 1) * AUX * 4;
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
                             BPW == 1 ? off_wave : ((e & 1) ? off_odd : off_even),
                             dst + A_BYTES + (wave * BPW + e) * 1024);
         islot = islot + 1 == NST ? 0 : islot + 1;
-        if (++ik == kst) { ik = 0; ++it; irow += (int64_t)S * o.tile_stride; }
+        if (++ik == kst) { ik = 0; irow = first_row(++it); }
     };
 
     // ---- fragments ------------------------------------------------------------------------------
