@@ -544,6 +544,9 @@ struct Plan {
     int seed_tiles = 0;     // ... its seeding pass: tiles of 256 rows, in runs of 16 rows
     int64_t run_stride = 0; // ... every run_stride rows
     int expect = 0;         // PLAN_MFMA_COLLECT: expected candidates per query
+    bool maxima = false;    // in place of either: a search by group maxima of all rows, finished by helpers workgroups per query
+    MaximaShape groups;
+    int helpers = 0, finish_threads = 0;
     size_t off_qcodes = 0, off_qnorms = 0, off_lists1 = 0, off_seedlist = 0, off_seeds = 0, off_lists2 = 0,
            off_gmax = 0, off_merge_tmp = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_qlist = 0, off_redo = 0, off_bounds2 = 0, off_over2 = 0,
            off_qlist2 = 0, total = 0;
@@ -566,6 +569,61 @@ int seed_rank(int64_t n, int64_t rows, int64_t nq, int k)
     const double z = 0.905 * std::sqrt(2.0 * std::log(100.0 * (double)(nq > 1 ? nq : 1)));
     const double r = std::ceil(mean + z * std::sqrt(mean * (1.0 - s)) + (z * z - 1.0) / 6.0 * (1.0 - 2.0 * s) + 1.0);
     return r < (double)k ? (int)r : k;
+}
+
+// Small batches by group maxima (search_maxima.hip): three launches, no sample, no candidates on the way.  The scan splits
+// rows between the waves of a workgroup, 64 queries each, so that every further 64 queries read the corpus again, and the
+// finishing workgroups read about k groups of rows per query: the lines below bound both.  us, other scans / this one,
+// 128 features, k = 10: one query on 1M rows 56 / 42, 16 on 10M x 96 200 / 197, 100 on 10 000 35 / 19, 1000 47 / 26, 100 on
+// 200 000 41 / 27, 256 46 / 35, 600 56 / 54 to 68, 100 on 1M 62 / 48, 200 67 / 76, 128 on 5M x 96 160 / 178.
+void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
+{
+    const int64_t n = idx->size;
+    for (int key : {LPQ_TUNE_PATH, LPQ_TUNE_SPLITS, LPQ_TUNE_SEED_ROWS, LPQ_TUNE_WAVE_QUERIES, LPQ_TUNE_REGION_CAP})
+        if (tune(key)) return;
+    // (Short rows of few bits tie, and every group that ties with the k-th has its rows scored again: 16 queries on 1M skewed
+    // integers of 24 features, 3 bits 46 / 341.)
+    if (nq < 1 || nq > 4096 || idx->bits < 4 || (idx->bits < 6 && idx->d < 64) || k > MAXIMA_MAX_K || idx->d_pad > MAXIMA_MAX_D || (idx->packed && nq > 64)) return;
+    const int waves = mfma_row_split_waves(idx->d_pad, idx->packed);
+    const int64_t tiles = ceil_div(nq, 64), row_bytes = idx->packed ? idx->d_pad / 2 : idx->d_pad;
+    if (idx->packed && idx->d_pad <= 128 && n > 3'000'000) return;   // (16 queries at 4 bits: 2M x 64 57 / 51, 10M x 96 139 / 155)
+    if (tiles == 2 && tiles * n * row_bytes > int64_t(512) << 20) return;
+    if (tiles > 2 && tiles * tiles * n * (row_bytes > 128 ? 2 * row_bytes : 128) > int64_t(512) << 20) return;
+    MaximaShape m;
+    m.parts = 2 * waves;
+    m.stage_rows = 32 * waves;
+    m.stages = (int)(n / m.stage_rows);
+    if (m.stages < 16) return;
+    const int slots = (int)(512 / tiles);
+    m.S = m.stages < slots ? m.stages : slots;
+    // As many groups as the finishing threads hold, 16 each: workgroups of 256 where there are no more groups than that, or
+    // where many queries need few rows each (a CU takes one of 1024 threads, or four).
+    int threads = 1024;
+    auto shape = [&]() {
+        int64_t seg = 16 * threads / (m.S * m.parts);
+        if (seg > m.stages / m.S) seg = m.stages / m.S;
+        m.SEG = (int)(seg < 1 ? 1 : seg);
+        m.G = m.S * m.SEG * m.parts;
+        m.seg_stages = (int)ceil_div(ceil_div(m.stages, m.S), m.SEG);
+        return 1.1 * (double)k * (double)n / (double)m.G;       // rows of the groups that reach the bound
+    };
+    double rows = shape();
+    if (m.G <= 16 * 256 || (tiles > 1 && 1.1 * (double)k * (double)n / (16.0 * 256.0) <= 768.0)) {
+        threads = 256;
+        rows = shape();
+    }
+    if (m.G % 16 || m.G > 16 * threads || m.G / (threads == 256 ? 4 : 16) < k || m.seg_stages > 1000) return;
+    const double finish_bytes = (double)nq * (rows * (double)row_bytes + 4.0 * m.G);
+    if (finish_bytes > (double)((tiles > 1 ? 32 : (k <= 10 ? 40 : 160)) << 20)) return;
+    int64_t h = (int64_t)(rows / 768.0), most = (threads == 256 ? 1024 : 256) / nq;
+    if (most > 16) most = 16;
+    if (h > most) h = most;
+    if (h * k > 2048) h = 2048 / k;
+    p.helpers = (int)(h < 1 ? 1 : h);
+    p.finish_threads = threads;
+    p.rsplit = true; p.rs_waves = waves;
+    p.groups = m;
+    p.maxima = true;
 }
 
 // compact: the plan for callers with a fixed workspace whose normal plan does not fit - fewer, larger splits
@@ -817,9 +875,20 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
         while (p.Sg > 4 && (size_t)nq * p.Sg * k * sizeof(cand_t) > (size_t(compact ? 16 : 256) << 20)) p.Sg /= 2;
     }
 
+    if (!compact && gmode) plan_maxima(p, idx, nq, k);
     size_t o = 0;
     p.off_qcodes = o;   o = align256(o + (size_t)p.nq_pad * idx->d_pad);
     p.off_qnorms = o;   o = align256(o + (size_t)p.nq_pad * sizeof(int32_t));
+    if (p.maxima) {
+        p.off_lists1 = p.off_seedlist = p.off_seeds = o;
+        p.off_lists2 = o;   o = align256(o + (size_t)nq * p.helpers * k * sizeof(cand_t));
+        p.off_gmax = o;     o = align256(o + (size_t)nq * p.groups.G * sizeof(int32_t));
+        p.off_merge_tmp = p.off_cbuf = o;
+        p.off_ccnt = o;     o = align256(o + (size_t)nq * p.helpers * sizeof(int32_t));
+        p.off_over = o;     o = align256(o + (size_t)nq * sizeof(int32_t));
+        p.off_qlist = p.off_redo = p.off_bounds2 = p.off_over2 = p.off_qlist2 = p.total = o;
+        return p;
+    }
     p.off_lists1 = o;   o = align256(o + (gmode ? 0 : (size_t)nq * p.S1 * k * sizeof(cand_t)));
     p.off_seedlist = o; o = align256(o + (size_t)nq * k * sizeof(cand_t));
     p.off_seeds = o;    o = align256(o + (size_t)p.nq_pad * sizeof(cand_t));
@@ -943,7 +1012,15 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
                                     coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
                                     coll ? p.rounds : 0, nq + 1);
     };
-    if (p.mode == PLAN_MFMA_COLLECT) {
+    if (p.maxima) {
+        int32_t *done = reinterpret_cast<int32_t *>(ws + p.off_over);
+        {
+            KernelSpan span(st);
+            HIP_TRY(launch_maxima_mfma(a, p.groups, gmax, done, st));
+        }
+        HIP_TRY(launch_maxima_finish(a, p.groups, gmax, p.finish_threads, p.helpers, lists2, reinterpret_cast<int32_t *>(ws + p.off_ccnt), done, ids, dist,
+                                     qnorms, emit_mode, st));
+    } else if (p.mode == PLAN_MFMA_COLLECT) {
         cand_t *cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf);
         int32_t *ccnt = reinterpret_cast<int32_t *>(ws + p.off_ccnt);
         int32_t *over = reinterpret_cast<int32_t *>(ws + p.off_over);
@@ -1234,11 +1311,15 @@ extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k
     *redone_queries = 0;
     *max_region_fill = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT && !p.maxima) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
     std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * p.SS);
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);
     HIP_TRY(hipMemcpy(over.data(), ws + p.off_over, over.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (p.maxima) {   // none is searched again; those that many groups tied for take longer
+        for (int32_t v : over) *redone_queries += (v & MAXIMA_MANY) != 0;
+        return LPQ_OK;
+    }
     HIP_TRY(hipMemcpy(cnt.data(), ws + p.off_ccnt, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     for (int32_t v : over) *redone_queries += v != 0;
     for (int32_t v : cnt) if (v > *max_region_fill) *max_region_fill = v;
@@ -1252,7 +1333,7 @@ extern "C" int lpq_search_overflow_left(const lpq_index *idx, int64_t nq, int k,
     if (!idx || !workspace_dev || !left_queries || nq < 1 || k < 1) return fail(LPQ_EINVAL, "bad argument");
     *left_queries = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT || !p.rounds) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT || p.maxima || !p.rounds) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
     std::vector<int32_t> over2((size_t)nq);
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);

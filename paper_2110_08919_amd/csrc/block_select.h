@@ -51,4 +51,21 @@ __device__ inline void block_compact_if_full(cand_t *buf, int cap, int k, int ne
     }
 }
 
+// Final id and distance of candidate c of query q, written at position `at`.
+__device__ __forceinline__ void emit_result(cand_t c, int64_t at, int64_t q, int32_t *__restrict__ ids,
+                                            int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
+{
+    const int32_t key = cand_key(c);
+    ids[at] = (c == CAND_NONE) ? -1 : (int32_t)cand_id(c);
+    int32_t v;
+    if (metric == MODE_I8_L2) v = key + qnorms[q];
+    else if (metric == MODE_I8_IP) v = -(key / 2);
+    else if (metric == MODE_I8_IP_ADJ) v = -(key / 2) + qnorms[q];
+    else {
+        const float f = sortable_to_float(key);
+        v = __float_as_int(metric == MODE_F32_L2 ? f : -f);
+    }
+    dists[at] = v;
+}
+
 }  // namespace lpq

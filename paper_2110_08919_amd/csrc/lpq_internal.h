@@ -207,6 +207,22 @@ int mfma_row_split_waves(int d_pad, bool packed);   // 4 on rows of up to 128 by
 hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int S, int SEG, int32_t *gmax,
                             hipStream_t st, int64_t stage_stride = 0, int stages_per_split = 0,
                             int64_t piece_stride = 0, int piece_stages = 0);
+// Search by group maxima (small batches; row-split workgroups, 64 queries each): the seeding pass over every row of the first
+// `stages` stages, dealt round-robin to S splits, leaves gmax[nq][G], G = S * SEG * parts.  Group (s * SEG + seg) * parts +
+// part holds the rows 32 (part / 2) + 8 i + 4 (part % 2) + 0 .. 3 (i = 0 .. 3) of the split's stages t with
+// floor(t SEG / T) = seg, T the number of its stages.
+struct MaximaShape {
+    int S = 0, SEG = 0, parts = 0, G = 0;
+    int stage_rows = 0, stages = 0;
+    int seg_stages = 0;     // most stages of a segment
+};
+enum { MAXIMA_MAX_K = 128, MAXIMA_MAX_D = 256, MAXIMA_MANY = 1 << 16 };
+// Also sets done[0 .. nq) to 0.
+hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
+// The k best from the maxima: H workgroups of 256 or 1024 threads (up to 16 groups to a thread) per query, lists[nq][H][k],
+// counts[nq][H].  done[q] holds MAXIMA_MANY afterwards if more groups reached the bound than are worked off at once.
+hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int H, cand_t *lists,
+                                int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st);
 // Collecting scan (any k up to MAX_K): thresholds stay at seeds[q] (required); every candidate beating its
 // query's seed is appended to cbuf[(q * SS + region) * Cs + ...], SS = mfma_collect_regions(S, rsplit),
 // and ccnt[q * SS + region] = number offered (entries beyond Cs were dropped).

@@ -103,23 +103,6 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_kernel(
 // 64-bit minimum over the wave; every lane gets the result.
 __device__ __forceinline__ cand_t wave_min_cand(cand_t c) { return wave_min_u64(c); }
 
-// Final id and distance of candidate c of query q, written at position `at`.
-__device__ __forceinline__ void emit_result(cand_t c, int64_t at, int64_t q, int32_t *__restrict__ ids,
-                                            int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
-{
-    const int32_t key = cand_key(c);
-    ids[at] = (c == CAND_NONE) ? -1 : (int32_t)cand_id(c);
-    int32_t v;
-    if (metric == MODE_I8_L2) v = key + qnorms[q];
-    else if (metric == MODE_I8_IP) v = -(key / 2);
-    else if (metric == MODE_I8_IP_ADJ) v = -(key / 2) + qnorms[q];
-    else {
-        const float f = sortable_to_float(key);
-        v = __float_as_int(metric == MODE_F32_L2 ? f : -f);
-    }
-    dists[at] = v;
-}
-
 // First candidate in (key, id) order that a bound taken from candidate c does not let through.
 __device__ __forceinline__ cand_t next_bound(cand_t c) { return c + 1; }
 

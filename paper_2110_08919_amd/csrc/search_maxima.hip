@@ -1,0 +1,266 @@
+// Last step of a search by group maxima (small batches).  The scan before it (search_mfma.hip, the seeding pass run over
+// every row) has left one number per query and group of rows: the largest E = dot - ceil(nx / 2) of the group.  At least k
+// items reach the k-th largest of the maxima, so the k nearest lie in groups that reach it, k of them and a few more; their
+// rows are scored again and the k best kept.  Nothing was sampled and no candidate was collected on the way, so three
+// launches make a search where five and eight did.  One query, k = 10, 1M x 128: scan 31 -> 24 us, what goes before and
+// after it 24 -> 14 (sample 7, bound 5, merge 6 and encoding against 9 here and encoding), 56 -> 41 in all; 100 queries on
+// 10 000 x 128 37 -> 19; 16 on 10M x 96 200 -> 195 (16 us here: 6700 rows a query, from memory).
+#include "block_select.h"
+#include "lpq_internal.h"
+#include "wave_ops.h"
+
+namespace lpq {
+
+namespace {
+
+constexpr int MF_FLY = 8;             // rows a lane has in flight
+constexpr int MF_UNITS = 1024;        // units worked off at a time; a unit is the 16 rows of a group in one stage
+constexpr int MF_TAIL = 8;            // blocks of 32 rows behind the last whole stage, at most
+constexpr int MF_MERGE = 2048;        // candidates of all helpers together, at most
+
+// 16 bytes of a row with the query's codes at that place, its chunk c (packed rows: two codes + 8 to a byte, see generic_scan).
+template <bool PACKED>
+__device__ __forceinline__ int chunk_dot(uint4 xv, const uint4 *qs, int c)
+{
+    int dot = 0;
+    if (PACKED) {
+        const uint4 q0 = qs[2 * c], q1 = qs[2 * c + 1];
+        const unsigned m = 0x0F0F0F0Fu;
+        dot = __builtin_amdgcn_sdot4((int)(xv.x & m), (int)q0.x, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)((xv.x >> 4) & m), (int)q0.y, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)(xv.y & m), (int)q0.z, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)((xv.y >> 4) & m), (int)q0.w, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)(xv.z & m), (int)q1.x, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)((xv.z >> 4) & m), (int)q1.y, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)(xv.w & m), (int)q1.z, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)((xv.w >> 4) & m), (int)q1.w, dot, false);
+    } else {
+        const uint4 qv = qs[c];
+        dot = __builtin_amdgcn_sdot4((int)xv.x, (int)qv.x, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)xv.y, (int)qv.y, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)xv.z, (int)qv.z, dot, false);
+        dot = __builtin_amdgcn_sdot4((int)xv.w, (int)qv.w, dot, false);
+    }
+    return dot;
+}
+
+// H workgroups per query: each finds the same bound from the maxima, scores its share of the rows of the groups that reach
+// it, and the one that ends last merges.  What bounds it is latency: a round trip to memory for the maxima (V 16-byte loads a
+// thread, all in flight at once), one per step of 1024 rows (512 beyond 128 bytes), and two with the fences where helpers
+// share the work.  LR lanes share a row, 16 bytes each.
+template <int NT, bool PACKED, int LR, int V>
+__global__ __launch_bounds__(NT) void maxima_finish_kernel(
+    SearchArgs a, MaximaShape m, const int32_t *__restrict__ gmax, int H, cand_t *lists, int32_t *counts, int32_t *done, int cap,
+    int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
+{
+    constexpr int ROWS = NT / LR;                           // rows side by side, 16 to a unit
+    extern __shared__ __align__(16) unsigned char smem[];
+    cand_t *buf = reinterpret_cast<cand_t *>(smem);                 // [max(cap, merge)]
+    __shared__ uint4 qs[MAXIMA_MAX_D / 16];
+    __shared__ int s_top[256], s_hit[MF_UNITS], s_unit[MF_UNITS];   // groups; first row of a unit, or -1
+    __shared__ int s_count[2], s_bound, s_hits, s_units, s_last;
+    __shared__ cand_t s_thr;
+    const int64_t q = blockIdx.x / H;
+    const int h = blockIdx.x % H, tid = threadIdx.x, lane = tid & 63, sub = tid % LR, grp = tid / LR;
+    const bool l2 = a.metric == LPQ_METRIC_L2SQ;
+
+    // ---- the bound: the k-th largest of the largest maxima of 256 foursomes of threads -----------
+    const int4 *gm = reinterpret_cast<const int4 *>(gmax + q * m.G);
+    int4 v[V];
+    int top = INT32_MIN;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        const int i = tid + j * NT;
+        v[j] = i < m.G / 4 ? gm[i] : int4{INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
+    }
+    if (tid < a.d_pad / 16) qs[tid] = reinterpret_cast<const uint4 *>(a.qcodes + q * a.d_pad)[tid];
+    for (int i = tid; i < cap; i += NT) buf[i] = CAND_NONE;
+    if (tid < 2) s_count[tid] = 0;
+    if (tid == 0) s_hits = s_units = 0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) top = max(top, max(max(v[j].x, v[j].y), max(v[j].z, v[j].w)));
+    const int own = top;
+    if (NT > 256) {
+        top = max(top, dpp_move<DPP_XOR1>(top));
+        top = max(top, dpp_move<DPP_XOR2>(top));
+    }
+    if (NT == 256 || (tid & 3) == 0) s_top[NT == 256 ? tid : tid >> 2] = top;
+    __syncthreads();
+    if (tid < 64) {                                                 // bisection: the largest value that k of them reach
+        int t[4], lo = INT32_MAX, hi = INT32_MIN;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            t[j] = s_top[lane + 64 * j];
+            lo = min(lo, t[j]);
+            hi = max(hi, t[j]);
+        }
+        long long low = wave_min_i32(lo), high = wave_max_i32(hi);
+        while (low < high) {                                        // wave-uniform
+            const long long mid = low + (high - low + 1) / 2;
+            int reach = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) reach += __popcll(__ballot(t[j] >= (int)mid));
+            if (reach >= a.k) low = mid; else high = mid - 1;
+        }
+        if (lane == 0) {
+            s_bound = (int)low;
+            s_thr = low == INT32_MIN ? CAND_NONE : make_cand(-2 * (int)low, 0xFFFFFFFFu);   // an item with E >= low has a key of no more
+        }
+    }
+    __syncthreads();
+    const int bound = s_bound;
+
+    // ---- rows of the groups that reach it --------------------------------------------------------
+    AppendSteps at;
+    const uint4 *rows = reinterpret_cast<const uint4 *>(a.codes);
+    const int chunks = a.d_pad >> (PACKED ? 5 : 4), chunk = sub < chunks ? sub : 0;
+    // one step: `pick(i)` is the row of slot i (0 .. MF_FLY * ROWS - 1) or -1
+    auto step = [&](auto pick) {
+        int row[MF_FLY], nx[MF_FLY];
+        uint4 x[MF_FLY];
+#pragma unroll
+        for (int u = 0; u < MF_FLY; ++u) {                          // all loads in flight before the first is used
+            row[u] = pick(grp + u * ROWS);
+            const size_t r = row[u] >= 0 ? row[u] : 0;
+            x[u] = rows[r * chunks + chunk];
+            nx[u] = l2 ? a.norms[r] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < MF_FLY; ++u) {
+            int dot = sub < chunks ? chunk_dot<PACKED>(x[u], qs, sub) : 0;
+            dot += dpp_move<DPP_XOR1>(dot);
+            dot += dpp_move<DPP_XOR2>(dot);
+            dot += dpp_move<DPP_HALF_MIRROR>(dot);
+            if (LR == 16) dot += dpp_move<DPP_ROW_MIRROR>(dot);
+            if (sub == 0 && row[u] >= 0) {
+                const cand_t c = make_cand(nx[u] - 2 * dot, (uint32_t)row[u]);
+                if (c < s_thr) buf[at.held - at.before + atomicAdd(&s_count[at.turn], 1)] = c;
+            }
+        }
+        __syncthreads();
+        at.step_done(__builtin_amdgcn_readfirstlane(s_count[at.turn]));
+        block_compact_if_full(buf, cap, a.k, MF_FLY * ROWS, at.held, &s_thr);
+    };
+    // all groups at once, or as many at a time as the list of units surely has room for
+    for (int from = 0, window = m.G; from < m.G;) {
+        const int to = from + window < m.G ? from + window : m.G;
+        if (own >= bound) {                                         // (few threads have a group that does)
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const int val[4] = {v[j].x, v[j].y, v[j].z, v[j].w}, first = 4 * (tid + j * NT);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (val[c] >= bound && first + c >= from && first + c < to) {
+                        const int slot = atomicAdd(&s_hits, 1);
+                        if (slot < MF_UNITS) s_hit[slot] = first + c;
+                    }
+            }
+        }
+        __syncthreads();
+        const int hits = s_hits;
+        // The helpers share the units, not the groups: a workgroup alone gets some 30 GB/s of rows from memory.
+        for (int u = tid; hits <= MF_UNITS && u < hits * m.seg_stages; u += NT) {
+            const int i = s_hit[u / m.seg_stages], nth = u % m.seg_stages;
+            if (H > 1 && (i + nth) % H != h) continue;
+            const int part = i % m.parts, seg = (i / m.parts) % m.SEG, s = i / (m.parts * m.SEG);
+            const int T = (m.stages - s + m.S - 1) / m.S;           // stages of the split
+            const int t = (int)(((int64_t)seg * T + m.SEG - 1) / m.SEG) + nth;
+            if (t >= (int)(((int64_t)(seg + 1) * T + m.SEG - 1) / m.SEG)) continue;
+            const int slot = atomicAdd(&s_units, 1);
+            if (slot < MF_UNITS) s_unit[slot] = (s + m.S * t) * m.stage_rows + (part >> 1) * 32 + (part & 1) * 4;
+        }
+        // the rows behind the last whole stage were not scanned: units of the same form
+        const int tail = m.stages * m.stage_rows;
+        if (h == 0 && to == m.G && tail + (tid >> 1) * 32 < (int)a.n && tid < 2 * MF_TAIL) {
+            const int slot = atomicAdd(&s_units, 1);
+            if (slot < MF_UNITS) s_unit[slot] = tail + (tid >> 1) * 32 + (tid & 1) * 4;
+        }
+        __syncthreads();
+        const int units = s_units;
+        __syncthreads();
+        if (tid == 0) s_hits = s_units = 0;
+        if (hits > MF_UNITS || units > MF_UNITS) {                  // (only the first window can hold more than that)
+            window = (MF_UNITS - 2 * MF_TAIL) / m.seg_stages;
+            if (tid == 0) atomicOr(&done[q], MAXIMA_MANY);
+            __syncthreads();
+            continue;
+        }
+        for (int base = 0; base < units; base += MF_FLY * ROWS / 16)
+            step([&](int i) {
+                const int j = i & 15, row = base + (i >> 4) < units ? s_unit[base + (i >> 4)] + 8 * (j >> 2) + (j & 3) : -1;
+                return row < (int)a.n ? row : -1;
+            });
+        __syncthreads();
+        from = to;
+    }
+
+    // ---- the k best: ranks are counted, or where there are many candidates they are sorted -------
+    auto finish = [&](int held, auto put) {
+        if (held <= NT) {
+            if (tid < held) {
+                const cand_t me = buf[tid];
+                int r = 0;
+                for (int j = 0; j < held; ++j) r += buf[j] < me;
+                if (r < a.k) put(r, me);
+            }
+            return;
+        }
+        const int pow2 = next_pow2(held);
+        for (int i = held + tid; i < pow2; i += NT) buf[i] = CAND_NONE;
+        __syncthreads();
+        block_bitonic_sort(buf, pow2);
+        for (int i = tid; i < a.k; i += NT) put(i, buf[i]);
+    };
+    int held = at.held;
+    if (H > 1) {
+        cand_t *mine = lists + (q * H + h) * a.k;
+        finish(held, [&](int r, cand_t c) { mine[r] = c; });
+        if (tid == 0) counts[q * H + h] = held < a.k ? held : a.k;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wave's part has reached the L2 ...
+        __syncthreads();
+        if (tid == 0) {
+            __threadfence();                                        // ... and is visible to the chip
+            s_last = (atomicAdd(&done[q], 1) & (MAXIMA_MANY - 1)) == H - 1;
+            if (s_last) __threadfence();                            // the other helpers' parts are read as they are now
+            s_hits = 0;
+        }
+        __syncthreads();
+        if (!s_last) return;                                        // the same in every thread of the workgroup
+        for (int i = tid; i < H * a.k; i += NT)
+            if (i % a.k < counts[q * H + i / a.k]) buf[atomicAdd(&s_hits, 1)] = lists[q * H * a.k + i];
+        __syncthreads();
+        held = s_hits;
+    }
+    finish(held, [&](int r, cand_t c) { emit_result(c, q * a.k + r, q, ids, dists, qnorms, metric); });
+}
+
+}  // namespace
+
+hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int H, cand_t *lists,
+                                int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st)
+{
+    if (a.nq <= 0) return hipSuccess;
+    const int chunks = a.d_pad / (a.packed ? 32 : 16), lr = chunks <= 8 ? 8 : 16, step = MF_FLY * threads / lr;
+    const int tops = threads == 256 ? m.G / 4 : m.G / 16;
+    // the bound is the k-th of the (foursomes of) threads' maxima, a unit list holds a group and the rows behind the last
+    // stage, and all that the helpers keep fits one merge
+    if ((threads != 256 && threads != 1024) || a.k < 1 || a.k > MAXIMA_MAX_K || chunks > 16 || a.d_pad > MAXIMA_MAX_D || H < 1 ||
+        H * a.k > MF_MERGE || m.G % 16 || tops < a.k || m.G > 16 * threads || m.seg_stages > MF_UNITS - 2 * MF_TAIL ||
+        a.n - (int64_t)m.stages * m.stage_rows > 32 * MF_TAIL)
+        return hipErrorInvalidValue;
+    const int cap = next_pow2(a.k + step);
+    const int most = H > 1 ? next_pow2(H * a.k) : cap;
+    const size_t lds = (size_t)(cap > most ? cap : most) * sizeof(cand_t);
+    auto launch = [&](auto kern) {
+        kern<<<(unsigned)(a.nq * H), threads, lds, st>>>(a, m, gmax, H, lists, counts, done, cap, ids, dists, qnorms, metric);
+        return hipGetLastError();
+    };
+    if (threads == 256) {
+        if (a.packed) return launch(maxima_finish_kernel<256, true, 8, 4>);
+        return lr == 8 ? launch(maxima_finish_kernel<256, false, 8, 4>) : launch(maxima_finish_kernel<256, false, 16, 4>);
+    }
+    if (a.packed) return launch(maxima_finish_kernel<1024, true, 8, 4>);
+    return lr == 8 ? launch(maxima_finish_kernel<1024, false, 8, 4>) : launch(maxima_finish_kernel<1024, false, 16, 4>);
+}
+
+}  // namespace lpq

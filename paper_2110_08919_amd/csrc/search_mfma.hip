@@ -114,6 +114,10 @@ struct MfmaIo {     // what a launch reads and writes besides the corpus and the
     // piece_stages stages.  0: stages of 64 consecutive rows as above.
     int64_t piece_stride;
     int piece_stages;
+    // Search by group maxima: the pass reads every row, every segment has stages, and gmax holds a.nq queries; done[0 .. nq)
+    // is set to 0.
+    bool whole;
+    int32_t *done;
 };
 
 struct WaveQ {      // pointers into the wave's private LDS region
@@ -418,6 +422,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     // extra registers spill in the 128-queries-per-wave kernel), so one group per lane half it is.
     constexpr int GR = 1;
     int thr[NB], gm[NB][GR];
+    constexpr bool CAN_WHOLE = SEED && RSPLIT;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         thr[nb] = SEED ? INT32_MAX : w.thrE[nb * 32 + col];
@@ -442,7 +447,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     constexpr bool CAN_PIECES = SEED && !RSPLIT;
     const bool pieces = CAN_PIECES && o.piece_stride > 0;
     const int64_t piece_gap = pieces ? (int64_t)S * o.piece_stride : 0;   // rows between the pieces of a stage
-    const int64_t shift_room = pieces ? o.piece_stride - 8 : (o.stage_stride ? o.stage_stride - RS : 0);
+    const int64_t shift_room = pieces ? o.piece_stride - 8 : (o.stage_stride && !o.whole ? o.stage_stride - RS : 0);
     int src_off[IPW];   // byte offset of the lane's source chunk relative to the first row of a stage (of its piece)
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -627,6 +632,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         int lane_ = lane;   /* addresses are formed here, not carried through the loop in registers */ \
         if (REFORM) LPQ_OPAQUE(lane_);                                                                  \
         _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                             \
+            if (CAN_WHOLE && o.whole && q_first + nb * 32 + (lane_ & 31) >= a.nq) continue;             \
             int32_t *dst_ = gmax + (size_t)(q_first + nb * 32 + (lane_ & 31)) * G +                     \
                 ((((size_t)s * SEG + (SEGIDX)) * (RSPLIT ? NW : 1) + (RSPLIT ? wave : 0)) * 2 + (lane_ >> 5)) * GR; \
             _Pragma("unroll") for (int r = 0; r < GR; ++r) {                                            \
@@ -635,7 +641,10 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
             }                                                                                           \
         }                                                                                               \
     } while (0)
-    if (SEED) {   // segments this split never reaches keep the neutral value
+    if (CAN_WHOLE && o.whole) {
+        if (blockIdx.x == 0)
+            for (int i = tid; i < a.nq; i += NW * 64) o.done[i] = 0;
+    } else if (SEED) {   // segments this split never reaches keep the neutral value
         for (int g = 0; g < SEG; ++g) LPQ_FLUSH_SEGMENT(g);
     }
 
@@ -667,7 +676,8 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
                 const int seg = (int)((int64_t)t * SEG / T), seg_next = (int)((int64_t)(t + 1) * SEG / T);
                 if (t + 1 == T || seg_next != seg) {
                     LPQ_FLUSH_SEGMENT(seg);
-                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    // (few segments: the stores stay in flight and only make the counted waits more conservative)
+                    if (!CAN_WHOLE || !o.whole) __builtin_amdgcn_s_waitcnt(0x0F70);
                 }
             }
         }
@@ -1402,7 +1412,7 @@ hipError_t launch_long(const SearchArgs &a, int64_t row0, int64_t row1, int S, c
 hipError_t launch_any(const SearchArgs &a, int64_t row0, int64_t row1, int S, const MfmaIo &o, hipStream_t st)
 {
     if (a.nq <= 0 || row1 <= row0) return hipSuccess;
-    if (row0 % 128 || o.split_stride % 128) return hipErrorInvalidValue;  // stages and parity words cover aligned blocks
+    if (row0 % 128 || o.split_stride % (o.whole ? 32 : 128)) return hipErrorInvalidValue;  // stages and parity words cover aligned blocks
     if (takes_long_scan(a) && (o.gmax || o.cbuf)) {
         switch (a.d_pad / 32) {
         case 6: return launch_long<6>(a, row0, row1, S, o, st);
@@ -1543,6 +1553,21 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
         o.split_stride_rows = (int64_t)rs_rows * stages_per_split;
     }
     return launch_any(a, row0, row1, S, o, st);
+}
+
+hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st)
+{
+    const int rows = 32 * a.rs_waves;
+    if (!a.rsplit || !gmax || !done || m.S < 1 || m.SEG < 1 || m.SEG > m.stages / m.S || m.stage_rows != rows ||
+        (int64_t)m.stages * rows > a.n || m.G != mfma_seed_groups(m.S, m.SEG, a.rs_waves))
+        return hipErrorInvalidValue;
+    MfmaIo o = {};
+    o.gmax = gmax; o.SEG = m.SEG;
+    o.whole = true; o.done = done;
+    o.split_stride = rows;
+    o.stage_stride = (int64_t)m.S * rows;
+    o.split_stride_rows = ceil_div(m.stages, m.S) * rows;
+    return launch_any(a, 0, (int64_t)m.stages * rows, m.S, o, st);
 }
 
 hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, int rank, cand_t *seeds, cand_t *certain, hipStream_t st,

@@ -1,0 +1,53 @@
+"""Small batches by group maxima (three launches): both metrics, row lengths of both kinds of workgroup, packed rows, rows left
+over behind the last whole stage, one and many groups to a split, every limit of k and batch, and more groups at the bound
+than a workgroup works off at a time (few distinct vectors).  Against the generic kernel.  Needs a real MI355X."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(x, q, k, metric, bits=8, packed=False):
+    from paper_2110_08919_amd import lpq
+    n, d = x.shape
+    quant = lpq.Quantizer(d, bits).calibrate(x, "absmax", "global")
+    index = lpq.Index(quant, n, packed=packed).add_f32(x)
+    ids, dists = index.search(q, k, metric)
+    again = index.search(q, k, metric)
+    lpq.set_tuning(lpq.TUNE_PATH, 1)
+    try:
+        want_ids, want = index.search(q, k, metric)
+    finally:
+        lpq.set_tuning(lpq.TUNE_PATH, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(dists, want) and torch.equal(ids, want_ids)
+    assert torch.equal(again[0], ids) and torch.equal(again[1], dists)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("n,d,nq,k", [
+    (4096, 24, 1, 1), (4223, 64, 3, 10), (10_000, 128, 64, 128), (65_535, 96, 16, 10), (70_001, 100, 63, 33), (200_129, 128, 5, 100),
+    (300_000, 40, 64, 2), (131_072, 192, 7, 10), (131_135, 256, 64, 100), (9000, 200, 1, 128), (1_000_000, 128, 1, 10),
+    (2_000_003, 33, 2, 17),
+])
+def test_small_batches(metric, n, d, nq, k):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    _check(*(torch.randn((m, d), generator=g, device="cuda") for m in (n, nq)), k, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("n,d,nq,k", [(50_000, 64, 40, 10), (100_001, 96, 64, 64), (70_000, 200, 2, 128)])
+def test_packed_rows(metric, n, d, nq, k):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    _check(*(torch.randn((m, d), generator=g, device="cuda") for m in (n, nq)), k, metric, bits=4, packed=True)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("n,distinct,nq,k", [(100_000, 1, 1, 100), (100_000, 7, 20, 10), (150_000, 900, 64, 30), (60_000, 0, 3, 10)])
+def test_many_groups_at_the_bound(metric, n, distinct, nq, k):
+    g = torch.Generator(device="cuda").manual_seed(n + distinct)
+    if distinct:
+        x = torch.randn((distinct, 32), generator=g, device="cuda")[torch.randint(0, distinct, (n,), generator=g, device="cuda")].contiguous()
+    else:            # two values to a feature
+        x = torch.randint(0, 2, (n, 32), generator=g, device="cuda").float()
+    _check(x, x[: nq].clone(), k, metric)
