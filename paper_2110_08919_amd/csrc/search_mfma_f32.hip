@@ -177,6 +177,128 @@ __global__ __launch_bounds__(256) void split_queries_kernel(const float *__restr
     }
 }
 
+// What a workgroup of a scan does first: which of its queries it has work for, and their thresholds.  Returns what rows are
+// scaled by (as a power of two).
+template <int QT, bool FP16>
+__device__ __forceinline__ int scan_begin(const FilterIo &o, int *ctl, float *thr_l, int *fill, float *h_l, int s, int64_t q_tile)
+{
+    const int tid = threadIdx.x;
+    if (tid < CTL_WORDS) ctl[tid] = 0;
+    __syncthreads();
+    // FP16: the tile's rows are scaled by two to the mean of its queries' scales
+    int xe = 0;
+    // More than a quarter of the tiles are hard: the others are left to the second scan, too, which takes two rounds of
+    // workgroups for all.  Up to a quarter one round is enough, beyond, it may be two behind the first scan: 1M x 128, some tiles hard and
+    // all, ms: 3000 queries, 6 of 24 2.3, 8 2.2 or 3.4, 10 3.6, all 2.8; 5000, 10 of 40 4.1, 12 4.0 or 6.1, all 4.6.
+    bool leave = false;
+    if (FP16) {
+        const float mean = *o.nxsum * o.nxper;
+        for (int i = tid; i < QT; i += FW * 64) {
+            const int e = o.qe[q_tile + i];
+            if (e != NO_SCALE) { atomicAdd(&ctl[CTL_SCALES], e); atomicAdd(&ctl[CTL_SCALED], 1); }
+        }
+        for (int64_t i = tid; 128 * i < o.nq; i += FW * 64)
+            if (o.hard[i]) atomicAdd(&ctl[CTL_HARD], 1);
+        __syncthreads();
+        leave = 4 * ctl[CTL_HARD] > (o.nq + 127) >> 7;
+        const int scaled = ctl[CTL_SCALED];
+        xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
+        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && mean <= NEAR_ONE_ROWS) xe = 0;
+        xe = __builtin_amdgcn_readfirstlane(xe);
+    }
+    for (int i = tid; i < QT; i += FW * 64) {
+        const int64_t q = q_tile + i;
+        float t = NAN;                                         // nothing compares: a slot that never collects
+        const bool hard = q < o.nq && o.hard[q >> 7];
+        // (The second scan may take two rounds of workgroups.  What overflowed in the first is left out of the other: where
+        // all do (1M x 128, 1000 queries, inner product, 1 % of the rows 10 000 times as long) 6.86 -> 6.65 ms.)
+        const int again = FP16 || q >= o.nq ? 0 : __hip_atomic_load(&o.again[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool mine = q < o.nq && (FP16 ? !hard : hard || again);
+        if (mine && !(again & DIRECT) && o.qn[q] <= HUGE_NORM) {
+            const int32_t kth = o.kth[q];
+            const float bound = kth == INT32_MIN ? -INFINITY : sortable_to_float(kth);
+            if (FP16) {
+                // (a norm of up to 2^-50 taken as zero is off by 2^-50 |x| <= 2^(-35 - xe), scaled by 2^2 xe)
+                const bool zero = o.qe[q] == NO_SCALE;
+                const int e = zero ? xe : o.qe[q];
+                if (e - xe > HALF_RANGE || xe - e > HALF_RANGE || (zero && xe > ZERO_SCALE) || leave) {
+                    mine = false;
+                    atomicOr(&o.again[q], AGAIN);
+                } else {
+                    t = ldexpf(bound - 0.5f * (o.c + o.ch) * o.qn[q] * 1.00001f - 0x1p-110f, xe + e) - f32_half_filter_small(o.d);
+                    h_l[i] = ldexpf(o.h, e - xe);
+                    if (s == 0) o.qx[q] = xe + e;
+                }
+            } else {
+                t = bound - o.c * o.qn[q] * 1.00001f - 0x1p-110f;
+            }
+        }
+        if (t != t) atomicAdd(&ctl[CTL_DONE], 1);
+        thr_l[i] = t;
+        fill[i] = mine ? (again & DIRECT ? o.Cs + 1 : 0) : -1;
+    }
+    return xe;
+}
+
+// What it does last: the rows set aside, and how many rows its queries have collected.
+template <int QT, bool FP16>
+__device__ __forceinline__ void scan_end(const FilterIo &o, int *ctl, const float *thr_l, int *fill, const float *h_l, int s, int64_t q_tile,
+                                         int xe, float xscale)
+{
+    const int tid = threadIdx.x, S = o.S;
+    cand_t *cbase = o.cbuf + ((size_t)q_tile * S + s) * o.Cs;
+    const size_t qstride = (size_t)S * o.Cs;
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (left early: the query copies on their way land before the LDS is given back)
+    __syncthreads();
+    // The rows set aside, summed in fp32 (off by less than the constant lets the rounded rows be): eight lanes to a row
+    // and query, eight values each at a time.  1M x 128, 1000 queries, one such row: 0.45 ms (L2) and 0.52 in all, as
+    // without it (the split's scan alone: 0.92; the first given up for it and the split's behind: 1.27).
+    const bool any = FP16 && ctl[CTL_ANY];
+#pragma clang loop unroll(disable)
+    for (int w = 0; any && w < FW; ++w) {
+        const int rows = ctl[CTL_ASIDE + w] < ASIDE ? ctl[CTL_ASIDE + w] : ASIDE, sub = tid & 7;
+        for (int at = tid >> 3; at < QT * rows; at += FW * 8) {
+            const int i = at % QT, tr = ctl[CTL_ROWS + w * ASIDE + at / QT];
+            const int64_t row = ((int64_t)s + (int64_t)(tr / TILE_ROWS) * S) * TILE_ROWS + tr % TILE_ROWS;
+            const _Float16 *qr = o.qf + (q_tile + i) * o.dp;
+            const float *xr = o.x + row * o.ldx;
+            float u = 0.0f, p = 0.0f;
+#pragma clang loop unroll(disable)
+            for (int c = 8 * sub; c < o.d; c += 64) {
+                const v8h qv = *reinterpret_cast<const v8h *>(qr + c);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = c + e < o.d ? xr[c + e] * xscale : 0.0f;
+                    u = fmaf((float)qv[e], v, u);
+                    p = fmaf(v, v, p);
+                }
+            }
+#pragma unroll
+            for (int m = 1; m < 8; m <<= 1) {
+                u += __shfl_xor(u, m, 64);
+                p += __shfl_xor(p, m, 64);
+            }
+            if (!(p <= LONG_NORM)) ctl[CTL_DONE] = ALL_LOST;
+            if (!(ldexpf(p, -2 * xe) <= HUGE_NORM)) ctl[CTL_HUGE] = 1;
+            u = fmaf(-h_l[i], p, u);
+            if (sub == 0 && u >= thr_l[i]) {
+                const int pos = atomicAdd(&fill[i], 1);
+                if (pos < o.Cs) cbase[(size_t)i * qstride + pos] = make_cand(~float_to_sortable(u), (uint32_t)row);
+            }
+        }
+    }
+    if (any) __syncthreads();                     // (the same in every thread)
+    // a row the bounds do not hold for: all queries of the tile overflow
+    const bool lost = ctl[CTL_DONE] >= ALL_LOST || ctl[CTL_HUGE];
+    for (int i = tid; i < QT; i += FW * 64) {
+        const int64_t q = q_tile + i;
+        if (q >= o.nq || (!FP16 && fill[i] < 0)) continue;
+        const int have = fill[i] < 0 ? 0 : (lost ? o.Cs + 1 : fill[i]);
+        o.ccnt[(size_t)q * S + s] = have;
+        if (have > o.Cs) atomicOr(&o.again[q], !FP16 || ctl[CTL_HUGE] ? DIRECT : AGAIN);
+    }
+}
+
 template <bool SEED, int WQ, bool WIDE, bool FP16, bool EVEN>
 __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 {
@@ -211,65 +333,9 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
     v4i *dmeta = reinterpret_cast<v4i *>(dval + DUMPS * 16);
     const int64_t q_tile = (int64_t)qt * QT, q_first = q_tile + wq * 64;
 
-    if (!SEED) {
-        if (tid < CTL_WORDS) ctl[tid] = 0;
-        __syncthreads();
-    }
-    // FP16: the tile's rows are scaled by two to the mean of its queries' scales
-    int xe = 0;
-    // More than a quarter of the tiles are hard: the others are left to the second scan, too, which takes two rounds of
-    // workgroups for all.  Up to a quarter one round is enough, beyond, it may be two behind the first scan: 1M x 128, some tiles hard and
-    // all, ms: 3000 queries, 6 of 24 2.3, 8 2.2 or 3.4, 10 3.6, all 2.8; 5000, 10 of 40 4.1, 12 4.0 or 6.1, all 4.6.
-    bool leave = false;
-    if (!SEED && FP16) {
-        const float mean = *o.nxsum * o.nxper;
-        for (int i = tid; i < QT; i += FW * 64) {
-            const int e = o.qe[q_tile + i];
-            if (e != NO_SCALE) { atomicAdd(&ctl[CTL_SCALES], e); atomicAdd(&ctl[CTL_SCALED], 1); }
-        }
-        for (int64_t i = tid; 128 * i < o.nq; i += FW * 64)
-            if (o.hard[i]) atomicAdd(&ctl[CTL_HARD], 1);
-        __syncthreads();
-        leave = 4 * ctl[CTL_HARD] > (o.nq + 127) >> 7;
-        const int scaled = ctl[CTL_SCALED];
-        xe = __builtin_amdgcn_readfirstlane(scaled ? ctl[CTL_SCALES] / scaled : 0);
-        if (xe >= NEAR_ONE_LO && xe <= NEAR_ONE_HI && mean <= NEAR_ONE_ROWS) xe = 0;
-        xe = __builtin_amdgcn_readfirstlane(xe);
-    }
+    int xe = 0;                       // FP16: rows are scaled by two to this
+    if (!SEED) xe = scan_begin<QT, FP16>(o, ctl, thr_l, fill, h_l, s, q_tile);
     const float xscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, xe))));
-    if (!SEED) {
-        for (int i = tid; i < QT; i += FW * 64) {
-            const int64_t q = q_tile + i;
-            float t = NAN;                                         // nothing compares: a slot that never collects
-            const bool hard = q < o.nq && o.hard[q >> 7];
-            // (The second scan may take two rounds of workgroups.  What overflowed in the first is left out of the other: where
-            // all do (1M x 128, 1000 queries, inner product, 1 % of the rows 10 000 times as long) 6.86 -> 6.65 ms.)
-            const int again = FP16 || q >= o.nq ? 0 : __hip_atomic_load(&o.again[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            bool mine = q < o.nq && (FP16 ? !hard : hard || again);
-            if (mine && !(again & DIRECT) && o.qn[q] <= HUGE_NORM) {
-                const int32_t kth = o.kth[q];
-                const float bound = kth == INT32_MIN ? -INFINITY : sortable_to_float(kth);
-                if (FP16) {
-                    // (a norm of up to 2^-50 taken as zero is off by 2^-50 |x| <= 2^(-35 - xe), scaled by 2^2 xe)
-                    const bool zero = o.qe[q] == NO_SCALE;
-                    const int e = zero ? xe : o.qe[q];
-                    if (e - xe > HALF_RANGE || xe - e > HALF_RANGE || (zero && xe > ZERO_SCALE) || leave) {
-                        mine = false;
-                        atomicOr(&o.again[q], AGAIN);
-                    } else {
-                        t = ldexpf(bound - 0.5f * (o.c + o.ch) * o.qn[q] * 1.00001f - 0x1p-110f, xe + e) - f32_half_filter_small(o.d);
-                        h_l[i] = ldexpf(o.h, e - xe);
-                        if (s == 0) o.qx[q] = xe + e;
-                    }
-                } else {
-                    t = bound - o.c * o.qn[q] * 1.00001f - 0x1p-110f;
-                }
-            }
-            if (t != t) atomicAdd(&ctl[CTL_DONE], 1);
-            thr_l[i] = t;
-            fill[i] = mine ? (again & DIRECT ? o.Cs + 1 : 0) : -1;
-        }
-    }
     __syncthreads();
     // Nothing to collect (to the second scan: the first has resolved all of them)?  The next barrier comes before any row
     // can be found lost, which is written to the same word.
@@ -655,57 +721,7 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
 #undef LPQF_MFMA
 #undef LPQF_ORDER
 
-    if (!SEED) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // (left early: the query copies on their way land before the LDS is given back)
-        __syncthreads();
-        // The rows set aside, summed in fp32 (off by less than the constant lets the rounded rows be): eight lanes to a row
-        // and query, eight values each at a time.  1M x 128, 1000 queries, one such row: 0.45 ms (L2) and 0.52 in all, as
-        // without it (the split's scan alone: 0.92; the first given up for it and the split's behind: 1.27).
-        const bool any = FP16 && ctl[CTL_ANY];
-#pragma clang loop unroll(disable)
-        for (int w = 0; any && w < FW; ++w) {
-            const int rows = ctl[CTL_ASIDE + w] < ASIDE ? ctl[CTL_ASIDE + w] : ASIDE, sub = tid & 7;
-            for (int at = tid >> 3; at < QT * rows; at += FW * 8) {
-                const int i = at % QT, tr = ctl[CTL_ROWS + w * ASIDE + at / QT];
-                const int64_t row = ((int64_t)s + (int64_t)(tr / TILE_ROWS) * S) * TILE_ROWS + tr % TILE_ROWS;
-                const _Float16 *qr = o.qf + (q_tile + i) * o.dp;
-                const float *xr = o.x + row * o.ldx;
-                float u = 0.0f, p = 0.0f;
-#pragma clang loop unroll(disable)
-                for (int c = 8 * sub; c < o.d; c += 64) {
-                    const v8h qv = *reinterpret_cast<const v8h *>(qr + c);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float v = c + e < o.d ? xr[c + e] * xscale : 0.0f;
-                        u = fmaf((float)qv[e], v, u);
-                        p = fmaf(v, v, p);
-                    }
-                }
-#pragma unroll
-                for (int m = 1; m < 8; m <<= 1) {
-                    u += __shfl_xor(u, m, 64);
-                    p += __shfl_xor(p, m, 64);
-                }
-                if (!(p <= LONG_NORM)) ctl[CTL_DONE] = ALL_LOST;
-                if (!(ldexpf(p, -2 * xe) <= HUGE_NORM)) ctl[CTL_HUGE] = 1;
-                u = fmaf(-h_l[i], p, u);
-                if (sub == 0 && u >= thr_l[i]) {
-                    const int pos = atomicAdd(&fill[i], 1);
-                    if (pos < o.Cs) cbase[(size_t)i * qstride + pos] = make_cand(~float_to_sortable(u), (uint32_t)row);
-                }
-            }
-        }
-        if (any) __syncthreads();                     // (the same in every thread)
-        // a row the bounds do not hold for: all queries of the tile overflow
-        const bool lost = ctl[CTL_DONE] >= ALL_LOST || ctl[CTL_HUGE];
-        for (int i = tid; i < QT; i += FW * 64) {
-            const int64_t q = q_tile + i;
-            if (q >= o.nq || (!FP16 && fill[i] < 0)) continue;
-            const int have = fill[i] < 0 ? 0 : (lost ? o.Cs + 1 : fill[i]);
-            o.ccnt[(size_t)q * S + s] = have;
-            if (have > o.Cs) atomicOr(&o.again[q], !FP16 || ctl[CTL_HUGE] ? DIRECT : AGAIN);
-        }
-    }
+    if (!SEED) scan_end<QT, FP16>(o, ctl, thr_l, fill, h_l, s, q_tile, xe, xscale);
     if (SEED) {
 #pragma unroll
         for (int o_ = 32; o_ > 0; o_ >>= 1) sum += __shfl_xor(sum, o_, 64);
@@ -718,6 +734,269 @@ __global__ __launch_bounds__(FW * 64, 2) void filter_f32_kernel(FilterIo o)
             atomicAdd(o.nxsum, sum);
         }
     }
+}
+
+// ---- the first scan of 65 to 128 features, queries kept in registers ---------------------------------
+// Eight waves on 512 queries, 64 to a wave, whose fp16 fragments stay in 64 registers; a stage is 64 whole rows, rounded
+// into one of two LDS slots and read by every wave.  Against the kernel above rows are rounded for 512 queries instead of
+// 256, the queries are not copied again for each tile of rows, and there is half a barrier to a matrix instruction: 1M x 128,
+// 1000 queries 390 -> 305 us (0.66 -> 0.84 PFLOP/s).  What bounds it is the power limit: 305 us in the first searches, 360
+// after a dozen, and neither epilogues that run during the next block's matrix instructions nor waits for one stage's loads
+// only (both built, 256 registers) changed it.
+constexpr int RQT = 512, RSR = 64, RKS = 8, RDP = 16 * RKS;
+constexpr size_t resident_lds_bytes()
+{
+    return (size_t)2 * RSR * RDP * 2 + 2 * RSR * 4 + (size_t)RQT * 12 + CTL_WORDS * 4 + (size_t)FW * FDUMPS * 80;
+}
+
+template <int FIX>   // rows shorter than 128 values, or scaled: decided once per workgroup
+__device__ __forceinline__ void resident_scan(const FilterIo &o, unsigned char *smem, float *nx, float *thr_l, int *fill, float *h_l, int *ctl,
+                                              int s, int64_t q_tile, int xe, float xscale, bool none)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int S = o.S;
+    float *dval = reinterpret_cast<float *>(ctl + CTL_WORDS) + wave * (FDUMPS * 20);
+    v4i *dmeta = reinterpret_cast<v4i *>(dval + FDUMPS * 16);
+    const int nt = (!none && o.tiles > s) ? (o.tiles - s + S - 1) / S : 0, T = nt * (TILE_ROWS / RSR);
+
+    v8h B[2][RKS];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int ks = 0; ks < RKS; ++ks)
+            B[j][ks] = *reinterpret_cast<const v8h *>(o.qf + (q_tile + wave * 64 + j * 32 + col) * RDP + ks * 16 + half * 8);
+
+    // ---- rows: registers -> fp16 in LDS ------------------------------------------------------------
+    // Eight lanes share a row, 16 bytes of each 128; chunk c (16 bytes in fp16) of row r sits in slot c ^ (r & 15).
+    const int lrow = tid >> 3, lcol = (tid & 7) * 4;
+    v4f pre[2][4];                    // stages on their way, stage t in set t & 1
+    int ft = 0, fb = 0;               // tile (of this split) and quarter of the tile that is fetched next
+    int pt = 0, pb = 0;               // ... and that goes to LDS next
+    auto fetch = [&](v4f (&to)[4]) LPQF_INLINE {
+        const int64_t t0 = ((int64_t)s + (int64_t)ft * S) * TILE_ROWS;
+        const int last = (int)(o.n - 1 - t0 < TILE_ROWS ? o.n - 1 - t0 : TILE_ROWS);   // rows past the end: any row, rejected later
+        const int r = fb * RSR + lrow;
+        const float *tile_rows = o.x + t0 * o.ldx;
+        const unsigned off = (unsigned)(r < last ? r : last) * (unsigned)o.ldx;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = j * 32 + lcol;
+            to[j] = *reinterpret_cast<const v4f_any *>(tile_rows + (off + (unsigned)(FIX && c > o.d - 4 ? o.d - 4 : c)));
+        }
+        const bool more = ft + 1 < nt;    // past the last stage the last tile's are fetched again
+        fb = fb + 1 == TILE_ROWS / RSR ? 0 : fb + 1;
+        ft += fb == 0 && more;
+    };
+    float part = 0.0f;
+    auto put = [&](v4f (&from)[4], int slot) LPQF_INLINE {
+        unsigned char *row = smem + slot * (RSR * RDP * 2) + lrow * (RDP * 2) + (tid & 1) * 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v4f v = from[j];
+            if (FIX) {
+                const int left = o.d - (j * 32 + lcol);
+                if (left < 4) v = left == 3 ? v4f{v[1], v[2], v[3], 0.f} : left == 2 ? v4f{v[2], v[3], 0.f, 0.f} : v4f{v[3], 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = e < left ? v[e] * xscale : 0.0f;
+            }
+            v4h f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                f[e] = (_Float16)v[e];
+                part = fmaf(v[e], v[e], part);
+            }
+            *reinterpret_cast<v4h *>(row + (((j * 4 + ((tid & 7) >> 1)) ^ (lrow & 15)) * 16)) = f;
+        }
+    };
+    auto put_done = [&](int slot) LPQF_INLINE {   // ... and the rows' norms
+        float p = part;
+        part = 0.0f;
+        p += __int_as_float(dpp_move<DPP_XOR1>(__float_as_int(p)));
+        p += __int_as_float(dpp_move<DPP_XOR2>(__float_as_int(p)));
+        p += __int_as_float(dpp_move<DPP_HALF_MIRROR>(__float_as_int(p)));
+        // set aside: without a norm no score of the row reaches a threshold
+        const unsigned long long far = __ballot(!(p <= HALF_NORM));
+        if (__builtin_expect(far != 0, 0)) {
+            const int at = pb * RSR + lrow;
+            const unsigned row = ((unsigned)s + (unsigned)(pt * S)) * TILE_ROWS + (unsigned)at;
+            if (((far >> lane) & 1) && (lane & 7) == 0 && row < (unsigned)o.n) {   // (not a copy of the last row)
+                const int pos = atomicAdd(&ctl[CTL_ASIDE + wave], 1);
+                ctl[CTL_ANY] = 1;
+                if (pos < ASIDE) ctl[CTL_ROWS + wave * ASIDE + pos] = pt * TILE_ROWS + at;
+                else ctl[CTL_DONE] = ALL_LOST;
+            }
+        }
+        if ((lane & 7) == 0) nx[slot * RSR + lrow] = p <= HALF_NORM ? p : NAN;
+        pb = pb + 1 == TILE_ROWS / RSR ? 0 : pb + 1;
+        pt += pb == 0;
+    };
+
+    cand_t *cbase = o.cbuf + ((size_t)q_tile * S + s) * o.Cs;
+    const size_t qstride = (size_t)S * o.Cs;
+    auto drain = [&](int dumps) LPQF_INLINE {     // queued scores that reach their query's threshold go to its region
+        wave_lds_sync();
+        for (int base = 0; base < dumps * 16; base += 64) {
+            const int at = base + lane;
+            if (at < dumps * 16) {
+                const float u = dval[at];
+                const v4i m4 = dmeta[at >> 4];
+                const int ql = m4[1] & (RQT - 1), r = at & 15;
+                const unsigned row = (unsigned)m4[0] + 8 * (r >> 2) + 4 * (m4[1] / RQT) + (r & 3);
+                if (u >= thr_l[ql] && row < (unsigned)o.n) {
+                    const int pos = atomicAdd(&fill[ql], 1);
+                    if (__builtin_expect(pos < o.Cs, 1)) {
+                        cbase[(size_t)ql * qstride + pos] = make_cand(~float_to_sortable(u), row);
+                    } else if (__builtin_expect(pos == o.Cs, 0)) {   // the second scan takes this query: collect no more for it
+                        thr_l[ql] = NAN;
+                        atomicAdd(&ctl[CTL_DONE], 1);
+                    }
+                }
+            }
+        }
+        wave_lds_sync();
+    };
+
+    const int a_base = col * (RDP * 2) + ((half ^ (col & 15)) * 16);
+    v8h A0[RKS], A1[RKS];
+    auto load = [&](v8h (&A)[RKS], int slot, int block) LPQF_INLINE {
+        const unsigned char *sb = smem + slot * (RSR * RDP * 2) + block * (32 * RDP * 2);
+#pragma unroll
+        for (int ks = 0; ks < RKS; ++ks) A[ks] = *reinterpret_cast<const v8h *>(sb + (a_base ^ (ks * 32)));
+    };
+    float thr[2], hq[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        thr[j] = thr_l[wave * 64 + j * 32 + col];
+        hq[j] = h_l[wave * 64 + j * 32 + col];
+    }
+    constexpr v16f ZERO = {};
+    int dumps = 0, t = 0;
+    auto block = [&](v8h (&A)[RKS], int slot, int blk, auto between) LPQF_INLINE {
+        v16f acc[2];
+#pragma unroll
+        for (int ks = 0; ks < RKS; ++ks)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[ks], B[j][ks], ks ? acc[j] : ZERO, 0, 0, 0);
+        between();
+        const float *np = nx + slot * RSR + blk * 32 + 4 * half;
+        v4f nv[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) nv[g] = *reinterpret_cast<const v4f *>(np + 8 * g);
+        __builtin_amdgcn_sched_barrier(0);        // nothing of the contraction drifts down into the epilogue
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            v16f v = acc[j];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = fmaf(-hq[j], nv[e >> 2][e & 3], v[e]);
+            float m = v[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) m = fmaxf(m, v[e]);
+            unsigned long long mask = __ballot(m >= thr[j]);
+            while (__builtin_expect(mask != 0, 0)) {   // queue the 16 scores of the lanes that pass
+                const int at = dumps + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                const bool put_ = ((mask >> lane) & 1) && at < FDUMPS;
+                if (put_) {
+                    v4f *dst = reinterpret_cast<v4f *>(dval + at * 16);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) dst[g] = v4f{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                    const int row0 = (s + (t / (TILE_ROWS / RSR)) * S) * TILE_ROWS + (t % (TILE_ROWS / RSR)) * RSR + blk * 32;
+                    dmeta[at] = v4i{row0, (wave * 64 + j * 32 + col) | (half * RQT), 0, 0};
+                }
+                const unsigned long long done = __ballot(put_);
+                dumps += __popcll(done);
+                mask &= ~done;
+                if (mask) { drain(dumps); dumps = 0; }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (T > 0) {
+        fetch(pre[0]);
+        fetch(pre[1]);
+        put(pre[0], 0);
+        put_done(0);
+        fetch(pre[0]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        load(A0, 0, 0);
+    }
+    auto stage = [&](auto parity) LPQF_INLINE {
+        constexpr int P = decltype(parity)::value;
+        load(A1, P, 1);
+        // stage t + 1 goes into the other slot, which was read out before the last barrier (after the last stage: stale
+        // values that nobody reads)
+        block(A0, P, 0, [&]() LPQF_INLINE { put(pre[P ^ 1], P ^ 1); });
+        fetch(pre[P ^ 1]);
+        block(A1, P, 1, [&]() LPQF_INLINE { if (t + 1 < T) put_done(P ^ 1); });
+        ++t;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // my reads of stage t and my writes of the next are complete
+        __syncthreads();
+        load(A0, P ^ 1, 0);                                  // (after the last stage: whatever the slot holds, unused)
+    };
+    constexpr std::integral_constant<int, 0> P0;
+    constexpr std::integral_constant<int, 1> P1;
+    int done = 0, said = 0, known = 0, next = 0;             // as in the kernel above
+    auto look = [&]() LPQF_INLINE {
+        done = ctl[CTL_DONE];
+        said = ctl[CTL_SAID + next];
+        next ^= 1;
+    };
+    look();
+#pragma clang loop unroll(disable)
+    while (t < T) {
+        stage(P0);
+        stage(P1);
+        stage(P0);
+        stage(P1);
+        if (dumps) { drain(dumps); dumps = 0; }
+        const int now = __builtin_amdgcn_readfirstlane(said);
+        if (__builtin_expect(now != known, 0)) {
+            if (now >= RQT) break;               // nothing left to collect
+            known = now;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) thr[j] = thr_l[wave * 64 + j * 32 + col];
+        }
+        if (tid == 0) ctl[CTL_SAID + (next ^ 1)] = done;
+        look();
+    }
+}
+
+__global__ __launch_bounds__(FW * 64, 2) void resident_scan_kernel(FilterIo o)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int total = o.qtiles * o.S, per = total / 8, b = blockIdx.x;
+    const int wk = (b < per * 8) ? (b % 8) * per + b / 8 : b;         // as in the kernel above
+    const int s = wk / o.qtiles, qt = (wk + s) % o.qtiles;
+    float *nx = reinterpret_cast<float *>(smem + 2 * RSR * RDP * 2);
+    float *thr_l = nx + 2 * RSR;
+    int *fill = reinterpret_cast<int *>(thr_l + RQT);
+    float *h_l = reinterpret_cast<float *>(fill + RQT);
+    int *ctl = fill + 2 * RQT;
+    const int64_t q_tile = (int64_t)qt * RQT;
+    const int xe = scan_begin<RQT, true>(o, ctl, thr_l, fill, h_l, s, q_tile);
+    const float xscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, xe))));
+    __syncthreads();
+    const bool none = ctl[CTL_DONE] >= RQT;      // nothing to collect
+    __syncthreads();
+    if (o.d == RDP && xe == 0) resident_scan<0>(o, smem, nx, thr_l, fill, h_l, ctl, s, q_tile, xe, xscale, none);
+    else resident_scan<1>(o, smem, nx, thr_l, fill, h_l, ctl, s, q_tile, xe, xscale, none);
+    scan_end<RQT, true>(o, ctl, thr_l, fill, h_l, s, q_tile, xe, xscale);
+}
+
+hipError_t launch_resident(const FilterIo &o, hipStream_t st)
+{
+    if (o.dp != RDP || o.d < 4) return hipErrorInvalidValue;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(resident_scan_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    resident_scan_kernel<<<(unsigned)(o.qtiles * o.S), FW * 64, resident_lds_bytes(), st>>>(o);
+    return hipGetLastError();
 }
 
 template <bool SEED, int WQ, bool FP16>
@@ -757,8 +1036,12 @@ F32Filter f32_filter_plan(int64_t n, int64_t nq, int d, int k)
     // 45 with it, 10 000 x 64, 2000 queries 48 and 52; 1M x 128, 128 queries 197 and 159).
     p.half = (double)n * (double)round_up(nq, 64) * (double)round_up(d, 2 * KF) >= 4e9;
     p.wq_half = !p.half ? p.wq : nq <= 64 ? 1 : (nq <= 128 ? 2 : 4);
+    // 65 to 128 features: queries in registers, where their padding to tiles of 512 is not more than a quarter above the one to 256
+    // (whole searches on 1M x 128, tiles of 256 / this, us: 1000 queries 430 / 356, 500 249 / 210, 300 229 / 191; 700, not taken,
+    // 333 / 329; 600 on 300 000 x 70, not taken, 154 / 170).
+    if (p.half && round_up(d, 2 * KF) == RDP && nq > 256 && 4 * round_up(nq, RQT) <= 5 * round_up(nq, 256)) p.wq_half = RQT / 64;
     p.qtiles_half = (int)ceil_div(nq, 64 * p.wq_half);
-    p.nq_pad = round_up(nq, 256);
+    p.nq_pad = round_up(nq, p.wq_half == RQT / 64 ? RQT : 256);
     p.dp = (int)round_up(d, 2 * KF);
     // The sample costs a contraction per row and query (or, for few queries, the bytes of its rows), each
     // item it lets through - about k n / rows per query - the bytes of a row: least at rows ~ sqrt(k n)
@@ -863,7 +1146,8 @@ hipError_t launch_f32_filter(const F32Filter &p, const float *x, int64_t n, int6
         o.h = l2 ? 0.5f * (1.0f - o.ch) : -0.5f * o.ch;
         o.qtiles = p.qtiles_half; o.kst = p.dp / KF;
         e = p.wq_half == 1 ? launch_filter<false, 1, true>(o, st)
-                           : (p.wq_half == 2 ? launch_filter<false, 2, true>(o, st) : launch_filter<false, 4, true>(o, st));
+                           : (p.wq_half == 2 ? launch_filter<false, 2, true>(o, st)
+                              : p.wq_half == 4 ? launch_filter<false, 4, true>(o, st) : launch_resident(o, st));
         if (e != hipSuccess) return e;
     }
     o.h = l2 ? 0.5f * (1.0f - o.c) : -0.5f * o.c;
