@@ -327,7 +327,7 @@ int lpq_probe_stream(const void *src_dev, size_t bytes, int mode, int reps, doub
  * searched again (0 when the search did not use the collecting variant) and the
  * largest number of candidates any region received in the last round of the scan.  Of a small batch
  * that was searched by group maxima: the queries that more groups of rows tie for than are worked off
- * at once, and 0.  Synchronises the device. */
+ * at once, and the most candidates one of the last workgroups kept.  Synchronises the device. */
 int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,
                               int64_t *redone_queries, int64_t *max_region_fill);
 

@@ -575,7 +575,9 @@ int seed_rank(int64_t n, int64_t rows, int64_t nq, int k)
 // rows between the waves of a workgroup, 64 queries each, so that every further 64 queries read the corpus again, and the
 // finishing workgroups read about k groups of rows per query: the lines below bound both.  us, other scans / this one,
 // 128 features, k = 10: one query on 1M rows 56 / 42, 16 on 10M x 96 200 / 197, 100 on 10 000 35 / 19, 1000 47 / 26, 100 on
-// 200 000 41 / 27, 256 46 / 35, 600 56 / 54 to 68, 100 on 1M 62 / 48, 200 67 / 76, 128 on 5M x 96 160 / 178.
+// 200 000 41 / 27, 256 46 / 35, 600 56 / 54 to 68, 100 on 1M 62 / 48, 200 67 / 76, 128 on 5M x 96 160 / 178.  Rows of 384 bytes
+// and more through the streaming scan: 16 on 300 000 x 512 89 / 43, 128 94 / 50, 16 on 500 000 x 768 107 / 91, 64, k = 100 124 /
+// 125, 128 114 / 123, 100 on 1M x 384 146 / 118, 200 on 100 000 x 768 62 / 51, on 30 000 x 2048 72 / 59, 1 on 40 000 x 1500 63 / 36.
 void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
 {
     const int64_t n = idx->size;
@@ -583,18 +585,21 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
         if (tune(key)) return;
     // (Short rows of few bits tie, and every group that ties with the k-th has its rows scored again: 16 queries on 1M skewed
     // integers of 24 features, 3 bits 46 / 341.)
-    if (nq < 1 || nq > 4096 || idx->bits < 4 || (idx->bits < 6 && idx->d < 64) || k > MAXIMA_MAX_K || idx->d_pad > MAXIMA_MAX_D || (idx->packed && nq > 64)) return;
-    const int waves = mfma_row_split_waves(idx->d_pad, idx->packed);
+    if (nq < 1 || nq > 4096 || idx->bits < 4 || (idx->bits < 6 && idx->d < 64) || k > MAXIMA_MAX_K || idx->d_pad > MAXIMA_MAX_D) return;
+    const bool stream = idx->d_pad > 256;     // by the streaming scan, whose workgroups have eight waves and a CU to themselves
+    if (nq > (idx->packed ? 64 : stream ? 512 : 4096)) return;
+    const int waves = stream ? 8 : mfma_row_split_waves(idx->d_pad, idx->packed);
     const int64_t tiles = ceil_div(nq, 64), row_bytes = idx->packed ? idx->d_pad / 2 : idx->d_pad;
     if (idx->packed && idx->d_pad <= 128 && n > 3'000'000) return;   // (16 queries at 4 bits: 2M x 64 57 / 51, 10M x 96 139 / 155)
-    if (tiles == 2 && tiles * n * row_bytes > int64_t(512) << 20) return;
-    if (tiles > 2 && tiles * tiles * n * (row_bytes > 128 ? 2 * row_bytes : 128) > int64_t(512) << 20) return;
+    if (stream && tiles > 1 && tiles * n * row_bytes > int64_t(row_bytes < 768 ? 1024 : 420) << 20) return;
+    if (!stream && tiles == 2 && tiles * n * row_bytes > int64_t(512) << 20) return;
+    if (!stream && tiles > 2 && tiles * tiles * n * (row_bytes > 128 ? 2 * row_bytes : 128) > int64_t(512) << 20) return;
     MaximaShape m;
     m.parts = 2 * waves;
     m.stage_rows = 32 * waves;
     m.stages = (int)(n / m.stage_rows);
     if (m.stages < 16) return;
-    const int slots = (int)(512 / tiles);
+    const int slots = (int)((stream ? 256 : 512) / tiles);
     m.S = m.stages < slots ? m.stages : slots;
     // As many groups as the finishing threads hold, 16 each: workgroups of 256 where there are no more groups than that, or
     // where many queries need few rows each (a CU takes one of 1024 threads, or four).
@@ -608,20 +613,22 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
         return 1.1 * (double)k * (double)n / (double)m.G;       // rows of the groups that reach the bound
     };
     double rows = shape();
-    if (m.G <= 16 * 256 || (tiles > 1 && 1.1 * (double)k * (double)n / (16.0 * 256.0) <= 768.0)) {
+    if (!stream && (m.G <= 16 * 256 || (tiles > 1 && 1.1 * (double)k * (double)n / (16.0 * 256.0) <= 768.0))) {
         threads = 256;
         rows = shape();
     }
     if (m.G % 16 || m.G > 16 * threads || m.G / (threads == 256 ? 4 : 16) < k || m.seg_stages > 1000) return;
     const double finish_bytes = (double)nq * (rows * (double)row_bytes + 4.0 * m.G);
-    if (finish_bytes > (double)((tiles > 1 ? 32 : (k <= 10 ? 40 : 160)) << 20)) return;
-    int64_t h = (int64_t)(rows / 768.0), most = (threads == 256 ? 1024 : 256) / nq;
+    // (streamed rows that the memory-side cache does not hold cost the other scans least and these workgroups most)
+    const int most_mb = stream ? (row_bytes < 768 || n * row_bytes < int64_t(128) << 20 ? 160 : 48) : tiles > 1 ? 32 : (k <= 10 ? 40 : 160);
+    if (finish_bytes > (double)most_mb * (1 << 20)) return;
+    int64_t h = (int64_t)(rows * (double)(row_bytes > 128 ? row_bytes : 128) / (768.0 * 128.0)), most = (threads == 256 ? 1024 : 256) / nq;
     if (most > 16) most = 16;
     if (h > most) h = most;
     if (h * k > 2048) h = 2048 / k;
     p.helpers = (int)(h < 1 ? 1 : h);
     p.finish_threads = threads;
-    p.rsplit = true; p.rs_waves = waves;
+    p.rsplit = !stream; p.rs_waves = waves;
     p.groups = m;
     p.maxima = true;
 }
@@ -882,7 +889,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     if (p.maxima) {
         p.off_lists1 = p.off_seedlist = p.off_seeds = o;
         p.off_lists2 = o;   o = align256(o + (size_t)nq * p.helpers * k * sizeof(cand_t));
-        p.off_gmax = o;     o = align256(o + (size_t)nq * p.groups.G * sizeof(int32_t));
+        p.off_gmax = o;     o = align256(o + (size_t)(idx->d_pad > 256 ? round_up(nq, 64) : nq) * p.groups.G * sizeof(int32_t));
         p.off_merge_tmp = p.off_cbuf = o;
         p.off_ccnt = o;     o = align256(o + (size_t)nq * p.helpers * sizeof(int32_t));
         p.off_over = o;     o = align256(o + (size_t)nq * sizeof(int32_t));
@@ -1016,7 +1023,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
         int32_t *done = reinterpret_cast<int32_t *>(ws + p.off_over);
         {
             KernelSpan span(st);
-            HIP_TRY(launch_maxima_mfma(a, p.groups, gmax, done, st));
+            HIP_TRY(idx->d_pad > 256 ? launch_maxima_stream(a, p.groups, gmax, done, st) : launch_maxima_mfma(a, p.groups, gmax, done, st));
         }
         HIP_TRY(launch_maxima_finish(a, p.groups, gmax, p.finish_threads, p.helpers, lists2, reinterpret_cast<int32_t *>(ws + p.off_ccnt), done, ids, dist,
                                      qnorms, emit_mode, st));
@@ -1313,13 +1320,11 @@ extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k
     const Plan p = make_plan(idx, nq, k);
     if (p.mode != PLAN_MFMA_COLLECT && !p.maxima) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
-    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * p.SS);
+    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * (p.maxima ? p.helpers : p.SS));
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);
     HIP_TRY(hipMemcpy(over.data(), ws + p.off_over, over.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (p.maxima) {   // none is searched again; those that many groups tied for take longer
-        for (int32_t v : over) *redone_queries += (v & MAXIMA_MANY) != 0;
-        return LPQ_OK;
-    }
+    for (int32_t &v : over)
+        if (p.maxima) v &= MAXIMA_MANY;   // none is searched again; those that many groups tie for take longer
     HIP_TRY(hipMemcpy(cnt.data(), ws + p.off_ccnt, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     for (int32_t v : over) *redone_queries += v != 0;
     for (int32_t v : cnt) if (v > *max_region_fill) *max_region_fill = v;

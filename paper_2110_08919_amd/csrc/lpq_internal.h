@@ -216,9 +216,12 @@ struct MaximaShape {
     int stage_rows = 0, stages = 0;
     int seg_stages = 0;     // most stages of a segment
 };
-enum { MAXIMA_MAX_K = 128, MAXIMA_MAX_D = 256, MAXIMA_MANY = 1 << 16 };
+enum { MAXIMA_MAX_K = 128, MAXIMA_MAX_D = 4096, MAXIMA_MANY = 1 << 16 };
 // Also sets done[0 .. nq) to 0.
 hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
+// The same for rows of 384 bytes and more, by the streaming scan in tiles of 64 queries: a stage is a tile of 256 rows, shared
+// by eight waves.  Writes gmax of whole tiles.
+hipError_t launch_maxima_stream(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
 // The k best from the maxima: H workgroups of 256 or 1024 threads (up to 16 groups to a thread) per query, lists[nq][H][k],
 // counts[nq][H].  done[q] holds MAXIMA_MANY afterwards if more groups reached the bound than are worked off at once.
 hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int H, cand_t *lists,

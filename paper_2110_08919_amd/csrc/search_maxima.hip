@@ -13,7 +13,7 @@ namespace lpq {
 
 namespace {
 
-constexpr int MF_FLY = 8;             // rows a lane has in flight
+constexpr int MF_FLY = 8;             // 16-byte loads of rows a lane has in flight
 constexpr int MF_UNITS = 1024;        // units worked off at a time; a unit is the 16 rows of a group in one stage
 constexpr int MF_TAIL = 8;            // blocks of 32 rows behind the last whole stage, at most
 constexpr int MF_MERGE = 2048;        // candidates of all helpers together, at most
@@ -46,14 +46,15 @@ __device__ __forceinline__ int chunk_dot(uint4 xv, const uint4 *qs, int c)
 
 // H workgroups per query: each finds the same bound from the maxima, scores its share of the rows of the groups that reach
 // it, and the one that ends last merges.  What bounds it is latency: a round trip to memory for the maxima (V 16-byte loads a
-// thread, all in flight at once), one per step of 1024 rows (512 beyond 128 bytes), and two with the fences where helpers
-// share the work.  LR lanes share a row, 16 bytes each.
-template <int NT, bool PACKED, int LR, int V>
+// thread, all in flight at once), one per step of 128 KB of rows, and two with the fences where helpers share the work.  LR lanes share a row, CPL times 16 bytes each.
+template <int NT, bool PACKED, int LR, int CPL>
 __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     SearchArgs a, MaximaShape m, const int32_t *__restrict__ gmax, int H, cand_t *lists, int32_t *counts, int32_t *done, int cap,
     int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
 {
-    constexpr int ROWS = NT / LR;                           // rows side by side, 16 to a unit
+    constexpr int ROWS = NT / LR, FLY = MF_FLY / CPL;               // rows side by side and behind one another in a step, 16 to a unit
+    constexpr int V = 4;
+    static_assert(FLY * ROWS % 16 == 0, "a step takes whole units");
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);                 // [max(cap, merge)]
     __shared__ uint4 qs[MAXIMA_MAX_D / 16];
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         const int i = tid + j * NT;
         v[j] = i < m.G / 4 ? gm[i] : int4{INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
     }
-    if (tid < a.d_pad / 16) qs[tid] = reinterpret_cast<const uint4 *>(a.qcodes + q * a.d_pad)[tid];
+    for (int i = tid; i < a.d_pad / 16; i += NT) qs[i] = reinterpret_cast<const uint4 *>(a.qcodes + q * a.d_pad)[i];
     for (int i = tid; i < cap; i += NT) buf[i] = CAND_NONE;
     if (tid < 2) s_count[tid] = 0;
     if (tid == 0) s_hits = s_units = 0;
@@ -113,25 +114,30 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     // ---- rows of the groups that reach it --------------------------------------------------------
     AppendSteps at;
     const uint4 *rows = reinterpret_cast<const uint4 *>(a.codes);
-    const int chunks = a.d_pad >> (PACKED ? 5 : 4), chunk = sub < chunks ? sub : 0;
-    // one step: `pick(i)` is the row of slot i (0 .. MF_FLY * ROWS - 1) or -1
+    const int chunks = a.d_pad >> (PACKED ? 5 : 4);
+    // one step: `pick(i)` is the row of slot i (0 .. FLY * ROWS - 1) or -1
     auto step = [&](auto pick) {
-        int row[MF_FLY], nx[MF_FLY];
-        uint4 x[MF_FLY];
+        int row[FLY], nx[FLY];
+        uint4 x[FLY][CPL];
 #pragma unroll
-        for (int u = 0; u < MF_FLY; ++u) {                          // all loads in flight before the first is used
+        for (int u = 0; u < FLY; ++u) {                             // all loads in flight before the first is used
             row[u] = pick(grp + u * ROWS);
             const size_t r = row[u] >= 0 ? row[u] : 0;
-            x[u] = rows[r * chunks + chunk];
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) x[u][c] = rows[r * chunks + (sub + c * LR < chunks ? sub + c * LR : 0)];
             nx[u] = l2 ? a.norms[r] : 0;
         }
 #pragma unroll
-        for (int u = 0; u < MF_FLY; ++u) {
-            int dot = sub < chunks ? chunk_dot<PACKED>(x[u], qs, sub) : 0;
+        for (int u = 0; u < FLY; ++u) {
+            int dot = 0;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) dot += sub + c * LR < chunks ? chunk_dot<PACKED>(x[u][c], qs, sub + c * LR) : 0;
             dot += dpp_move<DPP_XOR1>(dot);
             dot += dpp_move<DPP_XOR2>(dot);
             dot += dpp_move<DPP_HALF_MIRROR>(dot);
-            if (LR == 16) dot += dpp_move<DPP_ROW_MIRROR>(dot);
+            if (LR >= 16) dot += dpp_move<DPP_ROW_MIRROR>(dot);
+            if (LR >= 32) dot += __shfl_xor(dot, 16, 64);
+            if (LR >= 64) dot += __shfl_xor(dot, 32, 64);
             if (sub == 0 && row[u] >= 0) {
                 const cand_t c = make_cand(nx[u] - 2 * dot, (uint32_t)row[u]);
                 if (c < s_thr) buf[at.held - at.before + atomicAdd(&s_count[at.turn], 1)] = c;
@@ -139,7 +145,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         }
         __syncthreads();
         at.step_done(__builtin_amdgcn_readfirstlane(s_count[at.turn]));
-        block_compact_if_full(buf, cap, a.k, MF_FLY * ROWS, at.held, &s_thr);
+        block_compact_if_full(buf, cap, a.k, FLY * ROWS, at.held, &s_thr);
     };
     // all groups at once, or as many at a time as the list of units surely has room for
     for (int from = 0, window = m.G; from < m.G;) {
@@ -185,7 +191,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
             __syncthreads();
             continue;
         }
-        for (int base = 0; base < units; base += MF_FLY * ROWS / 16)
+        for (int base = 0; base < units; base += FLY * ROWS / 16)
             step([&](int i) {
                 const int j = i & 15, row = base + (i >> 4) < units ? s_unit[base + (i >> 4)] + 8 * (j >> 2) + (j & 3) : -1;
                 return row < (int)a.n ? row : -1;
@@ -212,10 +218,10 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         for (int i = tid; i < a.k; i += NT) put(i, buf[i]);
     };
     int held = at.held;
+    if (tid == 0) counts[q * H + h] = held < a.k ? held : a.k;
     if (H > 1) {
         cand_t *mine = lists + (q * H + h) * a.k;
         finish(held, [&](int r, cand_t c) { mine[r] = c; });
-        if (tid == 0) counts[q * H + h] = held < a.k ? held : a.k;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wave's part has reached the L2 ...
         __syncthreads();
         if (tid == 0) {
@@ -240,11 +246,13 @@ hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const
                                 int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st)
 {
     if (a.nq <= 0) return hipSuccess;
-    const int chunks = a.d_pad / (a.packed ? 32 : 16), lr = chunks <= 8 ? 8 : 16, step = MF_FLY * threads / lr;
+    const int chunks = a.d_pad / (a.packed ? 32 : 16), lr = chunks <= 8 ? 8 : chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
+    const int per_lane = chunks <= 64 ? 1 : (chunks <= 128 ? 2 : 4), step = MF_FLY / per_lane * threads / lr;
     const int tops = threads == 256 ? m.G / 4 : m.G / 16;
     // the bound is the k-th of the (foursomes of) threads' maxima, a unit list holds a group and the rows behind the last
     // stage, and all that the helpers keep fits one merge
-    if ((threads != 256 && threads != 1024) || a.k < 1 || a.k > MAXIMA_MAX_K || chunks > 16 || a.d_pad > MAXIMA_MAX_D || H < 1 ||
+    if ((threads != 256 && threads != 1024) || a.k < 1 || a.k > MAXIMA_MAX_K || (threads == 256 && chunks > 16) ||
+        (a.packed && chunks > 8) || a.d_pad > MAXIMA_MAX_D || H < 1 ||
         H * a.k > MF_MERGE || m.G % 16 || tops < a.k || m.G > 16 * threads || m.seg_stages > MF_UNITS - 2 * MF_TAIL ||
         a.n - (int64_t)m.stages * m.stage_rows > 32 * MF_TAIL)
         return hipErrorInvalidValue;
@@ -256,11 +264,18 @@ hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const
         return hipGetLastError();
     };
     if (threads == 256) {
-        if (a.packed) return launch(maxima_finish_kernel<256, true, 8, 4>);
-        return lr == 8 ? launch(maxima_finish_kernel<256, false, 8, 4>) : launch(maxima_finish_kernel<256, false, 16, 4>);
+        if (a.packed) return launch(maxima_finish_kernel<256, true, 8, 1>);
+        return lr == 8 ? launch(maxima_finish_kernel<256, false, 8, 1>) : launch(maxima_finish_kernel<256, false, 16, 1>);
     }
-    if (a.packed) return launch(maxima_finish_kernel<1024, true, 8, 4>);
-    return lr == 8 ? launch(maxima_finish_kernel<1024, false, 8, 4>) : launch(maxima_finish_kernel<1024, false, 16, 4>);
+    if (a.packed) return launch(maxima_finish_kernel<1024, true, 8, 1>);
+    switch (lr) {
+    case 8: return launch(maxima_finish_kernel<1024, false, 8, 1>);
+    case 16: return launch(maxima_finish_kernel<1024, false, 16, 1>);
+    case 32: return launch(maxima_finish_kernel<1024, false, 32, 1>);
+    default: break;
+    }
+    if (per_lane == 1) return launch(maxima_finish_kernel<1024, false, 64, 1>);
+    return per_lane == 2 ? launch(maxima_finish_kernel<1024, false, 64, 2>) : launch(maxima_finish_kernel<1024, false, 64, 4>);
 }
 
 }  // namespace lpq

@@ -52,6 +52,7 @@ struct StreamIo {
     int64_t run_gap;       // ... and its runs of 16 items are this far apart (16: consecutive rows)
     int kst;               // stages per tile = ceil(d / 128)
     int qgroup;            // query tiles that one XCD works on at a time
+    int32_t *done;         // search by group maxima (the pass reads every tile of consecutive rows, every segment has some): done[0 .. nq) = 0
 };
 
 // stages in the ring, and accumulator dumps a wave can queue: what 160 KB of LDS hold
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
     int it = 0, ik = 0, islot = 0;     // the next stage to issue: tile (of this split), stage of the tile, ring slot
     auto first_row = [&](int t) {      // of the split's t-th tile
         const int64_t r = ((int64_t)s + (int64_t)S * t) * o.tile_stride;
-        return SEED ? r + sample_shift((unsigned)(s + S * t), o.tile_stride - RUN) : r;
+        return SEED ? r + sample_shift((unsigned)(s + S * t), o.done ? 0 : o.tile_stride - RUN) : r;
     };
     int64_t irow = first_row(0);
     auto issue = [&]() {
@@ -219,7 +220,10 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
             gm[j] = INT32_MIN;
         }
     };
-    if (SEED) {   // segments this split never reaches keep the neutral value
+    if (SEED && o.done) {
+        if (blockIdx.x == 0)
+            for (int i = tid; i < a.nq; i += SW * 64) o.done[i] = 0;
+    } else if (SEED) {   // segments this split never reaches keep the neutral value
         for (int g = 0; g < o.SEG; ++g) flush_segment(g);
     }
 
@@ -414,6 +418,20 @@ hipError_t launch_stream_seed(const SearchArgs &a, int tiles, int64_t run_stride
     o.tiles = tiles; o.tile_stride = run_stride; o.run_gap = (int64_t)tiles * run_stride;
     o.kst = (int)ceil_div(a.d, KB);
     return launch_stream<true>(a, a.n, S, o, st);
+}
+
+hipError_t launch_maxima_stream(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st)
+{
+    if (a.nq < 1 || !gmax || !done || m.S < 1 || m.SEG < 1 || m.SEG > m.stages / m.S || m.stage_rows != TILE_ROWS ||
+        (int64_t)m.stages * TILE_ROWS > a.n || m.G != mfma_seed_groups(m.S, m.SEG, SW))
+        return hipErrorInvalidValue;
+    StreamIo o = {};
+    o.gmax = gmax; o.SEG = m.SEG; o.done = done;
+    o.tiles = m.stages; o.tile_stride = TILE_ROWS; o.run_gap = RUN;
+    o.kst = (int)ceil_div(a.d, KB);
+    if (a.packed || a.d_pad % KB || o.kst < 3) return hipErrorInvalidValue;   // (as launch_stream)
+    return a.metric == LPQ_METRIC_L2SQ ? launch_wq<true, true, 1>(a, (int64_t)m.stages * TILE_ROWS, m.S, o, st)
+                                       : launch_wq<false, true, 1>(a, (int64_t)m.stages * TILE_ROWS, m.S, o, st);
 }
 
 hipError_t launch_stream_collect(const SearchArgs &a, int S, const cand_t *seeds, cand_t *cbuf, int32_t *ccnt, int Cs,

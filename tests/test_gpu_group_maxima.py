@@ -1,4 +1,4 @@
-"""Small batches by group maxima (three launches): both metrics, row lengths of both kinds of workgroup, packed rows, rows left
+"""Small batches by group maxima (three launches): both metrics, row lengths of all kinds of workgroup, packed rows, rows left
 over behind the last whole stage, one and many groups to a split, every limit of k and batch, and more groups at the bound
 than a workgroup works off at a time (few distinct vectors).  Against the generic kernel.  Needs a real MI355X."""
 import pytest
@@ -29,6 +29,9 @@ def _check(x, q, k, metric, bits=8, packed=False):
     (4096, 24, 1, 1), (4223, 64, 3, 10), (10_000, 128, 64, 128), (65_535, 96, 16, 10), (70_001, 100, 63, 33), (200_129, 128, 5, 100),
     (300_000, 40, 64, 2), (131_072, 192, 7, 10), (131_135, 256, 64, 100), (9000, 200, 1, 128), (1_000_000, 128, 1, 10),
     (2_000_003, 33, 2, 17),
+    # streamed rows: one, two and four loads to a lane of the last kernel
+    (4096, 384, 5, 16), (70_001, 300, 64, 100), (66_000, 512, 1, 10), (100_255, 700, 16, 10), (50_007, 1024, 33, 128), (30_300, 1500, 64, 20),
+    (40_001, 2048, 9, 10), (20_100, 2100, 64, 33), (12_345, 4000, 3, 40),
 ])
 def test_small_batches(metric, n, d, nq, k):
     g = torch.Generator(device="cuda").manual_seed(n)
@@ -51,3 +54,10 @@ def test_many_groups_at_the_bound(metric, n, distinct, nq, k):
     else:            # two values to a feature
         x = torch.randint(0, 2, (n, 32), generator=g, device="cuda").float()
     _check(x, x[: nq].clone(), k, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+def test_many_groups_of_streamed_rows_at_the_bound(metric):
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((11, 600), generator=g, device="cuda")[torch.randint(0, 11, (40_000,), generator=g, device="cuda")].contiguous()
+    _check(x, x[:20].clone(), 10, metric)

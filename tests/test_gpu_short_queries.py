@@ -33,7 +33,7 @@ def _sampled_rows(n, d, nq, plan):
 @pytest.mark.parametrize("n,d,nq,k,short", [
     (200_000, 64, 300, 16, 1), (200_000, 128, 2000, 16, 70),     # by the generic kernel, by the register lists
     (200_000, 100, 300, 60, 2), (300_000, 128, 2100, 30, 40),    # by the generic kernel at once, by a further round
-    (200_000, 384, 600, 30, 15), (100_000, 700, 200, 20, 9),     # long rows, streamed rows
+    (200_000, 384, 600, 30, 15), (100_000, 700, 600, 20, 9),     # long rows, streamed rows (more than 512 queries: smaller batches are not sampled)
 ])
 def test_queries_with_too_few_candidates(metric, n, d, nq, k, short):
     from paper_2110_08919_amd import lpq
