@@ -546,7 +546,7 @@ struct Plan {
     int expect = 0;         // PLAN_MFMA_COLLECT: expected candidates per query
     bool maxima = false;    // in place of either: a search by group maxima of all rows, finished by helpers workgroups per query
     MaximaShape groups;
-    int helpers = 0, finish_threads = 0;
+    int helpers = 0, most_helpers = 0, finish_threads = 0;
     size_t off_qcodes = 0, off_qnorms = 0, off_lists1 = 0, off_seedlist = 0, off_seeds = 0, off_lists2 = 0,
            off_gmax = 0, off_merge_tmp = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_qlist = 0, off_redo = 0, off_bounds2 = 0, off_over2 = 0,
            off_qlist2 = 0, total = 0;
@@ -617,16 +617,17 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
         threads = 256;
         rows = shape();
     }
-    if (m.G % 16 || m.G > 16 * threads || m.G / (threads == 256 ? 4 : 16) < k || m.seg_stages > 1000) return;
+    if (m.G % 16 || m.G > 16 * threads || m.G / (threads == 256 ? 4 : 16) < k) return;
     const double finish_bytes = (double)nq * (rows * (double)row_bytes + 4.0 * m.G);
     // (streamed rows that the memory-side cache does not hold cost the other scans least and these workgroups most)
     const int most_mb = stream ? (row_bytes < 768 || n * row_bytes < int64_t(128) << 20 ? 160 : 48) : tiles > 1 ? 32 : (k <= 10 ? 40 : 160);
     if (finish_bytes > (double)most_mb * (1 << 20)) return;
     int64_t h = (int64_t)(rows * (double)(row_bytes > 128 ? row_bytes : 128) / (768.0 * 128.0)), most = (threads == 256 ? 1024 : 256) / nq;
     if (most > 16) most = 16;
-    if (h > most) h = most;
-    if (h * k > 2048) h = 2048 / k;
-    p.helpers = (int)(h < 1 ? 1 : h);
+    if (most * k > 2048) most = 2048 / k;
+    if (most < 1) most = 1;
+    p.most_helpers = (int)most;      // (one query on 1M x 64, every second row zero: 2.9 ms by one workgroup)
+    p.helpers = (int)(h < 1 ? 1 : (h > most ? most : h));
     p.finish_threads = threads;
     p.rsplit = !stream; p.rs_waves = waves;
     p.groups = m;
@@ -888,10 +889,10 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     p.off_qnorms = o;   o = align256(o + (size_t)p.nq_pad * sizeof(int32_t));
     if (p.maxima) {
         p.off_lists1 = p.off_seedlist = p.off_seeds = o;
-        p.off_lists2 = o;   o = align256(o + (size_t)nq * p.helpers * k * sizeof(cand_t));
+        p.off_lists2 = o;   o = align256(o + (size_t)nq * p.most_helpers * k * sizeof(cand_t));
         p.off_gmax = o;     o = align256(o + (size_t)(idx->d_pad > 256 ? round_up(nq, 64) : nq) * p.groups.G * sizeof(int32_t));
         p.off_merge_tmp = p.off_cbuf = o;
-        p.off_ccnt = o;     o = align256(o + (size_t)nq * p.helpers * sizeof(int32_t));
+        p.off_ccnt = o;     o = align256(o + (size_t)nq * p.most_helpers * sizeof(int32_t));
         p.off_over = o;     o = align256(o + (size_t)nq * sizeof(int32_t));
         p.off_qlist = p.off_redo = p.off_bounds2 = p.off_over2 = p.off_qlist2 = p.total = o;
         return p;
@@ -1025,7 +1026,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
             KernelSpan span(st);
             HIP_TRY(idx->d_pad > 256 ? launch_maxima_stream(a, p.groups, gmax, done, st) : launch_maxima_mfma(a, p.groups, gmax, done, st));
         }
-        HIP_TRY(launch_maxima_finish(a, p.groups, gmax, p.finish_threads, p.helpers, lists2, reinterpret_cast<int32_t *>(ws + p.off_ccnt), done, ids, dist,
+        HIP_TRY(launch_maxima_finish(a, p.groups, gmax, p.finish_threads, p.helpers, p.most_helpers, lists2, reinterpret_cast<int32_t *>(ws + p.off_ccnt), done, ids, dist,
                                      qnorms, emit_mode, st));
     } else if (p.mode == PLAN_MFMA_COLLECT) {
         cand_t *cbuf = reinterpret_cast<cand_t *>(ws + p.off_cbuf);
@@ -1320,12 +1321,15 @@ extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k
     const Plan p = make_plan(idx, nq, k);
     if (p.mode != PLAN_MFMA_COLLECT && !p.maxima) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
-    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * (p.maxima ? p.helpers : p.SS));
+    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * (p.maxima ? p.most_helpers : p.SS));
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);
     HIP_TRY(hipMemcpy(over.data(), ws + p.off_over, over.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    for (int32_t &v : over)
-        if (p.maxima) v &= MAXIMA_MANY;   // none is searched again; those that many groups tie for take longer
     HIP_TRY(hipMemcpy(cnt.data(), ws + p.off_ccnt, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (p.maxima) {   // none is searched again, those that many groups tie for take longer; a query's first workgroup has always worked
+        for (int32_t &v : over) v &= MAXIMA_MANY;
+        for (size_t i = 0; i < cnt.size(); ++i)
+            if (i % p.most_helpers) cnt[i] = 0;
+    }
     for (int32_t v : over) *redone_queries += v != 0;
     for (int32_t v : cnt) if (v > *max_region_fill) *max_region_fill = v;
     return LPQ_OK;

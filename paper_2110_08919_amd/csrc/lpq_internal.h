@@ -222,10 +222,10 @@ hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t
 // The same for rows of 384 bytes and more, by the streaming scan in tiles of 64 queries: a stage is a tile of 256 rows, shared
 // by eight waves.  Writes gmax of whole tiles.
 hipError_t launch_maxima_stream(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
-// The k best from the maxima: H workgroups of 256 or 1024 threads (up to 16 groups to a thread) per query, lists[nq][H][k],
-// counts[nq][H].  done[q] holds MAXIMA_MANY afterwards if more groups reached the bound than are worked off at once.
-hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int H, cand_t *lists,
-                                int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st);
+// The k best from the maxima: `helpers` workgroups of 256 or 1024 threads (up to 16 groups to a thread) per query, most_helpers
+// where much has to be scored again; lists[nq][most_helpers][k], counts[nq][most_helpers].  done[q] holds MAXIMA_MANY afterwards if more groups reached the bound than are worked off at once.
+hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int helpers, int most_helpers,
+                                cand_t *lists, int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st);
 // Collecting scan (any k up to MAX_K): thresholds stay at seeds[q] (required); every candidate beating its
 // query's seed is appended to cbuf[(q * SS + region) * Cs + ...], SS = mfma_collect_regions(S, rsplit),
 // and ccnt[q * SS + region] = number offered (entries beyond Cs were dropped).

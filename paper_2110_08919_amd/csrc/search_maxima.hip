@@ -44,12 +44,13 @@ __device__ __forceinline__ int chunk_dot(uint4 xv, const uint4 *qs, int c)
     return dot;
 }
 
-// H workgroups per query: each finds the same bound from the maxima, scores its share of the rows of the groups that reach
-// it, and the one that ends last merges.  What bounds it is latency: a round trip to memory for the maxima (V 16-byte loads a
+// One or more workgroups per query: each finds the same bound from the maxima, scores its share of the rows of the groups that
+// reach it, and the one that ends last merges.  What bounds it is latency: a round trip to memory for the maxima (V 16-byte loads a
 // thread, all in flight at once), one per step of 128 KB of rows, and two with the fences where helpers share the work.  LR lanes share a row, CPL times 16 bytes each.
 template <int NT, bool PACKED, int LR, int CPL>
 __global__ __launch_bounds__(NT) void maxima_finish_kernel(
-    SearchArgs a, MaximaShape m, const int32_t *__restrict__ gmax, int H, cand_t *lists, int32_t *counts, int32_t *done, int cap,
+    SearchArgs a, MaximaShape m, const int32_t *__restrict__ gmax, int helpers, int most_helpers, cand_t *lists, int32_t *counts,
+    int32_t *done, int cap,
     int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric)
 {
     constexpr int ROWS = NT / LR, FLY = MF_FLY / CPL;               // rows side by side and behind one another in a step, 16 to a unit
@@ -61,8 +62,8 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     __shared__ int s_top[256], s_hit[MF_UNITS], s_unit[MF_UNITS];   // groups; first row of a unit, or -1
     __shared__ int s_count[2], s_bound, s_hits, s_units, s_last;
     __shared__ cand_t s_thr;
-    const int64_t q = blockIdx.x / H;
-    const int h = blockIdx.x % H, tid = threadIdx.x, lane = tid & 63, sub = tid % LR, grp = tid / LR;
+    const int64_t q = blockIdx.x / most_helpers;
+    const int h = blockIdx.x % most_helpers, tid = threadIdx.x, lane = tid & 63, sub = tid % LR, grp = tid / LR;
     const bool l2 = a.metric == LPQ_METRIC_L2SQ;
 
     // ---- the bound: the k-th largest of the largest maxima of 256 foursomes of threads -----------
@@ -147,57 +148,78 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         at.step_done(__builtin_amdgcn_readfirstlane(s_count[at.turn]));
         block_compact_if_full(buf, cap, a.k, FLY * ROWS, at.held, &s_thr);
     };
-    // all groups at once, or as many at a time as the list of units surely has room for
-    for (int from = 0, window = m.G; from < m.G;) {
-        const int to = from + window < m.G ? from + window : m.G;
-        if (own >= bound) {                                         // (few threads have a group that does)
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const int val[4] = {v[j].x, v[j].y, v[j].z, v[j].w}, first = 4 * (tid + j * NT);
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (val[c] >= bound && first + c >= from && first + c < to) {
-                        const int slot = atomicAdd(&s_hits, 1);
-                        if (slot < MF_UNITS) s_hit[slot] = first + c;
-                    }
-            }
-        }
-        __syncthreads();
-        const int hits = s_hits;
-        // The helpers share the units, not the groups: a workgroup alone gets some 30 GB/s of rows from memory.
-        for (int u = tid; hits <= MF_UNITS && u < hits * m.seg_stages; u += NT) {
-            const int i = s_hit[u / m.seg_stages], nth = u % m.seg_stages;
-            if (H > 1 && (i + nth) % H != h) continue;
-            const int part = i % m.parts, seg = (i / m.parts) % m.SEG, s = i / (m.parts * m.SEG);
-            const int T = (m.stages - s + m.S - 1) / m.S;           // stages of the split
-            const int t = (int)(((int64_t)seg * T + m.SEG - 1) / m.SEG) + nth;
-            if (t >= (int)(((int64_t)(seg + 1) * T + m.SEG - 1) / m.SEG)) continue;
-            const int slot = atomicAdd(&s_units, 1);
-            if (slot < MF_UNITS) s_unit[slot] = (s + m.S * t) * m.stage_rows + (part >> 1) * 32 + (part & 1) * 4;
-        }
-        // the rows behind the last whole stage were not scanned: units of the same form
-        const int tail = m.stages * m.stage_rows;
-        if (h == 0 && to == m.G && tail + (tid >> 1) * 32 < (int)a.n && tid < 2 * MF_TAIL) {
-            const int slot = atomicAdd(&s_units, 1);
-            if (slot < MF_UNITS) s_unit[slot] = tail + (tid >> 1) * 32 + (tid & 1) * 4;
-        }
+    auto work_off = [&]() {                                         // the units listed
         __syncthreads();
         const int units = s_units;
         __syncthreads();
-        if (tid == 0) s_hits = s_units = 0;
-        if (hits > MF_UNITS || units > MF_UNITS) {                  // (only the first window can hold more than that)
-            window = (MF_UNITS - 2 * MF_TAIL) / m.seg_stages;
-            if (tid == 0) atomicOr(&done[q], MAXIMA_MANY);
-            __syncthreads();
-            continue;
-        }
+        if (tid == 0) s_units = 0;
         for (int base = 0; base < units; base += FLY * ROWS / 16)
             step([&](int i) {
                 const int j = i & 15, row = base + (i >> 4) < units ? s_unit[base + (i >> 4)] + 8 * (j >> 2) + (j & 3) : -1;
                 return row < (int)a.n ? row : -1;
             });
         __syncthreads();
-        from = to;
+    };
+    auto stages_of = [&](int s) { return (m.stages - s + m.S - 1) / m.S; };
+    if (own >= bound) {                                             // (few threads have a group that does)
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int val[4] = {v[j].x, v[j].y, v[j].z, v[j].w}, first = 4 * (tid + j * NT);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (val[c] >= bound && first + c < m.G) {
+                    const int slot = atomicAdd(&s_hits, 1);
+                    if (slot < MF_UNITS) s_hit[slot] = first + c;
+                }
+        }
+    }
+    __syncthreads();
+    const int hits = s_hits;
+    // How many of the query's workgroups work, the same answer in each: all where there is much to do.  (The others then
+    // cost nothing; all of them always, with the fences and the merge, 2 us of 9 for one query on 1M x 128.)
+    const int H = hits * m.seg_stages > MF_UNITS ? most_helpers : helpers;
+    if (h >= H) return;
+    // the rows behind the last whole stage were not scanned: units of the same form
+    const int tail = m.stages * m.stage_rows;
+    if (h == 0 && tid < 2 * MF_TAIL && tail + (tid >> 1) * 32 < (int)a.n) s_unit[atomicAdd(&s_units, 1)] = tail + (tid >> 1) * 32 + (tid & 1) * 4;
+    if (hits <= MF_UNITS) {
+        // The helpers share the units, not the groups: a workgroup alone gets some 30 GB/s of rows from memory.
+        const int total = hits * m.seg_stages, most = MF_UNITS - 2 * MF_TAIL;
+        for (int from = 0; from == 0 || from < total; from += most) {
+            const int to = from + most < total ? from + most : total;
+            for (int u = from + tid; u < to; u += NT) {
+                const int i = s_hit[u / m.seg_stages], nth = u % m.seg_stages;
+                if (H > 1 && (i + nth) % H != h) continue;
+                const int part = i % m.parts, seg = (i / m.parts) % m.SEG, s = i / (m.parts * m.SEG), T = stages_of(s);
+                const int t = (int)(((int64_t)seg * T + m.SEG - 1) / m.SEG) + nth;
+                if (t >= (int)(((int64_t)(seg + 1) * T + m.SEG - 1) / m.SEG)) continue;
+                s_unit[atomicAdd(&s_units, 1)] = (s + m.S * t) * m.stage_rows + (part >> 1) * 32 + (part & 1) * 4;
+            }
+            work_off();
+        }
+    } else {
+        // Items that tie with the k-th by the thousands (rows that repeat, features of few values).  Stage by stage, so that
+        // ids come in ascending order: once k are held, rows that tie with the k-th lose to it, and whole groups do where
+        // their maximum says so (of 16 queries on 1M x 64, every second row zero, 2.9 ms in the order of the groups).
+        if (tid == 0) atomicOr(&done[q], MAXIMA_MANY);
+        const int per = (MF_UNITS - 2 * MF_TAIL) / m.parts;         // splits at a time
+        for (int t = 0; t < stages_of(0); ++t)
+            for (int s0 = 0; s0 < m.S; s0 += per) {
+                const cand_t worst = s_thr;
+                for (int u = tid; u < per * m.parts; u += NT) {
+                    const int s = s0 + u / m.parts, part = u % m.parts;
+                    if (s >= m.S || (H > 1 && (s + t + part) % H != h)) continue;
+                    const int T = stages_of(s);
+                    if (t >= T) continue;
+                    const int largest = gmax[q * m.G + (s * m.SEG + (int)((int64_t)t * m.SEG / T)) * m.parts + part];
+                    const int row = (s + m.S * t) * m.stage_rows + (part >> 1) * 32 + (part & 1) * 4;
+                    if (largest < bound) continue;
+                    // (the norm of a row with the key -(2 largest + 1) is odd)
+                    const int odd = l2 && (a.parity[row >> 5] & (0x0F0F0F0Fu << (4 * (part & 1)))) != 0;
+                    if (make_cand(-2 * largest - odd, (uint32_t)row) < worst) s_unit[atomicAdd(&s_units, 1)] = row;
+                }
+                work_off();
+            }
     }
 
     // ---- the k best: ranks are counted, or where there are many candidates they are sorted -------
@@ -218,9 +240,9 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         for (int i = tid; i < a.k; i += NT) put(i, buf[i]);
     };
     int held = at.held;
-    if (tid == 0) counts[q * H + h] = held < a.k ? held : a.k;
+    if (tid == 0) counts[q * most_helpers + h] = held < a.k ? held : a.k;
     if (H > 1) {
-        cand_t *mine = lists + (q * H + h) * a.k;
+        cand_t *mine = lists + (q * most_helpers + h) * a.k;
         finish(held, [&](int r, cand_t c) { mine[r] = c; });
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // this wave's part has reached the L2 ...
         __syncthreads();
@@ -233,7 +255,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         __syncthreads();
         if (!s_last) return;                                        // the same in every thread of the workgroup
         for (int i = tid; i < H * a.k; i += NT)
-            if (i % a.k < counts[q * H + i / a.k]) buf[atomicAdd(&s_hits, 1)] = lists[q * H * a.k + i];
+            if (i % a.k < counts[q * most_helpers + i / a.k]) buf[atomicAdd(&s_hits, 1)] = lists[q * most_helpers * a.k + i];
         __syncthreads();
         held = s_hits;
     }
@@ -242,25 +264,25 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
 
 }  // namespace
 
-hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int H, cand_t *lists,
+hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int helpers, int most_helpers, cand_t *lists,
                                 int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st)
 {
     if (a.nq <= 0) return hipSuccess;
     const int chunks = a.d_pad / (a.packed ? 32 : 16), lr = chunks <= 8 ? 8 : chunks <= 16 ? 16 : chunks <= 32 ? 32 : 64;
     const int per_lane = chunks <= 64 ? 1 : (chunks <= 128 ? 2 : 4), step = MF_FLY / per_lane * threads / lr;
     const int tops = threads == 256 ? m.G / 4 : m.G / 16;
-    // the bound is the k-th of the (foursomes of) threads' maxima, a unit list holds a group and the rows behind the last
+    // the bound is the k-th of the (foursomes of) threads' maxima, the list of units has room for the rows behind the last
     // stage, and all that the helpers keep fits one merge
     if ((threads != 256 && threads != 1024) || a.k < 1 || a.k > MAXIMA_MAX_K || (threads == 256 && chunks > 16) ||
-        (a.packed && chunks > 8) || a.d_pad > MAXIMA_MAX_D || H < 1 ||
-        H * a.k > MF_MERGE || m.G % 16 || tops < a.k || m.G > 16 * threads || m.seg_stages > MF_UNITS - 2 * MF_TAIL ||
+        (a.packed && chunks > 8) || a.d_pad > MAXIMA_MAX_D || helpers < 1 ||
+        most_helpers < helpers || most_helpers * a.k > MF_MERGE || m.G % 16 || tops < a.k || m.G > 16 * threads ||
         a.n - (int64_t)m.stages * m.stage_rows > 32 * MF_TAIL)
         return hipErrorInvalidValue;
     const int cap = next_pow2(a.k + step);
-    const int most = H > 1 ? next_pow2(H * a.k) : cap;
+    const int most = most_helpers > 1 ? next_pow2(most_helpers * a.k) : cap;
     const size_t lds = (size_t)(cap > most ? cap : most) * sizeof(cand_t);
     auto launch = [&](auto kern) {
-        kern<<<(unsigned)(a.nq * H), threads, lds, st>>>(a, m, gmax, H, lists, counts, done, cap, ids, dists, qnorms, metric);
+        kern<<<(unsigned)(a.nq * most_helpers), threads, lds, st>>>(a, m, gmax, helpers, most_helpers, lists, counts, done, cap, ids, dists, qnorms, metric);
         return hipGetLastError();
     };
     if (threads == 256) {

@@ -61,3 +61,16 @@ def test_many_groups_of_streamed_rows_at_the_bound(metric):
     g = torch.Generator(device="cuda").manual_seed(1)
     x = torch.randn((11, 600), generator=g, device="cuda")[torch.randint(0, 11, (40_000,), generator=g, device="cuda")].contiguous()
     _check(x, x[:20].clone(), 10, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("n,d,nq,k", [(300_001, 64, 16, 10), (400_000, 32, 1, 100), (100_000, 300, 5, 10), (60_000, 16, 64, 20)])
+def test_corpora_of_repeated_and_sparse_rows(metric, n, d, nq, k):
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    q = x[1:2 * nq:2].clone()
+    x[::2] = 0.0                                          # every second row the same
+    q[: nq // 2] = 0.0
+    _check(x, q, k, metric)
+    x = (torch.rand((n, d), generator=g, device="cuda") < 0.05).float()
+    _check(x, (torch.rand((nq, d), generator=g, device="cuda") < 0.05).float(), k, metric)
