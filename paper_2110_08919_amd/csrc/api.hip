@@ -1050,10 +1050,18 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
                                       p.expect, nullptr, nullptr, 0, certain, bounds2));
         // Queries whose candidates did not fit are searched again, exactly.  Short lists on short rows: a few
         // by the generic kernel, many (a corpus full of duplicates or ties) by a pass of the register-list
-        // kernel over the query tiles that hold one; both are launched and the count on the device decides.
-        if (p.Sr)
+        // kernel over the query tiles that hold one; both are launched and the count on the device decides.  The generic
+        // kernel's launch also merges the other's lists (in a launch of their own 2 us more on every search).
+        if (p.Sr) {
+            cand_t *lists_r = reinterpret_cast<cand_t *>(ws + p.off_redo);
+            SearchArgs ar = a;
+            ar.rsplit = false;
+            ar.wave_queries = 64;
+            ar.redo_flags = over; ar.redo_count = qcount; ar.redo_min = REDO_GENERIC_MAX;
+            HIP_TRY(launch_search_mfma(ar, 0, a.n, p.Sr, certain, lists_r, st));
             HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, {qlist, qcount, over}, REDO_GENERIC_MAX, {}, lists2, ids, dist,
-                                               qnorms, emit_mode, st));
+                                               qnorms, emit_mode, st, lists_r, p.Sr));
+        }
         // Otherwise the selection has also left a bound per flagged query, taken from what the scan did
         // collect for it, and the scan runs again over the query tiles that hold one, up to p.rounds times
         // (what a round collects is the FIRST candidates of each region in scan order, not the best, so one
@@ -1077,16 +1085,6 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
             if (last)
                 HIP_TRY(launch_search_generic_list(a, 0, a.n, p.Sg, {qlist, qcount, over}, p.few, {qlist_r, count_r, over_r}, lists2,
                                                    ids, dist, qnorms, emit_mode, st));
-        }
-        if (p.Sr) {
-            cand_t *lists_r = reinterpret_cast<cand_t *>(ws + p.off_redo);
-            SearchArgs ar = a;
-            ar.rsplit = false;
-            ar.wave_queries = 64;
-            ar.redo_flags = over; ar.redo_count = qcount; ar.redo_min = REDO_GENERIC_MAX;
-            HIP_TRY(launch_search_mfma(ar, 0, a.n, p.Sr, certain, lists_r, st));
-            HIP_TRY(launch_merge(lists_r, nq, p.Sr, k, nullptr, nullptr, nullptr, ids, dist, qnorms, emit_mode, st, false,
-                                 over, qcount, REDO_GENERIC_MAX + 1, INT32_MAX));
         }
     } else if (p.mode == PLAN_MFMA_REG) {
         const cand_t *sd = nullptr;

@@ -172,10 +172,12 @@ struct RedoList {
 };
 // The same for the queries of `first`, or of `last` if first lists more than first_max (without last nothing is
 // done then): a fixed grid shares out the (query, split) pairs, and a query's lists are merged into its final
-// result (S k <= 4096).  The flags of the queries searched stay non-zero.
+// result (S k <= 4096).  The flags of the queries searched stay non-zero.  With done_lists, first's queries, where they are
+// more than first_max, have been searched by another kernel, and their done_count sorted or unsorted lists are merged.
 hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const RedoList &first,
                                       int first_max, const RedoList &last, cand_t *lists, int32_t *ids, int32_t *dists,
-                                      const int32_t *qnorms, int metric, hipStream_t st);
+                                      const int32_t *qnorms, int metric, hipStream_t st,
+                                      const cand_t *done_lists = nullptr, int done_count = 0);
 
 // Matrix-core kernels.  search_mfma.hip keeps the k best of a query in registers (k <= 16) and
 // has a seeding pass; search_mfma_lds.hip keeps them in LDS (larger k).  launch_search_mfma
@@ -284,9 +286,7 @@ hipError_t launch_seed_finalize(const int32_t *gmax, int64_t nq, int G, int k, i
 hipError_t launch_merge(const cand_t *lists, int64_t nq, int P, int k, const cand_t *extra_lists,
                         cand_t *out_lists, cand_t *seeds_out, int32_t *ids, int32_t *dists,
                         const int32_t *qnorms, int metric, hipStream_t st, bool sorted_lists = false,
-                        const int32_t *only = nullptr,   // only (optional): int[nq]; queries with only[q] == 0 are skipped
-                        const int32_t *gate_count = nullptr, int gate_lo = 0,   // gate (optional): nothing is done
-                        int gate_hi = INT32_MAX);                               // unless gate_lo <= *gate_count <= gate_hi
+                        const int32_t *only = nullptr);   // only (optional): int[nq]; queries with only[q] == 0 are skipped
 int merge_max_lists(int k);
 int merge_max_sorted_lists(int k);   // same for lists that are each sorted (k <= 32: more of them)
 // First pass of a two-pass merge: groups of `group` consecutive lists of each query are merged

@@ -116,16 +116,34 @@ __device__ __forceinline__ cand_t next_bound(cand_t c) { return c + 1; }
 constexpr int LIST_MERGE_CAP = 2048;
 __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
     SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, RedoList first, int first_max, RedoList last,
-    cand_t *lists, int cap, int32_t *__restrict__ ids, int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms,
-    int metric)
+    cand_t *lists, int cap, const cand_t *done_lists, int done_count, int32_t *__restrict__ ids, int32_t *__restrict__ dists,
+    const int32_t *__restrict__ qnorms, int metric)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);
     uint4 *qs = reinterpret_cast<uint4 *>(buf + cap);
     __shared__ int s_count[2], s_last;
     __shared__ cand_t s_thr;
+    // the m candidates of a query's lists, up to 4096, sorted in two or three parts
+    auto merge = [&](const cand_t *from_lists, int64_t q, int m) {
+        for (int from = 0, kept = 0; from < m; kept = a.k) {
+            const int take = m - from < LIST_MERGE_CAP - kept ? m - from : LIST_MERGE_CAP - kept;
+            int mcap = 2;
+            while (mcap < kept + take) mcap <<= 1;
+            for (int i = kept + threadIdx.x; i < mcap; i += GEN_THREADS)
+                buf[i] = i < kept + take ? from_lists[q * m + from + (i - kept)] : CAND_NONE;
+            __syncthreads();
+            block_bitonic_sort(buf, mcap);
+            from += take;
+        }
+        for (int i = threadIdx.x; i < a.k; i += GEN_THREADS) emit_result(buf[i], q * a.k + i, q, ids, dists, qnorms, metric);
+        __syncthreads();
+    };
     const bool many = *first.count > first_max;             // same for every thread of the grid
-    if (many && !last.queries) return;                      // another kernel takes them
+    if (many && !last.queries) {                            // another kernel has searched them
+        for (int64_t i = blockIdx.x; done_lists && i < *first.count; i += gridDim.x) merge(done_lists, first.queries[i], done_count * a.k);
+        return;
+    }
     const RedoList work = many ? last : first;
     const int64_t items = (int64_t)(*work.count) * S;
     for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
@@ -142,21 +160,7 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
             if (s_last) __threadfence();                    // the other lists are read as they are now
         }
         __syncthreads();
-        if (s_last) {                                       // the same answer in every thread of the workgroup
-            const int m = S * a.k;                          // up to 4096, sorted in two or three parts
-            for (int from = 0, kept = 0; from < m; kept = a.k) {
-                const int take = m - from < LIST_MERGE_CAP - kept ? m - from : LIST_MERGE_CAP - kept;
-                int mcap = 2;
-                while (mcap < kept + take) mcap <<= 1;
-                for (int i = kept + threadIdx.x; i < mcap; i += GEN_THREADS)
-                    buf[i] = i < kept + take ? lists[q * m + from + (i - kept)] : CAND_NONE;
-                __syncthreads();
-                block_bitonic_sort(buf, mcap);
-                from += take;
-            }
-            for (int i = threadIdx.x; i < a.k; i += GEN_THREADS) emit_result(buf[i], q * a.k + i, q, ids, dists, qnorms, metric);
-            __syncthreads();
-        }
+        if (s_last) merge(lists, q, S * a.k);               // the same answer in every thread of the workgroup
     }
 }
 
@@ -164,17 +168,12 @@ __global__ __launch_bounds__(GEN_THREADS) void search_generic_list_kernel(
 __global__ __launch_bounds__(256) void merge_kernel(
     const cand_t *__restrict__ lists, int P, int k, const cand_t *__restrict__ extra, int cap,
     cand_t *__restrict__ out_lists, cand_t *__restrict__ seeds_out, int32_t *__restrict__ ids,
-    int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric, const int32_t *__restrict__ only,
-    const int32_t *__restrict__ gate_count, int gate_lo, int gate_hi)
+    int32_t *__restrict__ dists, const int32_t *__restrict__ qnorms, int metric, const int32_t *__restrict__ only)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);
     const int64_t q = blockIdx.x;
     if (only && !only[q]) return;   // same for the whole workgroup
-    if (gate_count) {               // this merge belongs to one of two alternative redo paths
-        const int c = *gate_count;
-        if (c < gate_lo || c > gate_hi) return;
-    }
     const int m = P * k;
     for (int i = threadIdx.x; i < cap; i += 256) {
         cand_t c = CAND_NONE;
@@ -873,29 +872,29 @@ hipError_t launch_search_generic(const SearchArgs &a, int64_t row0, int64_t row1
 
 hipError_t launch_search_generic_list(const SearchArgs &a, int64_t row0, int64_t row1, int S, const RedoList &first,
                                       int first_max, const RedoList &last, cand_t *lists, int32_t *ids, int32_t *dists,
-                                      const int32_t *qnorms, int metric, hipStream_t st)
+                                      const int32_t *qnorms, int metric, hipStream_t st, const cand_t *done_lists, int done_count)
 {
     if (a.nq <= 0 || row1 <= row0) return hipSuccess;
-    if ((int64_t)S * a.k > 4096) return hipErrorInvalidValue;   // one workgroup merges a query's lists
+    if ((int64_t)S * a.k > 4096 || (int64_t)done_count * a.k > 4096) return hipErrorInvalidValue;   // one workgroup merges a query's lists
     const int cap = next_pow2((2 * a.k > a.k + 2 * GEN_ROWS) ? 2 * a.k : a.k + 2 * GEN_ROWS);
     const int64_t split_rows = round_up(ceil_div(row1 - row0, S), GEN_ROWS);
     const size_t shmem = (size_t)cap * sizeof(cand_t) + (size_t)a.d_pad;
-    const int merged = S * a.k < 2 ? 2 : (S * a.k < LIST_MERGE_CAP ? S * a.k : LIST_MERGE_CAP);
+    const int longest = (done_count > S ? done_count : S) * a.k;
+    const int merged = longest < 2 ? 2 : (longest < LIST_MERGE_CAP ? longest : LIST_MERGE_CAP);
     const size_t merge = (size_t)next_pow2(merged) * sizeof(cand_t);
     search_generic_list_kernel<<<2048, GEN_THREADS, shmem > merge ? shmem : merge, st>>>(
-        a, row0, row1, S, split_rows, first, first_max, last, lists, cap, ids, dists, qnorms, metric);
+        a, row0, row1, S, split_rows, first, first_max, last, lists, cap, done_lists, done_count, ids, dists, qnorms, metric);
     return hipGetLastError();
 }
 
 hipError_t launch_merge(const cand_t *lists, int64_t nq, int P, int k, const cand_t *extra_lists,
                         cand_t *out_lists, cand_t *seeds_out, int32_t *ids, int32_t *dists,
-                        const int32_t *qnorms, int metric, hipStream_t st, bool sorted_lists, const int32_t *only,
-                        const int32_t *gate_count, int gate_lo, int gate_hi)
+                        const int32_t *qnorms, int metric, hipStream_t st, bool sorted_lists, const int32_t *only)
 {
     if (nq <= 0) return hipSuccess;
     const int total = P * k + (extra_lists ? k : 0);
     // sorted lists of up to 32 (a sort of everything is as fast while it stays small: 39 lists of 10)
-    if (!only && !gate_count && sorted_lists && k <= 32 && total > 256 && P <= merge_max_sorted_lists(k)) {
+    if (!only && sorted_lists && k <= 32 && total > 256 && P <= merge_max_sorted_lists(k)) {
         const size_t lds = MERGE_SORTED_BUF * sizeof(cand_t);
         const int lpl = (int)ceil_div(P + (extra_lists ? 1 : 0), 256);   // lists a thread owns
         auto launch = [&](auto kern) -> hipError_t {
@@ -912,7 +911,7 @@ hipError_t launch_merge(const cand_t *lists, int64_t nq, int P, int k, const can
     const int cap = next_pow2(total < 2 ? 2 : total);
     if (cap > 4096) return hipErrorInvalidValue;
     merge_kernel<<<(unsigned)nq, 256, (size_t)cap * sizeof(cand_t), st>>>(
-        lists, P, k, extra_lists, cap, out_lists, seeds_out, ids, dists, qnorms, metric, only, gate_count, gate_lo, gate_hi);
+        lists, P, k, extra_lists, cap, out_lists, seeds_out, ids, dists, qnorms, metric, only);
     return hipGetLastError();
 }
 
