@@ -15,6 +15,8 @@ namespace {
 
 constexpr int MF_FLY = 8;             // 16-byte loads of rows a lane has in flight
 constexpr int MF_UNITS = 1024;        // units worked off at a time; a unit is the 16 rows of a group in one stage
+constexpr int MF_ROWS = 4096;         // rows listed at a time where many groups tie
+constexpr int MF_TIES = 256;          // ... and candidates whose ranks are counted between two lists
 constexpr int MF_TAIL = 8;            // blocks of 32 rows behind the last whole stage, at most
 constexpr int MF_MERGE = 2048;        // candidates of all helpers together, at most
 
@@ -59,8 +61,8 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     cand_t *buf = reinterpret_cast<cand_t *>(smem);                 // [max(cap, merge)]
     __shared__ uint4 qs[MAXIMA_MAX_D / 16];
-    __shared__ int s_top[256], s_hit[MF_UNITS], s_unit[MF_UNITS];   // groups; first row of a unit, or -1
-    __shared__ int s_count[2], s_bound, s_hits, s_units, s_last;
+    __shared__ int s_top[256], s_hit[MF_UNITS], s_unit[MF_UNITS], s_row[MF_ROWS];   // groups; first row of a unit, or -1; rows
+    __shared__ int s_count[2], s_bound, s_hits, s_units, s_rows, s_last;
     __shared__ cand_t s_thr;
     const int64_t q = blockIdx.x / most_helpers;
     const int h = blockIdx.x % most_helpers, tid = threadIdx.x, lane = tid & 63, sub = tid % LR, grp = tid / LR;
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     for (int i = tid; i < a.d_pad / 16; i += NT) qs[i] = reinterpret_cast<const uint4 *>(a.qcodes + q * a.d_pad)[i];
     for (int i = tid; i < cap; i += NT) buf[i] = CAND_NONE;
     if (tid < 2) s_count[tid] = 0;
-    if (tid == 0) s_hits = s_units = 0;
+    if (tid == 0) s_hits = s_units = s_rows = 0;
 #pragma unroll
     for (int j = 0; j < V; ++j) top = max(top, max(max(v[j].x, v[j].y), max(v[j].z, v[j].w)));
     const int own = top;
@@ -200,26 +202,60 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     } else {
         // Items that tie with the k-th by the thousands (rows that repeat, features of few values).  Stage by stage, so that
         // ids come in ascending order: once k are held, rows that tie with the k-th lose to it, and whole groups do where
-        // their maximum says so (of 16 queries on 1M x 64, every second row zero, 2.9 ms in the order of the groups).
+        // their maximum says so, or all their rows but those of odd norm.  A look at the maxima costs a round trip and its
+        // barriers however little it finds, and sorting a full buffer 15 us: the first looks are short and their candidates
+        // ranked by counting, to hold k early, the later ones as long as the list has room.
+        // 16 queries, L2, half of 1M x 64 rows zero: 361 us with all units scored a thousand at a time, 127 now (92 by lists);
+        // one feature in twenty 1, 1M x 32 293 -> 185 (81), inner product 134 -> 56 (76).
         if (tid == 0) atomicOr(&done[q], MAXIMA_MANY);
-        const int per = (MF_UNITS - 2 * MF_TAIL) / m.parts;         // splits at a time
-        for (int t = 0; t < stages_of(0); ++t)
-            for (int s0 = 0; s0 < m.S; s0 += per) {
-                const cand_t worst = s_thr;
-                for (int u = tid; u < per * m.parts; u += NT) {
-                    const int s = s0 + u / m.parts, part = u % m.parts;
-                    if (s >= m.S || (H > 1 && (s + t + part) % H != h)) continue;
-                    const int T = stages_of(s);
-                    if (t >= T) continue;
-                    const int largest = gmax[q * m.G + (s * m.SEG + (int)((int64_t)t * m.SEG / T)) * m.parts + part];
-                    const int row = (s + m.S * t) * m.stage_rows + (part >> 1) * 32 + (part & 1) * 4;
-                    if (largest < bound) continue;
-                    // (the norm of a row with the key -(2 largest + 1) is odd)
-                    const int odd = l2 && (a.parity[row >> 5] & (0x0F0F0F0Fu << (4 * (part & 1)))) != 0;
-                    if (make_cand(-2 * largest - odd, (uint32_t)row) < worst) s_unit[atomicAdd(&s_units, 1)] = row;
-                }
-                work_off();
+        work_off();                                                 // (the rows behind the last stage)
+        const int T0 = stages_of(0), longer = m.stages - (T0 - 1) * m.S;    // the first splits have T0 stages, the others T0 - 1
+        const int all = T0 * m.S * m.parts, share = (all + H - 1) / H;
+        for (int from = 0, width = MF_TIES / 16; from < share;) {
+            const cand_t worst = s_thr;
+            const int to = from + width < share ? from + width : share;
+            for (int j = from + tid; j < to; j += NT) {
+                const int u = j * H + (h + j) % H;                  // one of H units behind one another to each helper, in turn
+                const int part = u % m.parts, st = u / m.parts, s = st % m.S, t = st / m.S, T = s < longer ? T0 : T0 - 1;
+                if (u >= all || t >= T) continue;
+                const int largest = gmax[q * m.G + (s * m.SEG + t * m.SEG / T) * m.parts + part];
+                const int block = st * m.stage_rows + (part >> 1) * 32, row = block + (part & 1) * 4;
+                // (a row with E = largest has the key -2 largest, or one less if its norm is odd)
+                if (largest < bound || make_cand(-2 * largest - (l2 ? 1 : 0), (uint32_t)row) >= worst) continue;
+                unsigned mask = 0x0F0F0F0Fu << (4 * (part & 1));
+                if (make_cand(-2 * largest, (uint32_t)row) >= worst) mask &= a.parity[block >> 5];
+                for (int slot = atomicAdd(&s_rows, __popc(mask)); mask; mask &= mask - 1, ++slot)
+                    if (slot < MF_ROWS) s_row[slot] = block + __ffs(mask) - 1;
             }
+            __syncthreads();
+            const int rows_listed = s_rows;
+            __syncthreads();
+            if (tid == 0) s_rows = 0;
+            if (rows_listed > MF_ROWS) {                            // 256 units always fit
+                width = MF_ROWS / 16;
+                __syncthreads();
+                continue;
+            }
+            for (int base = 0; base < rows_listed; base += FLY * ROWS)
+                step([&](int i) { return base + i < rows_listed ? s_row[base + i] : -1; });
+            if (at.held > a.k && at.held <= MF_TIES) {              // the same in every thread
+                const int held = at.held;
+                const cand_t me = tid < held ? buf[tid] : CAND_NONE;
+                int r = 0;
+                for (int j = 0; tid < held && j < held; ++j) r += buf[j] < me;
+                __syncthreads();
+                if (tid >= a.k && tid < held) buf[tid] = CAND_NONE;
+                if (tid < held && r < a.k) buf[r] = me;
+                if (tid < held && r == a.k - 1 && me < s_thr) s_thr = me;
+                at.held = a.k;
+            }
+            __syncthreads();
+            from = to;
+            // as many units more as leave the list a quarter free, if they have as many rows each, up to four times as many as now
+            const int room = rows_listed > 0 ? width * (MF_ROWS / 4 * 3) / rows_listed : MF_ROWS / 4;
+            width = 4 * width < MF_ROWS / 4 ? 4 * width : MF_ROWS / 4;
+            if (width > MF_ROWS / 16 && width > room) width = room > MF_ROWS / 16 ? room : MF_ROWS / 16;
+        }
     }
 
     // ---- the k best: ranks are counted, or where there are many candidates they are sorted -------
@@ -276,7 +312,8 @@ hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const
     if ((threads != 256 && threads != 1024) || a.k < 1 || a.k > MAXIMA_MAX_K || (threads == 256 && chunks > 16) ||
         (a.packed && chunks > 8) || a.d_pad > MAXIMA_MAX_D || helpers < 1 ||
         most_helpers < helpers || most_helpers * a.k > MF_MERGE || m.G % 16 || tops < a.k || m.G > 16 * threads ||
-        a.n - (int64_t)m.stages * m.stage_rows > 32 * MF_TAIL)
+        a.n - (int64_t)m.stages * m.stage_rows > 32 * MF_TAIL || (m.stages / m.S + 1) * (int64_t)m.SEG > INT32_MAX ||
+        ((int64_t)m.stages + m.S) * m.parts + most_helpers > INT32_MAX)
         return hipErrorInvalidValue;
     const int cap = next_pow2(a.k + step);
     const int most = most_helpers > 1 ? next_pow2(most_helpers * a.k) : cap;
