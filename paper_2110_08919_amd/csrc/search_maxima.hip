@@ -179,12 +179,16 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
     const int hits = s_hits;
     // How many of the query's workgroups work, the same answer in each: all where there is much to do.  (The others then
     // cost nothing; all of them always, with the fences and the merge, 2 us of 9 for one query on 1M x 128.)
-    const int H = hits * m.seg_stages > MF_UNITS ? most_helpers : helpers;
+    // More than 4 k + 64 groups are ties, and from a sixteenth of the groups on a look at every unit's maximum costs less
+    // than their rows (half of 10 000 x 128 rows zero, 100 queries 127 us with the line at 1024 groups, 51 here; each of 1000
+    // vectors 1000 times, 1M x 64, 16 queries 61 here, 72 with a 64th).
+    const int few = max(4 * a.k + 64, m.G / 16) < MF_UNITS ? max(4 * a.k + 64, m.G / 16) : MF_UNITS;
+    const int H = hits > few || hits * m.seg_stages > MF_UNITS ? most_helpers : helpers;
     if (h >= H) return;
     // the rows behind the last whole stage were not scanned: units of the same form
     const int tail = m.stages * m.stage_rows;
     if (h == 0 && tid < 2 * MF_TAIL && tail + (tid >> 1) * 32 < (int)a.n) s_unit[atomicAdd(&s_units, 1)] = tail + (tid >> 1) * 32 + (tid & 1) * 4;
-    if (hits <= MF_UNITS) {
+    if (hits <= few) {
         // The helpers share the units, not the groups: a workgroup alone gets some 30 GB/s of rows from memory.
         const int total = hits * m.seg_stages, most = MF_UNITS - 2 * MF_TAIL;
         for (int from = 0; from == 0 || from < total; from += most) {
@@ -207,7 +211,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         // ranked by counting, to hold k early, the later ones as long as the list has room.
         // 16 queries, L2, half of 1M x 64 rows zero: 361 us with all units scored a thousand at a time, 127 now (92 by lists);
         // one feature in twenty 1, 1M x 32 293 -> 185 (81), inner product 134 -> 56 (76).
-        if (tid == 0) atomicOr(&done[q], MAXIMA_MANY);
+        if (tid == 0 && hits > MF_UNITS) atomicOr(&done[q], MAXIMA_MANY);
         work_off();                                                 // (the rows behind the last stage)
         const int T0 = stages_of(0), longer = m.stages - (T0 - 1) * m.S;    // the first splits have T0 stages, the others T0 - 1
         const int all = T0 * m.S * m.parts, share = (all + H - 1) / H;

@@ -64,7 +64,7 @@ def test_many_groups_of_streamed_rows_at_the_bound(metric):
 
 
 @pytest.mark.parametrize("metric", ["l2sq", "ip"])
-@pytest.mark.parametrize("n,d,nq,k", [(300_001, 64, 16, 10), (400_000, 32, 1, 100), (100_000, 300, 5, 10), (60_000, 16, 64, 20)])
+@pytest.mark.parametrize("n,d,nq,k", [(300_001, 64, 16, 10), (400_000, 32, 1, 100), (100_000, 300, 5, 10), (60_000, 16, 64, 20), (10_000, 128, 100, 10), (5003, 64, 3, 128)])
 def test_corpora_of_repeated_and_sparse_rows(metric, n, d, nq, k):
     g = torch.Generator(device="cuda").manual_seed(d)
     x = torch.randn((n, d), generator=g, device="cuda")
