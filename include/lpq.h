@@ -279,11 +279,12 @@ int lpq_profile_read_kind(int kind, int64_t *launches, double *total_ms);
  * return less its 256 bytes of alignment slack) and for checking the planner itself.  out receives
  * LPQ_PLAN_INFO_COUNT values:
  *   [0] kernel family (0 generic dot-product kernel, 1 matrix-core with lists in LDS, 2 matrix-core
- *       with lists in registers, 3 matrix-core collecting scan)   [1] row-split workgroups (0/1)
+ *       with lists in registers, 3 matrix-core collecting scan, 4 group maxima of all rows)
+ *   [1] row-split workgroups (0/1)
  *   [2] waves of a row-split workgroup   [3] queries per wave of the collecting scan
  *   [4] query rows the workspace holds (padded)   [5] rows of the threshold-seeding pass (0 = none)
  *   [6] corpus splits of the seeding pass   [7] corpus splits of the main scan   [8] segments per split
- *   and [9] group maxima per query of the seeding pass   [10] candidate regions per query and
+ *   and [9] group maxima per query of the seeding pass (family 4: of the main scan)   [10] candidate regions per query and
  *   [11] their capacity (collecting scan)   [12] splits of the generic redo   [13] splits of the
  *   register-list redo   [14] further rounds of the collecting scan   [15] lists merged per workgroup
  *   in a first merge pass (0 = one pass)   [16] workspace bytes   [17] offset of the per-tile plan
@@ -325,9 +326,8 @@ int lpq_probe_stream(const void *src_dev, size_t bytes, int mode, int reps, doub
 /* Diagnostics of the collecting variant: after a search with the same (idx, nq, k, metric) and
  * workspace has finished, the number of queries whose candidates did not fit and that were
  * searched again (0 when the search did not use the collecting variant) and the
- * largest number of candidates any region received in the last round of the scan.  Of a small batch
- * that was searched by group maxima: the queries that more groups of rows tie for than are worked off
- * at once, and the most candidates one of the last workgroups kept.  Synchronises the device. */
+ * largest number of candidates any region received in the last round of the scan.  Synchronises
+ * the device. */
 int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,
                               int64_t *redone_queries, int64_t *max_region_fill);
 

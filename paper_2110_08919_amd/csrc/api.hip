@@ -518,16 +518,16 @@ extern "C" int lpq_rerank_f32(const float *x_dev, int64_t n, int64_t ldx, const 
 namespace {
 
 // How a search over n items is cut up, and where its intermediates live in the workspace.
-enum PlanMode { PLAN_GENERIC = 0, PLAN_MFMA_LDS = 1, PLAN_MFMA_REG = 2, PLAN_MFMA_COLLECT = 3 };
+enum PlanMode { PLAN_GENERIC = 0, PLAN_MFMA_LDS = 1, PLAN_MFMA_REG = 2, PLAN_MFMA_COLLECT = 3, PLAN_MAXIMA = 4 };
 struct Plan {
     int mode = PLAN_GENERIC;
     int64_t nq_pad = 0;
     int64_t seed_rows = 0;  // rows of the threshold-seeding pass (0 = none)
     int rank = 0;           // PLAN_MFMA_COLLECT: the bound of the first scan is the rank-th largest group maximum
     int S1 = 0, S2 = 0;     // corpus splits of the seeding pass and of the main pass
-    int SEG = 0;            // PLAN_MFMA_REG: segments per split in the seeding pass
-    int G = 0;              // PLAN_MFMA_REG: group maxima per query
-    bool rsplit = false;    // PLAN_MFMA_REG, PLAN_MFMA_COLLECT: row-split workgroups (few queries)
+    int SEG = 0;            // segments per split in the seeding pass (PLAN_MAXIMA: in the main pass)
+    int G = 0;              // group maxima per query
+    bool rsplit = false;    // row-split workgroups (few queries)
     int rs_waves = 0;       // ... of this many waves (0 when not row-split)
     int merge_group = 0;    // lists merged per workgroup in the first merge pass (0 = single pass)
     int64_t seed_stride = 0;   // seeding pass: one stage every seed_stride rows (systematic sample)
@@ -544,8 +544,7 @@ struct Plan {
     int seed_tiles = 0;     // ... its seeding pass: tiles of 256 rows, in runs of 16 rows
     int64_t run_stride = 0; // ... every run_stride rows
     int expect = 0;         // PLAN_MFMA_COLLECT: expected candidates per query
-    bool maxima = false;    // in place of either: a search by group maxima of all rows, finished by helpers workgroups per query
-    MaximaShape groups;
+    MaximaShape groups;     // PLAN_MAXIMA: group maxima of all rows, finished by helpers workgroups per query
     int helpers = 0, most_helpers = 0, finish_threads = 0;
     size_t off_qcodes = 0, off_qnorms = 0, off_lists1 = 0, off_seedlist = 0, off_seeds = 0, off_lists2 = 0,
            off_gmax = 0, off_merge_tmp = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_qlist = 0, off_redo = 0, off_bounds2 = 0, off_over2 = 0,
@@ -626,12 +625,16 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
     if (most > 16) most = 16;
     if (most * k > 2048) most = 2048 / k;
     if (most < 1) most = 1;
+    const int64_t nq_pad = p.nq_pad;
+    p = Plan();
+    p.mode = PLAN_MAXIMA;
+    p.nq_pad = nq_pad;
+    p.rsplit = !stream; p.rs_waves = stream ? 0 : waves;
+    p.S2 = m.S; p.SEG = m.SEG; p.G = m.G;
+    p.groups = m;
     p.most_helpers = (int)most;      // (one query on 1M x 64, every second row zero: 2.9 ms by one workgroup)
     p.helpers = (int)(h < 1 ? 1 : (h > most ? most : h));
     p.finish_threads = threads;
-    p.rsplit = !stream; p.rs_waves = waves;
-    p.groups = m;
-    p.maxima = true;
 }
 
 // compact: the plan for callers with a fixed workspace whose normal plan does not fit - fewer, larger splits
@@ -887,14 +890,12 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     size_t o = 0;
     p.off_qcodes = o;   o = align256(o + (size_t)p.nq_pad * idx->d_pad);
     p.off_qnorms = o;   o = align256(o + (size_t)p.nq_pad * sizeof(int32_t));
-    if (p.maxima) {
-        p.off_lists1 = p.off_seedlist = p.off_seeds = o;
+    if (p.mode == PLAN_MAXIMA) {
         p.off_lists2 = o;   o = align256(o + (size_t)nq * p.most_helpers * k * sizeof(cand_t));
         p.off_gmax = o;     o = align256(o + (size_t)(idx->d_pad > 256 ? round_up(nq, 64) : nq) * p.groups.G * sizeof(int32_t));
-        p.off_merge_tmp = p.off_cbuf = o;
         p.off_ccnt = o;     o = align256(o + (size_t)nq * p.most_helpers * sizeof(int32_t));
         p.off_over = o;     o = align256(o + (size_t)nq * sizeof(int32_t));
-        p.off_qlist = p.off_redo = p.off_bounds2 = p.off_over2 = p.off_qlist2 = p.total = o;
+        p.total = o;
         return p;
     }
     p.off_lists1 = o;   o = align256(o + (gmode ? 0 : (size_t)nq * p.S1 * k * sizeof(cand_t)));
@@ -1020,7 +1021,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
                                     coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
                                     coll ? p.rounds : 0, nq + 1);
     };
-    if (p.maxima) {
+    if (p.mode == PLAN_MAXIMA) {
         int32_t *done = reinterpret_cast<int32_t *>(ws + p.off_over);
         {
             KernelSpan span(st);
@@ -1317,17 +1318,12 @@ extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k
     *redone_queries = 0;
     *max_region_fill = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT && !p.maxima) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
-    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * (p.maxima ? p.most_helpers : p.SS));
+    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * p.SS);
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);
     HIP_TRY(hipMemcpy(over.data(), ws + p.off_over, over.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(cnt.data(), ws + p.off_ccnt, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (p.maxima) {   // none is searched again, those that many groups tie for take longer; a query's first workgroup has always worked
-        for (int32_t &v : over) v &= MAXIMA_MANY;
-        for (size_t i = 0; i < cnt.size(); ++i)
-            if (i % p.most_helpers) cnt[i] = 0;
-    }
     for (int32_t v : over) *redone_queries += v != 0;
     for (int32_t v : cnt) if (v > *max_region_fill) *max_region_fill = v;
     return LPQ_OK;
@@ -1340,7 +1336,7 @@ extern "C" int lpq_search_overflow_left(const lpq_index *idx, int64_t nq, int k,
     if (!idx || !workspace_dev || !left_queries || nq < 1 || k < 1) return fail(LPQ_EINVAL, "bad argument");
     *left_queries = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT || p.maxima || !p.rounds) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT || !p.rounds) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
     std::vector<int32_t> over2((size_t)nq);
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);

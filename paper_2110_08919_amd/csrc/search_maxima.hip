@@ -211,7 +211,6 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         // ranked by counting, to hold k early, the later ones as long as the list has room.
         // 16 queries, L2, half of 1M x 64 rows zero: 361 us with all units scored a thousand at a time, 127 now (92 by lists);
         // one feature in twenty 1, 1M x 32 293 -> 185 (81), inner product 134 -> 56 (76).
-        if (tid == 0 && hits > MF_UNITS) atomicOr(&done[q], MAXIMA_MANY);
         work_off();                                                 // (the rows behind the last stage)
         const int T0 = stages_of(0), longer = m.stages - (T0 - 1) * m.S;    // the first splits have T0 stages, the others T0 - 1
         const int all = T0 * m.S * m.parts, share = (all + H - 1) / H;
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         __syncthreads();
         if (tid == 0) {
             __threadfence();                                        // ... and is visible to the chip
-            s_last = (atomicAdd(&done[q], 1) & (MAXIMA_MANY - 1)) == H - 1;
+            s_last = atomicAdd(&done[q], 1) == H - 1;
             if (s_last) __threadfence();                            // the other helpers' parts are read as they are now
             s_hits = 0;
         }

@@ -1,6 +1,6 @@
 """Small batches by group maxima (three launches): both metrics, row lengths of all kinds of workgroup, packed rows, rows left
-over behind the last whole stage, one and many groups to a split, every limit of k and batch, and more groups at the bound
-than a workgroup works off at a time (few distinct vectors).  Against the generic kernel.  Needs a real MI355X."""
+over behind the last whole stage, one and many groups to a split, one and many tiles of queries, the largest k, and more groups
+at the bound than a workgroup works off at a time (few distinct vectors).  Against the generic kernel.  Needs a real MI355X."""
 import pytest
 import torch
 
@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 def _check(x, q, k, metric, bits=8, packed=False):
     from paper_2110_08919_amd import lpq
     n, d = x.shape
+    assert lpq.search_plan_info(d, bits, packed, n, q.shape[0], k)[0] == 4, "group maxima were expected here"
     quant = lpq.Quantizer(d, bits).calibrate(x, "absmax", "global")
     index = lpq.Index(quant, n, packed=packed).add_f32(x)
     ids, dists = index.search(q, k, metric)
@@ -26,14 +27,27 @@ def _check(x, q, k, metric, bits=8, packed=False):
 
 @pytest.mark.parametrize("metric", ["l2sq", "ip"])
 @pytest.mark.parametrize("n,d,nq,k", [
-    (4096, 24, 1, 1), (4223, 64, 3, 10), (10_000, 128, 64, 128), (65_535, 96, 16, 10), (70_001, 100, 63, 33), (200_129, 128, 5, 100),
-    (300_000, 40, 64, 2), (131_072, 192, 7, 10), (131_135, 256, 64, 100), (9000, 200, 1, 128), (1_000_000, 128, 1, 10),
+    (4096, 24, 1, 1), (4223, 64, 3, 10), (33_100, 128, 64, 128), (65_407, 96, 16, 10), (70_001, 100, 63, 33), (200_129, 128, 5, 100),
+    (300_000, 40, 64, 2), (131_072, 192, 7, 10), (131_135, 256, 64, 100), (40_009, 200, 1, 128), (1_000_000, 128, 1, 10),
     (2_000_003, 33, 2, 17),
     # streamed rows: one, two and four loads to a lane of the last kernel
     (4096, 384, 5, 16), (70_001, 300, 64, 100), (66_000, 512, 1, 10), (100_255, 700, 16, 10), (50_007, 1024, 33, 128), (30_300, 1500, 64, 20),
     (40_001, 2048, 9, 10), (20_100, 2100, 64, 33), (12_345, 4000, 3, 40),
 ])
 def test_small_batches(metric, n, d, nq, k):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    _check(*(torch.randn((m, d), generator=g, device="cuda") for m in (n, nq)), k, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2sq", "ip"])
+@pytest.mark.parametrize("n,d,nq,k", [
+    # two, three and many tiles of 64 queries: the limits of each, rows of two and four waves, workgroups of 256 and 1024
+    (20_577, 100, 65, 10), (10_300, 64, 128, 40), (60_000, 128, 129, 1), (20_500, 24, 192, 10), (5200, 128, 513, 3), (4096, 60, 2048, 5),
+    (20_577, 192, 65, 10), (40_100, 256, 128, 33), (20_600, 200, 200, 10),
+    # streamed rows
+    (30_000, 300, 65, 10), (20_100, 512, 129, 20), (9000, 700, 512, 1), (30_001, 1024, 257, 10), (16_500, 2000, 100, 10),
+])
+def test_batches_of_several_tiles(metric, n, d, nq, k):
     g = torch.Generator(device="cuda").manual_seed(n)
     _check(*(torch.randn((m, d), generator=g, device="cuda") for m in (n, nq)), k, metric)
 
@@ -64,7 +78,7 @@ def test_many_groups_of_streamed_rows_at_the_bound(metric):
 
 
 @pytest.mark.parametrize("metric", ["l2sq", "ip"])
-@pytest.mark.parametrize("n,d,nq,k", [(300_001, 64, 16, 10), (400_000, 32, 1, 100), (100_000, 300, 5, 10), (60_000, 16, 64, 20), (10_000, 128, 100, 10), (5003, 64, 3, 128)])
+@pytest.mark.parametrize("n,d,nq,k", [(300_001, 64, 16, 10), (400_000, 32, 1, 100), (100_000, 300, 5, 10), (60_000, 16, 64, 20), (10_000, 128, 100, 10), (33_100, 64, 3, 128)])
 def test_corpora_of_repeated_and_sparse_rows(metric, n, d, nq, k):
     g = torch.Generator(device="cuda").manual_seed(d)
     x = torch.randn((n, d), generator=g, device="cuda")
