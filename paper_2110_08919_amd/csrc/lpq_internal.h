@@ -210,7 +210,8 @@ hipError_t launch_seed_mfma(const SearchArgs &a, int64_t row0, int64_t row1, int
                             hipStream_t st, int64_t stage_stride = 0, int stages_per_split = 0,
                             int64_t piece_stride = 0, int piece_stages = 0);
 // Search by group maxima (small batches; row-split workgroups, 64 queries each): the seeding pass over every row of the first
-// `stages` stages, dealt round-robin to S splits, leaves gmax[nq][G], G = S * SEG * parts.  Group (s * SEG + seg) * parts +
+// `stages` stages, dealt round-robin to S splits, leaves gmax[nq][G], G = S * SEG * parts, the largest 2 dot - nx of a group's rows
+// (L2) or the largest dot.  Group (s * SEG + seg) * parts +
 // part holds the rows 32 (part / 2) + 8 i + 4 (part % 2) + 0 .. 3 (i = 0 .. 3) of the split's stages t with
 // floor(t SEG / T) = seg, T the number of its stages.
 struct MaximaShape {

@@ -114,11 +114,13 @@ struct MfmaIo {     // what a launch reads and writes besides the corpus and the
     // piece_stages stages.  0: stages of 64 consecutive rows as above.
     int64_t piece_stride;
     int piece_stages;
-    // Search by group maxima: the pass reads every row, every segment has stages, and gmax holds a.nq queries; done[0 .. nq)
-    // is set to 0.
-    bool whole;
+    // Search by group maxima (row-split launches of the seeding pass, WHOLE): the pass reads every row, every segment has stages,
+    // gmax holds a.nq queries, and done[0 .. nq) is set to 0.
     int32_t *done;
 };
+
+// Product of 24-bit values: with an addend, one instruction.
+__device__ __forceinline__ int mul24(int x, int y) { return ((int)((unsigned)x << 8) >> 8) * ((int)((unsigned)y << 8) >> 8); }
 
 struct WaveQ {      // pointers into the wave's private LDS region
     cand_t *thrC;   // [NQW] exact threshold candidate per query
@@ -275,7 +277,7 @@ __device__ __forceinline__ void drain_queue(const WaveQ &w, int qcnt, int64_t ro
 constexpr bool big_stage(int kcap, bool seed, bool rsplit, int nb, bool pack, int ks = 4) { return !seed && !rsplit && !pack && ks <= 4; }
 constexpr int ring_depth(int ks, bool rsplit, bool pack, bool big = false) { return big ? 2 : (rsplit ? (pack ? 4 : 3) : (ks <= 4 ? 4 : 2)); }
 
-template <int KS, bool L2, int KCAP, bool SEED, int NW, bool RSPLIT, int NB, bool PACK>
+template <int KS, bool L2, int KCAP, bool SEED, int NW, bool RSPLIT, int NB, bool PACK, bool WHOLE>
 __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     SearchArgs a, int64_t row0, int64_t row1, int S, int64_t split_rows, int qtiles, MfmaIo o)
 {
@@ -422,13 +424,19 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     // extra registers spill in the 128-queries-per-wave kernel), so one group per lane half it is.
     constexpr int GR = 1;
     int thr[NB], gm[NB][GR];
-    constexpr bool CAN_WHOLE = SEED && RSPLIT;
+    static_assert(!WHOLE || (SEED && RSPLIT && GR == 1 && KS <= 8), "dot products of 24 bits");
+    // WHOLE, L2: the least key nx - 2 dot of a group, where other passes take the largest E, which rows of odd and even norm one key
+    // apart share.  One instruction more for each accumulator, which starts from zero: 1M x 128, one query 24.1 -> 24.7 us, 1M x 64,
+    // 16 queries 15.3 -> 16.8, made up for by the next line and by segments counted without divisions (22.7 and 13.2).
+    constexpr bool KEYS = WHOLE && L2;
+    constexpr int NO_ROW = KEYS ? INT32_MAX : INT32_MIN;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         thr[nb] = SEED ? INT32_MAX : w.thrE[nb * 32 + col];
 #pragma unroll
-        for (int r = 0; r < GR; ++r) gm[nb][r] = INT32_MIN;
+        for (int r = 0; r < GR; ++r) gm[nb][r] = NO_ROW;
     }
+    const bool all_blocks = !WHOLE || a.nq - q_first > 32;   // up to 32 queries: without the tile's second half
     int qcnt = 0;
     int a_off[KS];   // byte offset of this lane's A chunk of k-step ks inside a 32-row block of a stage
 #pragma unroll
@@ -441,13 +449,13 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     // `wave` copies positions [(wave*IPW + j)*64, +64) with instruction j; the lane's source
     // is the chunk that belongs in its slot, so every instruction reads whole rows.
     const unsigned ring_lds = lds_offset(ring), aux_lds = lds_offset(aux);
-    const int lpt = IPW + (!L2 ? 0 : (RSPLIT ? 2 : (wave < RS / 64 + 1 ? 1 : 0)));   // copies this wave issues per stage
+    const int lpt = IPW + (!L2 ? 0 : (RSPLIT ? (KEYS ? 1 : 2) : (wave < RS / 64 + 1 ? 1 : 0)));   // copies this wave issues per stage
     // Seeding pass by pieces: the 64 rows of a stage are eight runs of 8 rows taken S * piece_stride
     // rows apart, so that neighbouring rows of the corpus fall into different splits (and groups).
     constexpr bool CAN_PIECES = SEED && !RSPLIT;
     const bool pieces = CAN_PIECES && o.piece_stride > 0;
     const int64_t piece_gap = pieces ? (int64_t)S * o.piece_stride : 0;   // rows between the pieces of a stage
-    const int64_t shift_room = pieces ? o.piece_stride - 8 : (o.stage_stride && !o.whole ? o.stage_stride - RS : 0);
+    const int64_t shift_room = pieces ? o.piece_stride - 8 : (o.stage_stride ? o.stage_stride - RS : 0);
     int src_off[IPW];   // byte offset of the lane's source chunk relative to the first row of a stage (of its piece)
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -487,8 +495,8 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         }                                                                                               \
         if (L2 && RSPLIT) { /* each wave brings the seeds and the parity word of its own block */       \
             if (lane < 32)                                                                              \
-                async_copy4(a.cinit + r0_ + wave * 32 + lane, aux_lds + (ring_slot_ * AUX_INTS + wave * 32) * 4); \
-            if (lane < 1)                                                                               \
+                async_copy4((KEYS ? a.norms : a.cinit) + r0_ + wave * 32 + lane, aux_lds + (ring_slot_ * AUX_INTS + wave * 32) * 4); \
+            if (!KEYS && lane < 1)                                                                               \
                 async_copy4(a.parity + r0_ / 32 + wave, aux_lds + (ring_slot_ * AUX_INTS + RS + wave) * 4); \
         } else if (L2 && wave < RS / 64) {                                                              \
             async_copy4(a.cinit + r0_ + cin_off, aux_lds + (ring_slot_ * AUX_INTS + wave * 64) * 4);     \
@@ -527,11 +535,17 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     } while (0)
 
     // Filter epilogue of one block of 32 queries x 32 rows (accumulators VEC).
-#define LPQ_EPI(VEC, NBI, ROWBASE, PWORD)                                                               \
+#define LPQ_EPI(VEC, NBI, ROWBASE, PWORD, NORMS)                                                        \
     do {                                                                                                \
         const int nb = (NBI);                                                                           \
-        const v16i v = (VEC);                                                                           \
-        if (SEED && GR == 16) {                                                                         \
+        const v16i v = (VEC), norms = (NORMS);                                                          \
+        if (KEYS) {                                                                                     \
+            v16i u;                                                                                     \
+            _Pragma("unroll") for (int r = 0; r < 16; ++r) u[r] = mul24(v[r], minus_two) + norms[r];    \
+            int m = min(min(u[0], u[1]), u[2]);                                                         \
+            _Pragma("unroll") for (int r = 3; r < 15; r += 2) m = min(min(m, u[r]), u[r + 1]);          \
+            gm[nb][0] = min(gm[nb][0], min(m, u[15]));                                                  \
+        } else if (SEED && GR == 16) {                                                                         \
             _Pragma("unroll") for (int r = 0; r < GR; ++r) gm[nb][r] = max(gm[nb][r], v[r]);            \
         } else {                                                                                        \
             int m = max(max(v[0], v[1]), v[2]);                                                         \
@@ -576,7 +590,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
 
 #define LPQ_CHAIN(NBI, AREG, CREG)                                                                      \
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                                   \
-        acc[NBI] = __builtin_amdgcn_mfma_i32_32x32x32_i8(AREG[ks], B[NBI][ks], ks == 0 ? CREG : acc[NBI], 0, 0, 0)
+        acc[NBI] = __builtin_amdgcn_mfma_i32_32x32x32_i8(AREG[ks], B[NBI][ks], ks == 0 ? (KEYS ? NO_SEED : CREG) : acc[NBI], 0, 0, 0)
 
     // Order of the contraction and of the filter epilogue.  Each block of 32 queries gets its KS
     // matrix instructions as one chain (dependent instructions of a chain issue back to back), and
@@ -586,6 +600,9 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
     // four epilogues at the end this measured 5.4 % faster on the benchmark workload (1.347 ->
     // 1.274 ms per 10 000 queries) and needs 29 fewer registers (accumulators live shorter).  The
     // seeding pass tests the last block at once: its segment maxima are flushed at stage boundaries.
+    constexpr v16i NO_SEED = {};
+    int minus_two = -2;
+    if (KEYS) asm volatile("" : "+s"(minus_two));   // (a product by the constant would be taken apart again)
     v16i carry_acc = {};
     int carry_rowbase = 0;
     unsigned carry_p = 0;
@@ -596,13 +613,17 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         const unsigned PREG_ = (PREG);                                                                  \
         const int rowbase = (int)(rs + (int64_t)(TT) * sstride + (BLK) * 32);                           \
         LPQ_CHAIN(0, AREG, CREG);                                                                       \
-        if (have_carry) LPQ_EPI(carry_acc, NB - 1, carry_rowbase, carry_p);                             \
+        if (have_carry) LPQ_EPI(carry_acc, NB - 1, carry_rowbase, carry_p, CREG);                             \
+        if (WHOLE && !all_blocks) {                                                                     \
+            LPQ_EPI(acc[0], 0, rowbase, PREG_, CREG);                                                   \
+            break;                                                                                      \
+        }                                                                                               \
         _Pragma("unroll") for (int nbi = 1; nbi < NB; ++nbi) {                                          \
             LPQ_CHAIN(nbi, AREG, CREG);                                                                 \
-            LPQ_EPI(acc[nbi - 1], nbi - 1, rowbase, PREG_);                                             \
+            LPQ_EPI(acc[nbi - 1], nbi - 1, rowbase, PREG_, CREG);                                             \
         }                                                                                               \
         if (SEED) {                                                                                     \
-            LPQ_EPI(acc[NB - 1], NB - 1, rowbase, PREG_);                                               \
+            LPQ_EPI(acc[NB - 1], NB - 1, rowbase, PREG_, CREG);                                               \
         } else {                                                                                        \
             carry_acc = acc[NB - 1]; carry_rowbase = rowbase; carry_p = PREG_; have_carry = true;       \
         }                                                                                               \
@@ -632,16 +653,16 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         int lane_ = lane;   /* addresses are formed here, not carried through the loop in registers */ \
         if (REFORM) LPQ_OPAQUE(lane_);                                                                  \
         _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                             \
-            if (CAN_WHOLE && o.whole && q_first + nb * 32 + (lane_ & 31) >= a.nq) continue;             \
+            if (WHOLE && q_first + nb * 32 + (lane_ & 31) >= a.nq) continue;                            \
             int32_t *dst_ = gmax + (size_t)(q_first + nb * 32 + (lane_ & 31)) * G +                     \
                 ((((size_t)s * SEG + (SEGIDX)) * (RSPLIT ? NW : 1) + (RSPLIT ? wave : 0)) * 2 + (lane_ >> 5)) * GR; \
             _Pragma("unroll") for (int r = 0; r < GR; ++r) {                                            \
-                dst_[r] = gm[nb][r];                                                                    \
-                gm[nb][r] = INT32_MIN;                                                                  \
+                dst_[r] = KEYS ? -gm[nb][r] : gm[nb][r];                                                \
+                gm[nb][r] = NO_ROW;                                                                     \
             }                                                                                           \
         }                                                                                               \
     } while (0)
-    if (CAN_WHOLE && o.whole) {
+    if (WHOLE) {
         if (blockIdx.x == 0)
             for (int i = tid; i < a.nq; i += NW * 64) o.done[i] = 0;
     } else if (SEED) {   // segments this split never reaches keep the neutral value
@@ -663,6 +684,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
         v4i A0[KS];
         v16i C0;
         unsigned P0 = 0;
+        int seg = 0, part = 0;
         for (int st = 0; st < NST - 1 && st < T; ++st) LPQ_ISSUE(st);
         for (int t = 0; t < T; ++t) {
             // stages issued so far: 0 .. min(T-1, t+NST-2); wait until stage t has landed
@@ -673,12 +695,14 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
             LPQ_BLOCK(t, wave, A0, C0, P0);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // my reads of stage t are complete
             if (SEED) {
-                const int seg = (int)((int64_t)t * SEG / T), seg_next = (int)((int64_t)(t + 1) * SEG / T);
-                if (t + 1 == T || seg_next != seg) {
+                // stage t belongs to segment t SEG / T: close it when the next stage is in another one
+                part += SEG;
+                if (part >= T || t + 1 == T) {
                     LPQ_FLUSH_SEGMENT(seg);
                     // (few segments: the stores stay in flight and only make the counted waits more conservative)
-                    if (!CAN_WHOLE || !o.whole) __builtin_amdgcn_s_waitcnt(0x0F70);
+                    if (!WHOLE) __builtin_amdgcn_s_waitcnt(0x0F70);
                 }
+                for (; part >= T; part -= T) ++seg;
             }
         }
     } else {
@@ -741,7 +765,7 @@ __global__ __launch_bounds__(NW * 64, 2) void search_mfma_kernel(
             }
         }
     }
-    if (!SEED && have_carry) LPQ_EPI(carry_acc, NB - 1, carry_rowbase, carry_p);
+    if (!SEED && have_carry) LPQ_EPI(carry_acc, NB - 1, carry_rowbase, carry_p, carry_acc);
 #undef LPQ_ISSUE
 #undef LPQ_EPI
 #undef LPQ_CHAIN
@@ -1281,12 +1305,12 @@ size_t lds_bytes(int ks, bool seed, int nw, bool rsplit, int nb, bool pack, bool
     return (size_t)nst * rs * slots * 16 + (size_t)nst * (rs + 4) * 4 + 64 + (seed ? 0 : nw * waveq_bytes(nb * 32));
 }
 
-template <int KS, bool L2, int KCAP, bool SEED, int NW, bool RSPLIT, int NB = 2, bool PACK = false>
+template <int KS, bool L2, int KCAP, bool SEED, int NW, bool RSPLIT, int NB = 2, bool PACK = false, bool WHOLE = false>
 hipError_t launch_nw(const SearchArgs &a, int64_t row0, int64_t row1, int S, int64_t split_rows, MfmaIo o, hipStream_t st)
 {
     const int qtiles = (int)ceil_div(a.nq, RSPLIT ? NQW : NW * NB * 32);
     const size_t lds = lds_bytes(KS, SEED, NW, RSPLIT, NB, PACK, big_stage(KCAP, SEED, RSPLIT, NB, PACK, KS));
-    auto kern = search_mfma_kernel<KS, L2, KCAP, SEED, NW, RSPLIT, NB, PACK>;
+    auto kern = search_mfma_kernel<KS, L2, KCAP, SEED, NW, RSPLIT, NB, PACK, WHOLE>;
     static bool attr_set = false;  // per instantiation
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1313,6 +1337,8 @@ hipError_t launch_one(const SearchArgs &a, int64_t row0, int64_t row1, int S, Mf
         // seeding pass), 128 queries per wave on rows of up to 64 bytes, 64 on longer ones
         if (a.rsplit) {
             if (a.rs_waves != 4) return hipErrorInvalidValue;
+            if constexpr (SEED)
+                if (o.done) return launch_nw<KS, L2, KCAP, SEED, 4, true, 2, true, true>(a, row0, row1, S, split_rows, o, st);
             return launch_nw<KS, L2, KCAP, SEED, 4, true, 2, true>(a, row0, row1, S, split_rows, o, st);
         }
         if constexpr ((KCAP == 0 || SEED) && KS >= 3) {
@@ -1329,6 +1355,8 @@ hipError_t launch_one(const SearchArgs &a, int64_t row0, int64_t row1, int S, Mf
     if constexpr (KS <= 4) {
         if (a.rsplit) {
             if (a.rs_waves != 4) return hipErrorInvalidValue;
+            if constexpr (SEED)
+                if (o.done) return launch_nw<KS, L2, KCAP, SEED, 4, true, 2, false, true>(a, row0, row1, S, split_rows, o, st);
             return launch_nw<KS, L2, KCAP, SEED, 4, true>(a, row0, row1, S, split_rows, o, st);
         }
         if constexpr (KCAP == 0 || SEED) {
@@ -1337,6 +1365,8 @@ hipError_t launch_one(const SearchArgs &a, int64_t row0, int64_t row1, int S, Mf
     } else if (a.rsplit) {   // rows of 192 or 256 bytes: two waves per workgroup, 64-row stages (collecting scan and seeding pass)
         if constexpr (KCAP == 0 || SEED) {
             if (a.rs_waves != 2) return hipErrorInvalidValue;
+            if constexpr (SEED)
+                if (o.done) return launch_nw<KS, L2, KCAP, SEED, 2, true, 2, false, true>(a, row0, row1, S, split_rows, o, st);
             return launch_nw<KS, L2, KCAP, SEED, 2, true>(a, row0, row1, S, split_rows, o, st);
         }
         return hipErrorInvalidValue;
@@ -1412,7 +1442,7 @@ hipError_t launch_long(const SearchArgs &a, int64_t row0, int64_t row1, int S, c
 hipError_t launch_any(const SearchArgs &a, int64_t row0, int64_t row1, int S, const MfmaIo &o, hipStream_t st)
 {
     if (a.nq <= 0 || row1 <= row0) return hipSuccess;
-    if (row0 % 128 || o.split_stride % (o.whole ? 32 : 128)) return hipErrorInvalidValue;  // stages and parity words cover aligned blocks
+    if (row0 % 128 || o.split_stride % (o.done ? 32 : 128)) return hipErrorInvalidValue;  // stages and parity words cover aligned blocks
     if (takes_long_scan(a) && (o.gmax || o.cbuf)) {
         switch (a.d_pad / 32) {
         case 6: return launch_long<6>(a, row0, row1, S, o, st);
@@ -1563,7 +1593,7 @@ hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t
         return hipErrorInvalidValue;
     MfmaIo o = {};
     o.gmax = gmax; o.SEG = m.SEG;
-    o.whole = true; o.done = done;
+    o.done = done;
     o.split_stride = rows;
     o.stage_stride = (int64_t)m.S * rows;
     o.split_stride_rows = ceil_div(m.stages, m.S) * rows;

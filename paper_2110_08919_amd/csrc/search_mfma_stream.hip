@@ -159,7 +159,7 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
         if (L2 && ik == 0) {           // a tile's first stage brings its accumulator seeds and parity words
             const unsigned dst = aux_lds + (it & 1) * AUX * 4;
             if (wave < 4) async_copy4(a.cinit + irow + (int64_t)(wave * 4 + (lane >> 4)) * o.run_gap + (lane & 15), dst + wave * 256);
-            else if (!SEED && wave == 4 && lane < 8) async_copy4(a.parity + irow / 32 + lane, dst + TILE_ROWS * 4);
+            else if ((!SEED || o.done) && wave == 4 && lane < 8) async_copy4(a.parity + irow / 32 + lane, dst + TILE_ROWS * 4);
         }
         const unsigned dst = ring_lds + islot * STAGE;
         const int8_t *src = a.codes + (irow + (int64_t)(wave * APW / 2) * o.run_gap) * a.d_pad + ik * KB;
@@ -309,7 +309,12 @@ __global__ __launch_bounds__(SW * 64, 2) void search_stream_kernel(SearchArgs a,
         for (int i = 0; i < RB; ++i) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const v16i v = acc[i][j];
+                v16i v = acc[i][j];
+                if (SEED && L2 && o.done) {   // 2 E, and 1 for an odd norm: what the key is the negative of
+                    const unsigned odd = (unsigned)pw[i] >> (4 * half);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = 2 * v[r] + (int)((odd >> (8 * (r >> 2) + (r & 3))) & 1u);
+                }
                 int m = max(max(v[0], v[1]), v[2]);
                 m = max(max(m, v[3]), v[4]);
                 m = max(max(m, v[5]), v[6]);
