@@ -616,10 +616,18 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
         threads = 256;
         rows = shape();
     }
-    if (m.G % 16 || m.G > 16 * threads || m.G / (threads == 256 ? 4 : 16) < k) return;
-    const double finish_bytes = (double)nq * (rows * (double)row_bytes + 4.0 * m.G);
-    // (streamed rows that the memory-side cache does not hold cost the other scans least and these workgroups most)
-    const int most_mb = stream ? (row_bytes < 768 || n * row_bytes < int64_t(128) << 20 ? 160 : 48) : tiles > 1 ? 32 : (k <= 10 ? 40 : 160);
+    const int sets = m.G / (threads == 256 ? 4 : 16) < 256 ? m.G / (threads == 256 ? 4 : 16) : 256;
+    if (m.G % 16 || m.G > 16 * threads || sets < k) return;
+    // Streamed rows: the bound is the k-th largest of the maxima of so many sets of groups, and as many groups reach it as fall on k
+    // sets if they fall on any set alike: up to all where k is near their number (64 queries, k = 50, 12 902 x 1913, 50 sets: 55 us by the
+    // collecting scan, 119 here).  Of 1900 shapes of 257 to 4096 features (1 to 512 queries, k = 1 to 128) the 1686 within the line
+    // take a median of 0.65 of the collecting scan's time and 18 of them 4 % more or worse, up to 23 %; from 160 to 300 MB on it is as
+    // often slower, up to 1.7 times.  (On fewer than 8192 rows the other scan has little to sample: 4600 to 6600 rows, 163 to 384 MB 0.63 to 0.72.)
+    const double reach = !stream ? rows : k == sets ? (double)n : std::fmin((double)n, -sets * std::log1p(-(double)k / sets) * (double)n / (double)m.G);
+    const double finish_bytes = (double)nq * (reach * (double)row_bytes + 4.0 * m.G);
+    // One tile of short rows, k up to 10, whose other scans cost least (register lists, or few candidates): a median of 0.81 of their time up to
+    // 10 MB, 0.93 to 20, 0.97 to 30, 1.00 to 50.  k = 11 to 128: 0.76 to 40 MB, 0.88 to 110, 1.00 to 160, 1.08 to 250.
+    const int most_mb = stream ? (n < 8192 ? 256 : 140) : tiles > 1 ? 32 : (k <= 10 ? 40 : 160);
     if (finish_bytes > (double)most_mb * (1 << 20)) return;
     int64_t h = (int64_t)(rows * (double)(row_bytes > 128 ? row_bytes : 128) / (768.0 * 128.0)), most = (threads == 256 ? 1024 : 256) / nq;
     if (most > 16) most = 16;

@@ -48,6 +48,9 @@ def test_small_batches_collect_on_small_corpora_only(bits, n, nq, k, mode):
     (4096, 8, False, 20_000, 4, 10, True), (4097, 8, False, 20_000, 4, 10, False), (400, 8, False, 20_000, 512, 1, True),
     (400, 8, False, 20_000, 513, 1, False), (64, 8, False, 4096, 2048, 5, True), (64, 8, False, 4096, 2049, 5, False),
     (128, 8, False, 128 * 78, 100, 10, True), (200, 8, False, 64 * 160, 100, 10, True),
+    # streamed rows: few sets of groups for k, and so most rows scored again; few rows or few queries all the same
+    (1913, 8, False, 12_902, 64, 50, False), (647, 8, False, 26_441, 84, 100, False), (653, 8, False, 14_474, 152, 50, False),
+    (2777, 8, False, 5908, 4, 23, True), (3432, 8, False, 6551, 242, 10, True), (978, 8, False, 53_042, 64, 100, True),
 ])
 def test_group_maxima_of_small_batches(d, bits, packed, n, nq, k, taken):
     p = lpq.search_plan_info(d, bits, packed, n, nq, k)
