@@ -279,12 +279,11 @@ int lpq_profile_read_kind(int kind, int64_t *launches, double *total_ms);
  * return less its 256 bytes of alignment slack) and for checking the planner itself.  out receives
  * LPQ_PLAN_INFO_COUNT values:
  *   [0] kernel family (0 generic dot-product kernel, 1 matrix-core with lists in LDS, 2 matrix-core
- *       with lists in registers, 3 matrix-core collecting scan, 4 group maxima of all rows)
- *   [1] row-split workgroups (0/1)
+ *       with lists in registers, 3 matrix-core collecting scan)   [1] row-split workgroups (0/1)
  *   [2] waves of a row-split workgroup   [3] queries per wave of the collecting scan
  *   [4] query rows the workspace holds (padded)   [5] rows of the threshold-seeding pass (0 = none)
  *   [6] corpus splits of the seeding pass   [7] corpus splits of the main scan   [8] segments per split
- *   and [9] group maxima per query of the seeding pass (family 4: of the main scan)   [10] candidate regions per query and
+ *   and [9] group maxima per query of the seeding pass   [10] candidate regions per query and
  *   [11] their capacity (collecting scan)   [12] splits of the generic redo   [13] splits of the
  *   register-list redo   [14] further rounds of the collecting scan   [15] lists merged per workgroup
  *   in a first merge pass (0 = one pass)   [16] workspace bytes   [17] offset of the per-tile plan
@@ -293,10 +292,23 @@ int lpq_profile_read_kind(int kind, int64_t *launches, double *total_ms);
  *   their end.  Every offset is a multiple of 256 and the used ones never decrease.  (A packed
  *   index is searched in tiles of 64 queries unless one collecting scan takes the whole batch: the
  *   values then describe the plan of a full tile, [4], [16] and [17] the whole workspace.)
+ * Where lpq_search_maxima_info reports groups, the search goes by group maxima: [1], [2], [4] and
+ * [16..34] are of that search, [0], [3] and [5..15] of the one with lists or regions that it takes
+ * the place of, which runs as soon as a tuning key asks for another kernel, split, sample or region.
  * LPQ_EINVAL / LPQ_ERANGE as for lpq_quantizer_create, lpq_index_create and lpq_search. */
 #define LPQ_PLAN_INFO_COUNT 35
 int lpq_search_plan_info(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, int64_t *out,
                          int out_count);
+/* Whether such a search goes by group maxima (small batches: one scan of all rows that keeps the largest score of
+ * each group of rows, and one kernel that scores the groups again which reach the k-th largest; no sample, lists,
+ * regions or redo), and how.  out receives LPQ_MAXIMA_INFO_COUNT values, all 0 where it does not:
+ *   [0] groups per query   [1] corpus splits   [2] segments per split   [3] waves of a workgroup of the scan
+ *   [4] rows of a stage   [5] threads of a workgroup of the last kernel, and how many of them search for a query
+ *   [6] usually and [7] where many groups reach the bound.   Of a packed index: of a full tile of 64 queries.
+ * Errors as above. */
+#define LPQ_MAXIMA_INFO_COUNT 8
+int lpq_search_maxima_info(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, int64_t *out,
+                           int out_count);
 
 /* Attainable-rate probes (benchmarks only): what this GPU sustains on the two resources that
  * bound lpq_search, measured by kernels that do nothing else, so that a roofline fraction quoted
@@ -326,8 +338,9 @@ int lpq_probe_stream(const void *src_dev, size_t bytes, int mode, int reps, doub
 /* Diagnostics of the collecting variant: after a search with the same (idx, nq, k, metric) and
  * workspace has finished, the number of queries whose candidates did not fit and that were
  * searched again (0 when the search did not use the collecting variant) and the
- * largest number of candidates any region received in the last round of the scan.  Synchronises
- * the device. */
+ * largest number of candidates any region received in the last round of the scan.  Of a small batch
+ * that was searched by group maxima: the queries that more groups of rows tie for than are all
+ * scored again, and the most candidates one of the last workgroups kept.  Synchronises the device. */
 int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k, int metric, const void *workspace_dev,
                               int64_t *redone_queries, int64_t *max_region_fill);
 

@@ -518,16 +518,16 @@ extern "C" int lpq_rerank_f32(const float *x_dev, int64_t n, int64_t ldx, const 
 namespace {
 
 // How a search over n items is cut up, and where its intermediates live in the workspace.
-enum PlanMode { PLAN_GENERIC = 0, PLAN_MFMA_LDS = 1, PLAN_MFMA_REG = 2, PLAN_MFMA_COLLECT = 3, PLAN_MAXIMA = 4 };
+enum PlanMode { PLAN_GENERIC = 0, PLAN_MFMA_LDS = 1, PLAN_MFMA_REG = 2, PLAN_MFMA_COLLECT = 3 };
 struct Plan {
     int mode = PLAN_GENERIC;
     int64_t nq_pad = 0;
     int64_t seed_rows = 0;  // rows of the threshold-seeding pass (0 = none)
     int rank = 0;           // PLAN_MFMA_COLLECT: the bound of the first scan is the rank-th largest group maximum
     int S1 = 0, S2 = 0;     // corpus splits of the seeding pass and of the main pass
-    int SEG = 0;            // segments per split in the seeding pass (PLAN_MAXIMA: in the main pass)
-    int G = 0;              // group maxima per query
-    bool rsplit = false;    // row-split workgroups (few queries)
+    int SEG = 0;            // PLAN_MFMA_REG: segments per split in the seeding pass
+    int G = 0;              // PLAN_MFMA_REG: group maxima per query
+    bool rsplit = false;    // PLAN_MFMA_REG, PLAN_MFMA_COLLECT: row-split workgroups (few queries)
     int rs_waves = 0;       // ... of this many waves (0 when not row-split)
     int merge_group = 0;    // lists merged per workgroup in the first merge pass (0 = single pass)
     int64_t seed_stride = 0;   // seeding pass: one stage every seed_stride rows (systematic sample)
@@ -544,7 +544,8 @@ struct Plan {
     int seed_tiles = 0;     // ... its seeding pass: tiles of 256 rows, in runs of 16 rows
     int64_t run_stride = 0; // ... every run_stride rows
     int expect = 0;         // PLAN_MFMA_COLLECT: expected candidates per query
-    MaximaShape groups;     // PLAN_MAXIMA: group maxima of all rows, finished by helpers workgroups per query
+    bool maxima = false;    // in place of either: a search by group maxima of all rows, finished by helpers workgroups per query
+    MaximaShape groups;
     int helpers = 0, most_helpers = 0, finish_threads = 0;
     size_t off_qcodes = 0, off_qnorms = 0, off_lists1 = 0, off_seedlist = 0, off_seeds = 0, off_lists2 = 0,
            off_gmax = 0, off_merge_tmp = 0, off_cbuf = 0, off_ccnt = 0, off_over = 0, off_qlist = 0, off_redo = 0, off_bounds2 = 0, off_over2 = 0,
@@ -633,16 +634,12 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
     if (most > 16) most = 16;
     if (most * k > 2048) most = 2048 / k;
     if (most < 1) most = 1;
-    const int64_t nq_pad = p.nq_pad;
-    p = Plan();
-    p.mode = PLAN_MAXIMA;
-    p.nq_pad = nq_pad;
-    p.rsplit = !stream; p.rs_waves = stream ? 0 : waves;
-    p.S2 = m.S; p.SEG = m.SEG; p.G = m.G;
-    p.groups = m;
     p.most_helpers = (int)most;      // (one query on 1M x 64, every second row zero: 2.9 ms by one workgroup)
     p.helpers = (int)(h < 1 ? 1 : (h > most ? most : h));
     p.finish_threads = threads;
+    p.rsplit = !stream; p.rs_waves = waves;
+    p.groups = m;
+    p.maxima = true;
 }
 
 // compact: the plan for callers with a fixed workspace whose normal plan does not fit - fewer, larger splits
@@ -898,12 +895,14 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     size_t o = 0;
     p.off_qcodes = o;   o = align256(o + (size_t)p.nq_pad * idx->d_pad);
     p.off_qnorms = o;   o = align256(o + (size_t)p.nq_pad * sizeof(int32_t));
-    if (p.mode == PLAN_MAXIMA) {
+    if (p.maxima) {
+        p.off_lists1 = p.off_seedlist = p.off_seeds = o;
         p.off_lists2 = o;   o = align256(o + (size_t)nq * p.most_helpers * k * sizeof(cand_t));
         p.off_gmax = o;     o = align256(o + (size_t)(idx->d_pad > 256 ? round_up(nq, 64) : nq) * p.groups.G * sizeof(int32_t));
+        p.off_merge_tmp = p.off_cbuf = o;
         p.off_ccnt = o;     o = align256(o + (size_t)nq * p.most_helpers * sizeof(int32_t));
         p.off_over = o;     o = align256(o + (size_t)nq * sizeof(int32_t));
-        p.total = o;
+        p.off_qlist = p.off_redo = p.off_bounds2 = p.off_over2 = p.off_qlist2 = p.total = o;
         return p;
     }
     p.off_lists1 = o;   o = align256(o + (gmode ? 0 : (size_t)nq * p.S1 * k * sizeof(cand_t)));
@@ -1029,7 +1028,7 @@ int search_core(const lpq_index *idx, const Plan &p, char *ws, const int8_t *qco
                                     coll && p.rounds ? reinterpret_cast<int32_t *>(ws + p.off_qlist2) + nq : nullptr,
                                     coll ? p.rounds : 0, nq + 1);
     };
-    if (p.mode == PLAN_MAXIMA) {
+    if (p.maxima) {
         int32_t *done = reinterpret_cast<int32_t *>(ws + p.off_over);
         {
             KernelSpan span(st);
@@ -1174,29 +1173,47 @@ int search_packed(const lpq_index *idx, const PackedPlan &pp, char *ws, int64_t 
 
 }  // namespace
 
-extern "C" int lpq_search_plan_info(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, int64_t *out,
-                                    int out_count)
+namespace {
+
+// An index that is only described: no device memory behind it.
+int describe_index(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, lpq_index &shape)
 {
-    if (!out || out_count < LPQ_PLAN_INFO_COUNT) return fail(LPQ_EINVAL, "out must hold LPQ_PLAN_INFO_COUNT values");
     if (d < 1 || bits < 1 || bits > 8) return fail(LPQ_EINVAL, "d < 1 or bits outside 1..8");
     if (d > MAX_D) return fail(LPQ_ERANGE, "d = %d > %d", d, (int)MAX_D);
     if (packed && (bits > 4 || d > MAX_D_PACKED)) return fail(LPQ_EINVAL, "packed storage: at most 4 bits and %d features", (int)MAX_D_PACKED);
     if (n_items < 1 || n_items >= (int64_t(1) << 31) - 1024) return fail(LPQ_ERANGE, "n_items outside 1 .. 2^31 - 1025");
     if (nq < 0 || k < 1) return fail(LPQ_EINVAL, "nq < 0 or k < 1");
     if (k > MAX_K || k > n_items || (packed && k > MAX_K_PACKED)) return fail(LPQ_ERANGE, "k = %d out of range", k);
-    lpq_index shape;                     // a description only: no device memory behind it
     shape.d = d; shape.bits = bits; shape.packed = packed != 0;
     shape.d_pad = padded_row_length(d);
     shape.capacity = shape.size = n_items;
-    Plan p = make_plan(&shape, nq, k);
+    return LPQ_OK;
+}
+
+// Its plan; a packed index is searched in tiles of 64 queries unless one collecting scan takes the whole batch.
+Plan plan_of_tile(const lpq_index &shape, int64_t nq, int k)
+{
+    const Plan p = make_plan(&shape, nq, k);
+    if (!shape.packed || (p.mode == PLAN_MFMA_COLLECT && !p.rsplit)) return p;
+    return make_plan(&shape, nq < PACKED_TILE ? nq : PACKED_TILE, k);
+}
+
+}  // namespace
+
+extern "C" int lpq_search_plan_info(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, int64_t *out,
+                                    int out_count)
+{
+    if (!out || out_count < LPQ_PLAN_INFO_COUNT) return fail(LPQ_EINVAL, "out must hold LPQ_PLAN_INFO_COUNT values");
+    lpq_index shape;
+    if (int rc = describe_index(d, bits, packed, n_items, nq, k, shape)) return rc;
+    const Plan p = plan_of_tile(shape, nq, k);
     size_t total = p.total, base = 0;
     int64_t nq_rows = p.nq_pad;
-    if (shape.packed) {   // searched in tiles of 64 queries unless one collecting scan takes the whole batch
+    if (shape.packed) {
         const PackedPlan pp = make_packed_plan(&shape, nq, k);
         total = pp.total;
         base = pp.off_tile;
         nq_rows = pp.nq_pad;
-        if (!(p.mode == PLAN_MFMA_COLLECT && !p.rsplit)) p = make_plan(&shape, nq < PACKED_TILE ? nq : PACKED_TILE, k);
     }
     const int64_t v[LPQ_PLAN_INFO_COUNT] = {
         p.mode, p.rsplit ? 1 : 0, p.rs_waves, p.wave_queries, nq_rows, p.seed_rows, p.S1, p.S2, p.SEG, p.G, p.SS, p.Cs,
@@ -1206,6 +1223,19 @@ extern "C" int lpq_search_plan_info(int d, int bits, int packed, int64_t n_items
         (int64_t)p.off_over, (int64_t)p.off_qlist, (int64_t)p.off_redo, (int64_t)p.off_bounds2, (int64_t)p.off_over2,
         (int64_t)p.off_qlist2, (int64_t)p.total};
     for (int i = 0; i < LPQ_PLAN_INFO_COUNT; ++i) out[i] = v[i];
+    return LPQ_OK;
+}
+
+extern "C" int lpq_search_maxima_info(int d, int bits, int packed, int64_t n_items, int64_t nq, int k, int64_t *out,
+                                      int out_count)
+{
+    if (!out || out_count < LPQ_MAXIMA_INFO_COUNT) return fail(LPQ_EINVAL, "out must hold LPQ_MAXIMA_INFO_COUNT values");
+    lpq_index shape;
+    if (int rc = describe_index(d, bits, packed, n_items, nq, k, shape)) return rc;
+    const Plan p = plan_of_tile(shape, nq, k);
+    const MaximaShape m = p.maxima ? p.groups : MaximaShape();
+    const int64_t v[LPQ_MAXIMA_INFO_COUNT] = {m.G, m.S, m.SEG, m.parts / 2, m.stage_rows, p.finish_threads, p.helpers, p.most_helpers};
+    for (int i = 0; i < LPQ_MAXIMA_INFO_COUNT; ++i) out[i] = v[i];
     return LPQ_OK;
 }
 
@@ -1326,12 +1356,17 @@ extern "C" int lpq_search_overflow_stats(const lpq_index *idx, int64_t nq, int k
     *redone_queries = 0;
     *max_region_fill = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT && !p.maxima) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
-    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * p.SS);
+    std::vector<int32_t> over((size_t)nq), cnt((size_t)nq * (p.maxima ? p.most_helpers : p.SS));
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);
     HIP_TRY(hipMemcpy(over.data(), ws + p.off_over, over.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(cnt.data(), ws + p.off_ccnt, cnt.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (p.maxima) {   // none is searched again, those that many groups tie for take longer; a query's first workgroup has always worked
+        for (int32_t &v : over) v &= MAXIMA_MANY;
+        for (size_t i = 0; i < cnt.size(); ++i)
+            if (i % p.most_helpers) cnt[i] = 0;
+    }
     for (int32_t v : over) *redone_queries += v != 0;
     for (int32_t v : cnt) if (v > *max_region_fill) *max_region_fill = v;
     return LPQ_OK;
@@ -1344,7 +1379,7 @@ extern "C" int lpq_search_overflow_left(const lpq_index *idx, int64_t nq, int k,
     if (!idx || !workspace_dev || !left_queries || nq < 1 || k < 1) return fail(LPQ_EINVAL, "bad argument");
     *left_queries = 0;
     const Plan p = make_plan(idx, nq, k);
-    if (p.mode != PLAN_MFMA_COLLECT || !p.rounds) return LPQ_OK;
+    if (p.mode != PLAN_MFMA_COLLECT || p.maxima || !p.rounds) return LPQ_OK;
     HIP_TRY(hipDeviceSynchronize());
     std::vector<int32_t> over2((size_t)nq);
     const char *ws = static_cast<const char *>(workspace_dev) + (idx->packed ? make_packed_plan(idx, nq, k).off_tile : 0);

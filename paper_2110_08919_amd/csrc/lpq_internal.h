@@ -219,14 +219,15 @@ struct MaximaShape {
     int stage_rows = 0, stages = 0;
     int seg_stages = 0;     // most stages of a segment
 };
-enum { MAXIMA_MAX_K = 128, MAXIMA_MAX_D = 4096 };
+enum { MAXIMA_MAX_K = 128, MAXIMA_MAX_D = 4096, MAXIMA_MANY = 1 << 16 };
 // Also sets done[0 .. nq) to 0.
 hipError_t launch_maxima_mfma(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
 // The same for rows of 384 bytes and more, by the streaming scan in tiles of 64 queries: a stage is a tile of 256 rows, shared
 // by eight waves.  Writes gmax of whole tiles.
 hipError_t launch_maxima_stream(const SearchArgs &a, const MaximaShape &m, int32_t *gmax, int32_t *done, hipStream_t st);
 // The k best from the maxima: `helpers` workgroups of 256 or 1024 threads (up to 16 groups to a thread) per query, most_helpers
-// where much has to be scored again; lists[nq][most_helpers][k], counts[nq][most_helpers].
+// where much has to be scored again; lists[nq][most_helpers][k], counts[nq][most_helpers].  done[q] holds MAXIMA_MANY afterwards
+// if more groups tie at the bound than are all scored.
 hipError_t launch_maxima_finish(const SearchArgs &a, const MaximaShape &m, const int32_t *gmax, int threads, int helpers, int most_helpers,
                                 cand_t *lists, int32_t *counts, int32_t *done, int32_t *ids, int32_t *dists, const int32_t *qnorms, int metric, hipStream_t st);
 // Collecting scan (any k up to MAX_K): thresholds stay at seeds[q] (required); every candidate beating its

@@ -269,6 +269,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         // Items that tie with the k-th by the hundreds or thousands (rows that repeat, features of few values).  What the groups
         // above the bound do not give is taken from those at it, lowest ids first: block by block, until k are held.  (Groups
         // above the bound in numbers, the nearest rows in few of the sets it was taken from: any group that can still win is taken.)
+        if (tid == 0 && h == 0) atomicOr(&done[q], MAXIMA_MANY);
         const int longer = m.stages - (T0 - 1) * m.S;               // splits with T0 stages; the others have one less
         const int per_stage = m.parts / 2, share = (all + H - 1) / H;
         int better = 0;
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(NT) void maxima_finish_kernel(
         __syncthreads();
         if (tid == 0) {
             __threadfence();                                        // ... and is visible to the chip
-            s_last = atomicAdd(&done[q], 1) == H - 1;
+            s_last = (atomicAdd(&done[q], 1) & (MAXIMA_MANY - 1)) == H - 1;
             if (s_last) __threadfence();                            // the other helpers' parts are read as they are now
             s_hits = 0;
         }

@@ -75,6 +75,7 @@ def lib() -> C.CDLL:
             "lpq_profile_read": (i32, [C.POINTER(i64), C.POINTER(C.c_double)]),
             "lpq_profile_read_kind": (i32, [i32, C.POINTER(i64), C.POINTER(C.c_double)]),
             "lpq_search_plan_info": (i32, [i32, i32, i32, i64, i64, i32, C.POINTER(i64), i32]),
+            "lpq_search_maxima_info": (i32, [i32, i32, i32, i64, i64, i32, C.POINTER(i64), i32]),
             "lpq_probe_mfma_i8": (i32, [vp, C.c_size_t, i32, C.POINTER(C.c_double), vp]),
             "lpq_probe_scan_core": (i32, [vp, C.c_size_t, i32, C.POINTER(C.c_double), vp]),
             "lpq_probe_stream": (i32, [vp, C.c_size_t, i32, i32, C.POINTER(C.c_double), vp]),
@@ -134,6 +135,16 @@ def search_plan_info(d: int, bits: int, packed: bool, n_items: int, nq: int, k: 
     """lpq_search_plan_info: the plan of a search as a list of PLAN_INFO_COUNT integers (no device needed)."""
     out = (C.c_int64 * PLAN_INFO_COUNT)()
     _check(lib().lpq_search_plan_info(d, bits, 1 if packed else 0, n_items, nq, k, out, PLAN_INFO_COUNT))
+    return list(out)
+
+
+MAXIMA_INFO_COUNT = 8
+
+
+def search_maxima_info(d: int, bits: int, packed: bool, n_items: int, nq: int, k: int):
+    """lpq_search_maxima_info: how such a search goes by group maxima, MAXIMA_INFO_COUNT zeros where it does not (no device needed)."""
+    out = (C.c_int64 * MAXIMA_INFO_COUNT)()
+    _check(lib().lpq_search_maxima_info(d, bits, 1 if packed else 0, n_items, nq, k, out, MAXIMA_INFO_COUNT))
     return list(out)
 
 

@@ -130,7 +130,7 @@ static void planner_checks(void *lib)
             CHECK(rc == 0, "plan rc %d for d %d bits %d packed %d n %lld nq %lld k %d", rc, d, bits, packed, (long long)n, (long long)nq, k);
             if (rc) continue;
 #define SHAPE "(d %d bits %d packed %d n %lld nq %lld k %d)", d, bits, packed, (long long)n, (long long)nq, k
-            CHECK(v[0] >= 0 && v[0] <= 4, "mode " SHAPE);
+            CHECK(v[0] >= 0 && v[0] <= 3, "mode " SHAPE);
             CHECK(v[3] == 32 || v[3] == 64 || v[3] == 128, "queries per wave " SHAPE);
             if (v[3] == 32) CHECK(d > 512 && d <= 1536 && v[0] == 3 && !packed, "32 queries per wave: rows of 768, 1024 or 1536 bytes only " SHAPE);
             CHECK(v[4] >= nq && v[4] >= 1, "query rows cover the batch " SHAPE);
@@ -138,14 +138,6 @@ static void planner_checks(void *lib)
             CHECK(v[7] >= 1, "at least one split " SHAPE);
             if (v[5] > 0) CHECK(v[6] >= 1, "seeding pass has splits " SHAPE);
             if (v[0] == 3) CHECK(v[10] >= 1 && v[11] >= 1 && v[5] > 0, "collecting scan has regions and a seeding pass " SHAPE);
-            if (v[0] == 4) {   // what the kernels of a search by group maxima ask for
-                const int64_t waves = v[1] ? v[2] : 8, stage = 32 * waves, sets = v[9] <= 4096 ? v[9] / 4 : v[9] / 16;
-                CHECK(v[7] >= 1 && v[8] >= 1 && v[8] <= n / stage / v[7], "every segment of every split has stages " SHAPE);
-                CHECK(v[9] == v[7] * v[8] * 2 * waves && v[9] % 16 == 0 && v[9] <= 16 * 1024, "groups " SHAPE);
-                CHECK(k <= 128 && sets >= k, "sets of groups for the bound " SHAPE);
-                CHECK(n % stage <= 256 && (packed || nq <= 4096) && d <= 4096, "limits of the last kernel " SHAPE);
-                CHECK(v[5] == 0 && v[6] == 0 && v[10] == 0 && v[11] == 0 && v[12] == 0 && v[13] == 0 && v[14] == 0, "no sample, regions or redo " SHAPE);
-            }
             CHECK(v[16] > 0 && v[16] < (int64_t(1) << 46), "workspace size sane " SHAPE);
             CHECK(v[17] % 256 == 0 && v[17] + v[34] <= v[16], "tile plan inside the workspace " SHAPE);
             int64_t prev = 0;

@@ -35,16 +35,7 @@ def _case(lpq, oracle, w, k, metric, mode, scope, expect_collecting=True):
     assert np.array_equal(dists.cpu().numpy(), odists)
     assert np.array_equal(ids.cpu().numpy(), oids)
     if expect_collecting:
-        if lpq.search_plan_info(w.d, 8, 0, w.n, w.nq, k)[0] == 4:   # by group maxima: by the collecting scan, too
-            lpq.set_tuning(lpq.TUNE_PATH, 3)
-        try:
-            ws = torch.empty(index.workspace_bytes(w.nq, k, metric) + 256, dtype=torch.uint8, device="cuda")
-            ids2, dists2 = index.search(q, k, metric, workspace=ws)
-            torch.cuda.synchronize()
-            assert torch.equal(ids2, ids) and torch.equal(dists2, dists)
-            _, fill = index.overflow_stats(w.nq, k, metric, ws)
-        finally:
-            lpq.set_tuning(lpq.TUNE_PATH, 0)
+        _, fill = index.overflow_stats(w.nq, k, metric, ws)
         assert fill > 0, "the collecting scan was expected to run here"
     return index, ws
 
