@@ -706,6 +706,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     // per query survive.
     const bool gm = p.mode == PLAN_MFMA_REG || p.mode == PLAN_MFMA_COLLECT;
     int64_t seed = 0;
+    double room = 0.0;       // collecting scan: candidates per query that there is room for in any case
     if (tune(LPQ_TUNE_SEED_ROWS) > 0) seed = tune(LPQ_TUNE_SEED_ROWS);
     else if (tune(LPQ_TUNE_SEED_ROWS) == 0 && p.mode != PLAN_GENERIC) {
         // Few queries: the scan is bound by corpus bytes, so the sample stays small.  Otherwise a
@@ -731,14 +732,19 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
             // (k beyond 512: half the corpus; streamed rows up to two fifths: 33 527 x 904, 7013 queries, k = 76: 0.482 -> 0.450 ms)
             const int64_t most = k > 512 ? n / 2 : (stream ? n / 5 * 2 : n / 4);
             // What is best for the k-th largest maximum goes with sqrt(k n): compact plans keep it, others take no smaller
-            // a sample than lets three quarters more candidates through (the regions would take more memory).
+            // a sample than lets as many candidates through.  Their number is also the length of the shortest cluster stored in one piece
+            // that still holds as many of the sample's groups as the bound's rank; the bound of a shorter one comes from another cluster,
+            // and its queries are searched again.  With three quarters more, 92 random corpora of clusters of 30 to 5000 rows, k up to 16:
+            // 20 slower than with the k-th maximum by 5 % or more, 1.4 % in the mean; as it is 8 slower and 4 % faster in the mean (770 rows,
+            // 1.3M x 107, 2363 queries: 700 us, 1726, 697).  It costs a large batch on a corpus in no order 1 %: 1M x 128, 10 000 queries,
+            // k = 10 1118 -> 1131 us; 1000 on 1.2M x 100 nothing.
             double by_k = 125000.0 * std::sqrt((double)n / 1e6 * (double)k / 10.0);
             if (stream && !compact) by_k *= std::sqrt(128.0 / (double)idx->d);
             const double by_room = (double)k * (double)n / 1500.0;
             const double want_rows = by_k > by_room ? by_k : by_room;
             seed = want_rows > (double)most ? most : (int64_t)want_rows;
             const double per_candidate = 1200.0 * 128.0 / (double)idx->d_pad;
-            const double room = 1.75 * (double)k * (double)n / (double)(seed > 1 ? seed : 1);
+            room = (double)k * (double)n / (double)(seed > 1 ? seed : 1);
             double best = INFINITY;
             for (double share = 0.5; !compact && share > 1.0 / 80.0; share *= 0.86) {
                 const int64_t rows = (int64_t)((double)n * share);
@@ -878,9 +884,14 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
         // deals its stages round-robin to the splits); a region holds three times its share, at
         // least 64, which leaves room for bounds several times looser than expected (a corpus stored
         // in sorted order).  Overflow is caught per query and redone exactly.
+        // (Their size goes by the larger sample's candidates of the rule before the bound's rank: a further round's bound is the k-th best
+        // of what the regions hold, and a cluster stored in one piece is in few of them.  With regions for the fewer candidates that are
+        // expected now, 8080 queries, k = 200, 673 620 x 74 in clusters of 468 rows took 172 ms instead of 2.7, 4465, k = 100, 79 076 x 541
+        // in clusters of 439 52 instead of 1.5.)
         p.SS = mfma_collect_regions(p.S2, p.rs_waves);
-        const double per_region = 1.15 * (double)p.rank * (double)n / (double)seed / p.SS;
-        p.expect = (int)(per_region * p.SS + 1.0);
+        const double candidates = 1.15 * (double)p.rank * (double)n / (double)seed;
+        p.expect = (int)(candidates + 1.0);
+        const double per_region = (!compact && 1.3 * room > candidates ? 1.3 * room : candidates) / p.SS;
         int64_t cs = 64;
         while ((double)cs < (compact && stream ? 1.5 : 3.0) * per_region && cs < 4096) cs <<= 1;
         p.Cs = (int)cs;
