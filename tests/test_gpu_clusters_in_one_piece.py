@@ -33,3 +33,22 @@ def test_large_batches(n, d, nq, k, run, metric):
         lpq.set_tuning(lpq.TUNE_PATH, 0)
     torch.cuda.synchronize()
     assert torch.equal(dists[::16], want) and torch.equal(ids[::16], want_ids)
+
+
+# group maxima by workgroups of 1024 threads (streamed rows, and many groups) and of 256
+@pytest.mark.parametrize("n,d,nq,k,run,metric", [
+    (57_474, 667, 427, 10, 1646, "l2sq"), (95_962, 856, 5, 100, 2463, "ip"), (5600, 512, 3, 21, 700, "l2sq"), (700_001, 64, 4, 30, 3000, "ip"),
+    (1_100_000, 128, 2, 128, 5000, "l2sq"), (50_048, 100, 200, 10, 400, "l2sq"),
+])
+def test_small_batches(n, d, nq, k, run, metric):
+    assert lpq.search_maxima_info(d, 8, False, n, nq, k)[0] > 0
+    x, q = _clusters(n, d, nq, run, 0.25, n)
+    index = lpq.Index(lpq.Quantizer(d, 8).calibrate(x, "minmax", "global"), n).add_f32(x)
+    ids, dists = index.search(q, k, metric)
+    lpq.set_tuning(lpq.TUNE_PATH, 1)
+    try:
+        want_ids, want = index.search(q, k, metric)
+    finally:
+        lpq.set_tuning(lpq.TUNE_PATH, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(dists, want) and torch.equal(ids, want_ids)
