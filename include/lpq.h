@@ -150,7 +150,7 @@ int lpq_index_data(const lpq_index *idx, const int8_t **codes_dev, int64_t *ld_c
 
 /* Bytes of device workspace lpq_search / lpq_search_i8 need for nq queries and k results
  * (0 on invalid arguments).  The workspace needs 256-byte alignment.  It grows with the batch and
- * with k (1M x 128: 10 000 queries 247 MB at k = 10, 315 at k = 100; about 4 GB for 100 000 queries on long
+ * with k (1M x 128: 10 000 queries 247 MB at k = 10, 299 at k = 100; about 4 GB for 100 000 queries on long
  * rows): where that is too much, search a batch in parts. */
 size_t lpq_search_workspace_bytes(const lpq_index *idx, int64_t nq, int k, int metric);
 
@@ -178,7 +178,7 @@ int lpq_search(const lpq_index *idx, const float *q_dev, int64_t nq, int64_t ld,
  * hipGetSymbolAddress per device on the first call there.  A search whose plan needs more than
  * LPQ_STATIC_WORKSPACE_BYTES (lpq_search_workspace_bytes tells) takes a slower one that needs less; if
  * that does not fit either the call returns LPQ_ERANGE and launches nothing: it is meant for small
- * batches (1M x 128: the usual plan fits up to 256 queries at k = 10, 57 at k = 100).  All calls on one GPU share the array, which keeps the previous call's contents (every
+ * batches (1M x 128: the usual plan fits up to 256 queries at k = 10, 219 at k = 100).  All calls on one GPU share the array, which keeps the previous call's contents (every
  * counter in it is cleared by the kernels that precede its use): calls that overlap on one GPU -
  * different streams, or different threads - race; serialise them on one stream. */
 #define LPQ_STATIC_WORKSPACE_BYTES (64u << 20)

@@ -561,7 +561,10 @@ constexpr int REFINE_ROUNDS = 2;        // further rounds of the collecting scan
 // The bound of a collecting scan is the rank-th largest maximum of its sample.  With rank = k it is certain that k items
 // reach it.  But the k nearest items are in a sample of a share s of the corpus in number like k draws that hit with
 // probability s, and fewer than k items reach the bound only if rank of them or more are: the rank here is that number's
-// mean and as many standard deviations (with the term of its skew) as make it happen in about one batch of a hundred.
+// mean, and as many standard deviations (with the term of its skew) as make it happen to one query in 100 nq: in one batch of a
+// hundred, to one of 7000 queries at 70 and of 1M at 10 000.  (z is the normal quantile of that, 0.905 of sqrt(2 ln(100 nq)) within
+// 4 % from 100 nq = 2e4 on.)  That takes the places of the nearest items for independent.  Samples are runs of 8 or 16 rows or whole stages, so
+// neighbours stored side by side are hit together, and more queries fall short of k.
 // Such a query is found by its count and searched again, as one whose region overflows is.
 int seed_rank(int64_t n, int64_t rows, int64_t nq, int k)
 {
@@ -574,23 +577,25 @@ int seed_rank(int64_t n, int64_t rows, int64_t nq, int k)
 // Small batches by group maxima (search_maxima.hip): three launches, no sample, no candidates on the way.  The scan splits
 // rows between the waves of a workgroup, 64 queries each, so that every further 64 queries read the corpus again, and the
 // finishing workgroups read about k groups of rows per query: the lines below bound both.  us, other scans / this one,
-// 128 features, k = 10: one query on 1M rows 56 / 42, 16 on 10M x 96 200 / 197, 100 on 10 000 35 / 19, 1000 47 / 26, 100 on
-// 200 000 41 / 27, 256 46 / 35, 600 56 / 54 to 68, 100 on 1M 62 / 48, 200 67 / 76, 128 on 5M x 96 160 / 178.  Rows of 384 bytes
-// and more through the streaming scan: 16 on 300 000 x 512 89 / 43, 128 94 / 50, 16 on 500 000 x 768 107 / 91, 64, k = 100 124 /
-// 125, 128 114 / 123, 100 on 1M x 384 146 / 118, 200 on 100 000 x 768 62 / 51, on 30 000 x 2048 72 / 59, 1 on 40 000 x 1500 63 / 36.
+// 128 features, k = 10: one query on 1M rows 54 / 38, 16 on 10M x 96 202 / 188, 100 on 10 000 35 / 18, 1000 48 / 24, 100 on
+// 200 000 42 / 30, 256 47 / 38, 600 57 / 51, 100 on 1M 67 / 48, 200 72 / 73, 128 on 5M x 96 173 / 162.  Rows of 384 bytes
+// and more through the streaming scan: 16 on 300 000 x 512 94 / 45, 128 95 / 53, 16 on 500 000 x 768 108 / 94, 64, k = 100 122 /
+// 127, 128 121 / 128, 100 on 1M x 384 152 / 125, 200 on 100 000 x 768 64 / 52, on 30 000 x 2048 75 / 59, 1 on 40 000 x 1500 51 / 34.
 void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
 {
     const int64_t n = idx->size;
     for (int key : {LPQ_TUNE_PATH, LPQ_TUNE_SPLITS, LPQ_TUNE_SEED_ROWS, LPQ_TUNE_WAVE_QUERIES, LPQ_TUNE_REGION_CAP})
         if (tune(key)) return;
-    // (Short rows of few bits tie, and every group that ties with the k-th has its rows scored again: 16 queries on 1M skewed
-    // integers of 24 features, 3 bits 46 / 341.)
+    // (Codes of few bits go by lists.  The line is from when every group that ties with the k-th had its rows scored again, 16 queries on 1M
+    // skewed integers of 24 features, 3 bits 46 / 341; with the ties found from the first row on it would be 44 / 30, and 0.53 of the time by
+    // lists over 192 such shapes.)
     if (nq < 1 || nq > 4096 || idx->bits < 4 || (idx->bits < 6 && idx->d < 64) || k > MAXIMA_MAX_K || idx->d_pad > MAXIMA_MAX_D) return;
     const bool stream = idx->d_pad > 256;     // by the streaming scan, whose workgroups have eight waves and a CU to themselves
     if (nq > (idx->packed ? 64 : stream ? 512 : 4096)) return;
     const int waves = stream ? 8 : mfma_row_split_waves(idx->d_pad, idx->packed);
     const int64_t tiles = ceil_div(nq, 64), row_bytes = idx->packed ? idx->d_pad / 2 : idx->d_pad;
-    if (idx->packed && idx->d_pad <= 128 && n > 3'000'000) return;   // (16 queries at 4 bits: 2M x 64 57 / 51, 10M x 96 139 / 155)
+    if (idx->packed && idx->d_pad <= 128 && n > 3'000'000) return;   // (16 queries at 4 bits: 2M x 64 58 / 41; 10M x 96 139 / 155
+    // when the line was drawn, 147 / 125 since up to 32 queries skip half of a tile)
     if (stream && tiles > 1 && tiles * n * row_bytes > int64_t(row_bytes < 768 ? 1024 : 420) << 20) return;
     if (!stream && tiles == 2 && tiles * n * row_bytes > int64_t(512) << 20) return;
     if (!stream && tiles > 2 && tiles * tiles * n * (row_bytes > 128 ? 2 * row_bytes : 128) > int64_t(512) << 20) return;
@@ -618,10 +623,12 @@ void plan_maxima(Plan &p, const lpq_index *idx, int64_t nq, int k)
         rows = shape();
     }
     const int sets = m.G / (threads == 256 ? 4 : 16) < 256 ? m.G / (threads == 256 ? 4 : 16) : 256;
+    // (Groups in sixteens, as the last kernel reads them: below 65 536 rows, where a stage is a split and a segment, an even number of stages of
+    // 128 rows or a multiple of four of 64; half and a third of the corpora of 8000 to 65 536 rows keep the other scans.)
     if (m.G % 16 || m.G > 16 * threads || sets < k) return;
     // Streamed rows: the bound is the k-th largest of the maxima of so many sets of groups, and as many groups reach it as fall on k
     // sets if they fall on any set alike: up to all where k is near their number (64 queries, k = 50, 12 902 x 1913, 50 sets: 55 us by the
-    // collecting scan, 119 here).  Of 1900 shapes of 257 to 4096 features (1 to 512 queries, k = 1 to 128) the 1686 within the line
+    // collecting scan, 119 here, 49 since neighbouring groups fall in different sets).  Of 1900 shapes of 257 to 4096 features (1 to 512 queries, k = 1 to 128) the 1686 within the line
     // take a median of 0.65 of the collecting scan's time and 18 of them 4 % more or worse, up to 23 %; from 160 to 300 MB on it is as
     // often slower, up to 1.7 times.  (On fewer than 8192 rows the other scan has little to sample: 4600 to 6600 rows, 163 to 384 MB 0.63 to 0.72.)
     const double reach = !stream ? rows : k == sets ? (double)n : std::fmin((double)n, -sets * std::log1p(-(double)k / sets) * (double)n / (double)m.G);
@@ -670,6 +677,7 @@ Plan make_plan(const lpq_index *idx, int64_t nq, int k, bool compact = false)
     // lists in us, 128 features, 8 bits: 5000 items, 65 queries, k = 10 42 / 55, 640 queries 49 / 63; 20 000, 256
     // queries, k = 10 39 / 45, k = 5 38 / 36; 100 000, 65 queries, k = 10 42 / 35, 640 49 / 51; 300 000, 640 65 / 66,
     // 256 50 / 50; a million, 65 68 / 62, 640 127 / 125.  k = 4 and less: the lists (50 000, 256 queries, k = 1 38 / 29).
+    // (Of these batches 8-bit codes on small corpora go by group maxima first, see plan_maxima.)
     // (Codes of few bits tie at the bound and all that tie is collected.  1 bit always keeps the lists: a
     // million items, 100 queries 2.1 / 0.35 ms.  2 bits beyond 32 768 items too: 20 000, 256 queries 47 / 53 us,
     // 100 000 53 / 45, a million 114 / 78.  3 bits behave like 8.)

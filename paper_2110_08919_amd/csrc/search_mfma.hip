@@ -40,7 +40,7 @@
 // by a launch of this kernel in list mode that skips query tiles without a flagged query).  With short rows and many queries a wave
 // holds 128 queries (NB = 4 blocks of 32) instead of 64.
 //
-// Row-split launches (RSPLIT, at most 64 queries).  The four waves (two on rows of more than 128
+// Row-split launches (RSPLIT; lists and candidates of at most 64 queries, group maxima of any number in tiles of 64).  The four waves (two on rows of more than 128
 // bytes) share the 64 queries and split the rows of a stage, 32 rows per wave; each wave copies,
 // waits for and reads only its own 32 rows, so there is no workgroup barrier and the launch runs at
 // the speed the corpus streams in.  PACK: the rows hold two 4-bit codes per byte and are spread over
